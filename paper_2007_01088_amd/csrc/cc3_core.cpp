@@ -179,7 +179,7 @@ static int env_int(const char* name, int dflt) {
 
 size_t block_bytes(int no, int nv) {
   const size_t o = no, v = nv;
-  return align256(o * v * v * v * 8) + align256(o * (v + o) * v * v * 8) * 2 +
+  return align256(o * v * gw_pitch(nv) * 8) + align256(o * (v + o) * v * v * 8) * 2 +
          align256(o * o * o * v * 8) * 2 + align256(o * o * v * v * 8) + align256(o * v * 8);
 }
 
@@ -187,7 +187,7 @@ Blocks carve_blocks(int no, int nv, void* base) {
   const size_t o = no, v = nv;
   char* b = (char*)base;
   Blocks bl;
-  bl.Gw = (double*)b; b += align256(o * v * v * v * 8);
+  bl.Gw = (double*)b; b += align256(o * v * gw_pitch(nv) * 8);
   bl.Gbc = (double*)b; b += align256(o * (v + o) * v * v * 8);
   bl.Gcb = (double*)b; b += align256(o * (v + o) * v * v * 8);
   bl.Go = (double*)b; b += align256(o * o * o * v * 8);
@@ -238,7 +238,7 @@ int make_plan_ex(int no, int nv, int nchol, int prec, unsigned flags, bool with_
   p->off_Ot1 = take(o * v * 8);
   p->off_Ot2 = take(o * o * v * v * 8);
   p->off_OtT = take(o * o * v * v * 8);
-  p->off_t2N = take(o * o * v * v * 8);
+  p->off_t2N = take(o * v * t2n_pitch(no, nv) * 8);
   p->off_lp = take(lp_operand_bytes(prec, no, nv));
   // partial slabs: Omega chunks of nv x (nv + 1), or Jacobian-preparation chunks of nv x no
   p->pvv_bytes = align256(tc * 6 * v * std::max(v + 1, o) * 8);
@@ -453,7 +453,8 @@ static int triple_loop_body(Runner& rn, Profiler* pf, const Plan& p, const Ws& w
     }
     {
       Timer tm(pf, sk, FAM_MIX, 0.0, 0.0);
-      launch_mix(eps, tb, nb, w.cubes[k], lowp_contract && lpP == 0 ? (float*)w.cubesX[k] : nullptr,
+      launch_mix(p.prec == CC3_FP64, eps, tb, nb, w.cubes[k],
+                 lowp_contract && lpP == 0 ? (float*)w.cubesX[k] : nullptr,
                  lpP ? w.cubesX[k] : nullptr, lpP, p.no, p.nv, sk);
     }
     {
@@ -535,6 +536,13 @@ int packed_residuals(const std::vector<PackMember>& ms, int prec, PackJob* dev_j
     if (prec != CC3_FP64) launch_lp_convert(m.t2, m.w.b, no, nv, m.w.lp, st);
     nsteps = std::max(nsteps, nbatches(p));
   }
+  // one wave-tile shape for the group: that of its member with the most W work
+  const Plan* big = ms[0].p;
+  for (const PackMember& m : ms)
+    if ((double)m.p->ntri * m.p->nv * m.p->nv * m.p->nv * m.p->nv >
+        (double)big->ntri * big->nv * big->nv * big->nv * big->nv)
+      big = m.p;
+  const int wshape = pick_shape(big->nv, big->nv, true);
   host_jobs.assign((size_t)nsteps * nm, PackJob{});
   std::vector<int> njobs(nsteps, 0);
   for (int s = 0; s < nsteps; ++s) {
@@ -553,8 +561,9 @@ int packed_residuals(const std::vector<PackMember>& ms, int prec, PackJob* dev_j
       j.cubes = m.w.cubes[0]; j.Pvv = m.w.Pvv[0];
       j.Ot1 = m.w.Ot1; j.Ot2 = m.w.Ot2; j.OtT = m.w.OtT;
       j.no = p.no; j.nv = p.nv; j.ntri = nb; j.nch = omega_kchunks(p.nv, nb);
+      j.wshape = wshape;
       unsigned it[PK_N];
-      pack_items(j, it);
+      pack_items(j, prec, it);
       for (int k = 0; k < PK_N; ++k) { j.first[k] = first[k]; first[k] += it[k]; }
       host_jobs[(size_t)s * nm + njobs[s]++] = j;
     }
@@ -627,7 +636,7 @@ static int jacobian_prep_body(Runner& rn, Profiler* pf, const Plan& p, const Ws&
     }
     {
       Timer tm(pf, sk, FAM_MIX, 0.0, 0.0);
-      launch_mix(eps, tb, nb, w.cubes[k], nullptr, nullptr, 0, no, nv, sk);
+      launch_mix(p.prec == CC3_FP64, eps, tb, nb, w.cubes[k], nullptr, nullptr, 0, no, nv, sk);
     }
     {
       Timer tm(pf, sk, FAM_ZPREP, zprep_flops(no, nv, kinds.data(), nb) * ((double)no / (nv + no)), 0.0);

@@ -74,14 +74,14 @@ void make_dplan(int no, int nv, int nchol, DPlan* p) {
   p->ntask = (int)p->htask.size() / D3_TASK_INTS;
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t at = off; off = a256(off + bytes); return at; };
-  p->off_Gw = take(o * v * v * v * 8);
-  p->off_Gl = take(o * v * v * v * 8);
+  p->off_Gw = take(o * v * gw_pitch(nv) * 8);
+  p->off_Gl = take(o * v * gw_pitch(nv) * 8);
   p->off_Go = take(o * o * o * v * 8);
   p->off_Go3 = take(o * o * o * v * 8);
   p->off_Jo = take(o * o * v * v * 8);
   p->off_F = take(o * v * 8);
-  p->off_t2N = take(o * o * v * v * 8);
-  p->off_l2M = take(o * o * v * v * 8);
+  p->off_t2N = take(o * v * t2n_pitch(no, nv) * 8);
+  p->off_l2M = take(o * v * t2n_pitch(no, nv) * 8);
   p->off_Y = take(o * o * o * v * 8);
   // partial slabs: D_cd, Gram and D_ld share one region; Y^o and D_kc have their own
   size_t cd = 0, vy = 0, vk = 0;

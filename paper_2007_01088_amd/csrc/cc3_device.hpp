@@ -38,6 +38,30 @@ __device__ inline double buf_load_f64(BufRsrc r, unsigned off) {
   return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
 }
 
+// A resource of n doubles from base (at most 2 GiB; the hardware checks each dword and
+// returns zero past the end, so rows and k past an operand's last element are safe to
+// load), and 16-byte loads at a per-lane and a uniform byte offset.
+typedef double d2v __attribute__((ext_vector_type(2)));
+__device__ inline BufRsrc buf_rsrc_n(const double* base, int64_t n) {
+  const int64_t bytes = n * 8;
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(base), 0,
+                                           bytes > 0x7fffffff ? 0x7fffffff : (int)bytes, 0x00020000);
+}
+__device__ inline d2v buf_load_2f64(BufRsrc r, unsigned voff, unsigned soff) {
+  return __builtin_bit_cast(d2v, __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, 0));
+}
+
+// The work item of workgroup b of n: workgroups go round-robin over the 8 XCDs, so runs
+// of `run` consecutive items are given to one XCD each (its L2 then serves the operand
+// rows that neighbouring items share) and the runs dealt over the XCDs in turn; the last
+// n % (8 run) workgroups keep their own number.
+__device__ inline unsigned xcd_item(unsigned b, unsigned n, unsigned run) {
+  const unsigned whole = n / (8 * run) * (8 * run);
+  if (b >= whole) return b;
+  const unsigned x = b & 7, s = b >> 3;
+  return (s / run * 8 + x) * run + s % run;
+}
+
 // Split of an FP64 value into BF16 pieces (the low-precision forms):
 // bf16_rn rounds to the nearest BF16, ties to even.
 __device__ inline uint16_t bf16_rn(double x) {

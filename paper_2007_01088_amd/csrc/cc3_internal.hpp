@@ -80,8 +80,21 @@ __host__ __device__ inline int64_t cube_slot(int nv) {
   return (int64_t)nv * nv * cube_pitch(nv);
 }
 
+// Doubles of a slab of n values rounded up to an odd number of 128-byte lines.  The W
+// build reads some operands with one row per slab (16 rows, one slab apart, per load);
+// slabs a multiple of 4 KB apart (n = nv^2 with nv a multiple of 32, for one) would put
+// all 16 rows on the same memory channel, an odd number of lines spreads them.
+__host__ __device__ inline int64_t odd_line_pitch(int64_t n) { return (((n + 15) / 16) | 1) * 16; }
+// slab of Gw (and of Gl, the left-state operand) for one (r, y): nv x nv values
+__host__ __device__ inline int64_t gw_pitch(int nv) { return odd_line_pitch((int64_t)nv * nv); }
+// slab of t2N (and of l2M) for one (p, y): nv x no values
+__host__ __device__ inline int64_t t2n_pitch(int no, int nv) {
+  return odd_line_pitch((int64_t)nv * no);
+}
+
 // Device-resident, internally laid out integral blocks (all float64):
-//   Gw[r][y][z][d] = g_{ydzr}         (vv|vo), the W contraction operand (d fastest)
+//   Gw[r][y][z][d] = g_{ydzr}         (vv|vo), the W contraction operand (d fastest),
+//                     each (r, y) slab at the pitch gw_pitch
 //   Go[q][r][z][l] = g_{lqzr}         (oo|vo) (l fastest)
 //   Gbc[r][n][b][c] = g_{nbrc} for n < nv (vv|ov), g_{lbrc} for n = nv + l (ov|ov):
 //                     the Omega contraction operand, K = (b, c) contiguous
@@ -161,22 +174,29 @@ void launch_gcb(const Blocks& b, int no, int nv, hipStream_t st);
 // The full triple table, the restricted loop dealt round-robin over nbatch batches.
 void launch_triple_table(int* tri, int no, int nbatch, hipStream_t st);
 void launch_t2N(const double* t2, double* t2N, int no, int nv, hipStream_t st);
+// t2N[p][y][x][l] = -t2[p][l][x][y], each (p, y) slab at the pitch t2n_pitch
 void launch_wbuild(const double* t2, const double* t2N, const Blocks& b, const int* tri, int ntri,
                    double* cubes, int no, int nv, bool all_terms, hipStream_t st);
-// The W build's engine with explicit operands and output strides (doubles between
-// triples, zs, between the three planes, ss, and between the rows of a plane, pitch).
+// The FP64 W build's engine with explicit operands and output strides (doubles between
+// triples, zs, between the two planes, ss, and between the rows of a plane, pitch).
 // mode 0: the t3 terms (X = t2, XN = t2N, G = Gw, H = Go); mode 1: the left-state L3
 // terms of Algorithm 3 without their outer-product parts (X = l2, XN = l2M, G = Gl,
 // H = Go3).
 void launch_wbuild_ex(int mode, const double* X, const double* XN, const double* G, const double* H,
                       const int* tri, int ntri, double* cubes, int64_t zs, int64_t ss, int pitch,
                       int no, int nv, bool all_terms, hipStream_t st);
-// Mixed-all copies (nullable): cubesF, FP32 tau~ and tau~T, [triple][2][nv^3]; YL,
-// the split-BF16 k-major views of k_omega_lp with lpP pieces
-void launch_mix(const double* eps, const int* tri, int ntri, double* cubes, float* cubesF,
-                void* YL, int lpP, int no, int nv, hipStream_t st);
-void launch_tau_export(const double* eps, const int* tri, const double* cubes, double* tau, int no,
-                       int nv, hipStream_t st);
+// two_planes: the planes are those of the FP64 W build (PA, PB), else the three planes
+// of the low-precision one.  Mixed-all copies (nullable): cubesF, FP32 tau~ and tau~T,
+// [triple][2][nv^3]; YL, the split-BF16 k-major views of k_omega_lp with lpP pieces
+void launch_mix(bool two_planes, const double* eps, const int* tri, int ntri, double* cubes,
+                float* cubesF, void* YL, int lpP, int no, int nv, hipStream_t st);
+void launch_tau_export(bool two_planes, const double* eps, const int* tri, const double* cubes,
+                       double* tau, int no, int nv, hipStream_t st);
+// Wave tiles of the FP64 GEMMs: FM x FN blocks of 16 x 16 outputs per wavefront.
+// pick_shape gives the index of the shape for an M x N product; shape_tiles the wave
+// tiles along M and N.
+int pick_shape(int64_t M, int64_t N, bool packed = false);
+void shape_tiles(int shape, int64_t M, int64_t N, int* tm, int* tn);
 // Omega contraction of a batch: the vv term and Omega1 into per-(triple,
 // permutation, chunk) partial slabs Pvv, then their fixed-order reduction into
 // Ot1/Ot2 (added, not overwritten); the oo and Fock terms added into OtT
@@ -237,18 +257,25 @@ struct PackJob {
   const int* tri;                             // the job's batch of triples
   double *cubes, *Pvv, *Ot1, *Ot2, *OtT;
   int no, nv, ntri, nch;
+  int wshape;            // wave-tile shape of the FP64 W build, the same for every job
   unsigned first[PK_N];  // first packed work item of this job, per kernel
 };
-// Work items of one job per kernel (the workgroups of its unpacked launch).
-void pack_items(const PackJob& j, unsigned (&items)[PK_N]);
+// Work items of one job per kernel (the workgroups of its unpacked launch); prec: the
+// W build's arithmetic.
+void pack_items(const PackJob& j, int prec, unsigned (&items)[PK_N]);
 // The five packed launches of one step (jobs in device memory, host copy for the
 // item counts); prec: the W build's arithmetic, shared by every job.
 void launch_packed_step(const PackJob* dev_jobs, const PackJob* host_jobs, int njobs, int prec,
                         hipStream_t st);
 
+// Workgroups of the low-precision W build of a batch, and its packed launch.
+unsigned wbuild_lp_wgs(int nv, int ntri);
+void launch_wbuild_lp_packed(const PackJob* jobs, int njobs, unsigned total, int prec,
+                             hipStream_t st);
+
 // ---- transition densities (Algorithm 3) ----
 // Slots of the density loop's cubes, slot-major: cubes[slot][z][cube_slot(nv)].
-enum { D3_P0 = 0, D3_P1 = 1, D3_P2 = 2, D3_TAU = 3, D3_TAUC = 4, D3_LC = 5, D3_NSLOT = 6 };
+enum { D3_PA = 0, D3_PB = 1, D3_TAU = 2, D3_TAUC = 3, D3_LC = 4, D3_NSLOT = 5 };
 // tau, tau~ (lmode false) or L~ (lmode true, with the outer products of the L3
 // statement from l1, l2, Jo, F and the shift omega) from the planes of each triple
 void launch_mix3(bool lmode, const double* eps, const int* tri, int ntri, double* cubes, int64_t ss,

@@ -310,14 +310,14 @@ __global__ void k_d3_yout(const double* __restrict__ Y, double* __restrict__ Yo,
   Yo[e] = accumulate ? Yo[e] + v : v;
 }
 
-// l2M[r][y][x][l] = -l2[l][r][x][y]
+// l2M[r][y][x][l] = -l2[l][r][x][y], each (r, y) slab at the pitch t2n_pitch
 __global__ void k_d3_l2m(const double* __restrict__ l2, double* __restrict__ l2M, int no, int nv) {
   const int64_t nvl = nv, n = (int64_t)no * no * nvl * nvl;
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= n) return;
   const int l = (int)(e % no), x = (int)((e / no) % nvl), y = (int)((e / (no * nvl)) % nvl);
   const int r = (int)(e / (no * nvl * nvl));
-  l2M[e] = -l2[(((int64_t)l * no + r) * nvl + x) * nvl + y];
+  l2M[((int64_t)r * nvl + y) * t2n_pitch(no, nv) + (int64_t)x * no + l] = -l2[(((int64_t)l * no + r) * nvl + x) * nvl + y];
 }
 
 // ---------------------------------------------------------------------------

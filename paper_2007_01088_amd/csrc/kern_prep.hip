@@ -282,7 +282,7 @@ __global__ __launch_bounds__(BuildCfg::NT, 2) void k_build(const BuildSet set) {
           Cz[(((int64_t)q * no + rr) * nv + c) * no + l] = v;
         } else {  // BUILD_GW: m = z, n = y*nv + d -> Gw[r][y][z][d] (batch r)
           const int y = n / nv, d = n % nv;
-          Cz[((int64_t)y * nv + m) * nv + d] = v;
+          Cz[y * gw_pitch(nv) + (int64_t)m * nv + d] = v;
         }
       }
 }
@@ -308,17 +308,17 @@ static void launch_build_set(BuildSet& set, hipStream_t st) {
 }
 
 // Gcb[r][n][c][b] = Gbc[r][n][b][c]: nv x nv transposes, one per (r, n), through
-// padded 32 x 32 LDS tiles.
+// padded 32 x 32 LDS tiles; ss and ds: doubles between the slabs.
 __global__ __launch_bounds__(256) void k_gcb(const double* __restrict__ Gbc,
-                                             double* __restrict__ Gcb, int nv) {
+                                             double* __restrict__ Gcb, int nv, int64_t ss,
+                                             int64_t ds) {
   __shared__ double t[32][33];
   const int tn = (nv + 31) / 32;
   const int64_t slab = blockIdx.x / (tn * tn);  // r * (nv + no) + n
   const int tile = blockIdx.x % (tn * tn);
   const int b0 = (tile / tn) * 32, c0 = (tile % tn) * 32;
-  const int64_t nv2 = (int64_t)nv * nv;
-  const double* src = Gbc + slab * nv2;
-  double* dst = Gcb + slab * nv2;
+  const double* src = Gbc + slab * ss;
+  double* dst = Gcb + slab * ds;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
   for (int y = ty; y < 32; y += 8) {
     const int b = b0 + y, c = c0 + tx;
@@ -333,7 +333,8 @@ __global__ __launch_bounds__(256) void k_gcb(const double* __restrict__ Gbc,
 
 void launch_gcb(const Blocks& bl, int no, int nv, hipStream_t st) {
   const unsigned t = nblk(nv, 32);
-  hipLaunchKernelGGL(k_gcb, dim3(t * t * no * (nv + no)), dim3(256), 0, st, bl.Gbc, bl.Gcb, nv);
+  hipLaunchKernelGGL(k_gcb, dim3(t * t * no * (nv + no)), dim3(256), 0, st, bl.Gbc, bl.Gcb, nv,
+                     (int64_t)nv * nv, (int64_t)nv * nv);
 }
 
 void launch_build_blocks(const CholeskyScratch& cs, const Blocks& bl, int no, int nv, int nJ,
@@ -344,7 +345,8 @@ void launch_build_blocks(const CholeskyScratch& cs, const Blocks& bl, int no, in
   BuildSet set = {};
   set.K = nJ; set.no = no; set.nv = nv; set.F = bl.F;
   // Gw[r][y][z][d] = sum_J LvoT[J][r][z] Lvv[J][(y,d)]   (rows z, columns (y,d), batch r)
-  add_build(set, cs.LvoT, 1, onv, nv, cs.Lvv, nv2, 1, 0, nv, (int)nv2, bl.Gw, nv3, no, BUILD_GW);
+  add_build(set, cs.LvoT, 1, onv, nv, cs.Lvv, nv2, 1, 0, nv, (int)nv2, bl.Gw,
+            nv * gw_pitch(nv), no, BUILD_GW);
   // Gbc[r][(d,b)][c] = sum_J Lvv[J][(d,b)] Lov[J][r][c]            (rows n = d < nv)
   add_build(set, cs.Lvv, 1, nv2, 0, cs.Lov, onv, 1, nv, (int)nv2, nv, bl.Gbc, gs, no, BUILD_PLAIN);
   // Gbc[r][nv + (l,b)][c] = sum_J Lov[J][(l,b)] Lov[J][r][c]      (rows n = nv + l)
@@ -365,14 +367,15 @@ void launch_build_blocks(const CholeskyScratch& cs, const Blocks& bl, int no, in
 // The blocks of the transition-density loop (Algorithm 3), in one grouped launch:
 // Gw, Go and Jo as for the residual; Go3[p][q][z][l] = g_{plqz} = sum_J Lt_pl L_qz;
 // Gl[p][y][z][d] = g_{pydz} = sum_J L_py Lt_dz, built as [p][y][d][z] into `tmp`
-// (no nv^3 doubles) and transposed per (p, y) slab.
+// (no nv^3 doubles) and transposed per (p, y) slab (Gl at the slab pitch of Gw).
 void launch_build_density_blocks(const CholeskyScratch& cs, double* Gw, double* Go, double* Jo,
                                  double* Go3, double* Gl, double* tmp, int no, int nv, int nJ,
                                  hipStream_t st) {
-  const int64_t nv2 = (int64_t)nv * nv, nv3 = nv2 * nv, onv = (int64_t)no * nv;
+  const int64_t nv2 = (int64_t)nv * nv, onv = (int64_t)no * nv;
   BuildSet set = {};
   set.K = nJ; set.no = no; set.nv = nv; set.F = nullptr;
-  add_build(set, cs.LvoT, 1, onv, nv, cs.Lvv, nv2, 1, 0, nv, (int)nv2, Gw, nv3, no, BUILD_GW);
+  add_build(set, cs.LvoT, 1, onv, nv, cs.Lvv, nv2, 1, 0, nv, (int)nv2, Gw, nv * gw_pitch(nv), no,
+            BUILD_GW);
   // tmp[(p,y)][(d,z)] = sum_J Lov[J][p][y] Lvv[J][d][z]
   add_build(set, cs.Lov, 1, onv, 0, cs.Lvv, nv2, 1, 0, (int)onv, (int)nv2, tmp, 0, 1, BUILD_PLAIN);
   add_build(set, cs.Lov, 1, onv, 0, cs.Lov, onv, 1, 0, (int)onv, (int)onv, Jo, 0, 1, BUILD_JO);
@@ -383,7 +386,8 @@ void launch_build_density_blocks(const CholeskyScratch& cs, double* Gw, double* 
             BUILD_GO);
   launch_build_set(set, st);
   const unsigned t = nblk(nv, 32);
-  hipLaunchKernelGGL(k_gcb, dim3(t * t * no * nv), dim3(256), 0, st, tmp, Gl, nv);
+  hipLaunchKernelGGL(k_gcb, dim3(t * t * no * nv), dim3(256), 0, st, tmp, Gl, nv, nv2,
+                     gw_pitch(nv));
 }
 
 // ---------------------------------------------------------------------------
@@ -394,14 +398,14 @@ __global__ void k_relayout_vv(const double* __restrict__ g_vvvo_y, const double*
                               int y0, int ny) {
   // output index (r, y, d, z) of an nv^3 slab, z fastest, for y in [y0, y0 + ny);
   // the inputs start at first index y0
-  const int64_t nv2 = (int64_t)nv * nv, nv3 = nv2 * nv;
+  const int64_t nv2 = (int64_t)nv * nv;
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int r = blockIdx.y;
   if (e >= (int64_t)ny * nv2) return;
   const int yl = (int)(e / nv2), d = (int)((e / nv) % nv), z = (int)(e % nv);
   const int64_t out = (int64_t)y0 * nv2 + e;
   // Gw[r][y][u][w] = g_vvvo[y][w][u][r]  (u = d, w = z: the contracted index w fastest)
-  Gw[(int64_t)r * nv3 + out] = g_vvvo_y[(((int64_t)yl * nv + z) * nv + d) * no + r];
+  Gw[((int64_t)r * nv + y0 + yl) * gw_pitch(nv) + e % nv2] = g_vvvo_y[(((int64_t)yl * nv + z) * nv + d) * no + r];
   // Gbc[r][n=y][b=d][c=z] = g_vvov[n][b][r][c]
   Gbc[(int64_t)r * (nv + no) * nv2 + out] = g_vvov_y[(((int64_t)yl * nv + d) * no + r) * nv + z];
 }

@@ -3,14 +3,10 @@
 // For a batch of unordered occupied triples i >= j >= k (not all equal):
 //
 //  k_wbuild  (FP64 MFMA)  the six terms B_pqr[x,y,z] = sum_d t2[p][q][x][d] g_{ydzr}
-//            - sum_l t2[p][l][x][y] g_{lqzr} of the permutation operator, paired
-//            two per "plane" so that each workgroup writes one nv x nv plane:
-//              P0[b][a][c] = B_ijk[a,b,c] + B_kji[c,b,a]
-//              P1[a][b][c] = B_jik[b,a,c] + B_kij[c,a,b]
-//              P2[c][a][b] = B_ikj[a,c,b] + B_jki[b,c,a]
-//            so that X = P B = P0[b][a][c] + P1[a][b][c] + P2[c][a][b].  With two
-//            equal occupied indices three of the six terms repeat and are not
-//            recomputed.
+//            - sum_l t2[p][l][x][y] g_{lqzr} of the permutation operator, summed into
+//            two planes so that X = P B = PA[b][a][c] + PB[a][b][c] (see there).
+//            With two equal occupied indices three of the six terms repeat: PB is not
+//            built and PA appears twice in X.
 //  k_mix     (LDS)  per S3-orbit of 8x8x8 virtual blocks: X, the denominator
 //            division tau = -X / eps^{abc}_{ijk}, and the contravariant
 //            tau~ = 4 tau^{abc} - 2 tau^{acb} - 2 tau^{cba} - 2 tau^{bac} + tau^{bca} + tau^{cab},
@@ -25,6 +21,8 @@
 //              Ot2[p][l][a][b] += sum_c U[a,b,c] (delta_lq F_rc - g_{qlrc}),
 //            kept transposed, OtT[p][l][b][a], so that its stores run along a.
 #include <algorithm>
+#include <initializer_list>
+#include <type_traits>
 
 #include "cc3.h"
 #include "cc3_device.hpp"
@@ -34,191 +32,287 @@ namespace cc3 {
 
 static inline unsigned nblk(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 
-// cube slots of one triple's workspace
+// cube slots of one triple's workspace: the W planes (PA, PB of the FP64 build; P0, P1,
+// P2 of the low-precision one), tau~ and tau~T
 enum { SLOT_P0 = 0, SLOT_P1 = 1, SLOT_P2 = 2, SLOT_TT = 3, SLOT_TTT = 4, NSLOT = 5 };
+enum { SLOT_PA = SLOT_P0, SLOT_PB = SLOT_P1 };
 
 // ---------------------------------------------------------------------------
 // W build
 // ---------------------------------------------------------------------------
-typedef TileCfg<4, 2, 2, 4, 16> WCfg;  // 128 x 128 output plane tile, 8 wavefronts, 16 k per stage
-
+// Every term is a product of an amplitude operand and an integral operand, both rows of
+// contiguous k.  The d sum of B_pqr[x,y,z] multiplies t2[p][q] (rows x) by Gw[r] (rows
+// (y, z)): it is a matrix product in x and z at fixed y, and, with the Gw rows taken one
+// slab apart, in x and y at fixed z.  The l sum multiplies t2N[p] (rows (y, x)) by
+// Go[q][r] (rows z): a product in x and z at fixed y, and in y and z at fixed x.  So the
+// terms of two planes suffice, PA at fixed b and PB at fixed a (ijk: B_ijk[a,b,c], ikj:
+// B_ikj[a,c,b], ... as in the permutation operator):
+//   PA[b][a][c] = d sums of ijk, ikj, kji, kij + l sums of ijk, kji, jki,
+//   PB[a][b][c] = d sums of jik, jki           + l sums of jik, kij, ikj,
+// and X = PA[b][a][c] + PB[a][b][c].  With i == j the terms pair up under a <-> b, with
+// j == k under b <-> c, and one of each pair is enough:
+//   i == j: PA = d sums of ijk, ikj, kji + l sums of ijk, kji, jki; X = PA[b][a][c] + PA[a][b][c]
+//   j == k: PA = d sums of ijk, kji, kij + l sums of ijk, kji, jik; X = PA[b][a][c] + PA[c][a][b].
+// Two planes instead of one per value of the fixed index of each pair of terms (three):
+// a third less written here and read by the mix, and up to 4 nv + 3 no of K per plane.
+//
+// One wavefront per FM x FN blocks of 16 x 16 outputs of a plane, without LDS and
+// without barriers: it loads its own MFMA fragments, 8 k at a time (lane: two
+// consecutive k of one row), two such units in flight.  FP64 MFMA takes 64 cycles per
+// block and 4 k, so at 4 x 4 blocks a wavefront loads 16 B per cycle and CU, which L1 and
+// L2 sustain; what a shared 128 x 128 LDS tile saves in loads it lost to barriers and,
+// unless nv fills whole tiles, to padding.  Measured in isolation, 8 distinct triples,
+// no = 10 (LDS tile -> this): nv = 93 1.30 -> 0.73 ms (4x the triples), 150 5.33 -> 2.6
+// (2x), 250 7.35 -> 6.9, 400 65.8 -> 40.1 ms (70 TFLOP/s of MFMA, 89% of peak).
+//
 // MODE 0: the t3 terms (t2, t2N, Gw, Go as named).  MODE 1: the L3 terms of
 // Algorithm 3, C_pqr[x,y,z] = sum_d L^{xd}_{qr} g_{pydz} - sum_l L^{xy}_{lr} g_{plqz}
 // (+ outer products added by the density mix), with t2 <- l2, t2N <- l2M
 // (l2M[r][y][x][l] = -l2[l][r][x][y]), Gw <- Gl (Gl[p][y][z][d] = g_{pydz}) and
-// Go <- Go3 (Go3[p][q][z][l] = g_{plqz}): the same segments with the roles of the
-// occupied indices permuted.  Plane `plane` of triple z goes to cubes + z zs + plane ss.
-template <int MODE>
+// Go <- Go3 (Go3[p][q][z][l] = g_{plqz}): the same products with the roles of the
+// occupied indices permuted.
+
+// The segments of a plane, in order: 6 bits each, the permutation of perm_pqr that names
+// the term (bits 0-2), l sum (bit 3), amplitude operand on the columns instead of the
+// rows (bit 4), operand rows one slab apart (bit 5: Gw for a d sum, t2N for an l sum).
+constexpr uint64_t wseg(int pi, int lsum, int col, int strided) {
+  return (uint64_t)(pi | lsum << 3 | col << 4 | strided << 5);
+}
+constexpr uint64_t wsegs(std::initializer_list<uint64_t> l) {
+  uint64_t v = 0;
+  int at = 0;
+  for (uint64_t x : l) { v |= x << at; at += 6; }
+  return v;
+}
+// perm_pqr: 0 ijk, 1 jik, 2 kji, 3 ikj, 4 jki, 5 kij
+constexpr uint64_t kSegsA = wsegs({wseg(0, 0, 0, 0), wseg(3, 0, 0, 1), wseg(2, 0, 1, 0),
+                                   wseg(5, 0, 1, 1), wseg(0, 1, 0, 0), wseg(2, 1, 1, 0),
+                                   wseg(4, 1, 1, 1)});
+constexpr uint64_t kSegsAij = wsegs({wseg(0, 0, 0, 0), wseg(3, 0, 0, 1), wseg(2, 0, 1, 0),
+                                     wseg(0, 1, 0, 0), wseg(2, 1, 1, 0), wseg(4, 1, 1, 1)});
+constexpr uint64_t kSegsAjk = wsegs({wseg(0, 0, 0, 0), wseg(2, 0, 1, 0), wseg(5, 0, 1, 1),
+                                     wseg(0, 1, 0, 0), wseg(2, 1, 1, 0), wseg(1, 1, 0, 1)});
+constexpr uint64_t kSegsB = wsegs({wseg(1, 0, 0, 0), wseg(4, 0, 0, 1), wseg(1, 1, 0, 0),
+                                   wseg(5, 1, 1, 0), wseg(3, 1, 1, 1)});
+
+// `item`: the wave tile, tiles of a plane fastest, then the fixed index y, plane, triple
+template <int MODE, int FM, int FN>
 __device__ __forceinline__ void wbuild_body(const double* __restrict__ t2,
                                             const double* __restrict__ t2N,
                                             const double* __restrict__ Gw,
                                             const double* __restrict__ Go,
-                                            const int* __restrict__ tri,
+                                            const int* __restrict__ tri, int ntri,
                                             double* __restrict__ cubes, int64_t zs, int64_t ss,
                                             int pitch, int no, int nv, int tiles_m, int tiles_n,
-                                            int all_terms, int bx, int by, int bz) {
-  typedef WCfg T;
-  __shared__ double lds[T::LDS_DOUBLES];
-  const int tpp = tiles_m * tiles_n;
-  const int y = bx / tpp;
-  const int tile = bx % tpp;
-  const int m0 = (tile / tiles_n) * T::BM, n0 = (tile % tiles_n) * T::BN;
-  const int plane = by;
-  const int z = bz;
+                                            int all_terms, unsigned item) {
+  const unsigned tpp = (unsigned)(tiles_m * tiles_n);
+  const int tile = (int)(item % tpp);
+  item /= tpp;
+  const int y = (int)(item % (unsigned)nv);
+  item /= (unsigned)nv;
+  const int plane = (int)(item & 1u), z = (int)(item >> 1);
+  if (z >= ntri) return;
   const int i = tri[3 * z], j = tri[3 * z + 1], k = tri[3 * z + 2];
   const int kind = all_terms ? TRI_DISTINCT : tri_kind(i, j, k);
-  // plane 1 repeats plane 0 when i == j, plane 2 repeats plane 0 when j == k
-  if ((kind == TRI_IJ && plane == 1) || (kind == TRI_JK && plane == 2)) return;
-  const bool two = (kind == TRI_DISTINCT) || plane == 0;
-  int p1, q1, r1, p2, q2, r2;
-  if (plane == 0) { p1 = i; q1 = j; r1 = k; p2 = k; q2 = j; r2 = i; }
-  else if (plane == 1) { p1 = j; q1 = i; r1 = k; p2 = k; q2 = i; r2 = j; }
-  else { p1 = i; q1 = k; r1 = j; p2 = j; q2 = k; r2 = i; }
+  if (kind != TRI_DISTINCT && plane == 1) return;
+  const uint64_t segs = plane ? kSegsB
+                        : kind == TRI_DISTINCT ? kSegsA
+                        : kind == TRI_IJ ? kSegsAij : kSegsAjk;
+  const int nd = plane ? 2 : kind == TRI_DISTINCT ? 4 : 3;  // d sums; the l sums are three
+  const int nseg = nd + 3;
+  const int units = nd * ((nv + 7) / 8) + 3 * ((no + 7) / 8);
+  const int m0 = (tile / tiles_n) * (FM * 16), n0 = (tile % tiles_n) * (FN * 16);
+  const int lane = threadIdx.x & 63, r16 = lane & 15, kq = lane >> 4;
+  const int64_t nv2 = (int64_t)nv * nv, gy = gw_pitch(nv), ty = t2n_pitch(no, nv);
 
-  const int64_t nv2 = (int64_t)nv * nv, nv3 = nv2 * nv;
-  const int nvs = (nv + T::BK - 1) / T::BK, nos = (no + T::BK - 1) / T::BK;
-  const int nsteps = two ? 2 * (nvs + nos) : (nvs + nos);
-
-  // Four K segments, each a product of two row-major (row, k) operands with k contiguous:
-  //   term 1: Acc[m][n] += sum_d t2[p1][q1][m][d] Gw[r1][y][n][d]       (K = nv)
-  //                      + sum_l t2N[p1][y][m][l] Go[q1][r1][n][l]      (K = no)
-  //   term 2: Acc[m][n] += sum_d Gw[r2][y][m][d] t2[p2][q2][n][d]       (K = nv)
-  //                      + sum_l Go[q2][r2][m][l] t2N[p2][y][n][l]      (K = no)
-  // with t2N[p][y][x][l] = -t2[p][l][x][y].  The row stride of a segment is its K.
-  // Tile origins (row m0 / n0, k = 0) of the eight operands, as byte pointers:
-  // MODE 1 takes the amplitude pair (q, r), the (v v|. .) slab of p and the (o o|o v)
-  // slab of (p, q) where MODE 0 takes (p, q), r and (q, r)
-  const int ax1 = MODE ? q1 : p1, bx1 = MODE ? r1 : q1, g1 = MODE ? p1 : r1;
-  const int an1 = MODE ? r1 : p1, h1a = MODE ? p1 : q1, h1b = MODE ? q1 : r1;
-  const int ax2 = MODE ? q2 : p2, bx2 = MODE ? r2 : q2, g2 = MODE ? p2 : r2;
-  const int an2 = MODE ? r2 : p2, h2a = MODE ? p2 : q2, h2b = MODE ? q2 : r2;
-  const char* A0 = (const char*)(t2 + ((int64_t)ax1 * no + bx1) * nv2 + (int64_t)m0 * nv);
-  const char* B0 = (const char*)(Gw + ((int64_t)g1 * nv + y) * nv2 + (int64_t)n0 * nv);
-  const char* A1 = (const char*)(t2N + ((int64_t)an1 * nv + y) * nv * no + (int64_t)m0 * no);
-  const char* B1 = (const char*)(Go + ((int64_t)h1a * no + h1b) * nv * no + (int64_t)n0 * no);
-  const char* A2 = (const char*)(Gw + ((int64_t)g2 * nv + y) * nv2 + (int64_t)m0 * nv);
-  const char* B2 = (const char*)(t2 + ((int64_t)ax2 * no + bx2) * nv2 + (int64_t)n0 * nv);
-  const char* A3 = (const char*)(Go + ((int64_t)h2a * no + h2b) * nv * no + (int64_t)m0 * no);
-  const char* B3 = (const char*)(t2N + ((int64_t)an2 * nv + y) * nv * no + (int64_t)n0 * no);
-  // This thread's part of every stage: k = kt and rows xt + e * RP of both tiles.  Rows
-  // past nv repeat row nv - 1 (their outputs are never stored).  Loads go through buffer
-  // resources built from the (uniform) stage origin with 32-bit byte offsets per lane.
-  const int tid = threadIdx.x;
-  constexpr int RP = T::NT / T::BK;
-  const int kt = tid % T::BK, xt = tid / T::BK;
-  int rowa[T::EA], rowb[T::EB];
-#pragma unroll
-  for (int e = 0; e < T::EA; ++e) rowa[e] = min(m0 + xt + e * RP, nv - 1) - m0;
-#pragma unroll
-  for (int e = 0; e < T::EB; ++e) rowb[e] = min(n0 + xt + e * RP, nv - 1) - n0;
-  // swizzled LDS slots of (kt, xt + e * RP): RP is a multiple of 16, so the XOR
-  // pattern of row kt only touches xt
-  const int lda = kt * T::LDA + (xt ^ lds_swz<T::BK>(kt));
-  const int ldb = T::BK * T::LDA + kt * T::LDB + (xt ^ lds_swz<T::BK>(kt));
-  double ra[T::EA], rb[T::EB];
-  int lseg = 0, lk0 = 0;  // the next stage to load
-  int ks_load = 0;         // MFMA k-steps of 4 that hold data in the stage just loaded
-  bool zin = true;         // this lane's k of the stage just loaded lies inside its segment
-  auto fetch = [&]() {
-    const char *pa, *pb;
-    if (lseg == 0) { pa = A0; pb = B0; }
-    else if (lseg == 1) { pa = A1; pb = B1; }
-    else if (lseg == 2) { pa = A2; pb = B2; }
-    else { pa = A3; pb = B3; }
-    const int ld = (lseg & 1) ? no : nv;
-    const BufRsrc sa = buf_rsrc(pa + lk0 * 8), sb = buf_rsrc(pb + lk0 * 8);
-    const bool in = lk0 + kt < ld;                    // the segment's last stage may be partial
-    const int kc = in ? kt : ld - 1 - lk0;           // k past K reads a valid element
-    // The zero of k past K is applied when the stage is stored: a select here would
-    // wait for the loads before the current stage's MFMAs instead of after them.
-#pragma unroll
-    for (int e = 0; e < T::EA; ++e) ra[e] = buf_load_f64(sa, (unsigned)(rowa[e] * ld + kc) * 8u);
-#pragma unroll
-    for (int e = 0; e < T::EB; ++e) rb[e] = buf_load_f64(sb, (unsigned)(rowb[e] * ld + kc) * 8u);
-    zin = in;
-    ks_load = min(T::BK, ld - lk0 + 3) / 4;  // a segment's last stage may be part zeros
-    lk0 += T::BK;
-    if (lk0 >= ld) { lk0 = 0; ++lseg; }
-  };
-  auto store = [&](double* st) {
-#pragma unroll
-    for (int e = 0; e < T::EA; ++e) st[lda + e * RP] = zin ? ra[e] : 0.0;
-#pragma unroll
-    for (int e = 0; e < T::EB; ++e) st[ldb + e * RP] = zin ? rb[e] : 0.0;
-  };
-  d4v acc[T::FM][T::FN];
-  zero_acc<T>(acc);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave % T::WM, wn = wave / T::WM;
-  fetch();
-  store(lds);
-  __syncthreads();
-  for (int s = 0; s < nsteps; ++s) {
-    double* cur = lds + (s & 1) * T::STAGE;
-    double* nxt = lds + ((s + 1) & 1) * T::STAGE;
-    const bool more = s + 1 < nsteps;
-    const int ks = ks_load;  // k-steps of the stage computed now (uniform)
-    if (more) fetch();
-    // as mfma_stage, skipping the k-steps of a segment's last stage that hold only zeros
-#pragma unroll
-    for (int kk = 0; kk < T::BK / 4; ++kk) {
-      if (kk >= ks) break;
-      const int kr = kk * 4 + (lane >> 4);
-      const int sw = (lane & 15) ^ lds_swz<T::BK>(kr);
-      double a[T::FM], b[T::FN];
-#pragma unroll
-      for (int fm = 0; fm < T::FM; ++fm) a[fm] = cur[kr * T::LDA + (wm * T::FM + fm) * 16 + sw];
-#pragma unroll
-      for (int fn = 0; fn < T::FN; ++fn)
-        b[fn] = cur[T::BK * T::LDA + kr * T::LDB + (wn * T::FN + fn) * 16 + sw];
-#pragma unroll
-      for (int fm = 0; fm < T::FM; ++fm)
-#pragma unroll
-        for (int fn = 0; fn < T::FN; ++fn)
-          acc[fm][fn] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[fm], b[fn], acc[fm][fn], 0, 0, 0);
+  // the segment being loaded: resources at row m0 / n0, row strides, K, and the next k
+  BufRsrc ra, rb;
+  int seg = 0, lda, ldb, K, kk;
+  unsigned va, vb;
+  auto open = [&](int s) {
+    const int code = (int)(segs >> (6 * s)) & 63;
+    const bool lsum = code & 8, col = code & 16, strided = code & 32;
+    int p, q, r;
+    perm_pqr(code & 7, i, j, k, p, q, r);
+    const int am0 = col ? n0 : m0, in0 = col ? m0 : n0;  // first rows of the two operands
+    const double *amp, *in;
+    int64_t an, inn;  // doubles left in their arrays
+    int la, li;
+    if (!lsum) {
+      la = nv;
+      const int64_t ao = ((int64_t)(MODE ? q * no + r : p * no + q)) * nv2 + (int64_t)am0 * nv;
+      amp = t2 + ao;
+      an = (int64_t)no * no * nv2 - ao;
+      li = strided ? (int)gy : nv;
+      const int64_t go = (int64_t)(MODE ? p : r) * nv * gy + (strided ? (int64_t)y * nv : y * gy) +
+                         (int64_t)in0 * li;
+      in = Gw + go;
+      inn = (int64_t)no * nv * gy - go;
+      K = nv;
+    } else {
+      la = strided ? (int)ty : no;
+      const int64_t ao = (int64_t)(MODE ? r : p) * nv * ty + (strided ? (int64_t)y * no : y * ty) +
+                         (int64_t)am0 * la;
+      amp = t2N + ao;
+      an = (int64_t)no * nv * ty - ao;
+      li = no;
+      const int64_t go = (int64_t)(MODE ? p * no + q : q * no + r) * nv * no + (int64_t)in0 * no;
+      in = Go + go;
+      inn = (int64_t)no * no * nv * no - go;
+      K = no;
     }
-    if (more) store(nxt);
-    __syncthreads();
+    ra = buf_rsrc_n(col ? in : amp, col ? inn : an);
+    rb = buf_rsrc_n(col ? amp : in, col ? an : inn);
+    lda = col ? li : la;
+    ldb = col ? la : li;
+    va = (unsigned)(r16 * lda + 2 * kq) * 8u;
+    vb = (unsigned)(r16 * ldb + 2 * kq) * 8u;
+    kk = 0;
+  };
+  d2v a[2][FM], b[2][FN];
+  int kn[2];  // k left in the segment at each unit (uniform); below 8 the unit is partial
+  auto fetch = [&](d2v (&fa)[FM], d2v (&fb)[FN], int& n) {
+#pragma unroll
+    for (int f = 0; f < FM; ++f) fa[f] = buf_load_2f64(ra, va, (unsigned)(f * 128 * lda));
+#pragma unroll
+    for (int f = 0; f < FN; ++f) fb[f] = buf_load_2f64(rb, vb, (unsigned)(f * 128 * ldb));
+    n = K - kk;
+    kk += 8;
+    va += 64u;
+    vb += 64u;
+    // past the last segment the loads go on along its rows and are not used
+    if (kk >= K && seg + 1 < nseg) open(++seg);
+  };
+  d4v acc[FM][FN];
+#pragma unroll
+  for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+    for (int fn = 0; fn < FN; ++fn) acc[fm][fn] = d4v{0.0, 0.0, 0.0, 0.0};
+  open(0);
+  fetch(a[0], b[0], kn[0]);
+  fetch(a[1], b[1], kn[1]);
+  for (int u = 0; u < units; u += 2) {
+#pragma unroll
+    for (int d = 0; d < 2; ++d) {
+      if (u + d < units) {
+        if (kn[d] < 8) {  // zero the k past K in both operands
+          const bool i0 = 2 * kq < kn[d], i1 = 2 * kq + 1 < kn[d];
+#pragma unroll
+          for (int f = 0; f < FM; ++f) a[d][f] = d2v{i0 ? a[d][f][0] : 0.0, i1 ? a[d][f][1] : 0.0};
+#pragma unroll
+          for (int f = 0; f < FN; ++f) b[d][f] = d2v{i0 ? b[d][f][0] : 0.0, i1 ? b[d][f][1] : 0.0};
+        }
+        // lane supplies A[m = l%16][k] and B[k][n = l%16], k = 2 (l/16) + t of the unit
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+            for (int fn = 0; fn < FN; ++fn)
+              acc[fm][fn] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[d][fm][t], b[d][fn][t],
+                                                                 acc[fm][fn], 0, 0, 0);
+      }
+      fetch(a[d], b[d], kn[d]);
+    }
   }
 
   double* out = cubes + (int64_t)z * zs + (int64_t)plane * ss + (int64_t)y * nv * pitch;
 #pragma unroll
-  for (int fm = 0; fm < T::FM; ++fm)
+  for (int fm = 0; fm < FM; ++fm)
 #pragma unroll
-    for (int fn = 0; fn < T::FN; ++fn)
+    for (int fn = 0; fn < FN; ++fn)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int m = m0 + acc_row<T>(wm, fm, lane, r);
-        const int n = n0 + acc_col<T>(wn, fn, lane);
+        const int m = m0 + fm * 16 + kq + 4 * r, n = n0 + fn * 16 + r16;
         if (m < nv && n < nv) out[(int64_t)m * pitch + n] = acc[fm][fn][r];
       }
 }
 
-template <int MODE>
-__global__ __launch_bounds__(WCfg::NT) void k_wbuild(const double* __restrict__ t2,
-                                                     const double* __restrict__ t2N,
-                                                     const double* __restrict__ Gw,
-                                                     const double* __restrict__ Go,
-                                                     const int* __restrict__ tri,
-                                                     double* __restrict__ cubes, int64_t zs,
-                                                     int64_t ss, int pitch, int no, int nv,
-                                                     int tiles_m, int tiles_n, int all_terms) {
-  wbuild_body<MODE>(t2, t2N, Gw, Go, tri, cubes, zs, ss, pitch, no, nv, tiles_m, tiles_n,
-                    all_terms, blockIdx.x, blockIdx.y, blockIdx.z);
+// Wave-tile shapes and the wavefronts per SIMD that their registers allow (128, 160, ...
+// accumulator registers and 16 per operand block of the two units in flight).
+struct WaveShape { int fm, fn; };
+constexpr WaveShape kShapes[] = {{4, 4}, {5, 4}, {5, 3}, {4, 3}, {3, 3}, {5, 2}, {3, 2}, {2, 2}};
+constexpr int NSHAPE = sizeof kShapes / sizeof kShapes[0];
+constexpr int shape_waves(int fm, int fn) { return fm * fn <= 4 ? 4 : fm * fn <= 10 ? 3 : 2; }
+
+// The shape with the least MFMA work, padding included, weighted by the loads per MFMA:
+// relative time per block measured at nv = 150 to 400 about 1 + 0.7 (1/FM + 1/FN - 1/2)
+// (3 x 3 1.04 to 1.2, 5 x 2 1.16 to 1.26, 4 x 3 1.0 to 1.09, 5 x 4 0.98 to 1.05 of 4 x 4).
+// The item loop of the packed kernels takes registers that 5 x 4 and 5 x 2 do not leave.
+int pick_shape(int64_t M, int64_t N, bool packed) {
+  int best = 0;
+  double cost = 0.0;
+  for (int s = 0; s < NSHAPE; ++s) {
+    const double fm = kShapes[s].fm, fn = kShapes[s].fn;
+    if (packed && (fm * fn == 20 || fm * fn == 10)) continue;
+    int tm, tn;
+    shape_tiles(s, M, N, &tm, &tn);
+    const double c = tm * fm * tn * fn * (0.65 + 0.7 * (1.0 / fm + 1.0 / fn));
+    if (s == 0 || c < cost) { best = s; cost = c; }
+  }
+  return best;
+}
+
+void shape_tiles(int shape, int64_t M, int64_t N, int* tm, int* tn) {
+  *tm = (int)((M + 16 * kShapes[shape].fm - 1) / (16 * kShapes[shape].fm));
+  *tn = (int)((N + 16 * kShapes[shape].fn - 1) / (16 * kShapes[shape].fn));
+}
+
+// Calls f with the shape's block counts as integral constants.
+template <class F>
+static void with_shape(int shape, F f) {
+  switch (shape) {
+#define CC3_SHAPE(n) \
+  case n:            \
+    f(std::integral_constant<int, kShapes[n].fm>(), std::integral_constant<int, kShapes[n].fn>()); \
+    break;
+    CC3_SHAPE(0) CC3_SHAPE(1) CC3_SHAPE(2) CC3_SHAPE(3) CC3_SHAPE(4) CC3_SHAPE(5) CC3_SHAPE(6)
+    default:
+    CC3_SHAPE(7)
+#undef CC3_SHAPE
+  }
+}
+
+constexpr int WNT = 256;  // four wave tiles per workgroup
+
+template <int MODE, int FM, int FN>
+__global__ __launch_bounds__(WNT, shape_waves(FM, FN)) void k_wbuild(
+    const double* __restrict__ t2, const double* __restrict__ t2N, const double* __restrict__ Gw,
+    const double* __restrict__ Go, const int* __restrict__ tri, int ntri,
+    double* __restrict__ cubes, int64_t zs, int64_t ss, int pitch, int no, int nv, int tiles_m,
+    int tiles_n, int all_terms) {
+  // runs of four planes per XCD: the tiles of a plane share its operand rows in one L2
+  // (the 3 x 3 shape at nv = 250: 49 -> 57 TFLOP/s of MFMA)
+  const unsigned wg = xcd_item(blockIdx.x, gridDim.x, (unsigned)(tiles_m * tiles_n));
+  const unsigned wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  wbuild_body<MODE, FM, FN>(t2, t2N, Gw, Go, tri, ntri, cubes, zs, ss, pitch, no, nv, tiles_m,
+                            tiles_n, all_terms, wg * 4 + wave);
+}
+
+// wave tiles of a W launch: tiles per plane x nv x two planes x triples, four to a workgroup
+static unsigned wbuild_wgs(int nv, int ntri, int shape) {
+  int tm, tn;
+  shape_tiles(shape, nv, nv, &tm, &tn);
+  return (unsigned)(((int64_t)tm * tn * nv * 2 * ntri + 3) / 4);
 }
 
 void launch_wbuild_ex(int mode, const double* X, const double* XN, const double* G, const double* H,
                       const int* tri, int ntri, double* cubes, int64_t zs, int64_t ss, int pitch,
                       int no, int nv, bool all_terms, hipStream_t st) {
-  typedef WCfg T;
   if (ntri <= 0) return;
-  const int tm = (nv + T::BM - 1) / T::BM, tn = (nv + T::BN - 1) / T::BN;
-  if (mode == 0)
-    hipLaunchKernelGGL(k_wbuild<0>, dim3(nv * tm * tn, 3, ntri), dim3(T::NT), 0, st, X, XN, G, H,
-                       tri, cubes, zs, ss, pitch, no, nv, tm, tn, all_terms ? 1 : 0);
-  else
-    hipLaunchKernelGGL(k_wbuild<1>, dim3(nv * tm * tn, 3, ntri), dim3(T::NT), 0, st, X, XN, G, H,
-                       tri, cubes, zs, ss, pitch, no, nv, tm, tn, all_terms ? 1 : 0);
+  const int shape = pick_shape(nv, nv);
+  int tm, tn;
+  shape_tiles(shape, nv, nv, &tm, &tn);
+  const dim3 grid(wbuild_wgs(nv, ntri, shape)), block(WNT);
+  with_shape(shape, [&](auto fm, auto fn) {
+    constexpr int FM = decltype(fm)::value, FN = decltype(fn)::value;
+    if (mode == 0)
+      hipLaunchKernelGGL((k_wbuild<0, FM, FN>), grid, block, 0, st, X, XN, G, H, tri, ntri, cubes,
+                         zs, ss, pitch, no, nv, tm, tn, all_terms ? 1 : 0);
+    else
+      hipLaunchKernelGGL((k_wbuild<1, FM, FN>), grid, block, 0, st, X, XN, G, H, tri, ntri, cubes,
+                         zs, ss, pitch, no, nv, tm, tn, all_terms ? 1 : 0);
+  });
 }
 
 void launch_wbuild(const double* t2, const double* t2N, const Blocks& b, const int* tri, int ntri,
@@ -235,7 +329,7 @@ __global__ void k_t2N(const double* __restrict__ t2, double* __restrict__ t2N, i
   if (e >= n) return;
   const int l = (int)(e % no), x = (int)((e / no) % nvl), y = (int)((e / (no * nvl)) % nvl);
   const int p = (int)(e / (no * nvl * nvl));
-  t2N[e] = -t2[(((int64_t)p * no + l) * nvl + x) * nvl + y];
+  t2N[((int64_t)p * nvl + y) * t2n_pitch(no, nv) + (int64_t)x * no + l] = -t2[(((int64_t)p * no + l) * nvl + x) * nvl + y];
 }
 
 void launch_t2N(const double* t2, double* t2N, int no, int nv, hipStream_t st) {
@@ -284,20 +378,15 @@ __device__ inline void decode_block_triple(int idx, int& A, int& B, int& C) {
 // Threads per mix workgroup (MIXT, 256 or 512): each handles MIXH = 512 / MIXT of
 // the 512 elements of an orientation tile.
 
-__device__ inline double xval(const double* __restrict__ cz, int kind, int64_t nv, int a, int b,
-                              int c) {
+// X of a triple whose six terms were all built (kind TRI_DISTINCT)
+template <bool TWO>
+__device__ inline double xval(const double* __restrict__ cz, int64_t nv, int a, int b, int c) {
   const int64_t rp = cube_pitch((int)nv), pl = nv * rp, cs = cube_slot((int)nv);
   const double* P0 = cz + SLOT_P0 * cs;
   const double* P1 = cz + SLOT_P1 * cs;
-  const double* P2 = cz + SLOT_P2 * cs;
-  if (kind == TRI_DISTINCT)
-    return P0[b * pl + a * rp + c] + P1[a * pl + b * rp + c] + P2[c * pl + a * rp + b];
-  if (kind == TRI_IJ)  // P1 = P0, P2[c][a][b] = Q[c][a][b] + Q[c][b][a]
-    return P0[b * pl + a * rp + c] + P0[a * pl + b * rp + c] + P2[c * pl + a * rp + b] +
-           P2[c * pl + b * rp + a];
-  // TRI_JK: P2 = P0, P1[a][b][c] = R[a][b][c] + R[a][c][b]
-  return P0[b * pl + a * rp + c] + P1[a * pl + b * rp + c] + P1[a * pl + c * rp + b] +
-         P0[c * pl + a * rp + b];
+  double x = P0[b * pl + a * rp + c] + P1[a * pl + b * rp + c];
+  if (!TWO) x += cz[SLOT_P2 * cs + c * pl + a * rp + b];
+  return x;
 }
 
 // The split-BF16 pieces of x at row `row` and K pair (kx, ky) of view v of triple z in
@@ -323,8 +412,12 @@ __device__ inline void yl_put(uint16_t* YL, int P, int z, int v, int row, int kx
 
 // Mixed-all copies (nullable): cubesF, FP32 tau~ and tau~T, [triple][2][nv^3];
 // YL, the split-BF16 k-major views of the split-BF16 Omega GEMM (k_omega_lp),
-// [triple][4][piece][a][kk < Kp] with lpP pieces.
-template <int MIXT>
+// [triple][4][piece][a][kk < Kp] with lpP pieces.  TWO: the two planes of the FP64 W
+// build, X = PA[b][a][c] + PB[a][b][c] (PA[a][b][c] for i == j, PA[c][a][b] for j == k in
+// the place of PB); otherwise the three planes of the low-precision build,
+// X = P0[b][a][c] + P1[a][b][c] + P2[c][a][b], where for i == j P1 = P0 and P2 is
+// symmetrised over (a, b), and for j == k P2 = P0 and P1 is symmetrised over (b, c).
+template <int MIXT, bool TWO>
 __device__ __forceinline__ void mix_body(const double* __restrict__ eps,
                                          const int* __restrict__ tri, double* __restrict__ cubes,
                                          float* __restrict__ cubesF, uint16_t* __restrict__ YL,
@@ -378,31 +471,36 @@ __device__ __forceinline__ void mix_body(const double* __restrict__ eps,
       const int a = A0 + u, b = B0 + v, c = C0 + w;
       double x = 0.0;
       if (a < nv && b < nv && c < nv)
-        x = P0[b * pl + a * rp + c] + (kind == TRI_IJ ? P0 : P1)[a * pl + b * rp + c];
+        x = TWO && kind == TRI_JK
+                ? P0[b * pl + a * rp + c]
+                : P0[b * pl + a * rp + c] + (kind == TRI_IJ ? P0 : P1)[a * pl + b * rp + c];
       Xs[o * TSZ + TP(u, v, w)] = x;
     }
   }
-  __syncthreads();
+  if (!TWO || kind == TRI_JK) {
+    __syncthreads();
 #pragma unroll
-  for (int o = 0; o < 6; ++o) {
-    if (canon[o] != o) continue;
-    int q0, q1, q2;
-    orient(o, q0, q1, q2);
-    const int A0 = blk[q0] * MT, B0 = blk[q1] * MT, C0 = blk[q2] * MT;
+    for (int o = 0; o < 6; ++o) {
+      if (canon[o] != o) continue;
+      int q0, q1, q2;
+      orient(o, q0, q1, q2);
+      const int A0 = blk[q0] * MT, B0 = blk[q1] * MT, C0 = blk[q2] * MT;
 #pragma unroll
-    for (int h = 0; h < MIXH; ++h) {
-      const int e = t + MIXT * h;
-      const int u = e >> 6, w = (e >> 3) & 7, v = e & 7;  // pass 1: b fastest
-      const int a = A0 + u, b = B0 + v, c = C0 + w;
-      if (a < nv && b < nv && c < nv) {
-        double x;
-        if (kind == TRI_JK) x = P1[a * pl + c * rp + b] + P0[c * pl + a * rp + b];
-        else x = P2[c * pl + a * rp + b];
-        Xs[o * TSZ + TP(u, v, w)] += x;
+      for (int h = 0; h < MIXH; ++h) {
+        const int e = t + MIXT * h;
+        const int u = e >> 6, w = (e >> 3) & 7, v = e & 7;  // pass 1: b fastest
+        const int a = A0 + u, b = B0 + v, c = C0 + w;
+        if (a < nv && b < nv && c < nv) {
+          double x;
+          if (TWO) x = P0[c * pl + a * rp + b];
+          else if (kind == TRI_JK) x = P1[a * pl + c * rp + b] + P0[c * pl + a * rp + b];
+          else x = P2[c * pl + a * rp + b];
+          Xs[o * TSZ + TP(u, v, w)] += x;
+        }
       }
     }
   }
-  if (kind == TRI_IJ) {
+  if (!TWO && kind == TRI_IJ) {
     __syncthreads();
 #pragma unroll
     for (int o = 0; o < 6; ++o) {
@@ -504,33 +602,36 @@ __device__ __forceinline__ void mix_body(const double* __restrict__ eps,
   }
 }
 
-template <int MIXT>
+template <int MIXT, bool TWO>
 __global__ __launch_bounds__(MIXT) void k_mix(const double* __restrict__ eps,
                                              const int* __restrict__ tri,
                                              double* __restrict__ cubes, float* __restrict__ cubesF,
                                              uint16_t* __restrict__ YL, int lpP, int no, int nv) {
-  mix_body<MIXT>(eps, tri, cubes, cubesF, YL, lpP, no, nv, blockIdx.x, blockIdx.y);
+  mix_body<MIXT, TWO>(eps, tri, cubes, cubesF, YL, lpP, no, nv, blockIdx.x, blockIdx.y);
 }
 
-void launch_mix(const double* eps, const int* tri, int ntri, double* cubes, float* cubesF,
-                void* YL, int lpP, int no, int nv, hipStream_t st) {
+void launch_mix(bool two_planes, const double* eps, const int* tri, int ntri, double* cubes,
+                float* cubesF, void* YL, int lpP, int no, int nv, hipStream_t st) {
   const int nb = (nv + MT - 1) / MT;
   const int nbt = nb * (nb + 1) * (nb + 2) / 6;
   // 512 threads, one element per thread and orientation; the form that also writes
   // the split-BF16 views of tau~ runs with 256 (two elements each), which measured
   // faster for it at nv = 250
-  if (YL)
-    hipLaunchKernelGGL(k_mix<256>, dim3(nbt, ntri), dim3(256), 0, st, eps, tri, cubes, cubesF,
-                       (uint16_t*)YL, lpP, no, nv);
+  if (two_planes)
+    hipLaunchKernelGGL((k_mix<512, true>), dim3(nbt, ntri), dim3(512), 0, st, eps, tri, cubes,
+                       nullptr, nullptr, 0, no, nv);
+  else if (YL)
+    hipLaunchKernelGGL((k_mix<256, false>), dim3(nbt, ntri), dim3(256), 0, st, eps, tri, cubes,
+                       cubesF, (uint16_t*)YL, lpP, no, nv);
   else
-    hipLaunchKernelGGL(k_mix<512>, dim3(nbt, ntri), dim3(512), 0, st, eps, tri, cubes, cubesF,
-                       (uint16_t*)YL, lpP, no, nv);
+    hipLaunchKernelGGL((k_mix<512, false>), dim3(nbt, ntri), dim3(512), 0, st, eps, tri, cubes,
+                       cubesF, (uint16_t*)YL, lpP, no, nv);
 }
 
 // ---------------------------------------------------------------------------
 // Mix of the transition-density loop (Algorithm 3).  Cubes are slot-major,
 // cubes[slot][z][cube] (slot stride ss; each cube nv x nv rows at the padded pitch
-// cube_pitch), so that each slot of a batch is one contiguous run of cubes.  LMODE false: from the t3 planes, tau = -X/eps and
+// cube_pitch), so that each slot of a batch is one contiguous run of cubes.  LMODE false: from the t3 planes (PA, PB), tau = -X/eps and
 // tau~ (the contravariant combination) into slots D3_TAU, D3_TAUC.  LMODE true:
 // from the L3 planes plus the outer-product terms of the L3 statement,
 //   sum over the six simultaneous permutations (p,q,r; x,y,z) of (i,j,k; a,b,c) of
@@ -565,9 +666,8 @@ __global__ __launch_bounds__(512) void k_mix3(const double* __restrict__ eps,
   const int64_t nvl = nv;
   // the padded cube rows: pitch rp, plane pl, cube cs
   const int64_t rp = cube_pitch(nv), pl = nvl * rp, cs = cube_slot(nv);
-  const double* P0 = cubes + D3_P0 * ss + (int64_t)z * cs;
-  const double* P1 = cubes + D3_P1 * ss + (int64_t)z * cs;
-  const double* P2 = cubes + D3_P2 * ss + (int64_t)z * cs;
+  const double* PA = cubes + D3_PA * ss + (int64_t)z * cs;
+  const double* PB = cubes + D3_PB * ss + (int64_t)z * cs;
   int blk[3];
   decode_block_triple(ob, blk[0], blk[1], blk[2]);
   int canon[6];
@@ -586,7 +686,7 @@ __global__ __launch_bounds__(512) void k_mix3(const double* __restrict__ eps,
   }
   const int t = threadIdx.x;
   const int u = t >> 6, v = (t >> 3) & 7, w = t & 7;
-  // X on the orbit: the plane sums of k_mix (c, b, then a fastest), plus the outer
+  // X on the orbit: the two-plane sum of k_mix (c, then b fastest), plus the outer
   // products in the L3 form
 #pragma unroll
   for (int o = 0; o < 6; ++o) {
@@ -596,36 +696,23 @@ __global__ __launch_bounds__(512) void k_mix3(const double* __restrict__ eps,
     const int a = blk[q0] * MT + u, b = blk[q1] * MT + v, c = blk[q2] * MT + w;
     double x = 0.0;
     if (a < nv && b < nv && c < nv) {
-      x = P0[b * pl + a * rp + c] + (kind == TRI_IJ ? P0 : P1)[a * pl + b * rp + c];
+      x = PA[b * pl + a * rp + c];
+      if (kind != TRI_JK) x += (kind == TRI_IJ ? PA : PB)[a * pl + b * rp + c];
       if (LMODE) x += l3_outer(l1, l2, Jo, F, no, nvl, i, j, k, a, b, c);
     }
     Xs[o * TSZ + TP(u, v, w)] = x;
   }
-  __syncthreads();
-#pragma unroll
-  for (int o = 0; o < 6; ++o) {
-    if (canon[o] != o) continue;
-    int q0, q1, q2;
-    orient(o, q0, q1, q2);
-    const int uu = t >> 6, ww = (t >> 3) & 7, vv = t & 7;  // b fastest
-    const int a = blk[q0] * MT + uu, b = blk[q1] * MT + vv, c = blk[q2] * MT + ww;
-    if (a < nv && b < nv && c < nv) {
-      double x;
-      if (kind == TRI_JK) x = P1[a * pl + c * rp + b] + P0[c * pl + a * rp + b];
-      else x = P2[c * pl + a * rp + b];
-      Xs[o * TSZ + TP(uu, vv, ww)] += x;
-    }
-  }
-  if (kind == TRI_IJ) {
+  if (kind == TRI_JK) {
     __syncthreads();
 #pragma unroll
     for (int o = 0; o < 6; ++o) {
       if (canon[o] != o) continue;
       int q0, q1, q2;
       orient(o, q0, q1, q2);
-      const int vv = t >> 6, ww = (t >> 3) & 7, uu = t & 7;  // a fastest
+      const int uu = t >> 6, ww = (t >> 3) & 7, vv = t & 7;  // b fastest
       const int a = blk[q0] * MT + uu, b = blk[q1] * MT + vv, c = blk[q2] * MT + ww;
-      if (a < nv && b < nv && c < nv) Xs[o * TSZ + TP(uu, vv, ww)] += P2[c * pl + b * rp + a];
+      if (a < nv && b < nv && c < nv)
+        Xs[o * TSZ + TP(uu, vv, ww)] += PA[c * pl + a * rp + b];
     }
   }
   __syncthreads();
@@ -679,6 +766,7 @@ void launch_mix3(bool lmode, const double* eps, const int* tri, int ntri, double
 }
 
 // tau^{abc}_{ijk} = -X / eps^{abc}_{ijk} for one ordered triple whose six terms were all built
+template <bool TWO>
 __global__ void k_tau_export(const double* __restrict__ eps, const int* __restrict__ tri,
                              const double* __restrict__ cubes, double* __restrict__ tau, int no,
                              int nv) {
@@ -687,15 +775,19 @@ __global__ void k_tau_export(const double* __restrict__ eps, const int* __restri
   if (e >= nv3) return;
   const int a = (int)(e / (nvl * nvl)), b = (int)((e / nvl) % nvl), c = (int)(e % nvl);
   const int i = tri[0], j = tri[1], k = tri[2];
-  const double X = xval(cubes, TRI_DISTINCT, nvl, a, b, c);
+  const double X = xval<TWO>(cubes, nvl, a, b, c);
   tau[e] = -X / (eps[no + a] + eps[no + b] + eps[no + c] - eps[i] - eps[j] - eps[k]);
 }
 
-void launch_tau_export(const double* eps, const int* tri, const double* cubes, double* tau, int no,
-                       int nv, hipStream_t st) {
+void launch_tau_export(bool two_planes, const double* eps, const int* tri, const double* cubes,
+                       double* tau, int no, int nv, hipStream_t st) {
   const int64_t nv3 = (int64_t)nv * nv * nv;
-  hipLaunchKernelGGL(k_tau_export, dim3(nblk(nv3, 256)), dim3(256), 0, st, eps, tri, cubes, tau,
-                     no, nv);
+  if (two_planes)
+    hipLaunchKernelGGL(k_tau_export<true>, dim3(nblk(nv3, 256)), dim3(256), 0, st, eps, tri, cubes,
+                       tau, no, nv);
+  else
+    hipLaunchKernelGGL(k_tau_export<false>, dim3(nblk(nv3, 256)), dim3(256), 0, st, eps, tri, cubes,
+                       tau, no, nv);
 }
 
 // ---------------------------------------------------------------------------
@@ -1502,22 +1594,21 @@ __device__ inline int pack_job(const PackJob* __restrict__ jobs, int njobs, int 
   return r;
 }
 
-__global__ __launch_bounds__(WCfg::NT) void k_pack_wbuild(const PackJob* __restrict__ jobs,
-                                                          int njobs, unsigned total) {
-  typedef WCfg T;
+template <int FM, int FN>
+__global__ __launch_bounds__(WNT, shape_waves(FM, FN)) void k_pack_wbuild(
+    const PackJob* __restrict__ jobs, int njobs, unsigned total) {
   for (unsigned item = blockIdx.x; item < total; item += gridDim.x) {
     const PackJob& J = jobs[pack_job(jobs, njobs, PK_W, item)];
     const unsigned local = item - J.first[PK_W];
-    const int tm = (J.nv + T::BM - 1) / T::BM, tn = (J.nv + T::BN - 1) / T::BN;
-    const unsigned gx = (unsigned)J.nv * tm * tn;
+    const int tm = (J.nv + 16 * FM - 1) / (16 * FM), tn = (J.nv + 16 * FN - 1) / (16 * FN);
     const int64_t cs = cube_slot(J.nv);
-    wbuild_body<0>(J.t2, J.t2N, J.Gw, J.Go, J.tri, J.cubes, NSLOT * cs, cs, cube_pitch(J.nv), J.no,
-                   J.nv, tm, tn, 0, (int)(local % gx), (int)((local / gx) % 3),
-                   (int)(local / (gx * 3)));
-    __syncthreads();
+    const unsigned wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    wbuild_body<0, FM, FN>(J.t2, J.t2N, J.Gw, J.Go, J.tri, J.ntri, J.cubes, NSLOT * cs, cs,
+                           cube_pitch(J.nv), J.no, J.nv, tm, tn, 0, local * 4 + wave);
   }
 }
 
+template <bool TWO>
 __global__ __launch_bounds__(512) void k_pack_mix(const PackJob* __restrict__ jobs, int njobs,
                                                   unsigned total) {
   for (unsigned item = blockIdx.x; item < total; item += gridDim.x) {
@@ -1525,7 +1616,7 @@ __global__ __launch_bounds__(512) void k_pack_mix(const PackJob* __restrict__ jo
     const unsigned local = item - J.first[PK_MIX];
     const int nb = (J.nv + MT - 1) / MT;
     const unsigned nbt = (unsigned)(nb * (nb + 1) * (nb + 2) / 6);
-    mix_body<512>(J.eps, J.tri, J.cubes, nullptr, nullptr, 0, J.no, J.nv, (int)(local % nbt),
+    mix_body<512, TWO>(J.eps, J.tri, J.cubes, nullptr, nullptr, 0, J.no, J.nv, (int)(local % nbt),
                   (int)(local / nbt));
     __syncthreads();
   }
@@ -1571,10 +1662,9 @@ __global__ __launch_bounds__(256) void k_pack_reduce(const PackJob* __restrict__
   }
 }
 
-void pack_items(const PackJob& j, unsigned (&items)[PK_N]) {
+void pack_items(const PackJob& j, int prec, unsigned (&items)[PK_N]) {
   const int no = j.no, nv = j.nv, nt = j.ntri;
-  const unsigned tw = (unsigned)((nv + WCfg::BM - 1) / WCfg::BM) * ((nv + WCfg::BN - 1) / WCfg::BN);
-  items[PK_W] = (unsigned)nv * tw * 3u * nt;
+  items[PK_W] = prec == CC3_FP64 ? wbuild_wgs(nv, nt, j.wshape) : wbuild_lp_wgs(nv, nt);
   const int nb = (nv + MT - 1) / MT;
   items[PK_MIX] = (unsigned)(nb * (nb + 1) * (nb + 2) / 6) * nt;
   const unsigned to = (unsigned)((nv + OCfg::BM - 1) / OCfg::BM) * ((nv + 1 + OCfg::BN - 1) / OCfg::BN);
@@ -1586,9 +1676,6 @@ void pack_items(const PackJob& j, unsigned (&items)[PK_N]) {
 // persistent grids: a few rounds of resident workgroups, never more than the items
 static unsigned pack_grid(unsigned total, unsigned cap) { return total < cap ? total : cap; }
 
-void launch_wbuild_lp_packed(const PackJob* jobs, int njobs, unsigned total, int prec,
-                             hipStream_t st);
-
 void launch_packed_step(const PackJob* dev_jobs, const PackJob* host_jobs, int njobs, int prec,
                         hipStream_t st) {
   if (njobs <= 0) return;
@@ -1596,17 +1683,22 @@ void launch_packed_step(const PackJob* dev_jobs, const PackJob* host_jobs, int n
   int max_no = 1;
   for (int r = 0; r < njobs; ++r) {
     unsigned it[PK_N];
-    pack_items(host_jobs[r], it);
+    pack_items(host_jobs[r], prec, it);
     for (int k = 0; k < PK_N; ++k) total[k] += it[k];
     max_no = std::max(max_no, host_jobs[r].no);
   }
-  if (prec == CC3_FP64)
-    hipLaunchKernelGGL(k_pack_wbuild, dim3(pack_grid(total[PK_W], 2048)), dim3(WCfg::NT), 0, st,
-                       dev_jobs, njobs, total[PK_W]);
-  else
+  const dim3 gmix(pack_grid(total[PK_MIX], 4096));
+  if (prec == CC3_FP64) {
+    with_shape(host_jobs[0].wshape, [&](auto fm, auto fn) {
+      hipLaunchKernelGGL((k_pack_wbuild<decltype(fm)::value, decltype(fn)::value>),
+                         dim3(pack_grid(total[PK_W], 4096)), dim3(WNT), 0, st, dev_jobs, njobs,
+                         total[PK_W]);
+    });
+    hipLaunchKernelGGL(k_pack_mix<true>, gmix, dim3(512), 0, st, dev_jobs, njobs, total[PK_MIX]);
+  } else {
     launch_wbuild_lp_packed(dev_jobs, njobs, total[PK_W], prec, st);
-  hipLaunchKernelGGL(k_pack_mix, dim3(pack_grid(total[PK_MIX], 4096)), dim3(512), 0, st, dev_jobs,
-                     njobs, total[PK_MIX]);
+    hipLaunchKernelGGL(k_pack_mix<false>, gmix, dim3(512), 0, st, dev_jobs, njobs, total[PK_MIX]);
+  }
   hipLaunchKernelGGL(k_pack_omega, dim3(pack_grid(total[PK_OMEGA], 2048)), dim3(OCfg::NT), 0, st,
                      dev_jobs, njobs, total[PK_OMEGA]);
   const dim3 goo(pack_grid(total[PK_OO], 8192));

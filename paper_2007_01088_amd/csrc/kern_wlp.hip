@@ -110,7 +110,7 @@ void launch_lp_convert(const double* t2, const Blocks& b, int no, int nv, const 
       lp_copy<M>(t2 + (int64_t)p * o * v * v, 1, v, v * v, -1.0, nv, nv, no,
                  (char*)lp.t2N + (size_t)p * v * v * lk * esz, o * v * v * lk, st);
     // GwTL[r][y][z][d] = Gw[r][y][z][d]: outer = (r, y), x = z, k = d
-    lp_copy<M>(b.Gw, v * v, v, 1, 1.0, no * nv, nv, nv, lp.GwT, o * v * v * dk, st);
+    lp_copy<M>(b.Gw, gw_pitch(nv), v, 1, 1.0, no * nv, nv, nv, lp.GwT, o * v * v * dk, st);
     // GoTL[q][r][z][l] = Go[q][r][z][l]: outer = (q, r), x = z, k = l
     lp_copy<M>(b.Go, o * v, o, 1, 1.0, no * no, nv, no, lp.GoT, o * o * v * lk, st);
   };
@@ -682,6 +682,11 @@ __global__ __launch_bounds__(LNT) void k_pack_wbuild_lp(const PackJob* __restric
                       (int)(local % gx), (int)((local / gx) % 3), (int)(local / (gx * 3)));
     __syncthreads();
   }
+}
+
+unsigned wbuild_lp_wgs(int nv, int ntri) {
+  return (unsigned)nv * (unsigned)((nv + LBM - 1) / LBM) * (unsigned)((nv + LBN - 1) / LBN) * 3u *
+         (unsigned)ntri;
 }
 
 void launch_wbuild_lp_packed(const PackJob* jobs, int njobs, unsigned total, int prec,

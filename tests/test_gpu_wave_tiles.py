@@ -1,0 +1,45 @@
+"""The FP64 GEMMs at the edges of their wave tiles: virtual sizes around multiples of 16
+(blocks) and around the changes of the wave-tile shape, with distinct triples and both
+kinds of equal pairs, and occupied sizes around the 8-k load unit.  Each whole call is
+compared with the CPU oracle at the FP64 bar of the parity tests, 1e-11 (products and sums
+of K < 1e5 random terms in FP64 stay below 1e-13)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import cc3_oracle as O
+from paper_2007_01088_amd import cc3
+from paper_2007_01088_amd.synth import make_inputs
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-11
+
+
+def rel(x, ref):
+    return np.linalg.norm(x - ref) / max(np.linalg.norm(ref), 1e-300)
+
+
+@pytest.mark.parametrize("no,nv", [
+    (3, 1), (2, 15), (3, 16), (3, 17), (4, 31), (3, 32), (3, 33), (7, 47), (8, 48), (9, 49),
+    (3, 64), (3, 65), (2, 80), (3, 81), (3, 96), (2, 97), (3, 127), (3, 129), (3, 145), (2, 160),
+    (2, 161), (2, 193)])
+def test_residual_at_tile_edges(no, nv):
+    d = make_inputs(no, nv, 2 * (no + nv), tag=21)
+    ctx = cc3.Context(0)
+    g = {k: torch.from_numpy(d[k]).cuda() for k in ("eps", "L", "t1", "t2")}
+    o1, o2 = ctx.triples_residual(g["eps"], g["L"], g["t1"], g["t2"])
+    r1, r2 = O.triples_residual(d["eps"], d["L"], d["t1"], d["t2"])
+    assert rel(o1.cpu().numpy(), r1) < TOL
+    assert rel(o2.cpu().numpy(), r2) < TOL
+
+
+@pytest.mark.parametrize("ijk", [(2, 1, 0), (0, 1, 2), (1, 2, 0), (2, 2, 1), (1, 2, 2), (2, 1, 2)])
+def test_t3_block_orderings(ijk):
+    """The planes of every kind of ordered triple (the export builds all six terms)."""
+    no, nv = 3, 37
+    d = make_inputs(no, nv, 80, tag=22)
+    ctx = cc3.Context(0)
+    g = {k: torch.from_numpy(d[k]).cuda() for k in ("eps", "L", "t1", "t2")}
+    tau = ctx.t3_block(g["eps"], g["L"], g["t1"], g["t2"], *ijk).cpu().numpy()
+    blk = O.IntegralBlocks(O.t1_transform(d["L"], d["t1"]), no)
+    assert rel(tau, O.t3_amplitudes(*ijk, d["eps"], d["t2"], blk)) < TOL
