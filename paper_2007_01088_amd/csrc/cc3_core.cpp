@@ -179,7 +179,7 @@ static int env_int(const char* name, int dflt) {
 
 size_t block_bytes(int no, int nv) {
   const size_t o = no, v = nv;
-  return align256(o * v * gw_pitch(nv) * 8) + align256(o * (v + o) * v * v * 8) * 2 +
+  return align256(o * v * gw_pitch(nv) * 8) + align256(o * (v + o) * g_pitch(nv) * 8) * 2 +
          align256(o * o * o * v * 8) * 2 + align256(o * o * v * v * 8) + align256(o * v * 8);
 }
 
@@ -188,8 +188,8 @@ Blocks carve_blocks(int no, int nv, void* base) {
   char* b = (char*)base;
   Blocks bl;
   bl.Gw = (double*)b; b += align256(o * v * gw_pitch(nv) * 8);
-  bl.Gbc = (double*)b; b += align256(o * (v + o) * v * v * 8);
-  bl.Gcb = (double*)b; b += align256(o * (v + o) * v * v * 8);
+  bl.Gbc = (double*)b; b += align256(o * (v + o) * g_pitch(nv) * 8);
+  bl.Gcb = (double*)b; b += align256(o * (v + o) * g_pitch(nv) * 8);
   bl.Go = (double*)b; b += align256(o * o * o * v * 8);
   bl.Hs = (double*)b; b += align256(o * o * o * v * 8);
   bl.Jo = (double*)b; b += align256(o * o * v * v * 8);
@@ -413,9 +413,9 @@ static int triple_loop_body(Runner& rn, Profiler* pf, const Plan& p, const Ws& w
   const bool lowp_contract = w.GbcX != nullptr;
   const int lpP = !lowp_contract || p.prec == CC3_FP32 ? 0 : p.prec == CC3_BF16X3 ? 2 : 3;
   if (lowp_contract && lpP == 0) {
-    const int64_t gn = (int64_t)p.no * (p.nv + p.no) * p.nv * p.nv;
-    launch_to_f32(w.b.Gbc, (float*)w.GbcX, gn, st);
-    launch_to_f32(w.b.Gcb, (float*)w.GcbX, gn, st);
+    const int64_t rows = (int64_t)p.no * (p.nv + p.no);
+    launch_g_to_f32(w.b.Gbc, (float*)w.GbcX, rows, p.nv, st);
+    launch_g_to_f32(w.b.Gcb, (float*)w.GcbX, rows, p.nv, st);
   } else if (lowp_contract) {
     launch_lp_contract_convert(w.b, p.prec, p.no, p.nv, w.GbcX, w.GcbX, st);
     for (int k = 0; k < 2; ++k)
@@ -536,13 +536,14 @@ int packed_residuals(const std::vector<PackMember>& ms, int prec, PackJob* dev_j
     if (prec != CC3_FP64) launch_lp_convert(m.t2, m.w.b, no, nv, m.w.lp, st);
     nsteps = std::max(nsteps, nbatches(p));
   }
-  // one wave-tile shape for the group: that of its member with the most W work
+  // one wave-tile shape per kernel for the group: that of its member with the most work
   const Plan* big = ms[0].p;
   for (const PackMember& m : ms)
     if ((double)m.p->ntri * m.p->nv * m.p->nv * m.p->nv * m.p->nv >
         (double)big->ntri * big->nv * big->nv * big->nv * big->nv)
       big = m.p;
   const int wshape = pick_shape(big->nv, big->nv, true);
+  const int oshape = pick_shape(big->nv, big->nv + 1, true);
   host_jobs.assign((size_t)nsteps * nm, PackJob{});
   std::vector<int> njobs(nsteps, 0);
   for (int s = 0; s < nsteps; ++s) {
@@ -562,6 +563,7 @@ int packed_residuals(const std::vector<PackMember>& ms, int prec, PackJob* dev_j
       j.Ot1 = m.w.Ot1; j.Ot2 = m.w.Ot2; j.OtT = m.w.OtT;
       j.no = p.no; j.nv = p.nv; j.ntri = nb; j.nch = omega_kchunks(p.nv, nb);
       j.wshape = wshape;
+      j.oshape = oshape;
       unsigned it[PK_N];
       pack_items(j, prec, it);
       for (int k = 0; k < PK_N; ++k) { j.first[k] = first[k]; first[k] += it[k]; }

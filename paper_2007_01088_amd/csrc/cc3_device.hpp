@@ -38,6 +38,9 @@ __device__ inline double buf_load_f64(BufRsrc r, unsigned off) {
   return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
 }
 
+__device__ inline float buf_load_f32(BufRsrc r, unsigned off) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
+}
 // A resource of n doubles from base (at most 2 GiB; the hardware checks each dword and
 // returns zero past the end, so rows and k past an operand's last element are safe to
 // load), and 16-byte loads at a per-lane and a uniform byte offset.

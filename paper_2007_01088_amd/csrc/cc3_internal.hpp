@@ -72,9 +72,9 @@ __host__ __device__ inline int64_t lp_kb(int x, int y, int nv) {
 // The cubes of the triple loop (W planes P0..P2, tau~ and tau~T, [x][y][z] per slot)
 // keep their rows of nv values at a pitch padded to a multiple of 8 doubles, so that the
 // row segments of 8 or 16 values that the W build, the mix and the Omega kernels move
-// start on 64-byte boundaries; the padding columns are never read.  cube_slot is the
-// doubles of one slot.  (The low-precision copies and the transition-density cubes
-// are not padded.)
+// start on 64-byte boundaries.  The padding columns of tau~ hold zeros (the Omega GEMM's
+// K runs over them); those of the other slots are never read.  cube_slot is the doubles
+// of one slot.  (The low-precision copies are not padded.)
 __host__ __device__ inline int cube_pitch(int nv) { return (nv + 7) & ~7; }
 __host__ __device__ inline int64_t cube_slot(int nv) {
   return (int64_t)nv * nv * cube_pitch(nv);
@@ -92,13 +92,20 @@ __host__ __device__ inline int64_t t2n_pitch(int no, int nv) {
   return odd_line_pitch((int64_t)nv * no);
 }
 
+// row of Gbc / Gcb for one (r, n): nv x cube_pitch(nv) values
+__host__ __device__ inline int64_t g_pitch(int nv) {
+  return odd_line_pitch((int64_t)nv * cube_pitch(nv));
+}
+
 // Device-resident, internally laid out integral blocks (all float64):
 //   Gw[r][y][z][d] = g_{ydzr}         (vv|vo), the W contraction operand (d fastest),
 //                     each (r, y) slab at the pitch gw_pitch
 //   Go[q][r][z][l] = g_{lqzr}         (oo|vo) (l fastest)
 //   Gbc[r][n][b][c] = g_{nbrc} for n < nv (vv|ov), g_{lbrc} for n = nv + l (ov|ov):
-//                     the Omega contraction operand, K = (b, c) contiguous
-//   Gcb[r][n][c][b] = the same values with K = (c, b) contiguous
+//                     the Omega contraction operand, K = (b, c) contiguous with the c rows
+//                     at the pitch of the cubes and zeros in their padding, each (r, n)
+//                     row at the pitch g_pitch
+//   Gcb[r][n][c][b] = the same values with K = (c, b)
 //   Jo[q][r][b][c] = g_{qbrc}         (ov|ov)
 //   Hs[q][r][c][l] = delta_{lq} F_rc - g_{qlrc}   (oo|ov) and the Fock ov block (l fastest)
 //   F[k][c]
@@ -212,7 +219,8 @@ void launch_omega_oo(const double* cubes, const Blocks& b, const int* tri, int n
 // (tau~, tau~T per triple) and of Gbc / Gcb; partial slabs in FP64 as above.
 void launch_omega_f32(const float* cubesF, const float* GbcF, const float* GcbF, const int* tri,
                       int ntri, double* Pvv, int no, int nv, hipStream_t st);
-void launch_to_f32(const double* src, float* dst, int64_t n, hipStream_t st);
+// dst[row][x][y] = the FP32 rounding of the rows of Gbc or Gcb, without their padding
+void launch_g_to_f32(const double* src, float* dst, int64_t rows, int nv, hipStream_t st);
 // The mixed-all form with split BF16 (kern_wlp.hip): bytes of one of the two
 // operand blocks and of one triple's views; their conversion, the views' K
 // padding, and the GEMM.
@@ -257,7 +265,8 @@ struct PackJob {
   const int* tri;                             // the job's batch of triples
   double *cubes, *Pvv, *Ot1, *Ot2, *OtT;
   int no, nv, ntri, nch;
-  int wshape;            // wave-tile shape of the FP64 W build, the same for every job
+  int wshape, oshape;    // wave-tile shapes of the FP64 W build and Omega GEMM, the same
+                         // for every job
   unsigned first[PK_N];  // first packed work item of this job, per kernel
 };
 // Work items of one job per kernel (the workgroups of its unpacked launch); prec: the

@@ -208,7 +208,9 @@ void launch_fock(const double* t1, const CholeskyScratch& cs, double* F, int no,
 // Integral-block build: C[m][n] = sum_J A(m, J) B(J, n) on FP64 MFMA, batched
 // over blockIdx.z, with an output map per block kind.
 // ---------------------------------------------------------------------------
-enum BuildKind { BUILD_PLAIN = 0, BUILD_JO = 1, BUILD_HS = 2, BUILD_GO = 3, BUILD_GW = 4 };
+enum BuildKind {
+  BUILD_PLAIN = 0, BUILD_JO = 1, BUILD_HS = 2, BUILD_GO = 3, BUILD_GW = 4, BUILD_GBC = 5
+};
 
 typedef TileCfg<4, 2, 2, 4, 16> BuildCfg;  // 8 wavefronts, 128 x 128 tiles
 
@@ -267,6 +269,12 @@ __global__ __launch_bounds__(BuildCfg::NT, 2) void k_build(const BuildSet set) {
       for (int r = 0; r < 4; ++r) {
         const int m = m0 + acc_row<T>(wm, fm, lane, r);
         const int n = n0 + acc_col<T>(wn, fn, lane);
+        if (kind == BUILD_GBC) {  // m = n'*nv + b, n = c -> G[n'][b][c], zeros for c past nv
+          if (m < M && n < cube_pitch(nv))
+            Cz[(m / nv) * g_pitch(nv) + (int64_t)(m % nv) * cube_pitch(nv) + n] =
+                n < N ? acc[fm][fn][r] : 0.0;
+          continue;
+        }
         if (m >= M || n >= N) continue;
         const double v = acc[fm][fn][r];
         if (kind == BUILD_PLAIN) {
@@ -308,10 +316,11 @@ static void launch_build_set(BuildSet& set, hipStream_t st) {
 }
 
 // Gcb[r][n][c][b] = Gbc[r][n][b][c]: nv x nv transposes, one per (r, n), through
-// padded 32 x 32 LDS tiles; ss and ds: doubles between the slabs.
+// padded 32 x 32 LDS tiles; ss and ds: doubles between the slabs, rs and rd: between the
+// rows of a slab (past nv, the rows of dst are filled with zeros).
 __global__ __launch_bounds__(256) void k_gcb(const double* __restrict__ Gbc,
                                              double* __restrict__ Gcb, int nv, int64_t ss,
-                                             int64_t ds) {
+                                             int64_t ds, int rs, int rd) {
   __shared__ double t[32][33];
   const int tn = (nv + 31) / 32;
   const int64_t slab = blockIdx.x / (tn * tn);  // r * (nv + no) + n
@@ -322,25 +331,25 @@ __global__ __launch_bounds__(256) void k_gcb(const double* __restrict__ Gbc,
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
   for (int y = ty; y < 32; y += 8) {
     const int b = b0 + y, c = c0 + tx;
-    if (b < nv && c < nv) t[y][tx] = src[(int64_t)b * nv + c];
+    if (b < nv && c < nv) t[y][tx] = src[(int64_t)b * rs + c];
   }
   __syncthreads();
   for (int y = ty; y < 32; y += 8) {
     const int c = c0 + y, b = b0 + tx;
-    if (b < nv && c < nv) dst[(int64_t)c * nv + b] = t[tx][y];
+    if (b < rd && c < nv) dst[(int64_t)c * rd + b] = b < nv ? t[tx][y] : 0.0;
   }
 }
 
 void launch_gcb(const Blocks& bl, int no, int nv, hipStream_t st) {
   const unsigned t = nblk(nv, 32);
   hipLaunchKernelGGL(k_gcb, dim3(t * t * no * (nv + no)), dim3(256), 0, st, bl.Gbc, bl.Gcb, nv,
-                     (int64_t)nv * nv, (int64_t)nv * nv);
+                     g_pitch(nv), g_pitch(nv), cube_pitch(nv), cube_pitch(nv));
 }
 
 void launch_build_blocks(const CholeskyScratch& cs, const Blocks& bl, int no, int nv, int nJ,
                          hipStream_t st) {
-  const int64_t nv2 = (int64_t)nv * nv, nv3 = nv2 * nv, onv = (int64_t)no * nv;
-  const int64_t gs = (int64_t)(nv + no) * nv2;  // one r slab of Gbc / Gcb
+  const int64_t nv2 = (int64_t)nv * nv, onv = (int64_t)no * nv;
+  const int64_t gs = (nv + no) * g_pitch(nv);  // one r slab of Gbc / Gcb
   // all six products share K = nJ: one launch, the large ones first
   BuildSet set = {};
   set.K = nJ; set.no = no; set.nv = nv; set.F = bl.F;
@@ -348,10 +357,10 @@ void launch_build_blocks(const CholeskyScratch& cs, const Blocks& bl, int no, in
   add_build(set, cs.LvoT, 1, onv, nv, cs.Lvv, nv2, 1, 0, nv, (int)nv2, bl.Gw,
             nv * gw_pitch(nv), no, BUILD_GW);
   // Gbc[r][(d,b)][c] = sum_J Lvv[J][(d,b)] Lov[J][r][c]            (rows n = d < nv)
-  add_build(set, cs.Lvv, 1, nv2, 0, cs.Lov, onv, 1, nv, (int)nv2, nv, bl.Gbc, gs, no, BUILD_PLAIN);
+  add_build(set, cs.Lvv, 1, nv2, 0, cs.Lov, onv, 1, nv, (int)nv2, nv, bl.Gbc, gs, no, BUILD_GBC);
   // Gbc[r][nv + (l,b)][c] = sum_J Lov[J][(l,b)] Lov[J][r][c]      (rows n = nv + l)
-  add_build(set, cs.Lov, 1, onv, 0, cs.Lov, onv, 1, nv, (int)onv, nv, bl.Gbc + nv3, gs, no,
-            BUILD_PLAIN);
+  add_build(set, cs.Lov, 1, onv, 0, cs.Lov, onv, 1, nv, (int)onv, nv,
+            bl.Gbc + nv * g_pitch(nv), gs, no, BUILD_GBC);
   // Jo[q][r][b][c] = sum_J Lov[J][q][b] Lov[J][r][c]
   add_build(set, cs.Lov, 1, onv, 0, cs.Lov, onv, 1, 0, (int)onv, (int)onv, bl.Jo, 0, 1, BUILD_JO);
   // Hs[q][r][c][l] = delta_lq F[r][c] - sum_J Loo[J][q][l] Lov[J][r][c]
@@ -387,7 +396,7 @@ void launch_build_density_blocks(const CholeskyScratch& cs, double* Gw, double* 
   launch_build_set(set, st);
   const unsigned t = nblk(nv, 32);
   hipLaunchKernelGGL(k_gcb, dim3(t * t * no * nv), dim3(256), 0, st, tmp, Gl, nv, nv2,
-                     gw_pitch(nv));
+                     gw_pitch(nv), nv, nv);
 }
 
 // ---------------------------------------------------------------------------
@@ -403,11 +412,13 @@ __global__ void k_relayout_vv(const double* __restrict__ g_vvvo_y, const double*
   const int r = blockIdx.y;
   if (e >= (int64_t)ny * nv2) return;
   const int yl = (int)(e / nv2), d = (int)((e / nv) % nv), z = (int)(e % nv);
-  const int64_t out = (int64_t)y0 * nv2 + e;
   // Gw[r][y][u][w] = g_vvvo[y][w][u][r]  (u = d, w = z: the contracted index w fastest)
   Gw[((int64_t)r * nv + y0 + yl) * gw_pitch(nv) + e % nv2] = g_vvvo_y[(((int64_t)yl * nv + z) * nv + d) * no + r];
   // Gbc[r][n=y][b=d][c=z] = g_vvov[n][b][r][c]
-  Gbc[(int64_t)r * (nv + no) * nv2 + out] = g_vvov_y[(((int64_t)yl * nv + d) * no + r) * nv + z];
+  double* gr = Gbc + ((int64_t)r * (nv + no) + y0 + yl) * g_pitch(nv) + (int64_t)d * cube_pitch(nv);
+  if (z == nv - 1)
+    for (int c = nv; c < cube_pitch(nv); ++c) gr[c] = 0.0;
+  gr[z] = g_vvov_y[(((int64_t)yl * nv + d) * no + r) * nv + z];
 }
 
 __global__ void k_relayout_small(const double* __restrict__ g_oovo, const double* __restrict__ g_ovov,
@@ -421,7 +432,10 @@ __global__ void k_relayout_small(const double* __restrict__ g_oovo, const double
     const int b = e / nv, c = e % nv;  // Jo[q][r][b][c] = Gbc[r][nv + q][b][c] = g_ovov[q][b][r][c]
     const double g = g_ovov[(((int64_t)q * nv + b) * no + r) * nv + c];
     Jo[((int64_t)q * no + r) * nv2 + e] = g;
-    Gbc[((int64_t)r * (nv + no) + nv + q) * nv2 + e] = g;
+    double* gr = Gbc + ((int64_t)r * (nv + no) + nv + q) * g_pitch(nv) + (int64_t)b * cube_pitch(nv);
+    gr[c] = g;
+    if (c == nv - 1)
+      for (int p = nv; p < cube_pitch(nv); ++p) gr[p] = 0.0;
   }
   for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < no * nv; e += gridDim.x * blockDim.x) {
     const int l = e / nv, c = e % nv;

@@ -575,11 +575,11 @@ __device__ __forceinline__ void mix_body(const double* __restrict__ eps,
       {
         const int u = e >> 6, v = (e >> 3) & 7, w = e & 7;
         const int a = A0 + u, b = B0 + v, c = C0 + w;
-        if (a < nv && b < nv && c < nv) {
+        if (a < nv && b < nv) {  // with zeros in the padding columns c >= nv (X is zero there)
           const double x = Xs[o * TSZ + TP(u, v, w)];
           TT[(a * nvl + b) * rp + c] = x;
-          if (cubesF) cubesF[(int64_t)z * 2 * nv3 + (a * nvl + b) * nvl + c] = (float)x;
-          if (YL) {  // view 0 at [a][(b, c)], view 1 at [b][(a, c)]
+          if (cubesF && c < nv) cubesF[(int64_t)z * 2 * nv3 + (a * nvl + b) * nvl + c] = (float)x;
+          if (YL && c < nv) {  // view 0 at [a][(b, c)], view 1 at [b][(a, c)]
             yl_put(YL, lpP, z, 0, a, b, c, nv, x);
             yl_put(YL, lpP, z, 1, b, a, c, nv, x);
           }
@@ -798,68 +798,223 @@ void launch_tau_export(bool two_planes, const double* eps, const int* tri, const
 //   column  n = nv : Ot1[p][a]       += sum_bc U[a,b,c] g_{qbrc}
 // Both column kinds are rows of one block G[r][n'][.][.] (n' < nv: g_{n'brc};
 // n' = nv + l: g_{lbrc}), stored once with K in (b, c) order (Gbc) and once in
-// (c, b) order (Gcb).  Each of the six views U_pi of the contravariant cubes
-// (TT[x][y][z] = tau~[x][y][z], TTT[x][y][z] = tau~[x][z][y]) is affine in K in
-// one of the two orders:
-//   pi 0: tau~[a][b][c] = TT[a][(b,c)]      k contiguous (within the padded rows)
-//   pi 3: tau~[a][c][b] = TTT[a][(b,c)]
-//   pi 1: tau~[b][a][c] = TTT[(b,c)][a]     a contiguous, k stride: the row pitch
-//   pi 5: tau~[b][c][a] = TT[(b,c)][a]
-//   pi 2: tau~[c][b][a] = TT[(c,b)][a]      the same, K in (c, b) order
-//   pi 4: tau~[c][a][b] = TTT[(c,b)][a]
-// so every permutation is a plain long-K GEMM.  K is split into chunks of whole
-// LDS stages; each chunk writes a partial slab Pvv[z][pi][chunk][a][n] (n <= nv)
-// that k_reduce sums in a fixed order.  128 x 128 tiles on 8 wavefronts of
-// 32 x 64, 16 k per LDS stage, two workgroups per CU.
-// The same GEMM runs on FP64 MFMA (E = double) or, for the "mixed-all" form, on
-// FP32 MFMA over FP32 copies of the cubes and of Gbc / Gcb (E = float), with the
-// products of each K chunk summed in FP32 and the chunks summed in FP64 by k_reduce.
+// (c, b) order (Gcb).  With the K order of each permutation chosen to match, the six
+// views U_pi of tau~ are three operands of the one cube TT[x][y][z] = tau~[x][y][z]:
+//   rows TT[a][x][y]: pi 0 = tau~[a][b][c] by Gbc, pi 3 = tau~[a][c][b] by Gcb
+//   rows TT[x][a][y]: pi 1 = tau~[b][a][c] by Gbc, pi 4 = tau~[c][a][b] by Gcb
+//   rows TT[x][y][a]: pi 5 = tau~[b][c][a] by Gbc, pi 2 = tau~[c][b][a] by Gcb
+// with K = (x, y) and y contiguous in the first two, a in the third.  K runs over the
+// padded rows of y (zeros in G, and in tau~ where it is read along y), so that every unit
+// of 8 k has one x.  K is split into chunks of whole units; each chunk writes a partial
+// slab Pvv[z][pi][chunk][a][n] (n <= nv) that k_reduce sums in a fixed order.
+//
+// Wave tiles as in the W build: no LDS, two units of 8 k in flight.  The waves of one
+// (triple, operand, chunk) are neighbours on one XCD and share the rows of tau~ (both
+// permutations) and of G in its L2.  Bound by MFMA and by the loads' way through L1 and L2
+// (16 B per cycle and CU at 4 x 4 blocks).  Per launch, before (128 x 128 LDS tiles) and
+// now: 23/250, 8 triples 6.14 -> 5.81 ms; 8/400, 8 triples 49.0 -> 36.2; 7/93 1.91 -> 1.07;
+// 6/45 0.137 -> 0.032 ms.
+
+// The A operand of a unit: lane (r16, kq) holds k = 2 kq + t of row r16 of each block.
+// ROWS: y contiguous, one 16-byte load per block.  Otherwise a is contiguous: one 16-byte
+// load of two a per k and pair of blocks, so that block 2 f holds the even rows and block
+// 2 f + 1 the odd rows of 32 (and 8-byte loads for an odd last block).
+template <bool ROWS, int FM>
+__device__ __forceinline__ void omega_load_a(BufRsrc r, unsigned va, unsigned bs, unsigned ks,
+                                             double (&a)[FM][2]) {
+  if constexpr (ROWS) {
+#pragma unroll
+    for (int f = 0; f < FM; ++f) {
+      const d2v v = buf_load_2f64(r, va, (unsigned)f * bs);
+      a[f][0] = v[0];
+      a[f][1] = v[1];
+    }
+  } else {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+#pragma unroll
+      for (int f = 0; f + 1 < FM; f += 2) {
+        const d2v v = buf_load_2f64(r, va + (unsigned)t * ks, (unsigned)f * 128u);
+        a[f][t] = v[0];
+        a[f + 1][t] = v[1];
+      }
+      if constexpr (FM & 1) {  // va addresses two a per lane: back to one
+        const unsigned vo = va - (threadIdx.x & 15u) * 8u + (unsigned)t * ks;
+        a[FM - 1][t] = buf_load_f64(r, vo + (unsigned)(FM - 1) * 128u);
+      }
+    }
+  }
+}
+
+// row of accumulator element (fm, r) of a wave tile (see omega_load_a)
+template <bool ROWS, int FM>
+__device__ __forceinline__ int omega_row(int fm, int kq, int r) {
+  if (ROWS || ((FM & 1) && fm == FM - 1)) return fm * 16 + kq + 4 * r;
+  return (fm & ~1) * 16 + 2 * (kq + 4 * r) + (fm & 1);
+}
+
+template <bool ROWS, int FM, int FN>
+__device__ __forceinline__ void omega_tile(const double* __restrict__ U, int64_t un, unsigned va0,
+                                           unsigned bs, unsigned us, int64_t xs, BufRsrc rb,
+                                           unsigned vb, unsigned gs, unsigned dq, int u0, int u1,
+                                           int ux, double* __restrict__ pvv, int m0, int n0,
+                                           int nv) {
+  const int lane = threadIdx.x & 63, r16 = lane & 15, kq = lane >> 4;
+  // U, un: tau~ at the tile's first row and x = 0, and the doubles left in its slot.
+  // Unit u is at x = u / ux, y = 8 (u % ux): the resource moves to each x (offsets over
+  // all of K would not fit 32 bits), va by us bytes per unit within it; ks = us / 8 is
+  // the byte step of one k where a is contiguous.
+  const int x0 = u0 / ux;
+  const double* pa = U + x0 * xs;
+  int64_t na = un - x0 * xs;
+  int yu = u0 - x0 * ux;
+  BufRsrc ra = buf_rsrc_n(pa, na);
+  unsigned va = va0 + (unsigned)yu * us;
+  // B: row r16 of each block, gs bytes between the blocks; the lane of column nv reads dq
+  // bytes further on (the Omega1 row)
+  vb += (unsigned)u0 * 64u;
+  const int fq = (nv - n0) >> 4;  // the block of column nv (outside [0, FN): another tile's)
+  const unsigned dv = r16 == (nv & 15) ? dq : 0u;
+  double a[2][FM][2];
+  d2v b[2][FN];
+  auto fetch = [&](double (&fa)[FM][2], d2v (&fb)[FN]) {
+    omega_load_a<ROWS, FM>(ra, va, bs, us / 8u, fa);
+#pragma unroll
+    for (int f = 0; f < FN; ++f)
+      fb[f] = buf_load_2f64(rb, f == fq ? vb + dv : vb, (unsigned)f * gs);
+    vb += 64u;
+    va += us;
+    if (++yu == ux) {
+      yu = 0;
+      va = va0;
+      pa += xs;
+      na = na > xs ? na - xs : 0;
+      ra = buf_rsrc_n(pa, na);
+    }
+  };
+  d4v acc[FM][FN];
+#pragma unroll
+  for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+    for (int fn = 0; fn < FN; ++fn) acc[fm][fn] = d4v{0.0, 0.0, 0.0, 0.0};
+  fetch(a[0], b[0]);
+  fetch(a[1], b[1]);
+  for (int u = u0; u < u1; u += 2) {
+#pragma unroll
+    for (int d = 0; d < 2; ++d) {
+      if (u + d < u1) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+            for (int fn = 0; fn < FN; ++fn)
+              acc[fm][fn] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[d][fm][t], b[d][fn][t],
+                                                                 acc[fm][fn], 0, 0, 0);
+      }
+      fetch(a[d], b[d]);
+    }
+  }
+  const int NV1 = nv + 1;
+#pragma unroll
+  for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+    for (int fn = 0; fn < FN; ++fn)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int m = m0 + omega_row<ROWS, FM>(fm, kq, r), n = n0 + fn * 16 + r16;
+        if (m < nv && n <= nv) pvv[(int64_t)m * NV1 + n] = acc[fm][fn][r];
+      }
+}
+
+// `item`: the wave tile, column tiles fastest, then the permutation of the operand's two,
+// the row tile, the K chunk, the operand and the triple
+template <int FM, int FN>
+__device__ __forceinline__ void omega_body(const double* __restrict__ cubes,
+                                           const double* __restrict__ Gbc,
+                                           const double* __restrict__ Gcb,
+                                           const int* __restrict__ tri, int ntri,
+                                           double* __restrict__ Pvv, int no, int nv, int nchunks,
+                                           int tiles_m, int tiles_n, unsigned item) {
+  const int tn = (int)(item % (unsigned)tiles_n);
+  item /= (unsigned)tiles_n;
+  const bool cb = item & 1u;  // the permutation that takes Gcb
+  item >>= 1;
+  const int tm = (int)(item % (unsigned)tiles_m);
+  item /= (unsigned)tiles_m;
+  const int ch = (int)(item % (unsigned)nchunks);
+  item /= (unsigned)nchunks;
+  const int op = (int)(item % 3u), z = (int)(item / 3u);
+  if (z >= ntri) return;
+  const int i = tri[3 * z], j = tri[3 * z + 1], k = tri[3 * z + 2];
+  const int pi = op == 0 ? (cb ? 3 : 0) : op == 1 ? (cb ? 4 : 1) : (cb ? 2 : 5);
+  if (!perm_active(tri_kind(i, j, k), pi)) return;
+  int p, q, r;
+  perm_pqr(pi, i, j, k, p, q, r);
+  const int rp = cube_pitch(nv), ux = rp / 8, units = nv * ux;
+  const int u0 = (int)((int64_t)ch * units / nchunks), u1 = (int)((int64_t)(ch + 1) * units / nchunks);
+  const int m0 = tm * (FM * 16), n0 = tn * (FN * 16);
+  const int lane = threadIdx.x & 63, r16 = lane & 15, kq = lane >> 4;
+  const int64_t pl = (int64_t)nv * rp, css = cube_slot(nv), gp = g_pitch(nv);
+  // B rows n < nv are rows n of G; the Omega1 column n = nv reads row nv + q (columns past
+  // it read some row or zeros and are not stored)
+  const int64_t go = ((int64_t)r * (nv + no) + n0) * gp;
+  const BufRsrc rb = buf_rsrc_n((cb ? Gcb : Gbc) + go, (int64_t)no * (nv + no) * gp - go);
+  const unsigned vb = (unsigned)(r16 * gp + 2 * kq) * 8u;
+  const unsigned gs = (unsigned)(gp * 128), dq = (unsigned)(q * gp * 8);
+  const double* TT = cubes + ((int64_t)z * NSLOT + SLOT_TT) * css;
+  double* pvv = Pvv + (((int64_t)z * 6 + pi) * nchunks + ch) * nv * (int64_t)(nv + 1);
+  if (op == 2) {
+    omega_tile<false, FM, FN>(TT + m0, css - m0, (unsigned)(2 * kq * rp + 2 * r16) * 8u, 0u,
+                              (unsigned)rp * 64u, pl, rb, vb, gs, dq, u0, u1, ux, pvv, m0, n0,
+                              nv);
+  } else {
+    const int64_t rs = op == 0 ? pl : rp;  // row stride
+    omega_tile<true, FM, FN>(TT + m0 * rs, css - m0 * rs, (unsigned)(r16 * rs + 2 * kq) * 8u,
+                             (unsigned)(rs * 128), 64u, op == 0 ? rp : pl, rb, vb, gs, dq, u0, u1, ux,
+                             pvv, m0, n0, nv);
+  }
+}
+
+template <int FM, int FN>
+__global__ __launch_bounds__(WNT, shape_waves(FM, FN)) void k_omega(
+    const double* __restrict__ cubes, const double* __restrict__ Gbc,
+    const double* __restrict__ Gcb, const int* __restrict__ tri, int ntri,
+    double* __restrict__ Pvv, int no, int nv, int nchunks, int tiles_m, int tiles_n) {
+  // one (triple, operand, chunk) per run and XCD: 2 tiles_m tiles_n wave tiles
+  const unsigned wg = xcd_item(blockIdx.x, gridDim.x, (unsigned)(tiles_m * tiles_n + 1) / 2u);
+  const unsigned wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  omega_body<FM, FN>(cubes, Gbc, Gcb, tri, ntri, Pvv, no, nv, nchunks, tiles_m, tiles_n,
+                     wg * 4 + wave);
+}
+
+// The FP32 mixed-all form: the same products on FP32 MFMA over FP32 copies of tau~,
+// tau~T (TTT[x][y][z] = tau~[x][z][y], which makes every view affine in K with the K order
+// of G below) and of Gbc, Gcb, none of them padded; the products of each K chunk are
+// summed in FP32 and the chunks in FP64 by k_reduce.
+//   pi 0: tau~[a][b][c] = TT[a][(b,c)], pi 3: tau~[a][c][b] = TTT[a][(b,c)]  (k contiguous)
+//   pi 1: tau~[b][a][c] = TTT[(b,c)][a], pi 5: tau~[b][c][a] = TT[(b,c)][a]  (a contiguous)
+//   pi 2: tau~[c][b][a] = TT[(c,b)][a], pi 4: tau~[c][a][b] = TTT[(c,b)][a]  (K = (c, b))
+// 128 x 128 tiles on 8 wavefronts of 32 x 64 through LDS, 16 k per stage.
 typedef TileCfg<4, 2, 2, 4, 16> OCfg;
 typedef float f4v_ __attribute__((ext_vector_type(4)));
 
-template <class E>
-struct OmegaAcc;
-template <>
-struct OmegaAcc<double> {
-  typedef d4v V;
-  static __device__ V mfma(double a, double b, V c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-  }
-  static __device__ double load(BufRsrc r, unsigned off) { return buf_load_f64(r, off); }
-  // D[row][col] of the 16x16x4 FP64 MFMA: row = lane/16 + 4 r
-  static __device__ int row(int lane, int r) { return (lane >> 4) + 4 * r; }
-};
-template <>
-struct OmegaAcc<float> {
-  typedef f4v_ V;
-  static __device__ V mfma(float a, float b, V c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-  }
-  static __device__ float load(BufRsrc r, unsigned off) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
-  }
-  // D[row][col] of the 16x16x4 FP32 MFMA: row = 4 (lane/16) + r
-  static __device__ int row(int lane, int r) { return 4 * (lane >> 4) + r; }
-};
-
-// cubes: the batch's cube slots, nslot per triple, the first of them slot0 (the
-// FP64 cubes hold all five slots; the FP32 copies only TT and TTT)
-template <class E>
-__device__ __forceinline__ void omega_body(const E* __restrict__ cubes, int nslot, int slot0,
-                                           const E* __restrict__ Gbc, const E* __restrict__ Gcb,
-                                           const int* __restrict__ tri, double* __restrict__ Pvv,
-                                           int no, int nv, int nchunks, int tiles_n, int bx,
-                                           int by, int bz) {
+// cubes: TT and TTT of each triple
+__global__ __launch_bounds__(OCfg::NT) void k_omega_f32(const float* __restrict__ cubes,
+                                                        const float* __restrict__ Gbc,
+                                                        const float* __restrict__ Gcb,
+                                                        const int* __restrict__ tri,
+                                                        double* __restrict__ Pvv, int no, int nv,
+                                                        int nchunks, int tiles_n) {
   typedef OCfg T;
-  typedef OmegaAcc<E> M;
-  constexpr unsigned ES = sizeof(E);
-  __shared__ E lds[T::LDS_DOUBLES];
-  const int pi = by, z = bz;
+  constexpr unsigned ES = sizeof(float);
+  __shared__ float lds[T::LDS_DOUBLES];
+  const int pi = blockIdx.y, z = blockIdx.z;
   const int i = tri[3 * z], j = tri[3 * z + 1], k = tri[3 * z + 2];
   if (!perm_active(tri_kind(i, j, k), pi)) return;
   int p, q, r;
   perm_pqr(pi, i, j, k, p, q, r);
-  const int ch = bx % nchunks, tile = bx / nchunks;
+  const int ch = blockIdx.x % nchunks, tile = blockIdx.x / nchunks;
   const int m0 = (tile / tiles_n) * T::BM, n0 = (tile % tiles_n) * T::BN;
   const int64_t nvl = nv, nv2 = nvl * nvl, nv3 = nv2 * nvl;
   const int K = nv * nv;
@@ -867,26 +1022,21 @@ __device__ __forceinline__ void omega_body(const E* __restrict__ cubes, int nslo
   const int s0 = (int)((int64_t)ch * S / nchunks), s1 = (int)((int64_t)(ch + 1) * S / nchunks);
   if (s0 >= s1) return;  // nchunks <= S, so never taken
   const bool cb = (pi == 2 || pi == 4);
-  const bool amaj = !(pi == 0 || pi == 3);  // a contiguous, k stride pp
-  const int slot = (pi == 1 || pi == 3 || pi == 4) ? SLOT_TTT : SLOT_TT;
-  // the FP64 cubes keep padded rows (pitch pp, slot css); the FP32 copies do not
-  const int pp = (ES == 8) ? cube_pitch(nv) : nv;
-  const int64_t css = (ES == 8) ? cube_slot(nv) : nv3;
-  const E* U = cubes + ((int64_t)z * nslot + slot - slot0) * css;
-  const E* G = (cb ? Gcb : Gbc) + (int64_t)r * (nv + no) * nv2;
-  const int ask = amaj ? pp : 1;  // k stride of A in elements (within a padded row for !amaj)
-  // tile origins (k = 0) of the two operands; the A rows of the views with k
-  // contiguous are nv padded rows (b, .) apart: nv * pp elements
-  const E* A0 = amaj ? U + m0 : U + (int64_t)m0 * nv * pp;
-  const E* B0 = G + (int64_t)n0 * K;
+  const bool amaj = !(pi == 0 || pi == 3);  // a contiguous, k stride nv
+  const int ttt = (pi == 1 || pi == 3 || pi == 4) ? 1 : 0;
+  const float* U = cubes + ((int64_t)z * 2 + ttt) * nv3;
+  const float* G = (cb ? Gcb : Gbc) + (int64_t)r * (nv + no) * nv2;
+  const int ask = amaj ? nv : 1;  // k stride of A in elements
+  // tile origins (k = 0) of the two operands
+  const float* A0 = amaj ? U + m0 : U + (int64_t)m0 * K;
+  const float* B0 = G + (int64_t)n0 * K;
 
   // Per-thread part of every stage.  A: element e at (row/column x_e, k_e) of the
-  // stage, global byte offset aoff[e] plus that of k_e from the stage origin (k_e ask
-  // elements, or for k = (b, c) in padded rows the columns c past nv skipped), LDS
-  // slot alds[e].  Rows past nv repeat row nv - 1 (their outputs are never stored).
+  // stage, global byte offset aoff[e] plus that of k_e from the stage origin, LDS slot
+  // alds[e].  Rows past nv repeat row nv - 1 (their outputs are never stored).
   // B rows n < nv are G rows n; rows n >= nv (only in the last column tile) read the
   // Omega1 row nv + q.  Offsets are relative to the tile origin: below 191 rows of
-  // stride nv * pp <= 2^20, so below 2^31 bytes.
+  // stride nv^2 <= 2^20, so below 2^31 bytes.
   const int tid = threadIdx.x;
   constexpr int RP = T::NT / T::BK;  // k-fast mapping: 32 rows per element step
   constexpr int KP = T::NT / T::BM;  // a-fast mapping: 4 k per element step
@@ -906,7 +1056,7 @@ __device__ __forceinline__ void omega_body(const E* __restrict__ cubes, int nslo
 #pragma unroll
     for (int e = 0; e < T::EA; ++e) {
       ak[e] = kt;
-      aoff[e] = (unsigned)(min(m0 + xt + e * RP, nv - 1) - m0) * (unsigned)(nv * pp) * ES;
+      aoff[e] = (unsigned)(min(m0 + xt + e * RP, nv - 1) - m0) * (unsigned)K * ES;
       alds[e] = lds_idx<T::BK>(kt, xt + e * RP, T::LDA);
     }
   }
@@ -917,7 +1067,7 @@ __device__ __forceinline__ void omega_body(const E* __restrict__ cubes, int nslo
     blds[e] = T::BK * T::LDA + lds_idx<T::BK>(kt, xt + e * RP, T::LDB);
   }
   const unsigned ask8 = (unsigned)ask * ES;
-  E ra[T::EA], rb[T::EB];
+  float ra[T::EA], rb[T::EB];
   // which loaded elements lie inside K (bit e for A, one flag for B); the zero of the
   // others is applied at the LDS store, after the current stage's MFMAs, so that the
   // loads stay in flight during them
@@ -934,48 +1084,43 @@ __device__ __forceinline__ void omega_body(const E* __restrict__ cubes, int nslo
       for (int e = 0; e < T::EA; ++e) {
         const bool in = ak[e] <= kl;
         const int kc = in ? ak[e] : kl;  // k past K reads a valid element
-        ra[e] = M::load(sa, aoff[e] + (unsigned)kc * ask8);
+        ra[e] = buf_load_f32(sa, aoff[e] + (unsigned)kc * ask8);
         amask |= in ? (1u << e) : 0u;
       }
     } else {
-      // k = b nv + c lies at b pp + c: the stage starts at (b0, c0), and the lane's k
-      // (the same for all its elements) skips pp - nv columns per row end it passes
-      const int b0 = k0 / nv, c0 = k0 - b0 * nv;
-      const BufRsrc sa = buf_rsrc(A0 + (int64_t)b0 * pp + c0);
+      const BufRsrc sa = buf_rsrc(A0 + k0);
       const bool in = kt <= kl;
-      const int kc = in ? kt : kl;  // k past K reads a valid element
-      const unsigned ko =
-          (unsigned)(kc + (ES == 8 && pp != nv ? (c0 + kc) / nv * (pp - nv) : 0)) * ES;
+      const unsigned ko = (unsigned)(in ? kt : kl) * ES;  // k past K reads a valid element
 #pragma unroll
       for (int e = 0; e < T::EA; ++e) {
-        ra[e] = M::load(sa, aoff[e] + ko);
+        ra[e] = buf_load_f32(sa, aoff[e] + ko);
         amask |= in ? (1u << e) : 0u;
       }
     }
     inb = kt <= kl;
     const unsigned kb = (unsigned)(inb ? kt : kl) * ES;
 #pragma unroll
-    for (int e = 0; e < T::EB; ++e) rb[e] = M::load(sb, boff[e] + kb);
+    for (int e = 0; e < T::EB; ++e) rb[e] = buf_load_f32(sb, boff[e] + kb);
   };
-  auto store = [&](E* st) {
+  auto store = [&](float* st) {
 #pragma unroll
-    for (int e = 0; e < T::EA; ++e) st[alds[e]] = ((amask >> e) & 1u) ? ra[e] : E(0);
+    for (int e = 0; e < T::EA; ++e) st[alds[e]] = ((amask >> e) & 1u) ? ra[e] : 0.f;
 #pragma unroll
-    for (int e = 0; e < T::EB; ++e) st[blds[e]] = inb ? rb[e] : E(0);
+    for (int e = 0; e < T::EB; ++e) st[blds[e]] = inb ? rb[e] : 0.f;
   };
-  typename M::V acc[T::FM][T::FN];
+  f4v_ acc[T::FM][T::FN];
 #pragma unroll
   for (int fm = 0; fm < T::FM; ++fm)
 #pragma unroll
-    for (int fn = 0; fn < T::FN; ++fn) acc[fm][fn] = typename M::V{0, 0, 0, 0};
+    for (int fn = 0; fn < T::FN; ++fn) acc[fm][fn] = f4v_{0, 0, 0, 0};
   const int lane = tid & 63, wave = tid >> 6;
   const int wm = wave % T::WM, wn = wave / T::WM;
   fetch(s0);
   store(lds);
   __syncthreads();
   for (int s = s0; s < s1; ++s) {
-    E* cur = lds + ((s - s0) & 1) * T::STAGE;
-    E* nxt = lds + ((s - s0 + 1) & 1) * T::STAGE;
+    float* cur = lds + ((s - s0) & 1) * T::STAGE;
+    float* nxt = lds + ((s - s0 + 1) & 1) * T::STAGE;
     const bool more = s + 1 < s1;
     if (more) fetch(s + 1);
     // lane supplies A[m = l%16][k = l/16] and B[k = l/16][n = l%16] to each MFMA
@@ -983,7 +1128,7 @@ __device__ __forceinline__ void omega_body(const E* __restrict__ cubes, int nslo
     for (int kk = 0; kk < T::BK / 4; ++kk) {
       const int kr = kk * 4 + (lane >> 4);
       const int sw = (lane & 15) ^ lds_swz<T::BK>(kr);
-      E a[T::FM], b[T::FN];
+      float a[T::FM], b[T::FN];
 #pragma unroll
       for (int fm = 0; fm < T::FM; ++fm) a[fm] = cur[kr * T::LDA + (wm * T::FM + fm) * 16 + sw];
 #pragma unroll
@@ -992,7 +1137,8 @@ __device__ __forceinline__ void omega_body(const E* __restrict__ cubes, int nslo
 #pragma unroll
       for (int fm = 0; fm < T::FM; ++fm)
 #pragma unroll
-        for (int fn = 0; fn < T::FN; ++fn) acc[fm][fn] = M::mfma(a[fm], b[fn], acc[fm][fn]);
+        for (int fn = 0; fn < T::FN; ++fn)
+          acc[fm][fn] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[fm], b[fn], acc[fm][fn], 0, 0, 0);
     }
     if (more) store(nxt);
     __syncthreads();
@@ -1005,21 +1151,10 @@ __device__ __forceinline__ void omega_body(const E* __restrict__ cubes, int nslo
     for (int fn = 0; fn < T::FN; ++fn)
 #pragma unroll
       for (int rr = 0; rr < 4; ++rr) {
-        const int a = m0 + (wm * T::FM + fm) * 16 + M::row(lane, rr);
+        const int a = m0 + (wm * T::FM + fm) * 16 + 4 * (lane >> 4) + rr;  // FP32 16x16x4 MFMA rows
         const int n = n0 + acc_col<T>(wn, fn, lane);
         if (a < nv && n <= nv) pvv[(int64_t)a * NV1 + n] = (double)acc[fm][fn][rr];
       }
-}
-
-template <class E>
-__global__ __launch_bounds__(OCfg::NT) void k_omega(const E* __restrict__ cubes, int nslot,
-                                                    int slot0, const E* __restrict__ Gbc,
-                                                    const E* __restrict__ Gcb,
-                                                    const int* __restrict__ tri,
-                                                    double* __restrict__ Pvv, int no, int nv,
-                                                    int nchunks, int tiles_n) {
-  omega_body<E>(cubes, nslot, slot0, Gbc, Gcb, tri, Pvv, no, nv, nchunks, tiles_n, blockIdx.x,
-                blockIdx.y, blockIdx.z);
 }
 
 // The (triple, permutation) pairs of a batch whose first occupied index is p, in
@@ -1497,44 +1632,62 @@ int zo_nbchunks(int nv, int ntri) {
   return nbc < 1 ? 1 : nbc;
 }
 
-// K chunks (runs of whole LDS stages) of the Omega GEMM of one (triple,
-// permutation, tile): enough workgroups for several rounds over the chip (two
-// resident per CU), as a multiple of 8 beyond 8 so that the tiles of one
-// (triple, permutation, chunk) -- which share operand rows -- are dispatched to
-// the same XCD (workgroups go round-robin over the 8 XCDs in linear order, and
-// tiles of one chunk are nchunks apart) and meet in its L2; at least 16 stages
-// per chunk.
+// K chunks of the Omega GEMM of one (triple, permutation, tile).
+// FP64: enough wave tiles for six rounds of the 2048 that are resident at two per SIMD
+// (4096, 8192, 12288, 24576 tiles: 23/250 CVS list 585, 562, 548, 552 ms per call, 12/120
+// 40.5, 39.6, 39.5, 40.6), as long as a chunk keeps 64 units of 8 k; small products are split further, down to 8 units
+// per chunk, while there are fewer than 3072 wave tiles (CC3_OMEGA_WG in the environment
+// sets the larger target instead).
+// fp32acc (the mixed-all forms, 128 x 128 LDS tiles): about 2048 workgroups, as a
+// multiple of 8 beyond 8 so that the tiles of one (triple, permutation, chunk) are
+// dispatched to the same XCD; at least 16 stages of 16 k per chunk and at most 4096 k,
+// which the MFMA sums in FP32, so that their rounding does not grow with the batch (the
+// split-BF16 form's K is the blocked lp_kb_len(nv) >= nv^2).
 int omega_kchunks(int nv, int ntri, bool fp32acc) {
   static const int target = [] {
     const char* e = getenv("CC3_OMEGA_WG");
     const int v = e ? atoi(e) : 0;
-    return v > 0 ? v : 2048;
+    return v > 0 ? v : 0;
   }();
+  const int nt = ntri > 0 ? ntri : 1;
+  int nch;
+  if (!fp32acc) {
+    int tm, tn;
+    shape_tiles(pick_shape(nv, nv + 1), nv, nv + 1, &tm, &tn);
+    const int64_t per = 6ll * tm * tn * nt, units = (int64_t)nv * (cube_pitch(nv) / 8);
+    const int64_t big = ((target ? target : 12288) + per - 1) / per, small = (3072 + per - 1) / per;
+    nch = (int)std::max(std::min(big, units / 64), std::min(small, units / 8));
+    return nch < 1 ? 1 : nch;
+  }
   typedef OCfg T;
   const int tm = (nv + T::BM - 1) / T::BM, tn = (nv + 1 + T::BN - 1) / T::BN;
-  const int per = 6 * tm * tn * (ntri > 0 ? ntri : 1);
-  int nch = (target + per - 1) / per;
+  const int per = 6 * tm * tn * nt;
+  nch = ((target ? target : 2048) + per - 1) / per;
   if (nch > 8) nch = (nch + 7) / 8 * 8;
   const int S = (nv * nv + T::BK - 1) / T::BK;
   const int cap = S / 16 > 1 ? S / 16 : 1;
   if (nch > cap) nch = cap;
-  // chunks that the MFMA sums in FP32 (the mixed-all forms) hold at most 4096 k, so
-  // that their rounding does not grow with the batch (the split-BF16 form's K is the
-  // blocked lp_kb_len(nv) >= nv^2)
-  if (fp32acc) {
-    const int need = (int)((lp_kb_len(nv) + 4095) / 4096);
-    if (nch < need) nch = need > 8 ? (need + 7) / 8 * 8 : need;
-  }
+  const int need = (int)((lp_kb_len(nv) + 4095) / 4096);
+  if (nch < need) nch = need > 8 ? (need + 7) / 8 * 8 : need;
   return nch < 1 ? 1 : nch;
+}
+
+static unsigned omega_wgs(int nv, int ntri, int nch, int shape) {
+  int tm, tn;
+  shape_tiles(shape, nv, nv + 1, &tm, &tn);
+  return (unsigned)(((int64_t)tm * tn * 6 * nch * ntri + 3) / 4);
 }
 
 void launch_omega(const double* cubes, const Blocks& b, const int* tri, int ntri, double* Pvv,
                   int no, int nv, hipStream_t st) {
-  typedef OCfg T;
-  const int tm = (nv + T::BM - 1) / T::BM, tn = (nv + 1 + T::BN - 1) / T::BN;
-  const int nch = omega_kchunks(nv, ntri);
-  hipLaunchKernelGGL(k_omega<double>, dim3(nch * tm * tn, 6, ntri), dim3(T::NT), 0, st, cubes,
-                     (int)NSLOT, 0, b.Gbc, b.Gcb, tri, Pvv, no, nv, nch, tn);
+  const int shape = pick_shape(nv, nv + 1), nch = omega_kchunks(nv, ntri);
+  int tm, tn;
+  shape_tiles(shape, nv, nv + 1, &tm, &tn);
+  with_shape(shape, [&](auto fm, auto fn) {
+    hipLaunchKernelGGL((k_omega<decltype(fm)::value, decltype(fn)::value>),
+                       dim3(omega_wgs(nv, ntri, nch, shape)), dim3(WNT), 0, st, cubes, b.Gbc, b.Gcb,
+                       tri, ntri, Pvv, no, nv, nch, tm, tn);
+  });
 }
 
 void launch_omega_f32(const float* cubesF, const float* GbcF, const float* GcbF, const int* tri,
@@ -1542,21 +1695,25 @@ void launch_omega_f32(const float* cubesF, const float* GbcF, const float* GcbF,
   typedef OCfg T;
   const int tm = (nv + T::BM - 1) / T::BM, tn = (nv + 1 + T::BN - 1) / T::BN;
   const int nch = omega_kchunks(nv, ntri, true);
-  hipLaunchKernelGGL(k_omega<float>, dim3(nch * tm * tn, 6, ntri), dim3(T::NT), 0, st, cubesF, 2,
-                     (int)SLOT_TT, GbcF, GcbF, tri, Pvv, no, nv, nch, tn);
+  hipLaunchKernelGGL(k_omega_f32, dim3(nch * tm * tn, 6, ntri), dim3(T::NT), 0, st, cubesF, GbcF,
+                     GcbF, tri, Pvv, no, nv, nch, tn);
 }
 
-// FP32 copies for the mixed-all form: dst[e] = (float)src[e]
-__global__ void k_to_f32(const double* __restrict__ src, float* __restrict__ dst, int64_t n) {
+__global__ void k_g_to_f32(const double* __restrict__ src, float* __restrict__ dst, int64_t rows,
+                           int nv) {
+  const int64_t nv2 = (int64_t)nv * nv, gp = g_pitch(nv), n = rows * nv2;
+  const int rp = cube_pitch(nv);
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n;
-       e += (int64_t)gridDim.x * blockDim.x)
-    dst[e] = (float)src[e];
+       e += (int64_t)gridDim.x * blockDim.x) {
+    const int xy = (int)(e % nv2);
+    dst[e] = (float)src[e / nv2 * gp + (int64_t)(xy / nv) * rp + xy % nv];
+  }
 }
 
-void launch_to_f32(const double* src, float* dst, int64_t n, hipStream_t st) {
-  unsigned g = nblk(n, 256);
+void launch_g_to_f32(const double* src, float* dst, int64_t rows, int nv, hipStream_t st) {
+  unsigned g = nblk(rows * nv * nv, 256);
   if (g > 65536) g = 65536;
-  hipLaunchKernelGGL(k_to_f32, dim3(g), dim3(256), 0, st, src, dst, n);
+  hipLaunchKernelGGL(k_g_to_f32, dim3(g), dim3(256), 0, st, src, dst, rows, nv);
 }
 
 void launch_omega_oo(const double* cubes, const Blocks& b, const int* tri, int ntri, double* OtT,
@@ -1622,17 +1779,16 @@ __global__ __launch_bounds__(512) void k_pack_mix(const PackJob* __restrict__ jo
   }
 }
 
-__global__ __launch_bounds__(OCfg::NT) void k_pack_omega(const PackJob* __restrict__ jobs,
-                                                         int njobs, unsigned total) {
-  typedef OCfg T;
+template <int FM, int FN>
+__global__ __launch_bounds__(WNT, shape_waves(FM, FN)) void k_pack_omega(
+    const PackJob* __restrict__ jobs, int njobs, unsigned total) {
   for (unsigned item = blockIdx.x; item < total; item += gridDim.x) {
     const PackJob& J = jobs[pack_job(jobs, njobs, PK_OMEGA, item)];
     const unsigned local = item - J.first[PK_OMEGA];
-    const int tm = (J.nv + T::BM - 1) / T::BM, tn = (J.nv + 1 + T::BN - 1) / T::BN;
-    const unsigned gx = (unsigned)J.nch * tm * tn;
-    omega_body<double>(J.cubes, (int)NSLOT, 0, J.Gbc, J.Gcb, J.tri, J.Pvv, J.no, J.nv, J.nch, tn,
-                       (int)(local % gx), (int)((local / gx) % 6), (int)(local / (gx * 6)));
-    __syncthreads();
+    const int tm = (J.nv + 16 * FM - 1) / (16 * FM), tn = (J.nv + 16 * FN) / (16 * FN);
+    const unsigned wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    omega_body<FM, FN>(J.cubes, J.Gbc, J.Gcb, J.tri, J.ntri, J.Pvv, J.no, J.nv, J.nch, tm, tn,
+                       local * 4 + wave);
   }
 }
 
@@ -1667,8 +1823,7 @@ void pack_items(const PackJob& j, int prec, unsigned (&items)[PK_N]) {
   items[PK_W] = prec == CC3_FP64 ? wbuild_wgs(nv, nt, j.wshape) : wbuild_lp_wgs(nv, nt);
   const int nb = (nv + MT - 1) / MT;
   items[PK_MIX] = (unsigned)(nb * (nb + 1) * (nb + 2) / 6) * nt;
-  const unsigned to = (unsigned)((nv + OCfg::BM - 1) / OCfg::BM) * ((nv + 1 + OCfg::BN - 1) / OCfg::BN);
-  items[PK_OMEGA] = (unsigned)j.nch * to * 6u * nt;
+  items[PK_OMEGA] = omega_wgs(nv, nt, j.nch, j.oshape);
   items[PK_OO] = (unsigned)((nv + 1) / 2) * ((nv + 63) / 64) * no;
   items[PK_RED] = nblk((int64_t)nv * nv, 256) * no * no;
 }
@@ -1699,8 +1854,11 @@ void launch_packed_step(const PackJob* dev_jobs, const PackJob* host_jobs, int n
     launch_wbuild_lp_packed(dev_jobs, njobs, total[PK_W], prec, st);
     hipLaunchKernelGGL(k_pack_mix<false>, gmix, dim3(512), 0, st, dev_jobs, njobs, total[PK_MIX]);
   }
-  hipLaunchKernelGGL(k_pack_omega, dim3(pack_grid(total[PK_OMEGA], 2048)), dim3(OCfg::NT), 0, st,
-                     dev_jobs, njobs, total[PK_OMEGA]);
+  with_shape(host_jobs[0].oshape, [&](auto fm, auto fn) {
+    hipLaunchKernelGGL((k_pack_omega<decltype(fm)::value, decltype(fn)::value>),
+                       dim3(pack_grid(total[PK_OMEGA], 4096)), dim3(WNT), 0, st, dev_jobs, njobs,
+                       total[PK_OMEGA]);
+  });
   const dim3 goo(pack_grid(total[PK_OO], 8192));
   if (max_no <= 16)
     hipLaunchKernelGGL(k_pack_omega_oo<1>, goo, dim3(256), 0, st, dev_jobs, njobs, total[PK_OO]);

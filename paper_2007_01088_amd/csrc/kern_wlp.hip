@@ -616,20 +616,21 @@ size_t lp_contract_cube_bytes(int prec, int nv) {
   return (size_t)4 * P * nv * (size_t)lp_kb_pitch(nv) * 2;  // per triple
 }
 
-// Split-BF16 pieces of the rows of Gbc or Gcb with K = (x, y) (x nv + y in the source)
+// Split-BF16 pieces of the rows of Gbc or Gcb with K = (x, y) (padded rows in the source)
 // in the blocked order lp_kb: dst[piece][row][kb] at row pitch lp_kb_pitch, zero where x
 // or y is past nv (the pitch's tail is never read).
 template <int P>
 __global__ void k_lp_copy_blocked(const double* __restrict__ src, int64_t rows, int nv,
                                   uint16_t* __restrict__ dst, int64_t piece_stride) {
-  const int64_t Kb = lp_kb_len(nv), Kr = lp_kb_pitch(nv), K = (int64_t)nv * nv;
+  const int64_t Kb = lp_kb_len(nv), Kr = lp_kb_pitch(nv), gp = g_pitch(nv);
+  const int rp = cube_pitch(nv);
   const int nb = (nv + 7) / 8;
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= rows * Kb) return;
   const int64_t row = e / Kb;
   const int kb = (int)(e % Kb);
   const int blk = kb >> 6, x = (blk / nb) * 8 + ((kb >> 3) & 7), y = (blk % nb) * 8 + (kb & 7);
-  const double v = (x < nv && y < nv) ? src[row * K + (int64_t)x * nv + y] : 0.0;
+  const double v = (x < nv && y < nv) ? src[row * gp + (int64_t)x * rp + y] : 0.0;
   uint16_t pc[P];
   split_bf16<P>(v, pc);
 #pragma unroll
