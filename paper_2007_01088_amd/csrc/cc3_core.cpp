@@ -455,7 +455,7 @@ static int triple_loop_body(Runner& rn, Profiler* pf, const Plan& p, const Ws& w
       Timer tm(pf, sk, FAM_MIX, 0.0, 0.0);
       launch_mix(p.prec == CC3_FP64, eps, tb, nb, w.cubes[k],
                  lowp_contract && lpP == 0 ? (float*)w.cubesX[k] : nullptr,
-                 lpP ? w.cubesX[k] : nullptr, lpP, p.no, p.nv, sk);
+                 lpP ? w.cubesX[k] : nullptr, lpP, false, p.no, p.nv, sk);
     }
     {
       Timer tm(pf, sk, FAM_OMEGA, omega_flops(p.no, p.nv, kinds.data(), nb), 0.0);
@@ -470,7 +470,7 @@ static int triple_loop_body(Runner& rn, Profiler* pf, const Plan& p, const Ws& w
     if (nbatch > 0 && !own) HIPCHK(hipStreamWaitEvent(sk, rn.ev_red[(nbatch - 1) % nstream], 0));
     {
       Timer tm(pf, sk, FAM_OMEGA_OO, omega_oo_flops(p.no, p.nv, kinds.data(), nb), 0.0);
-      launch_omega_oo(w.cubes[k], w.b, tb, nb, w.OtT, p.no, p.nv, sk);
+      launch_omega_oo(w.cubes[k], w.b, tb, nb, w.Ot2, w.OtT, p.no, p.nv, sk);
     }
     {
       Timer tm(pf, sk, FAM_REDUCE, 0.0, 0.0);
@@ -638,7 +638,8 @@ static int jacobian_prep_body(Runner& rn, Profiler* pf, const Plan& p, const Ws&
     }
     {
       Timer tm(pf, sk, FAM_MIX, 0.0, 0.0);
-      launch_mix(p.prec == CC3_FP64, eps, tb, nb, w.cubes[k], nullptr, nullptr, 0, no, nv, sk);
+      launch_mix(p.prec == CC3_FP64, eps, tb, nb, w.cubes[k], nullptr, nullptr, 0, true, no, nv,
+                 sk);
     }
     {
       Timer tm(pf, sk, FAM_ZPREP, zprep_flops(no, nv, kinds.data(), nb) * ((double)no / (nv + no)), 0.0);

@@ -193,10 +193,10 @@ void launch_wbuild_ex(int mode, const double* X, const double* XN, const double*
                       const int* tri, int ntri, double* cubes, int64_t zs, int64_t ss, int pitch,
                       int no, int nv, bool all_terms, hipStream_t st);
 // two_planes: the planes are those of the FP64 W build (PA, PB), else the three planes
-// of the low-precision one.  Mixed-all copies (nullable): cubesF, FP32 tau~ and tau~T,
+// of the low-precision one.  transposed: write tau~T too.  Mixed-all copies (nullable): cubesF, FP32 tau~ and tau~T,
 // [triple][2][nv^3]; YL, the split-BF16 k-major views of k_omega_lp with lpP pieces
 void launch_mix(bool two_planes, const double* eps, const int* tri, int ntri, double* cubes,
-                float* cubesF, void* YL, int lpP, int no, int nv, hipStream_t st);
+                float* cubesF, void* YL, int lpP, bool transposed, int no, int nv, hipStream_t st);
 void launch_tau_export(bool two_planes, const double* eps, const int* tri, const double* cubes,
                        double* tau, int no, int nv, hipStream_t st);
 // Wave tiles of the FP64 GEMMs: FM x FN blocks of 16 x 16 outputs per wavefront.
@@ -206,15 +206,15 @@ int pick_shape(int64_t M, int64_t N, bool packed = false);
 void shape_tiles(int shape, int64_t M, int64_t N, int* tm, int* tn);
 // Omega contraction of a batch: the vv term and Omega1 into per-(triple,
 // permutation, chunk) partial slabs Pvv, then their fixed-order reduction into
-// Ot1/Ot2 (added, not overwritten); the oo and Fock terms added into OtT
-// (output-stationary).  The reduction and the OtT update of successive batches
-// must run in batch order.
+// Ot1/Ot2 (added, not overwritten); the oo and Fock terms added into
+// OtT and Ot2 (output-stationary).  The reduction and the oo update of successive
+// batches must run in batch order.
 void launch_omega(const double* cubes, const Blocks& b, const int* tri, int ntri, double* Pvv,
                   int no, int nv, hipStream_t st);
 void launch_reduce(const int* tri, int ntri, const double* Pvv, double* Ot1, double* Ot2, int no,
                    int nv, bool fp32acc, hipStream_t st);
-void launch_omega_oo(const double* cubes, const Blocks& b, const int* tri, int ntri, double* OtT,
-                     int no, int nv, hipStream_t st);
+void launch_omega_oo(const double* cubes, const Blocks& b, const int* tri, int ntri, double* Ot2,
+                     double* OtT, int no, int nv, hipStream_t st);
 // The mixed-all form of launch_omega: FP32 MFMA over FP32 copies of the cubes
 // (tau~, tau~T per triple) and of Gbc / Gcb; partial slabs in FP64 as above.
 void launch_omega_f32(const float* cubesF, const float* GbcF, const float* GcbF, const int* tri,
@@ -267,11 +267,13 @@ struct PackJob {
   int no, nv, ntri, nch;
   int wshape, oshape;    // wave-tile shapes of the FP64 W build and Omega GEMM, the same
                          // for every job
+  int rslices;           // shares and element blocks of the reduction (set by pack_items)
+  unsigned rgx;
   unsigned first[PK_N];  // first packed work item of this job, per kernel
 };
 // Work items of one job per kernel (the workgroups of its unpacked launch); prec: the
 // W build's arithmetic.
-void pack_items(const PackJob& j, int prec, unsigned (&items)[PK_N]);
+void pack_items(PackJob& j, int prec, unsigned (&items)[PK_N]);
 // The five packed launches of one step (jobs in device memory, host copy for the
 // item counts); prec: the W build's arithmetic, shared by every job.
 void launch_packed_step(const PackJob* dev_jobs, const PackJob* host_jobs, int njobs, int prec,

@@ -10,16 +10,18 @@
 //  k_mix     (LDS)  per S3-orbit of 8x8x8 virtual blocks: X, the denominator
 //            division tau = -X / eps^{abc}_{ijk}, and the contravariant
 //            tau~ = 4 tau^{abc} - 2 tau^{acb} - 2 tau^{cba} - 2 tau^{bac} + tau^{bca} + tau^{cab},
-//            written as tau~[a][b][c] and its transpose tau~T[a][c][b].
+//            written as tau~[a][b][c] (and, for the Jacobian preparation, its transpose
+//            tau~T[a][c][b]).
 //  k_omega   (FP64 MFMA)  for each distinct occupied permutation (p,q,r), with
-//            U = tau~_{pqr} read from tau~ or tau~T, one long-K GEMM over K = (b, c):
+//            U = tau~_{pqr} a view of tau~, one long-K GEMM over K = (b, c):
 //              Ot2[p][q][a][d] += sum_bc U[a,b,c] g_{dbrc}    (columns d < nv)
 //              Ot1[p][a]       += sum_bc U[a,b,c] g_{qbrc}    (column nv)
 //            split over K into per-(triple, permutation, chunk) partial slabs;
 //  k_reduce  adds the slabs into Ot1/Ot2 in a fixed order (deterministic, no atomics);
 //  k_omega_oo (FP64 MFMA, output-stationary)  the oo and Fock terms
 //              Ot2[p][l][a][b] += sum_c U[a,b,c] (delta_lq F_rc - g_{qlrc}),
-//            kept transposed, OtT[p][l][b][a], so that its stores run along a.
+//            four of the six permutations kept transposed, OtT[p][l][b][a], so that
+//            their stores run along a.
 #include <algorithm>
 #include <initializer_list>
 #include <type_traits>
@@ -421,7 +423,7 @@ template <int MIXT, bool TWO>
 __device__ __forceinline__ void mix_body(const double* __restrict__ eps,
                                          const int* __restrict__ tri, double* __restrict__ cubes,
                                          float* __restrict__ cubesF, uint16_t* __restrict__ YL,
-                                         int lpP, int no, int nv, int bx, int by) {
+                                         int lpP, int transposed, int no, int nv, int bx, int by) {
   constexpr int MIXH = 512 / MIXT;
   __shared__ double Xs[6 * TSZ];
   const int z = by, ob = bx;
@@ -518,7 +520,7 @@ __device__ __forceinline__ void mix_body(const double* __restrict__ eps,
     }
   }
   __syncthreads();
-  // 2. tau~ on the orbit, held in registers until every thread has read X
+  // 2. tau~ on the orbit, in registers
   double tt[6][MIXH];
 #pragma unroll
   for (int o = 0; o < 6; ++o) {
@@ -549,6 +551,33 @@ __device__ __forceinline__ void mix_body(const double* __restrict__ eps,
       tt[o][h] = val;
     }
   }
+  // 3. write tau~[a][b][c], with zeros in the padding columns c >= nv, and its FP32 or
+  //    split-BF16 copies of the same order, straight from the registers
+  double* TT = cz + SLOT_TT * cs;
+#pragma unroll
+  for (int o = 0; o < 6; ++o) {
+    if (canon[o] != o) continue;
+    int q0, q1, q2;
+    orient(o, q0, q1, q2);
+    const int A0 = blk[q0] * MT, B0 = blk[q1] * MT, C0 = blk[q2] * MT;
+#pragma unroll
+    for (int h = 0; h < MIXH; ++h) {
+      const int e = t + MIXT * h;
+      const int u = e >> 6, v = (e >> 3) & 7, w = e & 7;
+      const int a = A0 + u, b = B0 + v, c = C0 + w;
+      if (a < nv && b < nv) {
+        const double x = tt[o][h];
+        TT[(a * nvl + b) * rp + c] = x;
+        if (cubesF && c < nv) cubesF[(int64_t)z * 2 * nv3 + (a * nvl + b) * nvl + c] = (float)x;
+        if (YL && c < nv) {  // view 0 at [a][(b, c)], view 1 at [b][(a, c)]
+          yl_put(YL, lpP, z, 0, a, b, c, nv, x);
+          yl_put(YL, lpP, z, 1, b, a, c, nv, x);
+        }
+      }
+    }
+  }
+  // 4. the copies with a and b, or c and b, exchanged: through LDS, b fastest
+  if (!transposed && !cubesF && !YL) return;
   __syncthreads();
 #pragma unroll
   for (int o = 0; o < 6; ++o) {
@@ -560,8 +589,6 @@ __device__ __forceinline__ void mix_body(const double* __restrict__ eps,
     }
   }
   __syncthreads();
-  // 3. write tau~[a][b][c] (w fastest) and tau~T[a][c][b] (v fastest)
-  double* TT = cz + SLOT_TT * cs;
   double* TTT = cz + SLOT_TTT * cs;
 #pragma unroll
   for (int o = 0; o < 6; ++o) {
@@ -572,30 +599,15 @@ __device__ __forceinline__ void mix_body(const double* __restrict__ eps,
 #pragma unroll
     for (int h = 0; h < MIXH; ++h) {
       const int e = t + MIXT * h;
-      {
-        const int u = e >> 6, v = (e >> 3) & 7, w = e & 7;
-        const int a = A0 + u, b = B0 + v, c = C0 + w;
-        if (a < nv && b < nv) {  // with zeros in the padding columns c >= nv (X is zero there)
-          const double x = Xs[o * TSZ + TP(u, v, w)];
-          TT[(a * nvl + b) * rp + c] = x;
-          if (cubesF && c < nv) cubesF[(int64_t)z * 2 * nv3 + (a * nvl + b) * nvl + c] = (float)x;
-          if (YL && c < nv) {  // view 0 at [a][(b, c)], view 1 at [b][(a, c)]
-            yl_put(YL, lpP, z, 0, a, b, c, nv, x);
-            yl_put(YL, lpP, z, 1, b, a, c, nv, x);
-          }
-        }
-      }
-      {
-        const int u = e >> 6, w = (e >> 3) & 7, v = e & 7;
-        const int a = A0 + u, b = B0 + v, c = C0 + w;
-        if (a < nv && b < nv && c < nv) {
-          const double x = Xs[o * TSZ + TP(u, v, w)];
-          TTT[(a * nvl + c) * rp + b] = x;
-          if (cubesF) cubesF[((int64_t)z * 2 + 1) * nv3 + (a * nvl + c) * nvl + b] = (float)x;
-          if (YL) {  // view 2 at [c][(a, b)], view 3 at [a][(c, b)]
-            yl_put(YL, lpP, z, 2, c, a, b, nv, x);
-            yl_put(YL, lpP, z, 3, a, c, b, nv, x);
-          }
+      const int u = e >> 6, w = (e >> 3) & 7, v = e & 7;
+      const int a = A0 + u, b = B0 + v, c = C0 + w;
+      if (a < nv && b < nv && c < nv) {
+        const double x = Xs[o * TSZ + TP(u, v, w)];
+        if (transposed) TTT[(a * nvl + c) * rp + b] = x;
+        if (cubesF) cubesF[((int64_t)z * 2 + 1) * nv3 + (a * nvl + c) * nvl + b] = (float)x;
+        if (YL) {  // view 2 at [c][(a, b)], view 3 at [a][(c, b)]
+          yl_put(YL, lpP, z, 2, c, a, b, nv, x);
+          yl_put(YL, lpP, z, 3, a, c, b, nv, x);
         }
       }
     }
@@ -606,12 +618,13 @@ template <int MIXT, bool TWO>
 __global__ __launch_bounds__(MIXT) void k_mix(const double* __restrict__ eps,
                                              const int* __restrict__ tri,
                                              double* __restrict__ cubes, float* __restrict__ cubesF,
-                                             uint16_t* __restrict__ YL, int lpP, int no, int nv) {
-  mix_body<MIXT, TWO>(eps, tri, cubes, cubesF, YL, lpP, no, nv, blockIdx.x, blockIdx.y);
+                                             uint16_t* __restrict__ YL, int lpP, int transposed,
+                                             int no, int nv) {
+  mix_body<MIXT, TWO>(eps, tri, cubes, cubesF, YL, lpP, transposed, no, nv, blockIdx.x, blockIdx.y);
 }
 
 void launch_mix(bool two_planes, const double* eps, const int* tri, int ntri, double* cubes,
-                float* cubesF, void* YL, int lpP, int no, int nv, hipStream_t st) {
+                float* cubesF, void* YL, int lpP, bool transposed, int no, int nv, hipStream_t st) {
   const int nb = (nv + MT - 1) / MT;
   const int nbt = nb * (nb + 1) * (nb + 2) / 6;
   // 512 threads, one element per thread and orientation; the form that also writes
@@ -619,13 +632,13 @@ void launch_mix(bool two_planes, const double* eps, const int* tri, int ntri, do
   // faster for it at nv = 250
   if (two_planes)
     hipLaunchKernelGGL((k_mix<512, true>), dim3(nbt, ntri), dim3(512), 0, st, eps, tri, cubes,
-                       nullptr, nullptr, 0, no, nv);
+                       nullptr, nullptr, 0, transposed ? 1 : 0, no, nv);
   else if (YL)
     hipLaunchKernelGGL((k_mix<256, false>), dim3(nbt, ntri), dim3(256), 0, st, eps, tri, cubes,
-                       cubesF, (uint16_t*)YL, lpP, no, nv);
+                       cubesF, (uint16_t*)YL, lpP, transposed ? 1 : 0, no, nv);
   else
     hipLaunchKernelGGL((k_mix<512, false>), dim3(nbt, ntri), dim3(512), 0, st, eps, tri, cubes,
-                       cubesF, (uint16_t*)YL, lpP, no, nv);
+                       cubesF, (uint16_t*)YL, lpP, transposed ? 1 : 0, no, nv);
 }
 
 // ---------------------------------------------------------------------------
@@ -1157,90 +1170,52 @@ __global__ __launch_bounds__(OCfg::NT) void k_omega_f32(const float* __restrict_
       }
 }
 
-// The (triple, permutation) pairs of a batch whose first occupied index is p, in
-// batch order (triple, then permutation): lz = 6 z + pi, lqr = q no + r; at most two
-// per triple, so at most 2 * MAX_BATCH.  Every thread of the workgroup calls it (it
-// holds barriers); cz is LDS scratch of MAX_BATCH + 1 ints.  Returns the count.
+// The (triple, permutation) pairs of a batch with first occupied index p, second index q
+// (any with q < 0) and permutation in the mask `perms`, in batch order (triple, then
+// permutation): lz = 6 z + pi, lqr = q no + r; at most two per triple and p, so at most
+// 2 * MAX_BATCH.  Every thread of the workgroup (256 or more, whole wavefronts) calls it; it
+// holds barriers.  One candidate per thread and round, placed by ballots; cz is LDS scratch
+// of one int per wavefront.  Returns the count.
 #define PLIST_MAX (2 * MAX_BATCH)
-__device__ inline int pairs_with_p(const int* __restrict__ tri, int ntri, int p, int no, int* lz,
-                                   int* lqr, int* cz) {
-  if (ntri <= 8) {  // a short batch: one thread, one barrier
-    if (threadIdx.x == 0) {
-      int n = 0;
-      for (int z = 0; z < ntri; ++z) {
-        const int i = tri[3 * z], j = tri[3 * z + 1], k = tri[3 * z + 2];
-        const int kind = tri_kind(i, j, k);
-        for (int pi = 0; pi < 6; ++pi) {
-          if (!perm_active(kind, pi)) continue;
-          int pp, q, r;
-          perm_pqr(pi, i, j, k, pp, q, r);
-          if (pp != p) continue;
-          lz[n] = z * 6 + pi;
-          lqr[n] = q * no + r;
-          ++n;
-        }
-      }
-      cz[MAX_BATCH] = n;
+__device__ inline int list_pairs(const int* __restrict__ tri, int ntri, int p, int q,
+                                 unsigned perms, int no, int* lz, int* lqr, int* cz) {
+  const int nt = (int)blockDim.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = nt >> 6;
+  int base = 0;
+  for (int e0 = 0; e0 < 6 * ntri; e0 += nt) {
+    const int e = e0 + (int)threadIdx.x;
+    bool in = false;
+    int qr = 0;
+    if (e < 6 * ntri) {
+      const int z = e / 6, pi = e - 6 * z;
+      const int i = tri[3 * z], j = tri[3 * z + 1], k = tri[3 * z + 2];
+      int pp, qq, rr;
+      perm_pqr(pi, i, j, k, pp, qq, rr);
+      in = pp == p && (q < 0 || qq == q) && ((perms >> pi) & 1u) &&
+           perm_active(tri_kind(i, j, k), pi);
+      qr = qq * no + rr;
+    }
+    const unsigned long long hit = __ballot(in);
+    if (lane == 0) cz[wave] = __popcll(hit);
+    __syncthreads();
+    int at = base;
+    for (int w = 0; w < nw; ++w) {
+      const int c = cz[w];
+      if (w < wave) at += c;
+      base += c;
+    }
+    at += __popcll(hit & ((1ull << lane) - 1ull));
+    if (in && at < PLIST_MAX) {
+      lz[at] = e;
+      lqr[at] = qr;
     }
     __syncthreads();
-    return cz[MAX_BATCH];
   }
-  // the number of permutations with first index p of each triple (at most two)
-  for (int z = threadIdx.x; z < ntri; z += blockDim.x) {
-    const int i = tri[3 * z], j = tri[3 * z + 1], k = tri[3 * z + 2];
-    const int kind = tri_kind(i, j, k);
-    int c = 0;
-    for (int pi = 0; pi < 6; ++pi) {
-      if (!perm_active(kind, pi)) continue;
-      int pp, q, r;
-      perm_pqr(pi, i, j, k, pp, q, r);
-      c += pp == p;
-    }
-    cz[z] = c;
-  }
-  __syncthreads();
-  // exclusive prefix sums of the counts (wavefront 0, 64 triples at a time)
-  if (threadIdx.x < 64) {
-    const int lane = threadIdx.x;
-    int carry = 0;
-    for (int base = 0; base < ntri; base += 64) {
-      const int z = base + lane;
-      const int v = z < ntri ? cz[z] : 0;
-      int incl = v;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(incl, o);
-        if (lane >= o) incl += t;
-      }
-      if (z < ntri) cz[z] = carry + incl - v;
-      carry += __shfl(incl, 63);
-    }
-    if (lane == 0) cz[MAX_BATCH] = carry;
-  }
-  __syncthreads();
-  for (int z = threadIdx.x; z < ntri; z += blockDim.x) {
-    const int i = tri[3 * z], j = tri[3 * z + 1], k = tri[3 * z + 2];
-    const int kind = tri_kind(i, j, k);
-    int at = cz[z];
-    for (int pi = 0; pi < 6; ++pi) {
-      if (!perm_active(kind, pi)) continue;
-      int pp, q, r;
-      perm_pqr(pi, i, j, k, pp, q, r);
-      if (pp != p) continue;
-      if (at < PLIST_MAX) {
-        lz[at] = z * 6 + pi;
-        lqr[at] = q * no + r;
-      }
-      ++at;
-    }
-  }
-  const int n = min(cz[MAX_BATCH], PLIST_MAX);
-  __syncthreads();
-  return n;
+  return base < PLIST_MAX ? base : PLIST_MAX;
 }
+#define LIST_SCRATCH 16
 
-// The view of U_pi[a, b, c] at fixed b as a strided (a, c) matrix: base + b * sbb, (sm, sk),
-// in the cubes [x][y][z] with the row pitch rp (x stride nv rp, y stride rp).
+// The view of U_pi[a, b, c] at fixed b as a strided (a, c) matrix: base + b * sbb, (sm, sk)
+// (the Jacobian preparation, which keeps tau~T too), in the cubes [x][y][z] with the row pitch rp (x stride nv rp, y stride rp).
 __device__ inline void u_view(int pi, int nv, int rp, int& slot, int& sbb, int& sm, int& sk) {
   const int pl = nv * rp;
   switch (pi) {
@@ -1256,13 +1231,16 @@ __device__ inline void u_view(int pi, int nv, int rp, int& slot, int& sbb, int& 
 // ---------------------------------------------------------------------------
 // Omega contraction: the oo and Fock terms, output-stationary
 // ---------------------------------------------------------------------------
-// One workgroup of 4 wavefronts per (p, pair of b, 64-wide tile of a) sums, over
+// One workgroup of 4 wavefronts per (p, form, pair of b, 64-wide tile of a) sums, over
 // the batch's pairs with that p in batch order,
-//   OtT[p][l][b][a] += sum_c Hs[q][r][c][l] U[a,b,c]      (l < no)
-// (Hs[q][r][c][l] = delta_lq F_rc - g_{qlrc}) and adds the sum into OtT
-// (read-modify-write; successive batches are ordered by the caller).  Wavefront w
-// owns the 16 columns a0 = tile + 16 w of both b and every row l (FNO blocks of
-// 16), as D[l][a] of the FP64 MFMA with A = Hs, B = U.  The kernel streams U once
+//   Out[p][l][b][a] += sum_c Hs[q][r][c][l] U[a,b,c]      (l < no)
+// (Hs[q][r][c][l] = delta_lq F_rc - g_{qlrc}) and adds the sum into Out
+// (read-modify-write; successive batches are ordered by the caller).  Form 0 takes the
+// permutations whose view of tau~ has a or c contiguous (pi 0, 1, 2, 5) and Out = OtT;
+// form 1 those with b contiguous (pi 3, 4), with the roles of a and b exchanged and
+// Out = Ot2: both load rows of the one cube, and no transposed copy of it is needed.
+// Wavefront w owns the 16 columns a0 = tile + 16 w of both b and every row l (FNO blocks
+// of 16), as D[l][a] of the FP64 MFMA with A = Hs, B = U.  The kernel streams U once
 // per pair and is bound by the memory pipeline, so there are no workgroup
 // barriers in the loop: the next step's loads are in flight during the current
 // step's MFMAs, and the Hs fragments serve both b.  Within a 16-c step, lane
@@ -1271,22 +1249,34 @@ __device__ inline void u_view(int pi, int nv, int rp, int& slot, int& sbb, int& 
 // in the MFMA layout directly (16 consecutive a per row of c); views with c
 // contiguous are loaded along c (4 rows of 16 consecutive c per instruction) and
 // transposed through a wavefront-private LDS tile.
+// the view of U_pi as (column m, fixed index b, contracted c) in TT[x][y][z]
+__device__ inline void oo_view(int pi, int nv, int rp, int& sbb, int& sm, int& sk) {
+  const int pl = nv * rp;
+  switch (pi) {
+    case 0: sbb = rp; sm = pl; sk = 1; break;   // TT[a][b][c]
+    case 1: sbb = pl; sm = rp; sk = 1; break;   // TT[b][a][c]
+    case 2: sbb = rp; sm = 1; sk = pl; break;   // TT[c][b][a]
+    case 3: sbb = pl; sm = 1; sk = rp; break;   // TT[a][c][b], m = b, fixed a
+    case 4: sbb = rp; sm = 1; sk = pl; break;   // TT[c][a][b], m = b, fixed a
+    default: sbb = pl; sm = 1; sk = rp; break;  // TT[b][c][a]
+  }
+}
 template <int FNO>
 __device__ __forceinline__ void omega_oo_body(const double* __restrict__ cubes,
                                               const double* __restrict__ Hs,
                                               const int* __restrict__ tri, int ntri,
+                                              double* __restrict__ Ot2,
                                               double* __restrict__ OtT, int no, int nv,
-                                              int tiles_a, int bx, int by) {
+                                              int tiles_a, int bx, int by, int form) {
   constexpr int NB = 2;
-  __shared__ int lz[PLIST_MAX], lqr[PLIST_MAX], cz[MAX_BATCH + 1];
-  int cnt;
+  __shared__ int lz[PLIST_MAX], lqr[PLIST_MAX], cz[LIST_SCRATCH];
+  double* __restrict__ Out = form ? Ot2 : OtT;
   __shared__ double lt[4][NB][16][17];  // per wavefront: 16 rows a x 16 c (+1 pad)
   const int p = by;
   const int bp = bx / tiles_a;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int a0 = (bx % tiles_a) * 64 + 16 * wave;
-  cnt = pairs_with_p(tri, ntri, p, no, lz, lqr, cz);
-  const int n = cnt;
+  const int n = list_pairs(tri, ntri, p, -1, form ? 0x18u : 0x27u, no, lz, lqr, cz);
   if (n == 0 || a0 >= nv) return;  // no workgroup barrier follows
   const int m = lane & 15, kq = lane >> 4;
   int bb[NB];
@@ -1312,9 +1302,9 @@ __device__ __forceinline__ void omega_oo_body(const double* __restrict__ cubes,
                   unsigned& cm) {
     const int t = it / cs, c0 = (it - t * cs) * 16;
     const int zp = lz[t], zz = zp / 6, pi = zp % 6;
-    int slot, sbb, sm, sk;
-    u_view(pi, nv, cube_pitch(nv), slot, sbb, sm, sk);
-    const double* ub = cubes + ((int64_t)zz * NSLOT + slot) * cube_slot(nv);
+    int sbb, sm, sk;
+    oo_view(pi, nv, cube_pitch(nv), sbb, sm, sk);
+    const double* ub = cubes + ((int64_t)zz * NSLOT + SLOT_TT) * cube_slot(nv);
     ccont = (sk == 1);
     if (ccont) {  // element i: row a0 + 4 i + kq, c = c0 + m
       const int c = c0 + m;
@@ -1392,7 +1382,7 @@ __device__ __forceinline__ void omega_oo_body(const double* __restrict__ cubes,
       for (int rr = 0; rr < 4; ++rr) {
         const int l = 16 * f + kq + 4 * rr;
         if (l < no && ac < nv && b < nv)
-          OtT[(((int64_t)p * no + l) * nvl + b) * nvl + ac] += acc[j][f][rr];
+          Out[(((int64_t)p * no + l) * nvl + b) * nvl + ac] += acc[j][f][rr];
       }
   }
 }
@@ -1401,61 +1391,86 @@ template <int FNO>
 __global__ __launch_bounds__(256) void k_omega_oo(const double* __restrict__ cubes,
                                                   const double* __restrict__ Hs,
                                                   const int* __restrict__ tri, int ntri,
+                                                  double* __restrict__ Ot2,
                                                   double* __restrict__ OtT, int no, int nv,
                                                   int tiles_a) {
-  omega_oo_body<FNO>(cubes, Hs, tri, ntri, OtT, no, nv, tiles_a, blockIdx.x, blockIdx.y);
+  omega_oo_body<FNO>(cubes, Hs, tri, ntri, Ot2, OtT, no, nv, tiles_a, blockIdx.x, blockIdx.y,
+                     blockIdx.z);
 }
 
 // For output block (p, x):
 //   Ot2[p][x][a][d] += sum of Pvv[z][pi][chunk][a][d] over the batch's (triple,
 //                      permutation) pairs with that p and q == x, and chunks;
-//   Ot1[p][a]       += column nv of Pvv (block x == 0).
-// Fixed summation order: triple, permutation, chunk.
+//   Ot1[p][a]       += column nv of Pvv over the pairs with that p (block x == no).
+// 256 threads as 256 / slices elements by `slices` shares of the (pair, chunk) slabs (every
+// slices-th, in order), which are added in share order: a fixed order, no atomics.  One
+// share streams best where there are many blocks; a few blocks with many slabs each are a
+// chain of dependent adds, so small launches take more shares (reduce_slices), and the few
+// elements of Ot1 always 16 (at 6/45, 17 triples and 32 chunks the one-share form took 91 us).
+constexpr int OT1_SLICES = 16;
 __device__ __forceinline__ void reduce_body(const int* __restrict__ tri, int ntri,
                                             const double* __restrict__ Pvv,
                                             double* __restrict__ Ot1, double* __restrict__ Ot2,
-                                            int no, int nv, int nchunks, int bx, int by, int bz) {
-  __shared__ int lz[PLIST_MAX], lqr[PLIST_MAX], cz[MAX_BATCH + 1];
-  int cnt;
+                                            int no, int nv, int nchunks, int slices, int bx, int by,
+                                            int bz) {
+  __shared__ int lz[PLIST_MAX], lqr[PLIST_MAX], cz[LIST_SCRATCH];
+  __shared__ double part[256];
   const int p = bz, x = by;
-  cnt = pairs_with_p(tri, ntri, p, no, lz, lqr, cz);
-  const int64_t nvl = nv, nv2 = nvl * nvl;
+  const bool one = x == no;  // Ot1
+  if (one) slices = OT1_SLICES;
+  const int els = 256 / slices;
+  const int n = one ? nv : nv * nv;
+  if (bx * els >= n) return;
+  const int cnt = list_pairs(tri, ntri, p, one ? -1 : x, 0x3fu, no, lz, lqr, cz);
+  if (cnt == 0) return;  // a block without pairs leaves its output as it is
+  const int64_t nvl = nv;
   const int NV1 = nv + 1;
-  const int64_t pvs = (int64_t)nvl * NV1;  // one chunk slab
-  const int64_t e = (int64_t)bx * blockDim.x + threadIdx.x;
-  const bool o2 = e < nv2;
-  const bool o1 = (x == 0) && e < nv;  // Omega1 element a = e
-  if (!o2 && !o1) return;
-  const int a = (int)(e / nvl), d = (int)(e % nvl);
-  const int n = cnt;
-  if (o2) {
-    double s2 = 0.0;
-    bool any = false;  // uniform: a block (p, x) without pairs leaves Ot2 as it is
-    for (int t = 0; t < n; ++t) {
-      if (lqr[t] / no != x) continue;
-      any = true;
-      const double* pv = Pvv + (int64_t)lz[t] * nchunks * pvs + (int64_t)a * NV1 + d;
+  const int64_t pvs = nvl * NV1;  // one chunk slab
+  const int share = threadIdx.x / els, el = threadIdx.x % els;
+  const int e = bx * els + el;
+  double s = 0.0;
+  if (e < n) {
+    const int64_t off = one ? (int64_t)e * NV1 + nv : (int64_t)(e / nv) * NV1 + e % nv;
+    for (int t = 0; t < cnt; ++t) {
+      const double* pv = Pvv + (int64_t)lz[t] * nchunks * pvs + off;
+      // chunk c of pair t is slab t nchunks + c of the list
+      int c = (share - t * nchunks) % slices;
+      if (c < 0) c += slices;
 #pragma unroll 16
-      for (int c = 0; c < nchunks; ++c) s2 += pv[c * pvs];
+      for (; c < nchunks; c += slices) s += pv[c * pvs];
     }
-    if (any) Ot2[((int64_t)p * no + x) * nv2 + e] += s2;
   }
-  if (o1) {
-    double s1 = 0.0;
-    for (int t = 0; t < n; ++t) {
-      const double* pv = Pvv + (int64_t)lz[t] * nchunks * pvs + (int64_t)e * NV1 + nv;
-#pragma unroll 16
-      for (int c = 0; c < nchunks; ++c) s1 += pv[c * pvs];
-    }
-    Ot1[(int64_t)p * nvl + e] += s1;
+  if (slices > 1) {
+    part[threadIdx.x] = s;
+    __syncthreads();
+    if (share == 0)
+      for (int h = 1; h < slices; ++h) s += part[h * els + el];
+  }
+  if (share == 0 && e < n) {
+    if (one) Ot1[(int64_t)p * nvl + e] += s;
+    else Ot2[((int64_t)p * no + x) * nvl * nvl + e] += s;
   }
 }
 
 __global__ __launch_bounds__(256) void k_reduce(const int* __restrict__ tri, int ntri,
                                                 const double* __restrict__ Pvv,
                                                 double* __restrict__ Ot1, double* __restrict__ Ot2,
-                                                int no, int nv, int nchunks) {
-  reduce_body(tri, ntri, Pvv, Ot1, Ot2, no, nv, nchunks, blockIdx.x, blockIdx.y, blockIdx.z);
+                                                int no, int nv, int nchunks, int slices) {
+  reduce_body(tri, ntri, Pvv, Ot1, Ot2, no, nv, nchunks, slices, blockIdx.x, blockIdx.y,
+              blockIdx.z);
+}
+
+// Shares of k_reduce: enough workgroups for two per CU, at most 16 shares.
+static int reduce_slices(int no, int nv) {
+  int sl = 1;
+  while (sl < 16 && (int64_t)nblk((int64_t)nv * nv, 256 / sl) * no * no < 512) sl *= 4;
+  return sl;
+}
+// its grid: element blocks (at least those of Ot1), second index and Ot1, first index
+static dim3 reduce_grid(int no, int nv) {
+  const unsigned gx = std::max(nblk((int64_t)nv * nv, 256 / reduce_slices(no, nv)),
+                               nblk(nv, 256 / OT1_SLICES));
+  return dim3(gx, no + 1, no);
 }
 
 // ---------------------------------------------------------------------------
@@ -1477,14 +1492,12 @@ __global__ __launch_bounds__(ZvCfg::NT) void k_zv(const double* __restrict__ cub
                                                   int tiles_m, int tiles_n) {
   typedef ZvCfg T;
   __shared__ double lds[T::LDS_DOUBLES];
-  __shared__ int lz[PLIST_MAX], lqr[PLIST_MAX], cz[MAX_BATCH + 1];
-  int cnt;
+  __shared__ int lz[PLIST_MAX], lqr[PLIST_MAX], cz[LIST_SCRATCH];
   const int p = blockIdx.y;
   const int tpp = tiles_m * tiles_n;
   const int b = blockIdx.x / tpp, tile = blockIdx.x % tpp;
   const int m0 = (tile / tiles_n) * T::BM, n0 = (tile % tiles_n) * T::BN;
-  cnt = pairs_with_p(tri, ntri, p, no, lz, lqr, cz);
-  const int n = cnt;
+  const int n = list_pairs(tri, ntri, p, -1, 0x3fu, no, lz, lqr, cz);
   if (n == 0) return;
   const int64_t nvl = nv, nv2 = nvl * nvl;
   const int cs = (nv + T::BK - 1) / T::BK;
@@ -1574,18 +1587,15 @@ __global__ __launch_bounds__(256) void k_zo_reduce(const int* __restrict__ tri, 
                                                    const double* __restrict__ Pzo,
                                                    double* __restrict__ Zo, int no, int nv,
                                                    int nbchunks) {
-  __shared__ int lz[PLIST_MAX], lqr[PLIST_MAX], cz[MAX_BATCH + 1];
-  int cnt;
+  __shared__ int lz[PLIST_MAX], lqr[PLIST_MAX], cz[LIST_SCRATCH];
   const int q = blockIdx.y, p = blockIdx.z;
-  cnt = pairs_with_p(tri, ntri, p, no, lz, lqr, cz);
-  const int n = cnt;
+  const int n = list_pairs(tri, ntri, p, q, 0x3fu, no, lz, lqr, cz);
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (n == 0 || e >= (int64_t)nv * no) return;
   const int a = (int)(e / no), l = (int)(e % no);
   const int64_t slab = (int64_t)nv * no;
   double s = 0.0;
   for (int t = 0; t < n; ++t) {
-    if (lqr[t] / no != q) continue;
     const double* pz = Pzo + (int64_t)lz[t] * nbchunks * slab + e;
     for (int c = 0; c < nbchunks; ++c) s += pz[c * slab];
   }
@@ -1716,26 +1726,29 @@ void launch_g_to_f32(const double* src, float* dst, int64_t rows, int nv, hipStr
   hipLaunchKernelGGL(k_g_to_f32, dim3(g), dim3(256), 0, st, src, dst, rows, nv);
 }
 
-void launch_omega_oo(const double* cubes, const Blocks& b, const int* tri, int ntri, double* OtT,
-                     int no, int nv, hipStream_t st) {
+void launch_omega_oo(const double* cubes, const Blocks& b, const int* tri, int ntri, double* Ot2,
+                     double* OtT, int no, int nv, hipStream_t st) {
   const int ta = (nv + 63) / 64;
-  const dim3 grid(((nv + 1) / 2) * ta, no), block(256);
+  const dim3 grid(((nv + 1) / 2) * ta, no, 2), block(256);
   if (no <= 16)
-    hipLaunchKernelGGL(k_omega_oo<1>, grid, block, 0, st, cubes, b.Hs, tri, ntri, OtT, no, nv, ta);
+    hipLaunchKernelGGL(k_omega_oo<1>, grid, block, 0, st, cubes, b.Hs, tri, ntri, Ot2, OtT, no, nv,
+                       ta);
   else if (no <= 32)
-    hipLaunchKernelGGL(k_omega_oo<2>, grid, block, 0, st, cubes, b.Hs, tri, ntri, OtT, no, nv, ta);
+    hipLaunchKernelGGL(k_omega_oo<2>, grid, block, 0, st, cubes, b.Hs, tri, ntri, Ot2, OtT, no, nv,
+                       ta);
   else if (no <= 48)
-    hipLaunchKernelGGL(k_omega_oo<3>, grid, block, 0, st, cubes, b.Hs, tri, ntri, OtT, no, nv, ta);
+    hipLaunchKernelGGL(k_omega_oo<3>, grid, block, 0, st, cubes, b.Hs, tri, ntri, Ot2, OtT, no, nv,
+                       ta);
   else
-    hipLaunchKernelGGL(k_omega_oo<4>, grid, block, 0, st, cubes, b.Hs, tri, ntri, OtT, no, nv, ta);
+    hipLaunchKernelGGL(k_omega_oo<4>, grid, block, 0, st, cubes, b.Hs, tri, ntri, Ot2, OtT, no, nv,
+                       ta);
 }
 
 void launch_reduce(const int* tri, int ntri, const double* Pvv, double* Ot1, double* Ot2, int no,
                    int nv, bool fp32acc, hipStream_t st) {
   const int nch = omega_kchunks(nv, ntri, fp32acc);
-  const int64_t nv2 = (int64_t)nv * nv;
-  hipLaunchKernelGGL(k_reduce, dim3(nblk(nv2, 256), no, no), dim3(256), 0, st, tri, ntri, Pvv, Ot1,
-                     Ot2, no, nv, nch);
+  hipLaunchKernelGGL(k_reduce, reduce_grid(no, nv), dim3(256), 0, st, tri, ntri, Pvv, Ot1, Ot2, no,
+                     nv, nch, reduce_slices(no, nv));
 }
 
 // ---------------------------------------------------------------------------
@@ -1773,7 +1786,7 @@ __global__ __launch_bounds__(512) void k_pack_mix(const PackJob* __restrict__ jo
     const unsigned local = item - J.first[PK_MIX];
     const int nb = (J.nv + MT - 1) / MT;
     const unsigned nbt = (unsigned)(nb * (nb + 1) * (nb + 2) / 6);
-    mix_body<512, TWO>(J.eps, J.tri, J.cubes, nullptr, nullptr, 0, J.no, J.nv, (int)(local % nbt),
+    mix_body<512, TWO>(J.eps, J.tri, J.cubes, nullptr, nullptr, 0, 0, J.no, J.nv, (int)(local % nbt),
                   (int)(local / nbt));
     __syncthreads();
   }
@@ -1800,8 +1813,8 @@ __global__ __launch_bounds__(256) void k_pack_omega_oo(const PackJob* __restrict
     const unsigned local = item - J.first[PK_OO];
     const int ta = (J.nv + 63) / 64;
     const unsigned gx = (unsigned)((J.nv + 1) / 2) * ta;
-    omega_oo_body<FNO>(J.cubes, J.Hs, J.tri, J.ntri, J.OtT, J.no, J.nv, ta, (int)(local % gx),
-                       (int)(local / gx));
+    omega_oo_body<FNO>(J.cubes, J.Hs, J.tri, J.ntri, J.Ot2, J.OtT, J.no, J.nv, ta,
+                       (int)(local % gx), (int)((local / gx) % J.no), (int)(local / (gx * J.no)));
     __syncthreads();
   }
 }
@@ -1811,21 +1824,24 @@ __global__ __launch_bounds__(256) void k_pack_reduce(const PackJob* __restrict__
   for (unsigned item = blockIdx.x; item < total; item += gridDim.x) {
     const PackJob& J = jobs[pack_job(jobs, njobs, PK_RED, item)];
     const unsigned local = item - J.first[PK_RED];
-    const unsigned gx = (unsigned)(((int64_t)J.nv * J.nv + 255) / 256);
-    reduce_body(J.tri, J.ntri, J.Pvv, J.Ot1, J.Ot2, J.no, J.nv, J.nch, (int)(local % gx),
-                (int)((local / gx) % J.no), (int)(local / (gx * J.no)));
+    const unsigned gx = J.rgx;
+    reduce_body(J.tri, J.ntri, J.Pvv, J.Ot1, J.Ot2, J.no, J.nv, J.nch, J.rslices,
+                (int)(local % gx), (int)((local / gx) % (J.no + 1)), (int)(local / (gx * (J.no + 1))));
     __syncthreads();
   }
 }
 
-void pack_items(const PackJob& j, int prec, unsigned (&items)[PK_N]) {
+void pack_items(PackJob& j, int prec, unsigned (&items)[PK_N]) {
   const int no = j.no, nv = j.nv, nt = j.ntri;
   items[PK_W] = prec == CC3_FP64 ? wbuild_wgs(nv, nt, j.wshape) : wbuild_lp_wgs(nv, nt);
   const int nb = (nv + MT - 1) / MT;
   items[PK_MIX] = (unsigned)(nb * (nb + 1) * (nb + 2) / 6) * nt;
   items[PK_OMEGA] = omega_wgs(nv, nt, j.nch, j.oshape);
-  items[PK_OO] = (unsigned)((nv + 1) / 2) * ((nv + 63) / 64) * no;
-  items[PK_RED] = nblk((int64_t)nv * nv, 256) * no * no;
+  items[PK_OO] = (unsigned)((nv + 1) / 2) * ((nv + 63) / 64) * no * 2u;
+  const dim3 rg = reduce_grid(no, nv);
+  j.rgx = rg.x;
+  j.rslices = reduce_slices(no, nv);
+  items[PK_RED] = rg.x * rg.y * rg.z;
 }
 
 // persistent grids: a few rounds of resident workgroups, never more than the items
@@ -1837,8 +1853,9 @@ void launch_packed_step(const PackJob* dev_jobs, const PackJob* host_jobs, int n
   unsigned total[PK_N] = {0, 0, 0, 0, 0};
   int max_no = 1;
   for (int r = 0; r < njobs; ++r) {
+    PackJob j = host_jobs[r];
     unsigned it[PK_N];
-    pack_items(host_jobs[r], prec, it);
+    pack_items(j, prec, it);
     for (int k = 0; k < PK_N; ++k) total[k] += it[k];
     max_no = std::max(max_no, host_jobs[r].no);
   }
