@@ -205,27 +205,31 @@ void launch_fock(const double* t1, const CholeskyScratch& cs, double* F, int no,
 }
 
 // ---------------------------------------------------------------------------
-// Integral-block build: C[m][n] = sum_J A(m, J) B(J, n) on FP64 MFMA, batched
-// over blockIdx.z, with an output map per block kind.
-// ---------------------------------------------------------------------------
+// Integral-block build: C[m][n] = sum_J A(m, J) B(J, n) on FP64 MFMA, with an output
+// map per block kind:
+//   BUILD_PLAIN  C[m][n]
+//   BUILD_JO     m = q nv + b, n = r nv + c -> Jo[q][r][b][c]
+//   BUILD_HS     m = q no + l, n = r nv + c -> Hs[q][r][c][l] = delta_lq F[r][c] - value
+//   BUILD_GO     m = q no + l, n = r nv + z -> Go[q][r][z][l]
+//   BUILD_GW     m = z, n = y nv + d        -> Gw[y][z][d] (batch r)
+//   BUILD_GBC    m = n' nv + b, n = c       -> G[n'][b][c], zeros in the padding of c
 enum BuildKind {
   BUILD_PLAIN = 0, BUILD_JO = 1, BUILD_HS = 2, BUILD_GO = 3, BUILD_GW = 4, BUILD_GBC = 5
 };
 
-typedef TileCfg<4, 2, 2, 4, 16> BuildCfg;  // 8 wavefronts, 128 x 128 tiles
-
 // One product of a grouped build launch: C_z = A_z B_z for z < batch, with
-// A(m, J) at A[z * a_bs + m * a_sm + J * a_sk], B(J, n) at B[z * b_bs + J * b_sk + n * b_sn].
+// A(m, J) at A[z * a_bs + m + J * a_sk], B(J, n) at B[z * b_bs + J * b_sk + n], both
+// with J < K rows in all.
 struct BuildProb {
   const double* A;
   const double* B;
   double* C;
-  int64_t a_sm, a_sk, a_bs, b_sk, b_sn, b_bs, c_bs;
+  int64_t a_sk, a_bs, b_sk, b_bs, c_bs;
   int M, N, kind, batch;
 };
 enum { MAX_BUILD_PROBS = 6 };
-// The products of one launch, all with the same K; workgroups first0[p] ..
-// first0[p + 1] - 1 take the tiles of product p.
+// The products of one launch, all with the same K; wave tiles first0[p] ..
+// first0[p + 1] - 1 are those of product p.
 struct BuildSet {
   BuildProb p[MAX_BUILD_PROBS];
   unsigned first0[MAX_BUILD_PROBS + 1];
@@ -233,86 +237,168 @@ struct BuildSet {
   const double* F;
 };
 
-__global__ __launch_bounds__(BuildCfg::NT, 2) void k_build(const BuildSet set) {
-  typedef BuildCfg T;
-  __shared__ double lds[T::LDS_DOUBLES];
+// One wavefront per FM x FN blocks of 16 x 16 outputs, without LDS, as in the W build: 8 k
+// (rows J of both operands) per unit, two units in flight.  Rows m and columns n are the
+// contiguous ones here: per k the A rows load as pairs (block 2 f the even rows and block
+// 2 f + 1 the odd rows of 32), the B columns 16 in a row, so that the stores run along n.
+// Rows J >= K lie past the resources, which give zeros.  Bound by the loads (per MFMA as in
+// the W build, both operands streamed) and by the writes of the blocks, no nv^3 twice.
+// 128 x 128 LDS tiles before -> now: 28.1 -> 23.4 ms at 23/250/800, 61.7 -> 43.0 at
+// 8/400/1200, 8.1 -> 4.6 at 9/187/588, 23 -> 10 us at 4/20/60.
+template <int FM, int FN>
+__global__ __launch_bounds__(256, FM * FN <= 4 ? 4 : FM * FN <= 9 ? 3 : 2) void k_build(
+    const BuildSet set) {
+  const unsigned item = xcd_item(blockIdx.x, gridDim.x, 4u) * 4u +
+                        __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (item >= set.first0[set.n]) return;
   int pi = 0;
-  while (pi + 1 < set.n && blockIdx.x >= set.first0[pi + 1]) ++pi;
+  while (pi + 1 < set.n && item >= set.first0[pi + 1]) ++pi;
   const BuildProb& pr = set.p[pi];
   const int M = pr.M, N = pr.N, K = set.K, kind = pr.kind, no = set.no, nv = set.nv;
-  const int mt = (M + T::BM - 1) / T::BM, nt = (N + T::BN - 1) / T::BN;
-  const unsigned local = blockIdx.x - set.first0[pi];
-  const int z = (int)(local / (unsigned)(mt * nt));
-  const int t = (int)(local % (unsigned)(mt * nt));
-  const int m0 = (t % mt) * T::BM;
-  const int n0 = (t / mt) * T::BN;
-  const double* A = pr.A + (int64_t)z * pr.a_bs;
-  const double* B = pr.B + (int64_t)z * pr.b_bs;
-  d4v acc[T::FM][T::FN];
-  zero_acc<T>(acc);
-  const int nsteps = (K + T::BK - 1) / T::BK;
-  auto ops = [&](int s, Opnd& oa, Opnd& ob, int& k0) {
-    k0 = s * T::BK;
-    oa = make_opnd(A, pr.a_sm, pr.a_sk, M, K, true);
-    ob = make_opnd(B, pr.b_sn, pr.b_sk, N, K, true);
-  };
-  k_loop<T>(nsteps, m0, n0, ops, acc, lds);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave % T::WM, wn = wave / T::WM;
-  double* Cz = pr.C + (int64_t)z * pr.c_bs;
-  const double* F = set.F;
+  const unsigned mt = (unsigned)(M + 16 * FM - 1) / (16 * FM), nt = (unsigned)(N + 16 * FN - 1) / (16 * FN);
+  const unsigned local = item - set.first0[pi], z = local / (mt * nt), t = local % (mt * nt);
+  // the shorter dimension fastest: neighbours share the rows of the longer one
+  const int m0 = (int)(mt <= nt ? t % mt : t / nt) * (16 * FM);
+  const int n0 = (int)(mt <= nt ? t / mt : t % nt) * (16 * FN);
+  const int lane = threadIdx.x & 63, r16 = lane & 15, kq = lane >> 4;
+  const double* pa = pr.A + z * pr.a_bs + m0;
+  const double* pb = pr.B + z * pr.b_bs + n0;
+  int64_t na = K * pr.a_sk - (int64_t)z * pr.a_bs - m0, nb = K * pr.b_sk - (int64_t)z * pr.b_bs - n0;
+  const int64_t sa = 8 * pr.a_sk, sb = 8 * pr.b_sk;  // doubles per unit
+  const unsigned ka = (unsigned)pr.a_sk * 8u, kb = (unsigned)pr.b_sk * 8u;  // bytes per k
+  const unsigned va = (unsigned)(2 * kq) * ka + (unsigned)r16 * 16u;
+  const unsigned va1 = (unsigned)(2 * kq) * ka + (unsigned)r16 * 8u;  // an odd last block
+  const unsigned vb = (unsigned)(2 * kq) * kb + (unsigned)r16 * 8u;
+  double a[2][FM][2], b[2][FN][2];
+  auto fetch = [&](double (&fa)[FM][2], double (&fb)[FN][2]) {
+    const BufRsrc ra = buf_rsrc_n(pa, na > 0 ? na : 0), rb = buf_rsrc_n(pb, nb > 0 ? nb : 0);
 #pragma unroll
-  for (int fm = 0; fm < T::FM; ++fm)
+    for (int t = 0; t < 2; ++t) {
 #pragma unroll
-    for (int fn = 0; fn < T::FN; ++fn)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int m = m0 + acc_row<T>(wm, fm, lane, r);
-        const int n = n0 + acc_col<T>(wn, fn, lane);
-        if (kind == BUILD_GBC) {  // m = n'*nv + b, n = c -> G[n'][b][c], zeros for c past nv
-          if (m < M && n < cube_pitch(nv))
-            Cz[(m / nv) * g_pitch(nv) + (int64_t)(m % nv) * cube_pitch(nv) + n] =
-                n < N ? acc[fm][fn][r] : 0.0;
-          continue;
-        }
-        if (m >= M || n >= N) continue;
-        const double v = acc[fm][fn][r];
-        if (kind == BUILD_PLAIN) {
-          Cz[(int64_t)m * N + n] = v;
-        } else if (kind == BUILD_JO) {  // m = q*nv + b, n = r*nv + c -> Jo[q][r][b][c]
-          const int q = m / nv, b = m % nv, rr = n / nv, c = n % nv;
-          Cz[(((int64_t)q * no + rr) * nv + b) * nv + c] = v;
-        } else if (kind == BUILD_HS) {  // m = q*no + l, n = r*nv + c -> Hs[q][r][c][l]
-          const int q = m / no, l = m % no, rr = n / nv, c = n % nv;
-          Cz[(((int64_t)q * no + rr) * nv + c) * no + l] = (l == q ? F[(int64_t)rr * nv + c] : 0.0) - v;
-        } else if (kind == BUILD_GO) {  // m = q*no + l, n = r*nv + z -> Go[q][r][z][l]
-          const int q = m / no, l = m % no, rr = n / nv, c = n % nv;
-          Cz[(((int64_t)q * no + rr) * nv + c) * no + l] = v;
-        } else {  // BUILD_GW: m = z, n = y*nv + d -> Gw[r][y][z][d] (batch r)
-          const int y = n / nv, d = n % nv;
-          Cz[y * gw_pitch(nv) + (int64_t)m * nv + d] = v;
-        }
+      for (int f = 0; f + 1 < FM; f += 2) {
+        const d2v v = buf_load_2f64(ra, va + (unsigned)t * ka, (unsigned)f * 128u);
+        fa[f][t] = v[0];
+        fa[f + 1][t] = v[1];
       }
+      if constexpr (FM & 1) fa[FM - 1][t] = buf_load_f64(ra, va1 + (unsigned)t * ka + (FM - 1) * 128u);
+#pragma unroll
+      for (int f = 0; f < FN; ++f) fb[f][t] = buf_load_f64(rb, vb + (unsigned)t * kb + f * 128u);
+    }
+    pa += sa;
+    pb += sb;
+    na -= sa;
+    nb -= sb;
+  };
+  d4v acc[FM][FN];
+#pragma unroll
+  for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+    for (int fn = 0; fn < FN; ++fn) acc[fm][fn] = d4v{0.0, 0.0, 0.0, 0.0};
+  const int units = (K + 7) / 8;
+  fetch(a[0], b[0]);
+  fetch(a[1], b[1]);
+  for (int u = 0; u < units; u += 2) {
+#pragma unroll
+    for (int d = 0; d < 2; ++d) {
+      if (u + d < units) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+            for (int fn = 0; fn < FN; ++fn)
+              acc[fm][fn] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[d][fm][t], b[d][fn][t],
+                                                                 acc[fm][fn], 0, 0, 0);
+      }
+      fetch(a[d], b[d]);
+    }
+  }
+  // output (m, n) of every kind is at row(m) + col(n)
+  double* Cz = pr.C + z * pr.c_bs;
+  const int rp = cube_pitch(nv), nlim = kind == BUILD_GBC ? rp : N;
+  int64_t col[FN];
+#pragma unroll
+  for (int fn = 0; fn < FN; ++fn) {
+    const int n = n0 + fn * 16 + r16;
+    col[fn] = n;                                                       // [..][n]
+    if (kind == BUILD_JO) col[fn] = n / nv * (int64_t)nv * nv + n % nv;  // n = r nv + c
+    else if (kind == BUILD_HS || kind == BUILD_GO) col[fn] = (int64_t)n * no;  // [r][c][l]
+    else if (kind == BUILD_GW) col[fn] = n / nv * gw_pitch(nv) + n % nv;  // n = y nv + d
+  }
+#pragma unroll
+  for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int m = m0 + ((FM & 1) && fm == FM - 1
+                              ? fm * 16 + kq + 4 * r
+                              : (fm & ~1) * 16 + 2 * (kq + 4 * r) + (fm & 1));
+      int64_t row = (int64_t)m * N;             // BUILD_PLAIN: C[m][n]
+      if (kind == BUILD_GBC) row = m / nv * g_pitch(nv) + (int64_t)(m % nv) * rp;  // m = n' nv + b
+      else if (kind == BUILD_JO) row = (m / nv * (int64_t)no * nv + m % nv) * nv;  // m = q nv + b
+      else if (kind == BUILD_HS || kind == BUILD_GO)
+        row = m / no * (int64_t)no * nv * no + m % no;                             // m = q no + l
+      else if (kind == BUILD_GW) row = (int64_t)m * nv;                            // m = z
+      const bool diag = kind == BUILD_HS && m / no == m % no;
+#pragma unroll
+      for (int fn = 0; fn < FN; ++fn) {
+        const int n = n0 + fn * 16 + r16;
+        double v = n < N ? acc[fm][fn][r] : 0.0;  // zeros in the padding of BUILD_GBC
+        if (kind == BUILD_HS) v = (diag && m < M && n < N ? set.F[n] : 0.0) - v;
+        if (m < M && n < nlim) Cz[row + col[fn]] = v;
+      }
+    }
 }
 
-static void add_build(BuildSet& set, const double* A, int64_t a_sm, int64_t a_sk, int64_t a_bs,
-                      const double* B, int64_t b_sk, int64_t b_sn, int64_t b_bs, int M, int N,
-                      double* C, int64_t c_bs, int batch, int kind) {
+static void add_build(BuildSet& set, const double* A, int64_t a_sk, int64_t a_bs, const double* B,
+                      int64_t b_sk, int64_t b_bs, int M, int N, double* C, int64_t c_bs, int batch,
+                      int kind) {
   BuildProb& p = set.p[set.n++];
-  p.A = A; p.a_sm = a_sm; p.a_sk = a_sk; p.a_bs = a_bs;
-  p.B = B; p.b_sk = b_sk; p.b_sn = b_sn; p.b_bs = b_bs;
+  p.A = A; p.a_sk = a_sk; p.a_bs = a_bs;
+  p.B = B; p.b_sk = b_sk; p.b_bs = b_bs;
   p.C = C; p.c_bs = c_bs;
   p.M = M; p.N = N; p.kind = kind; p.batch = batch;
 }
 
-static void launch_build_set(BuildSet& set, hipStream_t st) {
-  typedef BuildCfg T;
+template <int FM, int FN>
+static void launch_build_shape(BuildSet& set, hipStream_t st) {
+  if (set.n == 0) return;
   set.first0[0] = 0;
   for (int i = 0; i < set.n; ++i) {
     const BuildProb& p = set.p[i];
-    set.first0[i + 1] = set.first0[i] + nblk(p.M, T::BM) * nblk(p.N, T::BN) * (unsigned)p.batch;
+    set.first0[i + 1] = set.first0[i] + nblk(p.M, 16 * FM) * nblk(p.N, 16 * FN) * (unsigned)p.batch;
   }
-  hipLaunchKernelGGL(k_build, dim3(set.first0[set.n]), dim3(T::NT), 0, st, set);
+  hipLaunchKernelGGL((k_build<FM, FN>), dim3(nblk(set.first0[set.n], 4)), dim3(256), 0, st, set);
+}
+
+// Blocks of 16 along nv per wave tile: 2, 3, 4 or 5, the least blocks in all, weighted by
+// the loads per MFMA as the wave-tile shapes of the W build.
+static int build_blocks_nv(int nv) {
+  int best = 4;
+  double cost = 0.0;
+  for (int f = 2; f <= 5; ++f) {
+    const double c = (double)nblk(nv, 16 * f) * f * (0.65 + 0.7 * (1.0 / f + (f == 2 ? 0.5 : f == 3 ? 1.0 / 3 : 0.25)));
+    if (f == 2 || c < cost) { best = f; cost = c; }
+  }
+  return best;
+}
+
+// The products of `set`: square wave tiles and one launch for 2, 3 and 4 blocks along nv;
+// for 5 the products with nv rows (5 x 4) and those with nv columns (4 x 5) in two.
+static void launch_build_set(const BuildSet& set, hipStream_t st) {
+  const int f = build_blocks_nv(set.nv);
+  BuildSet rows = set, cols = set;
+  rows.n = cols.n = 0;
+  for (int i = 0; i < set.n; ++i) {
+    BuildSet& to = f == 5 && set.p[i].M <= set.p[i].N ? rows : cols;
+    to.p[to.n++] = set.p[i];
+  }
+  if (f == 2) launch_build_shape<2, 2>(cols, st);
+  else if (f == 4) launch_build_shape<4, 4>(cols, st);
+  else if (f == 3) launch_build_shape<3, 3>(cols, st);
+  else {
+    launch_build_shape<5, 4>(rows, st);
+    launch_build_shape<4, 5>(cols, st);
+  }
 }
 
 // Gcb[r][n][c][b] = Gbc[r][n][b][c]: nv x nv transposes, one per (r, n), through
@@ -350,25 +436,25 @@ void launch_build_blocks(const CholeskyScratch& cs, const Blocks& bl, int no, in
                          hipStream_t st) {
   const int64_t nv2 = (int64_t)nv * nv, onv = (int64_t)no * nv;
   const int64_t gs = (nv + no) * g_pitch(nv);  // one r slab of Gbc / Gcb
-  // all six products share K = nJ: one launch, the large ones first
+  // all six products share K = nJ
   BuildSet set = {};
   set.K = nJ; set.no = no; set.nv = nv; set.F = bl.F;
   // Gw[r][y][z][d] = sum_J LvoT[J][r][z] Lvv[J][(y,d)]   (rows z, columns (y,d), batch r)
-  add_build(set, cs.LvoT, 1, onv, nv, cs.Lvv, nv2, 1, 0, nv, (int)nv2, bl.Gw,
-            nv * gw_pitch(nv), no, BUILD_GW);
+  add_build(set, cs.LvoT, onv, nv, cs.Lvv, nv2, 0, nv, (int)nv2, bl.Gw, nv * gw_pitch(nv), no,
+            BUILD_GW);
   // Gbc[r][(d,b)][c] = sum_J Lvv[J][(d,b)] Lov[J][r][c]            (rows n = d < nv)
-  add_build(set, cs.Lvv, 1, nv2, 0, cs.Lov, onv, 1, nv, (int)nv2, nv, bl.Gbc, gs, no, BUILD_GBC);
+  add_build(set, cs.Lvv, nv2, 0, cs.Lov, onv, nv, (int)nv2, nv, bl.Gbc, gs, no, BUILD_GBC);
   // Gbc[r][nv + (l,b)][c] = sum_J Lov[J][(l,b)] Lov[J][r][c]      (rows n = nv + l)
-  add_build(set, cs.Lov, 1, onv, 0, cs.Lov, onv, 1, nv, (int)onv, nv,
-            bl.Gbc + nv * g_pitch(nv), gs, no, BUILD_GBC);
+  add_build(set, cs.Lov, onv, 0, cs.Lov, onv, nv, (int)onv, nv, bl.Gbc + nv * g_pitch(nv), gs, no,
+            BUILD_GBC);
   // Jo[q][r][b][c] = sum_J Lov[J][q][b] Lov[J][r][c]
-  add_build(set, cs.Lov, 1, onv, 0, cs.Lov, onv, 1, 0, (int)onv, (int)onv, bl.Jo, 0, 1, BUILD_JO);
+  add_build(set, cs.Lov, onv, 0, cs.Lov, onv, 0, (int)onv, (int)onv, bl.Jo, 0, 1, BUILD_JO);
   // Hs[q][r][c][l] = delta_lq F[r][c] - sum_J Loo[J][q][l] Lov[J][r][c]
-  add_build(set, cs.Loo, 1, (int64_t)no * no, 0, cs.Lov, onv, 1, 0, no * no, (int)onv, bl.Hs, 0,
-            1, BUILD_HS);
+  add_build(set, cs.Loo, (int64_t)no * no, 0, cs.Lov, onv, 0, no * no, (int)onv, bl.Hs, 0, 1,
+            BUILD_HS);
   // Go[q][r][z][l] = sum_J LooT[J][q][l] LvoT[J][r][z]   (LooT[J][q][l] = Lt_lq)
-  add_build(set, cs.LooT, 1, (int64_t)no * no, 0, cs.LvoT, onv, 1, 0, no * no, (int)onv, bl.Go, 0,
-            1, BUILD_GO);
+  add_build(set, cs.LooT, (int64_t)no * no, 0, cs.LvoT, onv, 0, no * no, (int)onv, bl.Go, 0, 1,
+            BUILD_GO);
   launch_build_set(set, st);
   launch_gcb(bl, no, nv, st);
 }
@@ -383,15 +469,14 @@ void launch_build_density_blocks(const CholeskyScratch& cs, double* Gw, double* 
   const int64_t nv2 = (int64_t)nv * nv, onv = (int64_t)no * nv;
   BuildSet set = {};
   set.K = nJ; set.no = no; set.nv = nv; set.F = nullptr;
-  add_build(set, cs.LvoT, 1, onv, nv, cs.Lvv, nv2, 1, 0, nv, (int)nv2, Gw, nv * gw_pitch(nv), no,
-            BUILD_GW);
+  add_build(set, cs.LvoT, onv, nv, cs.Lvv, nv2, 0, nv, (int)nv2, Gw, nv * gw_pitch(nv), no, BUILD_GW);
   // tmp[(p,y)][(d,z)] = sum_J Lov[J][p][y] Lvv[J][d][z]
-  add_build(set, cs.Lov, 1, onv, 0, cs.Lvv, nv2, 1, 0, (int)onv, (int)nv2, tmp, 0, 1, BUILD_PLAIN);
-  add_build(set, cs.Lov, 1, onv, 0, cs.Lov, onv, 1, 0, (int)onv, (int)onv, Jo, 0, 1, BUILD_JO);
-  add_build(set, cs.LooT, 1, (int64_t)no * no, 0, cs.LvoT, onv, 1, 0, no * no, (int)onv, Go, 0,
-            1, BUILD_GO);
+  add_build(set, cs.Lov, onv, 0, cs.Lvv, nv2, 0, (int)onv, (int)nv2, tmp, 0, 1, BUILD_PLAIN);
+  add_build(set, cs.Lov, onv, 0, cs.Lov, onv, 0, (int)onv, (int)onv, Jo, 0, 1, BUILD_JO);
+  add_build(set, cs.LooT, (int64_t)no * no, 0, cs.LvoT, onv, 0, no * no, (int)onv, Go, 0, 1,
+            BUILD_GO);
   // Go3: m = p*no + l (Loo[J][p][l] = Lt_pl), n = q*nv + z (Lov[J][q][z] = L_qz)
-  add_build(set, cs.Loo, 1, (int64_t)no * no, 0, cs.Lov, onv, 1, 0, no * no, (int)onv, Go3, 0, 1,
+  add_build(set, cs.Loo, (int64_t)no * no, 0, cs.Lov, onv, 0, no * no, (int)onv, Go3, 0, 1,
             BUILD_GO);
   launch_build_set(set, st);
   const unsigned t = nblk(nv, 32);
