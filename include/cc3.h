@@ -260,6 +260,11 @@ int cc3_batch_plan(int no, int nv, int nchol, int prec, unsigned flags, int* tri
                    int* nbatches);
 
 /* Bytes of device workspace for cc3_transition_density at these sizes (host-only).
+ * Where the two cubes of every unordered triple fit 64 GiB (twice the per-set cube budget,
+ * CC3_CUBE_BUDGET_MB in the environment) the size includes them, and each triple is built
+ * once; otherwise, and for a call that is given less, down to about 4 no + 2 cubes of
+ * nv^3 doubles, the loop rebuilds triples per occupied pair (the same densities to
+ * rounding, two to three times the time).
  * Supported sizes: 1 <= no <= 63, 1 <= nv <= 400, nchol >= 1.
  * Errors: CC3_E_INVAL. */
 int cc3_transition_density_workspace_size(int no, int nv, int nchol, size_t* bytes);

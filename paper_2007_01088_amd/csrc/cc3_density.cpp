@@ -1,16 +1,25 @@
 // The transition-density loop (Algorithm 3, the triples contributions to
-// D^{m,0}) on the caller's stream: workspace plan, the loop over occupied pairs,
-// and its C-ABI entry points.
+// D^{m,0}) on the caller's stream: workspace plan, the batched loop, and its C-ABI entry
+// points.
 //
-// Each pair (i, j), i >= j, is one batch holding the ordered triples (i, j, k)
-// for every k: their t3 (W build, mix) and left-state L3 (the same engine with
-// the L3 operands, the mix with the outer products and the (omega - eps)
-// denominator), then the contractions of kern_density.hip.  Each unordered
-// triple is sorted in exactly one pair and contributes its D_cd, Y^o and D_kc
-// terms there; every pair contributes its Gram matrix to D_lk.
+// Each triple's t3 (W build, mix) and left-state L3 (the same engine with the L3
+// operands, the mix with the outer products and the (omega - eps) denominator) feed the
+// contractions of kern_density.hip.  Two loops:
+//  - resident: the unordered triples in batches, every cube of tau and L~ kept, then the
+//    Gram matrices of every occupied pair for D_lk from the kept cubes.  Each triple is
+//    built once.
+//  - by pairs: each pair (i, j), i >= j, is one batch holding the ordered triples
+//    (i, j, k) for every k and contributes its Gram matrix at once; each unordered triple
+//    is sorted in exactly one pair and contributes its D_cd, Y^o and D_kc terms there, but
+//    is built in each of its up to three pairs.
+// The resident loop needs no (no + 1) (no + 2) / 3 cubes.  It is taken where they fit the
+// cube budget (64 GiB, two of the residual's buffer sets) and the caller's workspace;
+// a smaller workspace, down to that of the loop by pairs, takes the latter.  At 12/120/400
+// (10 GB of cubes) the resident loop builds 364 triples where the loop by pairs builds 936.
 #include <hip/hip_runtime.h>
 
-#include <cstring>
+#include <algorithm>
+#include <cstdlib>
 #include <vector>
 
 #include "cc3_density.hpp"
@@ -23,55 +32,51 @@ namespace {
 size_t a256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct DPlan {
-  int no, nv, nchol, npairs, ntask;
+  int no, nv, nchol, npairs;
+  bool resident;
+  int nall;     // triples of the loop's table
+  int batch;    // most triples of a batch
   size_t cube;  // doubles per cube (cube_slot: nv x nv rows at the padded pitch)
-  size_t off_Gw, off_Gl, off_Go, off_Go3, off_Jo, off_F, off_t2N, off_l2M, off_Y;
-  size_t off_part, off_py, off_pkc, off_tri, off_task, off_cubes;
-  size_t part_doubles, py_doubles, pkc_doubles, chol_bytes;
+  size_t off_Gw, off_Gl, off_Go, off_Go3, off_Jo, off_F, off_t2N, off_l2M, off_E, off_Y;
+  size_t off_part, off_tri, off_planes, off_tau, off_lc, off_cubes;
+  size_t chol_bytes;
   size_t total;
-  std::vector<int> htri;             // [pair][k][3]
-  std::vector<int> htask;            // [task][D3_TASK_INTS]
-  std::vector<int> task0, ntasks;    // per pair
-  std::vector<int> pi, pj;           // the pair's (i, j)
+  std::vector<int> htri;  // [triple][3]: unordered, lexicographic, or [pair][k]
 };
 
-// The distinct orderings of (i, j, k) in the order of itertools.permutations.
-const int kPermH[6][3] = {{0, 1, 2}, {0, 2, 1}, {1, 0, 2}, {1, 2, 0}, {2, 0, 1}, {2, 1, 0}};
+size_t cube_budget() {
+  const char* e = getenv("CC3_CUBE_BUDGET_MB");  // per buffer set, as for the residual
+  const long v = e ? atol(e) : 0;
+  return (size_t)(v > 0 ? v : 32768) << 21;
+}
 
-void make_dplan(int no, int nv, int nchol, DPlan* p) {
+void make_dplan(int no, int nv, int nchol, bool resident, DPlan* p) {
   const size_t o = no, v = nv, J = nchol;
   p->no = no; p->nv = nv; p->nchol = nchol;
   p->cube = (size_t)cube_slot(nv);  // one padded cube
   p->npairs = no * (no + 1) / 2;
-  p->htri.clear(); p->htask.clear(); p->task0.clear(); p->ntasks.clear(); p->pi.clear();
-  p->pj.clear();
+  p->resident = resident;
+  p->htri.clear();
   for (int i = 0; i < no; ++i)
-    for (int j = 0; j <= i; ++j) {
-      p->pi.push_back(i);
-      p->pj.push_back(j);
-      for (int k = 0; k < no; ++k) {
+    for (int j = 0; j <= i; ++j)
+      for (int k = 0; k < (resident ? j + 1 : no); ++k) {
         p->htri.push_back(i); p->htri.push_back(j); p->htri.push_back(k);
       }
-      p->task0.push_back((int)p->htask.size() / D3_TASK_INTS);
-      const int nown = (i == j) ? j : j + 1;
-      int nt = 0;
-      for (int k = 0; k < nown; ++k) {
-        const int tr[3] = {i, j, k};
-        for (int oi = 0; oi < 6; ++oi) {
-          const int pp = tr[kPermH[oi][0]], qq = tr[kPermH[oi][1]], rr = tr[kPermH[oi][2]];
-          bool dup = false;
-          for (int o2 = 0; o2 < oi; ++o2)
-            dup = dup || (tr[kPermH[o2][0]] == pp && tr[kPermH[o2][1]] == qq &&
-                          tr[kPermH[o2][2]] == rr);
-          if (dup) continue;
-          const int e[D3_TASK_INTS] = {k, oi, pp, qq, rr};
-          p->htask.insert(p->htask.end(), e, e + D3_TASK_INTS);
-          ++nt;
-        }
-      }
-      p->ntasks.push_back(nt);
-    }
-  p->ntask = (int)p->htask.size() / D3_TASK_INTS;
+  p->nall = (int)p->htri.size() / 3;
+  if (resident) {
+    // about 16384 wave tiles of the W build per launch (eight rounds), the planes of a
+    // batch within 4 GiB
+    int tm, tn;
+    shape_tiles(pick_shape(nv, nv), nv, nv, &tm, &tn);
+    const int64_t per = 2ll * nv * tm * tn;
+    int64_t b = std::min<int64_t>(D3_MAXB, (16384 + per - 1) / per);
+    b = std::min<int64_t>(std::max<int64_t>(b, 4), ((size_t)4 << 30) / (16 * p->cube));
+    b = std::max<int64_t>(1, std::min<int64_t>(b, p->nall));
+    const int64_t nb = (p->nall + b - 1) / b;  // balanced
+    p->batch = (int)((p->nall + nb - 1) / nb);
+  } else {
+    p->batch = no;
+  }
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t at = off; off = a256(off + bytes); return at; };
   p->off_Gw = take(o * v * gw_pitch(nv) * 8);
@@ -82,33 +87,27 @@ void make_dplan(int no, int nv, int nchol, DPlan* p) {
   p->off_F = take(o * v * 8);
   p->off_t2N = take(o * v * t2n_pitch(no, nv) * 8);
   p->off_l2M = take(o * v * t2n_pitch(no, nv) * 8);
+  p->off_E = take(o * o * v * v * 8);
   p->off_Y = take(o * o * o * v * 8);
-  // partial slabs: D_cd, Gram and D_ld share one region; Y^o and D_kc have their own
-  size_t cd = 0, vy = 0, vk = 0;
-  for (int nown = 1; nown <= no; ++nown)
-    cd = std::max(cd, (size_t)nown * 3 * d3_cd_chunks(nv, nown) * v * v);
-  int maxt = 1;
-  for (int x : p->ntasks) maxt = std::max(maxt, x);
-  for (int nt = 1; nt <= maxt; ++nt) {
-    vy = std::max(vy, (size_t)nt * d3_vec_chunks(nv, nt, no) * v * o);
-    vk = std::max(vk, (size_t)nt * d3_vec_chunks(nv, nt, 1) * v);
-  }
-  const size_t gr = (size_t)d3_gram_chunks(nv, no) * o * o;
-  const size_t ld = (size_t)d3_ld_chunks(no, nv) * o * v;
-  p->part_doubles = std::max(std::max(cd, gr), ld);
-  p->py_doubles = vy;
-  p->pkc_doubles = vk;
-  p->off_part = take(p->part_doubles * 8);
-  p->off_py = take(vy * 8);
-  p->off_pkc = take(vk * 8);
+  p->off_part = take(d3_partial_doubles(no, nv, p->batch, resident ? p->npairs : 1) * 8);
   p->off_tri = take(p->htri.size() * sizeof(int));
-  p->off_task = take(std::max<size_t>(1, p->htask.size()) * sizeof(int));
-  // the Cholesky scratch and the build's temporary (vv|ov) block share the cube region
+  // the planes (PA, then PB) of a batch, then the cubes of tau and L~; before the loop
+  // the Cholesky scratch and the build's temporary (vv|ov) block use the same region
   p->chol_bytes = a256(J * v * v * 8) + a256(J * o * o * 8) * 2 + a256(J * o * v * 8) * 2 +
                   a256(J * 8) + a256(J * o * o * 8);
-  const size_t cubes = a256((size_t)D3_NSLOT * o * p->cube * 8);
-  p->off_cubes = take(std::max(cubes, p->chol_bytes + a256(o * v * v * v * 8)));
+  const size_t kept = resident ? (size_t)p->nall : o, cb = p->cube * 8;
+  const size_t planes = a256(2 * (size_t)p->batch * cb), one = a256(kept * cb);
+  p->off_cubes = take(std::max(planes + 2 * one, p->chol_bytes + a256(o * v * v * v * 8)));
+  p->off_planes = p->off_cubes;
+  p->off_tau = p->off_cubes + planes;
+  p->off_lc = p->off_tau + one;
   p->total = off;
+}
+
+// Whether the resident loop's cubes fit the budget.
+bool resident_fits(int no, int nv) {
+  const size_t n = (size_t)no * (no + 1) * (no + 2) / 6;
+  return 2 * n * (size_t)cube_slot(nv) * 8 <= cube_budget();
 }
 
 int check_density_sizes(int no, int nv, int nchol) {
@@ -127,8 +126,12 @@ extern "C" int cc3_transition_density_workspace_size(int no, int nv, int nchol, 
   int rc = check_density_sizes(no, nv, nchol);
   if (rc) return rc;
   DPlan p;
-  make_dplan(no, nv, nchol, &p);
+  make_dplan(no, nv, nchol, false, &p);
   *bytes = p.total;
+  if (resident_fits(no, nv)) {
+    make_dplan(no, nv, nchol, true, &p);
+    *bytes = std::max(*bytes, p.total);
+  }
   return CC3_OK;
 }
 
@@ -153,7 +156,9 @@ extern "C" int cc3_transition_density(cc3_ctx* c, int no, int nv, int nchol, con
   if (Yo && (rc = check_dev_ptr(Yo, "Yo"))) return rc;
   if (((uintptr_t)ws) & 255) return fail(CC3_E_INVAL, "workspace must be 256-byte aligned");
   DPlan p;
-  make_dplan(no, nv, nchol, &p);
+  p.total = (size_t)-1;
+  if (resident_fits(no, nv)) make_dplan(no, nv, nchol, true, &p);
+  if (ws_bytes < p.total) make_dplan(no, nv, nchol, false, &p);
   if (ws_bytes < p.total)
     return fail(CC3_E_NOMEM, "workspace too small: %zu bytes given, %zu needed", ws_bytes, p.total);
   const bool acc = (flags & CC3_ACCUMULATE) != 0;
@@ -168,12 +173,12 @@ extern "C" int cc3_transition_density(cc3_ctx* c, int no, int nv, int nchol, con
   double* t2N = (double*)(base + p.off_t2N);
   double* l2M = (double*)(base + p.off_l2M);
   double* Y = (double*)(base + p.off_Y);
+  double* E = (double*)(base + p.off_E);
   double* Ppart = (double*)(base + p.off_part);
-  double* Py = (double*)(base + p.off_py);
-  double* Pkc = (double*)(base + p.off_pkc);
   int* dtri = (int*)(base + p.off_tri);
-  int* dtask = (int*)(base + p.off_task);
-  double* cubes = (double*)(base + p.off_cubes);
+  double* planes = (double*)(base + p.off_planes);
+  double* tau = (double*)(base + p.off_tau);
+  double* lc = (double*)(base + p.off_lc);
   // the Cholesky scratch, then the temporary (vv|ov) block, in the cube region
   const size_t o = no, v = nv, J = nchol;
   CholeskyScratch cs;
@@ -190,15 +195,12 @@ extern "C" int cc3_transition_density(cc3_ctx* c, int no, int nv, int nchol, con
     cs.M = take(J * o * o * 8);
   }
   double* gtmp = (double*)(base + p.off_cubes + p.chol_bytes);
-  const int64_t csl = (int64_t)p.cube, ss = (int64_t)no * csl;
+  const int64_t csl = (int64_t)p.cube;
   std::lock_guard<std::mutex> g(c->mu);
   Profiler* pf = &c->prof;
   HIPCHK(hipMemcpyAsync(dtri, p.htri.data(), p.htri.size() * sizeof(int), hipMemcpyHostToDevice,
                         st));
-  if (p.ntask)
-    HIPCHK(hipMemcpyAsync(dtask, p.htask.data(), p.htask.size() * sizeof(int),
-                          hipMemcpyHostToDevice, st));
-  HIPCHK(hipStreamSynchronize(st));  // the host tables may go out of scope
+  HIPCHK(hipStreamSynchronize(st));  // the host table may go out of scope
   {
     Timer tm(pf, st, FAM_T1, 0.0, 0.0);
     launch_t1_transform(L, t1, cs, no, nv, nchol, st);
@@ -210,7 +212,7 @@ extern "C" int cc3_transition_density(cc3_ctx* c, int no, int nv, int nchol, con
     launch_build_density_blocks(cs, Gw, Go, Jo, Go3, Gl, gtmp, no, nv, nchol, st);
   }
   launch_t2N(t2, t2N, no, nv, st);
-  launch_d3_l2m(l2, l2M, no, nv, st);
+  launch_d3_l2(l2, l2M, E, no, nv, st);
   launch_fill(Y, (int64_t)o * o * o * v, 0.0, st);
   if (!acc) {
     launch_fill(D_cd, (int64_t)v * v, 0.0, st);
@@ -218,40 +220,56 @@ extern "C" int cc3_transition_density(cc3_ctx* c, int no, int nv, int nchol, con
     launch_fill(D_ld, (int64_t)o * v, 0.0, st);
     launch_fill(D_lk, (int64_t)o * o, 0.0, st);
   }
-  std::vector<int> kinds(no);
-  for (int pr = 0; pr < p.npairs; ++pr) {
-    const int i = p.pi[pr], j = p.pj[pr];
-    const int* tb = dtri + (size_t)pr * no * 3;
-    for (int k = 0; k < no; ++k) kinds[k] = tri_kind(i, j, k);
-    const double wfl = wbuild_flops(no, nv, kinds.data(), no);
+  std::vector<int> kinds;
+  const int ngroups = p.resident ? (p.nall + p.batch - 1) / p.batch : p.npairs;
+  for (int g = 0; g < ngroups; ++g) {
+    const int t0 = g * p.batch, nb = std::min(p.batch, p.nall - t0);
+    const int* tb = dtri + (size_t)t0 * 3;
+    const int* hb = p.htri.data() + (size_t)t0 * 3;
+    double* bt = p.resident ? tau + t0 * csl : tau;
+    double* bl = p.resident ? lc + t0 * csl : lc;
+    double* PB = planes + nb * csl;
+    kinds.resize(nb);
+    for (int t = 0; t < nb; ++t) kinds[t] = tri_kind(hb[3 * t], hb[3 * t + 1], hb[3 * t + 2]);
+    const double wfl = wbuild_flops(no, nv, kinds.data(), nb);
     {
       Timer tm(pf, st, FAM_W, wfl, 0.0);
-      launch_wbuild_ex(0, t2, t2N, Gw, Go, tb, no, cubes, csl, ss, cube_pitch(nv), no, nv, false, st);
+      launch_wbuild_ex(0, t2, t2N, Gw, Go, tb, nb, planes, csl, nb * csl, cube_pitch(nv), no, nv,
+                       false, st);
     }
     {
       Timer tm(pf, st, FAM_MIX, 0.0, 0.0);
-      launch_mix3(false, eps, tb, no, cubes, ss, 0.0, l1, l2, Jo, F, no, nv, st);
+      launch_mix3(false, eps, tb, nb, planes, PB, bt, 0.0, l1, l2, Jo, F, no, nv, st);
     }
     {
       Timer tm(pf, st, FAM_L3, wfl, 0.0);
-      launch_wbuild_ex(1, l2, l2M, Gl, Go3, tb, no, cubes, csl, ss, cube_pitch(nv), no, nv, false, st);
+      launch_wbuild_ex(1, l2, l2M, Gl, Go3, tb, nb, planes, csl, nb * csl, cube_pitch(nv), no, nv,
+                       false, st);
     }
     {
       Timer tm(pf, st, FAM_MIX, 0.0, 0.0);
-      launch_mix3(true, eps, tb, no, cubes, ss, omega, l1, l2, Jo, F, no, nv, st);
+      launch_mix3(true, eps, tb, nb, planes, PB, bl, omega, l1, l2, Jo, F, no, nv, st);
     }
-    const int nown = (i == j) ? j : j + 1;
-    const int nt = p.ntasks[pr];
-    const double dfl = (double)nown * 3 * 2.0 * v * v * v * v + (double)nt * 2.0 * v * v * v * (o + 1) +
-                       2.0 * o * o * v * v * v;
+    // the triples that contribute to D_cd, Y^o and D_kc: all of a batch of unordered
+    // triples; of a pair (i, j) the sorted ones, k <= j
+    const int nown = p.resident ? nb : (hb[0] == hb[1] ? hb[1] : hb[1] + 1);
+    double dfl = 0.0;
+    for (int t = 0; t < nown; ++t) {
+      if (hb[3 * t] == hb[3 * t + 2]) continue;
+      dfl += 6.0 * v * v * v * v + (kinds[t] == TRI_DISTINCT ? 6.0 : 3.0) * 2.0 * v * v * v * (o + 1);
+    }
+    if (!p.resident) dfl += 2.0 * o * o * v * v * v;
     {
       Timer tm(pf, st, FAM_DENSITY, dfl, 0.0);
-      launch_d3_cd(cubes, ss, tb, 0, nown, Ppart, D_cd, nv, st);
-      launch_d3_vec(cubes, ss, dtask + (size_t)p.task0[pr] * D3_TASK_INTS, nt, t2, l2, Py, Pkc, Y,
-                    D_kc, no, nv, st);
-      launch_d3_gram(cubes, ss, 0, no, Ppart, D_lk, i > j ? -1.0 : -0.5, no, nv, st);
+      launch_d3_cd(bt, bl, tb, nown, Ppart, D_cd, nv, st);
+      launch_d3_vec(bt, bl, tb, nown, t2, E, Ppart, Y, D_kc, no, nv, st);
+      if (!p.resident) launch_d3_gram(tau, lc, false, g, 1, Ppart, D_lk, no, nv, st);
     }
     HIPCHK(hipGetLastError());
+  }
+  if (p.resident) {
+    Timer tm(pf, st, FAM_DENSITY, p.npairs * 2.0 * o * o * v * v * v, 0.0);
+    launch_d3_gram(tau, lc, true, 0, p.npairs, Ppart, D_lk, no, nv, st);
   }
   {
     Timer tm(pf, st, FAM_DENSITY, 2.0 * o * v * o * o * v, 0.0);

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace cc3 {
 
 typedef double d4v __attribute__((ext_vector_type(4)));
@@ -64,6 +66,76 @@ __device__ inline unsigned xcd_item(unsigned b, unsigned n, unsigned run) {
   const unsigned x = b & 7, s = b >> 3;
   return (s / run * 8 + x) * run + s % run;
 }
+
+// One operand of a unit of 8 k for the FP64 MFMA, FM blocks of 16 rows: lane (r16, kq) =
+// (lane % 16, lane / 16) holds k = 2 kq + t of row r16 of each block.  ROWS: k contiguous,
+// one 16-byte load per block (bs: bytes between blocks).  Otherwise the rows are
+// contiguous (ks: bytes between k): one 16-byte load of two rows per k and pair of blocks,
+// so that block 2 f holds the even rows and block 2 f + 1 the odd rows of 32 (and 8-byte
+// loads for an odd last block).
+template <bool ROWS, int FM>
+__device__ __forceinline__ void frag_load(BufRsrc r, unsigned va, unsigned bs, unsigned ks,
+                                             double (&a)[FM][2]) {
+  if constexpr (ROWS) {
+#pragma unroll
+    for (int f = 0; f < FM; ++f) {
+      const d2v v = buf_load_2f64(r, va, (unsigned)f * bs);
+      a[f][0] = v[0];
+      a[f][1] = v[1];
+    }
+  } else {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+#pragma unroll
+      for (int f = 0; f + 1 < FM; f += 2) {
+        const d2v v = buf_load_2f64(r, va + (unsigned)t * ks, (unsigned)f * 128u);
+        a[f][t] = v[0];
+        a[f + 1][t] = v[1];
+      }
+      if constexpr (FM & 1) {  // va addresses two a per lane: back to one
+        const unsigned vo = va - (threadIdx.x & 15u) * 8u + (unsigned)t * ks;
+        a[FM - 1][t] = buf_load_f64(r, vo + (unsigned)(FM - 1) * 128u);
+      }
+    }
+  }
+}
+
+// row of accumulator element (fm, r) of a wave tile (see frag_load), and the column of
+// block fn for a B operand loaded by frag_load
+template <bool ROWS, int FM>
+__device__ __forceinline__ int frag_row(int fm, int kq, int r) {
+  if (ROWS || ((FM & 1) && fm == FM - 1)) return fm * 16 + kq + 4 * r;
+  return (fm & ~1) * 16 + 2 * (kq + 4 * r) + (fm & 1);
+}
+template <bool ROWS, int FN>
+__device__ __forceinline__ int frag_col(int fn, int r16) {
+  if (ROWS || ((FN & 1) && fn == FN - 1)) return fn * 16 + r16;
+  return (fn & ~1) * 16 + 2 * r16 + (fn & 1);
+}
+
+// Wave-tile shapes and the wavefronts per SIMD that their registers allow (128, 160, ...
+// accumulator registers and 16 per operand block of the two units in flight).
+struct WaveShape { int fm, fn; };
+constexpr WaveShape kShapes[] = {{4, 4}, {5, 4}, {5, 3}, {4, 3}, {3, 3}, {5, 2}, {3, 2}, {2, 2}};
+constexpr int NSHAPE = sizeof kShapes / sizeof kShapes[0];
+constexpr int shape_waves(int fm, int fn) { return fm * fn <= 4 ? 4 : fm * fn <= 10 ? 3 : 2; }
+
+// Calls f with the shape's block counts as integral constants.
+template <class F>
+static void with_shape(int shape, F f) {
+  switch (shape) {
+#define CC3_SHAPE(n) \
+  case n:            \
+    f(std::integral_constant<int, kShapes[n].fm>(), std::integral_constant<int, kShapes[n].fn>()); \
+    break;
+    CC3_SHAPE(0) CC3_SHAPE(1) CC3_SHAPE(2) CC3_SHAPE(3) CC3_SHAPE(4) CC3_SHAPE(5) CC3_SHAPE(6)
+    default:
+    CC3_SHAPE(7)
+#undef CC3_SHAPE
+  }
+}
+
+constexpr int WNT = 256;  // threads of a workgroup of four wave tiles
 
 // Split of an FP64 value into BF16 pieces (the low-precision forms):
 // bf16_rn rounds to the nearest BF16, ties to even.

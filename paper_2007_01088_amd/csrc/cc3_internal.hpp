@@ -285,13 +285,12 @@ void launch_wbuild_lp_packed(const PackJob* jobs, int njobs, unsigned total, int
                              hipStream_t st);
 
 // ---- transition densities (Algorithm 3) ----
-// Slots of the density loop's cubes, slot-major: cubes[slot][z][cube_slot(nv)].
-enum { D3_PA = 0, D3_PB = 1, D3_TAU = 2, D3_TAUC = 3, D3_LC = 4, D3_NSLOT = 5 };
-// tau, tau~ (lmode false) or L~ (lmode true, with the outer products of the L3
-// statement from l1, l2, Jo, F and the shift omega) from the planes of each triple
-void launch_mix3(bool lmode, const double* eps, const int* tri, int ntri, double* cubes, int64_t ss,
-                 double omega, const double* l1, const double* l2, const double* Jo,
-                 const double* F, int no, int nv, hipStream_t st);
+// tau (lmode false) or L~ (lmode true, with the outer products of the L3 statement from
+// l1, l2, Jo, F and the shift omega) of each triple from its planes PA and PB, one cube
+// (cube_slot) per triple each, with zeros in the padding columns
+void launch_mix3(bool lmode, const double* eps, const int* tri, int ntri, const double* PA,
+                 const double* PB, double* out, double omega, const double* l1, const double* l2,
+                 const double* Jo, const double* F, int no, int nv, hipStream_t st);
 
 // Algorithmic FLOP of one launch of the two dominant kernels (padding excluded).
 double wbuild_flops(int no, int nv, const int* host_types, int n);

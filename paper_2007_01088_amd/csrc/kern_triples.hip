@@ -24,7 +24,6 @@
 //            their stores run along a.
 #include <algorithm>
 #include <initializer_list>
-#include <type_traits>
 
 #include "cc3.h"
 #include "cc3_device.hpp"
@@ -230,13 +229,6 @@ __device__ __forceinline__ void wbuild_body(const double* __restrict__ t2,
       }
 }
 
-// Wave-tile shapes and the wavefronts per SIMD that their registers allow (128, 160, ...
-// accumulator registers and 16 per operand block of the two units in flight).
-struct WaveShape { int fm, fn; };
-constexpr WaveShape kShapes[] = {{4, 4}, {5, 4}, {5, 3}, {4, 3}, {3, 3}, {5, 2}, {3, 2}, {2, 2}};
-constexpr int NSHAPE = sizeof kShapes / sizeof kShapes[0];
-constexpr int shape_waves(int fm, int fn) { return fm * fn <= 4 ? 4 : fm * fn <= 10 ? 3 : 2; }
-
 // The shape with the least MFMA work, padding included, weighted by the loads per MFMA:
 // relative time per block measured at nv = 150 to 400 about 1 + 0.7 (1/FM + 1/FN - 1/2)
 // (3 x 3 1.04 to 1.2, 5 x 2 1.16 to 1.26, 4 x 3 1.0 to 1.09, 5 x 4 0.98 to 1.05 of 4 x 4).
@@ -259,23 +251,6 @@ void shape_tiles(int shape, int64_t M, int64_t N, int* tm, int* tn) {
   *tm = (int)((M + 16 * kShapes[shape].fm - 1) / (16 * kShapes[shape].fm));
   *tn = (int)((N + 16 * kShapes[shape].fn - 1) / (16 * kShapes[shape].fn));
 }
-
-// Calls f with the shape's block counts as integral constants.
-template <class F>
-static void with_shape(int shape, F f) {
-  switch (shape) {
-#define CC3_SHAPE(n) \
-  case n:            \
-    f(std::integral_constant<int, kShapes[n].fm>(), std::integral_constant<int, kShapes[n].fn>()); \
-    break;
-    CC3_SHAPE(0) CC3_SHAPE(1) CC3_SHAPE(2) CC3_SHAPE(3) CC3_SHAPE(4) CC3_SHAPE(5) CC3_SHAPE(6)
-    default:
-    CC3_SHAPE(7)
-#undef CC3_SHAPE
-  }
-}
-
-constexpr int WNT = 256;  // four wave tiles per workgroup
 
 template <int MODE, int FM, int FN>
 __global__ __launch_bounds__(WNT, shape_waves(FM, FN)) void k_wbuild(
@@ -642,32 +617,33 @@ void launch_mix(bool two_planes, const double* eps, const int* tri, int ntri, do
 }
 
 // ---------------------------------------------------------------------------
-// Mix of the transition-density loop (Algorithm 3).  Cubes are slot-major,
-// cubes[slot][z][cube] (slot stride ss; each cube nv x nv rows at the padded pitch
-// cube_pitch), so that each slot of a batch is one contiguous run of cubes.  LMODE false: from the t3 planes (PA, PB), tau = -X/eps and
-// tau~ (the contravariant combination) into slots D3_TAU, D3_TAUC.  LMODE true:
-// from the L3 planes plus the outer-product terms of the L3 statement,
+// Mix of the transition-density loop (Algorithm 3).  LMODE false: tau = -X/eps from the t3
+// planes (PA, PB).  LMODE true: from the L3 planes plus the outer-product terms of the L3
+// statement,
 //   sum over the six simultaneous permutations (p,q,r; x,y,z) of (i,j,k; a,b,c) of
 //   L^x_p g_{qyrz} + L^{xy}_{pq} F_{rz},
-// L = X / (omega - eps) and its contravariant L~ into slot D3_LC.
-// Same S3-orbit tiling of 8^3 virtual blocks as k_mix; outputs are written in
-// [a][b][c] order straight from the orientation tiles.
+// L = X / (omega - eps) and its contravariant L~.  Same S3-orbit tiling of 8^3 virtual
+// blocks as k_mix; outputs are written in [a][b][c] order straight from the orientation
+// tiles.  The six terms are equal in pairs (g_{qyrz} = g_{rzqy}, L^{xy}_{pq} = L^{yx}_{qp}),
+// so three of each are loaded and doubled: the loads of the outer products, and not the
+// cubes, had set the time of this form (374 against 210 us per 12 triples at nv = 120).
 // ---------------------------------------------------------------------------
 __device__ inline double l3_outer(const double* __restrict__ l1, const double* __restrict__ l2,
                                   const double* __restrict__ Jo, const double* __restrict__ F,
                                   int no, int64_t nv, int i, int j, int k, int a, int b, int c) {
-  auto term = [&](int p, int q, int r, int x, int y, int z) {
-    return l1[(int64_t)p * nv + x] * Jo[(((int64_t)q * no + r) * nv + y) * nv + z] +
-           l2[(((int64_t)p * no + q) * nv + x) * nv + y] * F[(int64_t)r * nv + z];
+  auto term = [&](int p, int q, int r, int x, int y, int z) {  // p, x outside; (q, y), (r, z) inside
+    const int64_t at = (((int64_t)q * no + r) * nv + y) * nv + z;
+    return l1[p * nv + x] * Jo[at] + F[p * nv + x] * l2[at];
   };
-  return term(i, j, k, a, b, c) + term(j, i, k, b, a, c) + term(k, j, i, c, b, a) +
-         term(i, k, j, a, c, b) + term(j, k, i, b, c, a) + term(k, i, j, c, a, b);
+  return 2.0 * (term(i, j, k, a, b, c) + term(j, i, k, b, a, c) + term(k, i, j, c, a, b));
 }
 
 template <bool LMODE>
 __global__ __launch_bounds__(512) void k_mix3(const double* __restrict__ eps,
                                              const int* __restrict__ tri,
-                                             double* __restrict__ cubes, int64_t ss, double omega,
+                                             const double* __restrict__ planesA,
+                                             const double* __restrict__ planesB,
+                                             double* __restrict__ cubes, double omega,
                                              const double* __restrict__ l1,
                                              const double* __restrict__ l2,
                                              const double* __restrict__ Jo,
@@ -679,8 +655,8 @@ __global__ __launch_bounds__(512) void k_mix3(const double* __restrict__ eps,
   const int64_t nvl = nv;
   // the padded cube rows: pitch rp, plane pl, cube cs
   const int64_t rp = cube_pitch(nv), pl = nvl * rp, cs = cube_slot(nv);
-  const double* PA = cubes + D3_PA * ss + (int64_t)z * cs;
-  const double* PB = cubes + D3_PB * ss + (int64_t)z * cs;
+  const double* PA = planesA + (int64_t)z * cs;
+  const double* PB = planesB + (int64_t)z * cs;
   int blk[3];
   decode_block_triple(ob, blk[0], blk[1], blk[2]);
   int canon[6];
@@ -730,11 +706,10 @@ __global__ __launch_bounds__(512) void k_mix3(const double* __restrict__ eps,
   }
   __syncthreads();
   // the denominators and the contravariant combination; outputs in [a][b][c] order,
-  // with zeros in the padding columns c >= nv of each row (the Gram contraction runs
-  // over whole padded cubes)
+  // with zeros in the padding columns c >= nv of each row (c < rp: the blocks cover
+  // exactly rp values)
   const double eijk = eps[i] + eps[j] + eps[k];
-  double* outC = cubes + (LMODE ? D3_LC : D3_TAUC) * ss + (int64_t)z * cs;
-  double* outT = cubes + D3_TAU * ss + (int64_t)z * cs;
+  double* out = cubes + (int64_t)z * cs;
 #pragma unroll
   for (int o = 0; o < 6; ++o) {
     if (canon[o] != o) continue;
@@ -742,40 +717,41 @@ __global__ __launch_bounds__(512) void k_mix3(const double* __restrict__ eps,
     orient(o, q0, q1, q2);
     const int a = blk[q0] * MT + u, b = blk[q1] * MT + v, c = blk[q2] * MT + w;
     if (!(a < nv && b < nv)) continue;
-    if (c >= nv) {  // a padding column (c < rp: the blocks cover exactly rp values)
-      const int64_t e = (a * nvl + b) * rp + c;
-      outC[e] = 0.0;
-      if (!LMODE) outT[e] = 0.0;
+    const int64_t e = (a * nvl + b) * rp + c;
+    if (c >= nv) {
+      out[e] = 0.0;
+      continue;
+    }
+    const double x_abc = Xs[o * TSZ + TP(u, v, w)];
+    const double D = eps[no + a] + eps[no + b] + eps[no + c] - eijk - (LMODE ? omega : 0.0);
+    if (!LMODE) {
+      out[e] = -x_abc / D;
       continue;
     }
     const int o_acb = canon[orient_of(q0, q2)], o_cba = canon[orient_of(q2, q1)];
     const int o_bac = canon[orient_of(q1, q0)], o_bca = canon[orient_of(q1, q2)];
     const int o_cab = canon[orient_of(q2, q0)];
-    const double x_abc = Xs[o * TSZ + TP(u, v, w)];
     const double x_acb = Xs[o_acb * TSZ + TP(u, w, v)];
     const double x_cba = Xs[o_cba * TSZ + TP(w, v, u)];
     const double x_bac = Xs[o_bac * TSZ + TP(v, u, w)];
     const double x_bca = Xs[o_bca * TSZ + TP(v, w, u)];
     const double x_cab = Xs[o_cab * TSZ + TP(w, u, v)];
-    const double D = eps[no + a] + eps[no + b] + eps[no + c] - eijk - (LMODE ? omega : 0.0);
-    const int64_t e = (a * nvl + b) * rp + c;
-    outC[e] = -(4.0 * x_abc - 2.0 * x_acb - 2.0 * x_cba - 2.0 * x_bac + x_bca + x_cab) / D;
-    if (!LMODE) outT[e] = -x_abc / D;
+    out[e] = -(4.0 * x_abc - 2.0 * x_acb - 2.0 * x_cba - 2.0 * x_bac + x_bca + x_cab) / D;
   }
 }
 
-void launch_mix3(bool lmode, const double* eps, const int* tri, int ntri, double* cubes, int64_t ss,
-                 double omega, const double* l1, const double* l2, const double* Jo,
-                 const double* F, int no, int nv, hipStream_t st) {
+void launch_mix3(bool lmode, const double* eps, const int* tri, int ntri, const double* PA,
+                 const double* PB, double* out, double omega, const double* l1, const double* l2,
+                 const double* Jo, const double* F, int no, int nv, hipStream_t st) {
   if (ntri <= 0) return;
   const int nb = (nv + MT - 1) / MT;
   const int nbt = nb * (nb + 1) * (nb + 2) / 6;
   if (lmode)
-    hipLaunchKernelGGL(k_mix3<true>, dim3(nbt, ntri), dim3(512), 0, st, eps, tri, cubes, ss,
+    hipLaunchKernelGGL(k_mix3<true>, dim3(nbt, ntri), dim3(512), 0, st, eps, tri, PA, PB, out,
                        omega, l1, l2, Jo, F, no, nv);
   else
-    hipLaunchKernelGGL(k_mix3<false>, dim3(nbt, ntri), dim3(512), 0, st, eps, tri, cubes, ss,
-                       0.0, l1, l2, Jo, F, no, nv);
+    hipLaunchKernelGGL(k_mix3<false>, dim3(nbt, ntri), dim3(512), 0, st, eps, tri, PA, PB, out, 0.0,
+                       l1, l2, Jo, F, no, nv);
 }
 
 // tau^{abc}_{ijk} = -X / eps^{abc}_{ijk} for one ordered triple whose six terms were all built
@@ -828,44 +804,6 @@ void launch_tau_export(bool two_planes, const double* eps, const int* tri, const
 // now: 23/250, 8 triples 6.14 -> 5.81 ms; 8/400, 8 triples 49.0 -> 36.2; 7/93 1.91 -> 1.07;
 // 6/45 0.137 -> 0.032 ms.
 
-// The A operand of a unit: lane (r16, kq) holds k = 2 kq + t of row r16 of each block.
-// ROWS: y contiguous, one 16-byte load per block.  Otherwise a is contiguous: one 16-byte
-// load of two a per k and pair of blocks, so that block 2 f holds the even rows and block
-// 2 f + 1 the odd rows of 32 (and 8-byte loads for an odd last block).
-template <bool ROWS, int FM>
-__device__ __forceinline__ void omega_load_a(BufRsrc r, unsigned va, unsigned bs, unsigned ks,
-                                             double (&a)[FM][2]) {
-  if constexpr (ROWS) {
-#pragma unroll
-    for (int f = 0; f < FM; ++f) {
-      const d2v v = buf_load_2f64(r, va, (unsigned)f * bs);
-      a[f][0] = v[0];
-      a[f][1] = v[1];
-    }
-  } else {
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-#pragma unroll
-      for (int f = 0; f + 1 < FM; f += 2) {
-        const d2v v = buf_load_2f64(r, va + (unsigned)t * ks, (unsigned)f * 128u);
-        a[f][t] = v[0];
-        a[f + 1][t] = v[1];
-      }
-      if constexpr (FM & 1) {  // va addresses two a per lane: back to one
-        const unsigned vo = va - (threadIdx.x & 15u) * 8u + (unsigned)t * ks;
-        a[FM - 1][t] = buf_load_f64(r, vo + (unsigned)(FM - 1) * 128u);
-      }
-    }
-  }
-}
-
-// row of accumulator element (fm, r) of a wave tile (see omega_load_a)
-template <bool ROWS, int FM>
-__device__ __forceinline__ int omega_row(int fm, int kq, int r) {
-  if (ROWS || ((FM & 1) && fm == FM - 1)) return fm * 16 + kq + 4 * r;
-  return (fm & ~1) * 16 + 2 * (kq + 4 * r) + (fm & 1);
-}
-
 template <bool ROWS, int FM, int FN>
 __device__ __forceinline__ void omega_tile(const double* __restrict__ U, int64_t un, unsigned va0,
                                            unsigned bs, unsigned us, int64_t xs, BufRsrc rb,
@@ -891,7 +829,7 @@ __device__ __forceinline__ void omega_tile(const double* __restrict__ U, int64_t
   double a[2][FM][2];
   d2v b[2][FN];
   auto fetch = [&](double (&fa)[FM][2], d2v (&fb)[FN]) {
-    omega_load_a<ROWS, FM>(ra, va, bs, us / 8u, fa);
+    frag_load<ROWS, FM>(ra, va, bs, us / 8u, fa);
 #pragma unroll
     for (int f = 0; f < FN; ++f)
       fb[f] = buf_load_2f64(rb, f == fq ? vb + dv : vb, (unsigned)f * gs);
@@ -935,7 +873,7 @@ __device__ __forceinline__ void omega_tile(const double* __restrict__ U, int64_t
     for (int fn = 0; fn < FN; ++fn)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int m = m0 + omega_row<ROWS, FM>(fm, kq, r), n = n0 + fn * 16 + r16;
+        const int m = m0 + frag_row<ROWS, FM>(fm, kq, r), n = n0 + fn * 16 + r16;
         if (m < nv && n <= nv) pvv[(int64_t)m * NV1 + n] = acc[fm][fn][r];
       }
 }

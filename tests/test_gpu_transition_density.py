@@ -158,3 +158,25 @@ def test_transition_density_edge_cases_and_accumulate(ctx):
     with pytest.raises(ValueError):
         ctx.transition_density(torch.from_numpy(d["eps"]), g["L"], g["t1"], g["t2"], l1, l2,
                                lf["omega"])
+
+
+@pytest.mark.parametrize("no,nv,nJ", [(1, 64, 20), (6, 15, 24), (5, 16, 24), (4, 17, 24),
+                                      (16, 7, 20), (17, 9, 20), (33, 3, 12), (3, 65, 40),
+                                      (2, 81, 40)])
+def test_loop_by_pairs_equals_resident_loop(ctx, no, nv, nJ, monkeypatch):
+    """The loop by occupied pairs (taken where the resident cubes exceed the budget, here
+    2 MiB) gives the resident loop's densities: sizes around the 16-wide patches and blocks of the
+    contractions and the 16- and 32-row Gram tiles.  Both orders of the same FP64 sums: the
+    parity bar, 1e-11."""
+    torch, cc3 = _setup()
+    d, lf = make_inputs(no, nv, nJ, tag=31), make_left_inputs(no, nv, tag=31)
+    a = run(ctx, torch, d, lf)
+    monkeypatch.setenv("CC3_CUBE_BUDGET_MB", "1")
+    c2 = cc3.Context(0)
+    b = run(c2, torch, d, lf)
+    for name, x, y in zip(("D_cd", "D_kc", "D_ld", "D_lk", "Y^o"), a, b):
+        if np.any(x):
+            close(name, y, x)
+        else:
+            assert not np.any(y)
+    c2.close()
