@@ -460,9 +460,12 @@ static int t3_from_blocks(const Plan& p, const Ws& w, HostArgs& hs, const double
     launch_wbuild(t2, w.t2N, w.b, w.tri, 1, w.cubes[0], no, nv, true, st);
   } else {
     launch_lp_convert(t2, w.b, no, nv, w.lp, st);
-    launch_wbuild_lp(w.lp, w.tri, 1, w.cubes[0], no, nv, true, st);
+    if (p.prec == CC3_FP32 && fp32_wave_tiles(nv))
+      launch_wbuild_f32(w.lp, w.tri, 1, w.cubes[0], no, nv, true, st);
+    else
+      launch_wbuild_lp(w.lp, w.tri, 1, w.cubes[0], no, nv, true, st);
   }
-  launch_tau_export(p.prec == CC3_FP64, eps, w.tri, w.cubes[0], T.dev, no, nv, st);
+  launch_tau_export(two_planes(p.prec), eps, w.tri, w.cubes[0], T.dev, no, nv, st);
   HIPCHK(hipGetLastError());
   if ((rc = hs.finish({&T}))) return rc;
   HIPCHK(hipStreamSynchronize(st));  // the host triple was copied on st

@@ -448,12 +448,14 @@ static int triple_loop_body(Runner& rn, Profiler* pf, const Plan& p, const Ws& w
       Timer tm(pf, sk, FAM_W, wbuild_flops(p.no, p.nv, kinds.data(), nb), 0.0);
       if (p.prec == CC3_FP64)
         launch_wbuild(t2, w.t2N, w.b, tb, nb, w.cubes[k], p.no, p.nv, false, sk);
+      else if (p.prec == CC3_FP32 && fp32_wave_tiles(p.nv))
+        launch_wbuild_f32(w.lp, tb, nb, w.cubes[k], p.no, p.nv, false, sk);
       else
         launch_wbuild_lp(w.lp, tb, nb, w.cubes[k], p.no, p.nv, false, sk);
     }
     {
       Timer tm(pf, sk, FAM_MIX, 0.0, 0.0);
-      launch_mix(p.prec == CC3_FP64, eps, tb, nb, w.cubes[k],
+      launch_mix(two_planes(p.prec), eps, tb, nb, w.cubes[k],
                  lowp_contract && lpP == 0 ? (float*)w.cubesX[k] : nullptr,
                  lpP ? w.cubesX[k] : nullptr, lpP, false, p.no, p.nv, sk);
     }
@@ -542,8 +544,8 @@ int packed_residuals(const std::vector<PackMember>& ms, int prec, PackJob* dev_j
     if ((double)m.p->ntri * m.p->nv * m.p->nv * m.p->nv * m.p->nv >
         (double)big->ntri * big->nv * big->nv * big->nv * big->nv)
       big = m.p;
-  const int wshape = pick_shape(big->nv, big->nv, true);
-  const int oshape = pick_shape(big->nv, big->nv + 1, true);
+  int wshape, oshape;
+  pack_shapes(prec, big->nv, &wshape, &oshape);
   host_jobs.assign((size_t)nsteps * nm, PackJob{});
   std::vector<int> njobs(nsteps, 0);
   for (int s = 0; s < nsteps; ++s) {
@@ -633,12 +635,14 @@ static int jacobian_prep_body(Runner& rn, Profiler* pf, const Plan& p, const Ws&
       Timer tm(pf, sk, FAM_W, wbuild_flops(no, nv, kinds.data(), nb), 0.0);
       if (p.prec == CC3_FP64)
         launch_wbuild(t2, w.t2N, w.b, tb, nb, w.cubes[k], no, nv, false, sk);
+      else if (p.prec == CC3_FP32 && fp32_wave_tiles(p.nv))
+        launch_wbuild_f32(w.lp, tb, nb, w.cubes[k], no, nv, false, sk);
       else
         launch_wbuild_lp(w.lp, tb, nb, w.cubes[k], no, nv, false, sk);
     }
     {
       Timer tm(pf, sk, FAM_MIX, 0.0, 0.0);
-      launch_mix(p.prec == CC3_FP64, eps, tb, nb, w.cubes[k], nullptr, nullptr, 0, true, no, nv,
+      launch_mix(two_planes(p.prec), eps, tb, nb, w.cubes[k], nullptr, nullptr, 0, true, no, nv,
                  sk);
     }
     {

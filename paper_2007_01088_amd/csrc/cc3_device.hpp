@@ -43,17 +43,22 @@ __device__ inline double buf_load_f64(BufRsrc r, unsigned off) {
 __device__ inline float buf_load_f32(BufRsrc r, unsigned off) {
   return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
 }
-// A resource of n doubles from base (at most 2 GiB; the hardware checks each dword and
+// A resource of n elements from base (at most 2 GiB; the hardware checks each dword and
 // returns zero past the end, so rows and k past an operand's last element are safe to
 // load), and 16-byte loads at a per-lane and a uniform byte offset.
 typedef double d2v __attribute__((ext_vector_type(2)));
-__device__ inline BufRsrc buf_rsrc_n(const double* base, int64_t n) {
-  const int64_t bytes = n * 8;
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(base), 0,
+template <class E>
+__device__ inline BufRsrc buf_rsrc_n(const E* base, int64_t n) {
+  const int64_t bytes = n * (int64_t)sizeof(E);
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<E*>(base), 0,
                                            bytes > 0x7fffffff ? 0x7fffffff : (int)bytes, 0x00020000);
 }
+template <class V>
+__device__ inline V buf_load_16(BufRsrc r, unsigned voff, unsigned soff) {
+  return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, 0));
+}
 __device__ inline d2v buf_load_2f64(BufRsrc r, unsigned voff, unsigned soff) {
-  return __builtin_bit_cast(d2v, __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, 0));
+  return buf_load_16<d2v>(r, voff, soff);
 }
 
 // The work item of workgroup b of n: workgroups go round-robin over the 8 XCDs, so runs

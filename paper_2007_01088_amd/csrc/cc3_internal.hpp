@@ -53,6 +53,13 @@ __host__ __device__ inline void perm_pqr(int pi, int i, int j, int k, int& p, in
 // K padded to a multiple of 32 (the low-precision operand rows)
 __host__ __device__ inline int64_t kpad32(int64_t k) { return (k + 31) / 32 * 32; }
 
+// Slab (elements of esz bytes) of the low-precision W operands GwT and t2N: nv rows of k
+// values padded to 32, rounded up to an odd number of 128-byte lines as the FP64 slabs
+// (odd_line_pitch)
+__host__ __device__ inline int64_t lp_slab(int nv, int k, int esz) {
+  return (((nv * kpad32(k) * esz + 127) / 128) | 1) * 128 / esz;
+}
+
 // K of the split-BF16 Omega contraction (the mixed-all form): the pair (x, y) of the
 // contracted virtual indices in 8 x 8 blocks, kb = ((X nb + Y) 8 + x % 8) 8 + y % 8 with
 // X = x / 8, Y = y / 8 and nb = ceil(nv / 8), so that the 64 values of one block, which
@@ -96,6 +103,9 @@ __host__ __device__ inline int64_t t2n_pitch(int no, int nv) {
 __host__ __device__ inline int64_t g_pitch(int nv) {
   return odd_line_pitch((int64_t)nv * cube_pitch(nv));
 }
+
+// Whether the W build of a precision writes two planes per triple (all but CC3_BF16X3).
+inline bool two_planes(int prec) { return prec != 2; }
 
 // Device-resident, internally laid out integral blocks (all float64):
 //   Gw[r][y][z][d] = g_{ydzr}         (vv|vo), the W contraction operand (d fastest),
@@ -157,6 +167,11 @@ size_t lp_operand_bytes(int prec, int no, int nv);
 void lp_operand_ptrs(int prec, int no, int nv, void* base, LpOperands& lp);
 void launch_lp_convert(const double* t2, const Blocks& b, int no, int nv, const LpOperands& lp,
                        hipStream_t st);
+// The W build from them: launch_wbuild_lp, on LDS tiles, or for FP32 where those would be
+// mostly padding launch_wbuild_f32, the wave-tile form (fp32_wave_tiles).
+bool fp32_wave_tiles(int nv);
+void launch_wbuild_f32(const LpOperands& lp, const int* tri, int ntri, double* cubes, int no, int nv,
+                       bool all_terms, hipStream_t st);
 void launch_wbuild_lp(const LpOperands& lp, const int* tri, int ntri, double* cubes, int no, int nv,
                       bool all_terms, hipStream_t st);
 
@@ -192,8 +207,7 @@ void launch_wbuild(const double* t2, const double* t2N, const Blocks& b, const i
 void launch_wbuild_ex(int mode, const double* X, const double* XN, const double* G, const double* H,
                       const int* tri, int ntri, double* cubes, int64_t zs, int64_t ss, int pitch,
                       int no, int nv, bool all_terms, hipStream_t st);
-// two_planes: the planes are those of the FP64 W build (PA, PB), else the three planes
-// of the low-precision one.  transposed: write tau~T too.  Mixed-all copies (nullable): cubesF, FP32 tau~ and tau~T,
+// two_planes: the planes are PA and PB, else the three of the BF16x3 W build.  transposed: write tau~T too.  Mixed-all copies (nullable): cubesF, FP32 tau~ and tau~T,
 // [triple][2][nv^3]; YL, the split-BF16 k-major views of k_omega_lp with lpP pieces
 void launch_mix(bool two_planes, const double* eps, const int* tri, int ntri, double* cubes,
                 float* cubesF, void* YL, int lpP, bool transposed, int no, int nv, hipStream_t st);
@@ -202,7 +216,8 @@ void launch_tau_export(bool two_planes, const double* eps, const int* tri, const
 // Wave tiles of the FP64 GEMMs: FM x FN blocks of 16 x 16 outputs per wavefront.
 // pick_shape gives the index of the shape for an M x N product; shape_tiles the wave
 // tiles along M and N.
-int pick_shape(int64_t M, int64_t N, bool packed = false);
+// packed: for a packed launch; most: the largest FM x FN.
+int pick_shape(int64_t M, int64_t N, bool packed = false, int most = 20);
 void shape_tiles(int shape, int64_t M, int64_t N, int* tm, int* tn);
 // Omega contraction of a batch: the vv term and Omega1 into per-(triple,
 // permutation, chunk) partial slabs Pvv, then their fixed-order reduction into
@@ -265,7 +280,7 @@ struct PackJob {
   const int* tri;                             // the job's batch of triples
   double *cubes, *Pvv, *Ot1, *Ot2, *OtT;
   int no, nv, ntri, nch;
-  int wshape, oshape;    // wave-tile shapes of the FP64 W build and Omega GEMM, the same
+  int wshape, oshape;    // tile shapes of the W build and the Omega GEMM, the same
                          // for every job
   int rslices;           // shares and element blocks of the reduction (set by pack_items)
   unsigned rgx;
@@ -274,14 +289,17 @@ struct PackJob {
 // Work items of one job per kernel (the workgroups of its unpacked launch); prec: the
 // W build's arithmetic.
 void pack_items(PackJob& j, int prec, unsigned (&items)[PK_N]);
+void pack_shapes(int prec, int nv, int* wshape, int* oshape);
 // The five packed launches of one step (jobs in device memory, host copy for the
 // item counts); prec: the W build's arithmetic, shared by every job.
 void launch_packed_step(const PackJob* dev_jobs, const PackJob* host_jobs, int njobs, int prec,
                         hipStream_t st);
 
-// Workgroups of the low-precision W build of a batch, and its packed launch.
-unsigned wbuild_lp_wgs(int nv, int ntri);
-void launch_wbuild_lp_packed(const PackJob* jobs, int njobs, unsigned total, int prec,
+// Workgroups of the LDS-tile W build of a batch with tile edge 16 nw, its choice, and its
+// packed launch.
+unsigned wbuild_lp_wgs(int prec, int nv, int ntri, int nw);
+int lp_tile_waves(int64_t M, int64_t N);
+void launch_wbuild_lp_packed(const PackJob* jobs, int njobs, unsigned total, int prec, int nw,
                              hipStream_t st);
 
 // ---- transition densities (Algorithm 3) ----

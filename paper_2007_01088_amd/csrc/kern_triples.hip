@@ -23,18 +23,18 @@
 //            four of the six permutations kept transposed, OtT[p][l][b][a], so that
 //            their stores run along a.
 #include <algorithm>
-#include <initializer_list>
 
 #include "cc3.h"
 #include "cc3_device.hpp"
 #include "cc3_internal.hpp"
+#include "cc3_wplanes.hpp"
 
 namespace cc3 {
 
 static inline unsigned nblk(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 
-// cube slots of one triple's workspace: the W planes (PA, PB of the FP64 build; P0, P1,
-// P2 of the low-precision one), tau~ and tau~T
+// cube slots of one triple's workspace: the W planes (PA and PB; P0, P1, P2 of the BF16x3
+// build), tau~ and tau~T
 enum { SLOT_P0 = 0, SLOT_P1 = 1, SLOT_P2 = 2, SLOT_TT = 3, SLOT_TTT = 4, NSLOT = 5 };
 enum { SLOT_PA = SLOT_P0, SLOT_PB = SLOT_P1 };
 
@@ -73,39 +73,68 @@ enum { SLOT_PA = SLOT_P0, SLOT_PB = SLOT_P1 };
 // Go <- Go3 (Go3[p][q][z][l] = g_{plqz}): the same products with the roles of the
 // occupied indices permuted.
 
-// The segments of a plane, in order: 6 bits each, the permutation of perm_pqr that names
-// the term (bits 0-2), l sum (bit 3), amplitude operand on the columns instead of the
-// rows (bit 4), operand rows one slab apart (bit 5: Gw for a d sum, t2N for an l sum).
-constexpr uint64_t wseg(int pi, int lsum, int col, int strided) {
-  return (uint64_t)(pi | lsum << 3 | col << 4 | strided << 5);
+// Operand element types.  double: the arrays themselves, K = nv and no, the k past K of a
+// segment's last unit zeroed in registers.  float (CC3_FP32): FP32 copies whose rows are
+// padded with zeros to a multiple of 32 k; every 32 k are summed on the MFMA in FP32 from
+// zero and added into FP64 accumulators.  A unit of loads is 64 bytes of each row: lane
+// group kq = lane / 16 holds the KL consecutive k from KL kq on, and feeds its t-th to
+// MFMA step t.
+template <class E>
+struct WElem;
+template <>
+struct WElem<double> {
+  static constexpr int KL = 2, UK = 8;
+  typedef d2v Frag;
+  typedef d4v Acc;
+  static __device__ Acc mfma(double a, double b, Acc c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
+  static __device__ int row(int kq, int r) { return kq + 4 * r; }
+};
+template <>
+struct WElem<float> {
+  static constexpr int KL = 4, UK = 16;
+  typedef float Frag __attribute__((ext_vector_type(4)));
+  typedef float Acc __attribute__((ext_vector_type(4)));
+  static __device__ Acc mfma(float a, float b, Acc c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+  static __device__ int row(int kq, int r) { return 4 * kq + r; }
+};
+// strides of the operands, in elements: rows of K = nv and K = no (rv, ro), their K
+// (padded for float), slabs of Gw and of t2N
+struct WDims {
+  int rv, ro, kv, ko;
+  int64_t gy, ty;
+};
+template <class E>
+__host__ __device__ inline WDims wdims(int no, int nv) {
+  WDims d;
+  if (sizeof(E) == 8) {
+    d.rv = d.kv = nv;
+    d.ro = d.ko = no;
+    d.gy = gw_pitch(nv);
+    d.ty = t2n_pitch(no, nv);
+  } else {
+    d.rv = d.kv = (int)kpad32(nv);
+    d.ro = d.ko = (int)kpad32(no);
+    d.gy = lp_slab(nv, nv, 4);
+    d.ty = lp_slab(nv, no, 4);
+  }
+  return d;
 }
-constexpr uint64_t wsegs(std::initializer_list<uint64_t> l) {
-  uint64_t v = 0;
-  int at = 0;
-  for (uint64_t x : l) { v |= x << at; at += 6; }
-  return v;
-}
-// perm_pqr: 0 ijk, 1 jik, 2 kji, 3 ikj, 4 jki, 5 kij
-constexpr uint64_t kSegsA = wsegs({wseg(0, 0, 0, 0), wseg(3, 0, 0, 1), wseg(2, 0, 1, 0),
-                                   wseg(5, 0, 1, 1), wseg(0, 1, 0, 0), wseg(2, 1, 1, 0),
-                                   wseg(4, 1, 1, 1)});
-constexpr uint64_t kSegsAij = wsegs({wseg(0, 0, 0, 0), wseg(3, 0, 0, 1), wseg(2, 0, 1, 0),
-                                     wseg(0, 1, 0, 0), wseg(2, 1, 1, 0), wseg(4, 1, 1, 1)});
-constexpr uint64_t kSegsAjk = wsegs({wseg(0, 0, 0, 0), wseg(2, 0, 1, 0), wseg(5, 0, 1, 1),
-                                     wseg(0, 1, 0, 0), wseg(2, 1, 1, 0), wseg(1, 1, 0, 1)});
-constexpr uint64_t kSegsB = wsegs({wseg(1, 0, 0, 0), wseg(4, 0, 0, 1), wseg(1, 1, 0, 0),
-                                   wseg(5, 1, 1, 0), wseg(3, 1, 1, 1)});
 
 // `item`: the wave tile, tiles of a plane fastest, then the fixed index y, plane, triple
-template <int MODE, int FM, int FN>
-__device__ __forceinline__ void wbuild_body(const double* __restrict__ t2,
-                                            const double* __restrict__ t2N,
-                                            const double* __restrict__ Gw,
-                                            const double* __restrict__ Go,
+template <class E, int MODE, int FM, int FN>
+__device__ __forceinline__ void wbuild_body(const E* __restrict__ t2, const E* __restrict__ t2N,
+                                            const E* __restrict__ Gw, const E* __restrict__ Go,
                                             const int* __restrict__ tri, int ntri,
                                             double* __restrict__ cubes, int64_t zs, int64_t ss,
                                             int pitch, int no, int nv, int tiles_m, int tiles_n,
                                             int all_terms, unsigned item) {
+  typedef WElem<E> T;
+  constexpr int KL = T::KL, UK = T::UK;
+  constexpr bool F64 = sizeof(E) == 8;
   const unsigned tpp = (unsigned)(tiles_m * tiles_n);
   const int tile = (int)(item % tpp);
   item /= tpp;
@@ -116,15 +145,13 @@ __device__ __forceinline__ void wbuild_body(const double* __restrict__ t2,
   const int i = tri[3 * z], j = tri[3 * z + 1], k = tri[3 * z + 2];
   const int kind = all_terms ? TRI_DISTINCT : tri_kind(i, j, k);
   if (kind != TRI_DISTINCT && plane == 1) return;
-  const uint64_t segs = plane ? kSegsB
-                        : kind == TRI_DISTINCT ? kSegsA
-                        : kind == TRI_IJ ? kSegsAij : kSegsAjk;
-  const int nd = plane ? 2 : kind == TRI_DISTINCT ? 4 : 3;  // d sums; the l sums are three
-  const int nseg = nd + 3;
-  const int units = nd * ((nv + 7) / 8) + 3 * ((no + 7) / 8);
+  const uint64_t segs = wplane_segs(plane, kind);
+  const int nd = wplane_dsums(plane, kind), nseg = nd + 3;  // the l sums are three
+  const WDims D = wdims<E>(no, nv);
+  const int units = nd * ((D.kv + UK - 1) / UK) + 3 * ((D.ko + UK - 1) / UK);
   const int m0 = (tile / tiles_n) * (FM * 16), n0 = (tile % tiles_n) * (FN * 16);
   const int lane = threadIdx.x & 63, r16 = lane & 15, kq = lane >> 4;
-  const int64_t nv2 = (int64_t)nv * nv, gy = gw_pitch(nv), ty = t2n_pitch(no, nv);
+  const int64_t xm = (int64_t)nv * D.rv, hm = (int64_t)nv * D.ro;  // one matrix of t2, of Go
 
   // the segment being loaded: resources at row m0 / n0, row strides, K, and the next k
   BufRsrc ra, rb;
@@ -136,59 +163,63 @@ __device__ __forceinline__ void wbuild_body(const double* __restrict__ t2,
     int p, q, r;
     perm_pqr(code & 7, i, j, k, p, q, r);
     const int am0 = col ? n0 : m0, in0 = col ? m0 : n0;  // first rows of the two operands
-    const double *amp, *in;
-    int64_t an, inn;  // doubles left in their arrays
+    const E *amp, *in;
+    int64_t an, inn;  // elements left in their arrays
     int la, li;
     if (!lsum) {
-      la = nv;
-      const int64_t ao = ((int64_t)(MODE ? q * no + r : p * no + q)) * nv2 + (int64_t)am0 * nv;
+      la = D.rv;
+      const int64_t ao = (MODE ? q * no + r : p * no + q) * xm + (int64_t)am0 * la;
       amp = t2 + ao;
-      an = (int64_t)no * no * nv2 - ao;
-      li = strided ? (int)gy : nv;
-      const int64_t go = (int64_t)(MODE ? p : r) * nv * gy + (strided ? (int64_t)y * nv : y * gy) +
+      an = no * no * xm - ao;
+      li = strided ? (int)D.gy : D.rv;
+      const int64_t go = (MODE ? p : r) * nv * D.gy + (strided ? (int64_t)y * D.rv : y * D.gy) +
                          (int64_t)in0 * li;
       in = Gw + go;
-      inn = (int64_t)no * nv * gy - go;
-      K = nv;
+      inn = no * nv * D.gy - go;
+      K = D.kv;
     } else {
-      la = strided ? (int)ty : no;
-      const int64_t ao = (int64_t)(MODE ? r : p) * nv * ty + (strided ? (int64_t)y * no : y * ty) +
+      la = strided ? (int)D.ty : D.ro;
+      const int64_t ao = (MODE ? r : p) * nv * D.ty + (strided ? (int64_t)y * D.ro : y * D.ty) +
                          (int64_t)am0 * la;
       amp = t2N + ao;
-      an = (int64_t)no * nv * ty - ao;
-      li = no;
-      const int64_t go = (int64_t)(MODE ? p * no + q : q * no + r) * nv * no + (int64_t)in0 * no;
+      an = no * nv * D.ty - ao;
+      li = D.ro;
+      const int64_t go = (MODE ? p * no + q : q * no + r) * hm + (int64_t)in0 * li;
       in = Go + go;
-      inn = (int64_t)no * no * nv * no - go;
-      K = no;
+      inn = no * no * hm - go;
+      K = D.ko;
     }
     ra = buf_rsrc_n(col ? in : amp, col ? inn : an);
     rb = buf_rsrc_n(col ? amp : in, col ? an : inn);
-    lda = col ? li : la;
-    ldb = col ? la : li;
-    va = (unsigned)(r16 * lda + 2 * kq) * 8u;
-    vb = (unsigned)(r16 * ldb + 2 * kq) * 8u;
+    lda = (col ? li : la) * (int)sizeof(E);
+    ldb = (col ? la : li) * (int)sizeof(E);
+    va = (unsigned)(r16 * lda + kq * 16);
+    vb = (unsigned)(r16 * ldb + kq * 16);
     kk = 0;
   };
-  d2v a[2][FM], b[2][FN];
-  int kn[2];  // k left in the segment at each unit (uniform); below 8 the unit is partial
-  auto fetch = [&](d2v (&fa)[FM], d2v (&fb)[FN], int& n) {
+  typename T::Frag a[2][FM], b[2][FN];
+  int kn[2];  // k left in the segment at each unit (uniform); below UK the unit is partial
+  auto fetch = [&](typename T::Frag (&fa)[FM], typename T::Frag (&fb)[FN], int& n) {
 #pragma unroll
-    for (int f = 0; f < FM; ++f) fa[f] = buf_load_2f64(ra, va, (unsigned)(f * 128 * lda));
+    for (int f = 0; f < FM; ++f) fa[f] = buf_load_16<typename T::Frag>(ra, va, (unsigned)(f * 16 * lda));
 #pragma unroll
-    for (int f = 0; f < FN; ++f) fb[f] = buf_load_2f64(rb, vb, (unsigned)(f * 128 * ldb));
+    for (int f = 0; f < FN; ++f) fb[f] = buf_load_16<typename T::Frag>(rb, vb, (unsigned)(f * 16 * ldb));
     n = K - kk;
-    kk += 8;
+    kk += UK;
     va += 64u;
     vb += 64u;
     // past the last segment the loads go on along its rows and are not used
     if (kk >= K && seg + 1 < nseg) open(++seg);
   };
-  d4v acc[FM][FN];
+  typename T::Acc acc[FM][FN];
+  d4v accd[FM][FN];  // float: the 32-k stages summed in FP64
 #pragma unroll
   for (int fm = 0; fm < FM; ++fm)
 #pragma unroll
-    for (int fn = 0; fn < FN; ++fn) acc[fm][fn] = d4v{0.0, 0.0, 0.0, 0.0};
+    for (int fn = 0; fn < FN; ++fn) {
+      acc[fm][fn] = typename T::Acc{0, 0, 0, 0};
+      accd[fm][fn] = d4v{0.0, 0.0, 0.0, 0.0};
+    }
   open(0);
   fetch(a[0], b[0], kn[0]);
   fetch(a[1], b[1], kn[1]);
@@ -196,24 +227,35 @@ __device__ __forceinline__ void wbuild_body(const double* __restrict__ t2,
 #pragma unroll
     for (int d = 0; d < 2; ++d) {
       if (u + d < units) {
-        if (kn[d] < 8) {  // zero the k past K in both operands
-          const bool i0 = 2 * kq < kn[d], i1 = 2 * kq + 1 < kn[d];
+        if constexpr (F64) {
+          if (kn[d] < 8) {  // zero the k past K in both operands
+            const bool i0 = 2 * kq < kn[d], i1 = 2 * kq + 1 < kn[d];
 #pragma unroll
-          for (int f = 0; f < FM; ++f) a[d][f] = d2v{i0 ? a[d][f][0] : 0.0, i1 ? a[d][f][1] : 0.0};
+            for (int f = 0; f < FM; ++f) a[d][f] = d2v{i0 ? a[d][f][0] : 0.0, i1 ? a[d][f][1] : 0.0};
 #pragma unroll
-          for (int f = 0; f < FN; ++f) b[d][f] = d2v{i0 ? b[d][f][0] : 0.0, i1 ? b[d][f][1] : 0.0};
+            for (int f = 0; f < FN; ++f) b[d][f] = d2v{i0 ? b[d][f][0] : 0.0, i1 ? b[d][f][1] : 0.0};
+          }
         }
-        // lane supplies A[m = l%16][k] and B[k][n = l%16], k = 2 (l/16) + t of the unit
+        // lane supplies A[m = l%16][k] and B[k][n = l%16], k = KL (l/16) + t of the unit
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
+        for (int t = 0; t < KL; ++t)
 #pragma unroll
           for (int fm = 0; fm < FM; ++fm)
 #pragma unroll
             for (int fn = 0; fn < FN; ++fn)
-              acc[fm][fn] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[d][fm][t], b[d][fn][t],
-                                                                 acc[fm][fn], 0, 0, 0);
+              acc[fm][fn] = T::mfma(a[d][fm][t], b[d][fn][t], acc[fm][fn]);
       }
       fetch(a[d], b[d], kn[d]);
+    }
+    if constexpr (!F64) {  // both units of a 32-k stage (units are even in every segment)
+#pragma unroll
+      for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+        for (int fn = 0; fn < FN; ++fn) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) accd[fm][fn][r] += (double)acc[fm][fn][r];
+          acc[fm][fn] = typename T::Acc{0, 0, 0, 0};
+        }
     }
   }
 
@@ -224,8 +266,9 @@ __device__ __forceinline__ void wbuild_body(const double* __restrict__ t2,
     for (int fn = 0; fn < FN; ++fn)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int m = m0 + fm * 16 + kq + 4 * r, n = n0 + fn * 16 + r16;
-        if (m < nv && n < nv) out[(int64_t)m * pitch + n] = acc[fm][fn][r];
+        const int m = m0 + fm * 16 + T::row(kq, r), n = n0 + fn * 16 + r16;
+        if (m < nv && n < nv)
+          out[(int64_t)m * pitch + n] = F64 ? (double)acc[fm][fn][r] : accd[fm][fn][r];
       }
 }
 
@@ -233,16 +276,16 @@ __device__ __forceinline__ void wbuild_body(const double* __restrict__ t2,
 // relative time per block measured at nv = 150 to 400 about 1 + 0.7 (1/FM + 1/FN - 1/2)
 // (3 x 3 1.04 to 1.2, 5 x 2 1.16 to 1.26, 4 x 3 1.0 to 1.09, 5 x 4 0.98 to 1.05 of 4 x 4).
 // The item loop of the packed kernels takes registers that 5 x 4 and 5 x 2 do not leave.
-int pick_shape(int64_t M, int64_t N, bool packed) {
+int pick_shape(int64_t M, int64_t N, bool packed, int most) {
   int best = 0;
   double cost = 0.0;
   for (int s = 0; s < NSHAPE; ++s) {
     const double fm = kShapes[s].fm, fn = kShapes[s].fn;
-    if (packed && (fm * fn == 20 || fm * fn == 10)) continue;
+    if (fm * fn > most || (packed && (fm * fn == 20 || fm * fn == 10))) continue;
     int tm, tn;
     shape_tiles(s, M, N, &tm, &tn);
     const double c = tm * fm * tn * fn * (0.65 + 0.7 * (1.0 / fm + 1.0 / fn));
-    if (s == 0 || c < cost) { best = s; cost = c; }
+    if (cost == 0.0 || c < cost) { best = s; cost = c; }
   }
   return best;
 }
@@ -252,18 +295,24 @@ void shape_tiles(int shape, int64_t M, int64_t N, int* tm, int* tn) {
   *tn = (int)((N + 16 * kShapes[shape].fn - 1) / (16 * kShapes[shape].fn));
 }
 
-template <int MODE, int FM, int FN>
-__global__ __launch_bounds__(WNT, shape_waves(FM, FN)) void k_wbuild(
-    const double* __restrict__ t2, const double* __restrict__ t2N, const double* __restrict__ Gw,
-    const double* __restrict__ Go, const int* __restrict__ tri, int ntri,
-    double* __restrict__ cubes, int64_t zs, int64_t ss, int pitch, int no, int nv, int tiles_m,
-    int tiles_n, int all_terms) {
+// Wavefronts per SIMD of the FP32 form: 12 accumulator registers per block and lane
+// instead of 8.
+template <class E>
+constexpr int wbuild_waves(int fm, int fn) {
+  return sizeof(E) == 8 ? shape_waves(fm, fn) : fm * fn <= 4 ? 4 : fm * fn <= 6 ? 3 : 2;
+}
+
+template <class E, int MODE, int FM, int FN>
+__global__ __launch_bounds__(WNT, wbuild_waves<E>(FM, FN)) void k_wbuild(
+    const E* __restrict__ t2, const E* __restrict__ t2N, const E* __restrict__ Gw,
+    const E* __restrict__ Go, const int* __restrict__ tri, int ntri, double* __restrict__ cubes,
+    int64_t zs, int64_t ss, int pitch, int no, int nv, int tiles_m, int tiles_n, int all_terms) {
   // runs of four planes per XCD: the tiles of a plane share its operand rows in one L2
   // (the 3 x 3 shape at nv = 250: 49 -> 57 TFLOP/s of MFMA)
   const unsigned wg = xcd_item(blockIdx.x, gridDim.x, (unsigned)(tiles_m * tiles_n));
   const unsigned wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  wbuild_body<MODE, FM, FN>(t2, t2N, Gw, Go, tri, ntri, cubes, zs, ss, pitch, no, nv, tiles_m,
-                            tiles_n, all_terms, wg * 4 + wave);
+  wbuild_body<E, MODE, FM, FN>(t2, t2N, Gw, Go, tri, ntri, cubes, zs, ss, pitch, no, nv, tiles_m,
+                               tiles_n, all_terms, wg * 4 + wave);
 }
 
 // wave tiles of a W launch: tiles per plane x nv x two planes x triples, four to a workgroup
@@ -273,22 +322,37 @@ static unsigned wbuild_wgs(int nv, int ntri, int shape) {
   return (unsigned)(((int64_t)tm * tn * nv * 2 * ntri + 3) / 4);
 }
 
+// FP32 runs on wave tiles where the 128 x 128 LDS tiles of kern_wlp.hip would be less than
+// 85% outputs: the FP64 sums of its stages leave a wavefront 4 x 3 blocks at most, and where
+// the LDS tiles are filled they load less.  MEASURED, whole calls, wave tiles / LDS tiles:
+// nv = 93: 3.31 / 3.84 ms, 140: 17.0 / 20.2, 180: 37.8 / 40.7, 400: 172 / 182 (fill 51 to
+// 61%); 120: 9.91 / 9.63, 250: 469 / 447 (88 and 95%).
+bool fp32_wave_tiles(int nv) {
+  const double f = nv / (128.0 * ((nv + 127) / 128));
+  return f * f < 0.85;
+}
+
+// The FP32 form takes the shapes up to 4 x 3 (its accumulators: 144 registers).
+static int wbuild_shape(int prec, int nv, bool packed) {
+  return pick_shape(nv, nv, packed, prec == CC3_FP32 ? 12 : 20);
+}
+
 void launch_wbuild_ex(int mode, const double* X, const double* XN, const double* G, const double* H,
                       const int* tri, int ntri, double* cubes, int64_t zs, int64_t ss, int pitch,
                       int no, int nv, bool all_terms, hipStream_t st) {
   if (ntri <= 0) return;
-  const int shape = pick_shape(nv, nv);
+  const int shape = wbuild_shape(CC3_FP64, nv, false);
   int tm, tn;
   shape_tiles(shape, nv, nv, &tm, &tn);
   const dim3 grid(wbuild_wgs(nv, ntri, shape)), block(WNT);
   with_shape(shape, [&](auto fm, auto fn) {
     constexpr int FM = decltype(fm)::value, FN = decltype(fn)::value;
     if (mode == 0)
-      hipLaunchKernelGGL((k_wbuild<0, FM, FN>), grid, block, 0, st, X, XN, G, H, tri, ntri, cubes,
-                         zs, ss, pitch, no, nv, tm, tn, all_terms ? 1 : 0);
+      hipLaunchKernelGGL((k_wbuild<double, 0, FM, FN>), grid, block, 0, st, X, XN, G, H, tri, ntri,
+                         cubes, zs, ss, pitch, no, nv, tm, tn, all_terms ? 1 : 0);
     else
-      hipLaunchKernelGGL((k_wbuild<1, FM, FN>), grid, block, 0, st, X, XN, G, H, tri, ntri, cubes,
-                         zs, ss, pitch, no, nv, tm, tn, all_terms ? 1 : 0);
+      hipLaunchKernelGGL((k_wbuild<double, 1, FM, FN>), grid, block, 0, st, X, XN, G, H, tri, ntri,
+                         cubes, zs, ss, pitch, no, nv, tm, tn, all_terms ? 1 : 0);
   });
 }
 
@@ -297,6 +361,23 @@ void launch_wbuild(const double* t2, const double* t2N, const Blocks& b, const i
   const int64_t cs = cube_slot(nv);
   launch_wbuild_ex(0, t2, t2N, b.Gw, b.Go, tri, ntri, cubes, NSLOT * cs, cs, cube_pitch(nv), no,
                    nv, all_terms, st);
+}
+
+void launch_wbuild_f32(const LpOperands& lp, const int* tri, int ntri, double* cubes, int no, int nv,
+                       bool all_terms, hipStream_t st) {
+  if (ntri <= 0) return;
+  const int shape = wbuild_shape(CC3_FP32, nv, false);
+  const int64_t cs = cube_slot(nv);
+  int tm, tn;
+  shape_tiles(shape, nv, nv, &tm, &tn);
+  with_shape(shape, [&](auto fm, auto fn) {
+    constexpr int FM = decltype(fm)::value, FN = decltype(fn)::value;
+    if constexpr (FM * FN <= 12)
+      hipLaunchKernelGGL((k_wbuild<float, 0, FM, FN>), dim3(wbuild_wgs(nv, ntri, shape)), dim3(WNT),
+                         0, st, (const float*)lp.t2, (const float*)lp.t2N, (const float*)lp.GwT,
+                         (const float*)lp.GoT, tri, ntri, cubes, NSLOT * cs, cs, cube_pitch(nv), no,
+                         nv, tm, tn, all_terms ? 1 : 0);
+  });
 }
 
 // t2N[p][y][x][l] = -t2[p][l][x][y]
@@ -391,7 +472,7 @@ __device__ inline void yl_put(uint16_t* YL, int P, int z, int v, int row, int kx
 // YL, the split-BF16 k-major views of the split-BF16 Omega GEMM (k_omega_lp),
 // [triple][4][piece][a][kk < Kp] with lpP pieces.  TWO: the two planes of the FP64 W
 // build, X = PA[b][a][c] + PB[a][b][c] (PA[a][b][c] for i == j, PA[c][a][b] for j == k in
-// the place of PB); otherwise the three planes of the low-precision build,
+// the place of PB); otherwise the three planes of the BF16x3 build,
 // X = P0[b][a][c] + P1[a][b][c] + P2[c][a][b], where for i == j P1 = P0 and P2 is
 // symmetrised over (a, b), and for j == k P2 = P0 and P1 is symmetrised over (b, c).
 template <int MIXT, bool TWO>
@@ -605,15 +686,22 @@ void launch_mix(bool two_planes, const double* eps, const int* tri, int ntri, do
   // 512 threads, one element per thread and orientation; the form that also writes
   // the split-BF16 views of tau~ runs with 256 (two elements each), which measured
   // faster for it at nv = 250
-  if (two_planes)
-    hipLaunchKernelGGL((k_mix<512, true>), dim3(nbt, ntri), dim3(512), 0, st, eps, tri, cubes,
-                       nullptr, nullptr, 0, transposed ? 1 : 0, no, nv);
-  else if (YL)
-    hipLaunchKernelGGL((k_mix<256, false>), dim3(nbt, ntri), dim3(256), 0, st, eps, tri, cubes,
-                       cubesF, (uint16_t*)YL, lpP, transposed ? 1 : 0, no, nv);
-  else
-    hipLaunchKernelGGL((k_mix<512, false>), dim3(nbt, ntri), dim3(512), 0, st, eps, tri, cubes,
-                       cubesF, (uint16_t*)YL, lpP, transposed ? 1 : 0, no, nv);
+  const int tr = transposed ? 1 : 0;
+  if (YL) {
+    if (two_planes)
+      hipLaunchKernelGGL((k_mix<256, true>), dim3(nbt, ntri), dim3(256), 0, st, eps, tri, cubes,
+                         cubesF, (uint16_t*)YL, lpP, tr, no, nv);
+    else
+      hipLaunchKernelGGL((k_mix<256, false>), dim3(nbt, ntri), dim3(256), 0, st, eps, tri, cubes,
+                         cubesF, (uint16_t*)YL, lpP, tr, no, nv);
+  } else {
+    if (two_planes)
+      hipLaunchKernelGGL((k_mix<512, true>), dim3(nbt, ntri), dim3(512), 0, st, eps, tri, cubes,
+                         cubesF, nullptr, 0, tr, no, nv);
+    else
+      hipLaunchKernelGGL((k_mix<512, false>), dim3(nbt, ntri), dim3(512), 0, st, eps, tri, cubes,
+                         cubesF, nullptr, 0, tr, no, nv);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1702,8 +1790,8 @@ __device__ inline int pack_job(const PackJob* __restrict__ jobs, int njobs, int 
   return r;
 }
 
-template <int FM, int FN>
-__global__ __launch_bounds__(WNT, shape_waves(FM, FN)) void k_pack_wbuild(
+template <class E, int FM, int FN>
+__global__ __launch_bounds__(WNT, wbuild_waves<E>(FM, FN)) void k_pack_wbuild(
     const PackJob* __restrict__ jobs, int njobs, unsigned total) {
   for (unsigned item = blockIdx.x; item < total; item += gridDim.x) {
     const PackJob& J = jobs[pack_job(jobs, njobs, PK_W, item)];
@@ -1711,8 +1799,11 @@ __global__ __launch_bounds__(WNT, shape_waves(FM, FN)) void k_pack_wbuild(
     const int tm = (J.nv + 16 * FM - 1) / (16 * FM), tn = (J.nv + 16 * FN - 1) / (16 * FN);
     const int64_t cs = cube_slot(J.nv);
     const unsigned wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    wbuild_body<0, FM, FN>(J.t2, J.t2N, J.Gw, J.Go, J.tri, J.ntri, J.cubes, NSLOT * cs, cs,
-                           cube_pitch(J.nv), J.no, J.nv, tm, tn, 0, local * 4 + wave);
+    const void *t2 = J.t2, *t2N = J.t2N, *Gw = J.Gw, *Go = J.Go;
+    if (sizeof(E) == 4) { t2 = J.lpt2; t2N = J.lpt2N; Gw = J.lpGwT; Go = J.lpGoT; }
+    wbuild_body<E, 0, FM, FN>((const E*)t2, (const E*)t2N, (const E*)Gw, (const E*)Go, J.tri, J.ntri,
+                              J.cubes, NSLOT * cs, cs, cube_pitch(J.nv), J.no, J.nv, tm, tn, 0,
+                              local * 4 + wave);
   }
 }
 
@@ -1769,9 +1860,20 @@ __global__ __launch_bounds__(256) void k_pack_reduce(const PackJob* __restrict__
   }
 }
 
+// The packed tile shapes for a member of nv: wave tiles (below NSHAPE) or, for the W build,
+// NSHAPE plus the wavefronts of an LDS tile.
+void pack_shapes(int prec, int nv, int* wshape, int* oshape) {
+  *wshape = prec == CC3_FP64 || (prec == CC3_FP32 && fp32_wave_tiles(nv))
+                ? wbuild_shape(prec, nv, true)
+                : NSHAPE + (prec == CC3_FP32 ? 8 : lp_tile_waves(nv, nv));
+  *oshape = pick_shape(nv, nv + 1, true);
+}
+
 void pack_items(PackJob& j, int prec, unsigned (&items)[PK_N]) {
   const int no = j.no, nv = j.nv, nt = j.ntri;
-  items[PK_W] = prec == CC3_FP64 ? wbuild_wgs(nv, nt, j.wshape) : wbuild_lp_wgs(nv, nt);
+  items[PK_W] = prec == CC3_FP64 || (prec == CC3_FP32 && j.wshape < NSHAPE)
+                    ? wbuild_wgs(nv, nt, j.wshape)
+                    : wbuild_lp_wgs(prec, nv, nt, j.wshape - NSHAPE);
   const int nb = (nv + MT - 1) / MT;
   items[PK_MIX] = (unsigned)(nb * (nb + 1) * (nb + 2) / 6) * nt;
   items[PK_OMEGA] = omega_wgs(nv, nt, j.nch, j.oshape);
@@ -1798,21 +1900,31 @@ void launch_packed_step(const PackJob* dev_jobs, const PackJob* host_jobs, int n
     max_no = std::max(max_no, host_jobs[r].no);
   }
   const dim3 gmix(pack_grid(total[PK_MIX], 4096));
-  if (prec == CC3_FP64) {
+  if (host_jobs[0].wshape < NSHAPE) {
+    const dim3 gw(pack_grid(total[PK_W], 4096));
     with_shape(host_jobs[0].wshape, [&](auto fm, auto fn) {
-      hipLaunchKernelGGL((k_pack_wbuild<decltype(fm)::value, decltype(fn)::value>),
-                         dim3(pack_grid(total[PK_W], 4096)), dim3(WNT), 0, st, dev_jobs, njobs,
-                         total[PK_W]);
+      constexpr int FM = decltype(fm)::value, FN = decltype(fn)::value;
+      if constexpr (FM * FN != 20 && FM * FN != 10) {  // see pick_shape
+        if (prec == CC3_FP64)
+          hipLaunchKernelGGL((k_pack_wbuild<double, FM, FN>), gw, dim3(WNT), 0, st, dev_jobs, njobs,
+                             total[PK_W]);
+        else if constexpr (FM * FN <= 12)
+          hipLaunchKernelGGL((k_pack_wbuild<float, FM, FN>), gw, dim3(WNT), 0, st, dev_jobs, njobs,
+                             total[PK_W]);
+      }
     });
-    hipLaunchKernelGGL(k_pack_mix<true>, gmix, dim3(512), 0, st, dev_jobs, njobs, total[PK_MIX]);
   } else {
-    launch_wbuild_lp_packed(dev_jobs, njobs, total[PK_W], prec, st);
-    hipLaunchKernelGGL(k_pack_mix<false>, gmix, dim3(512), 0, st, dev_jobs, njobs, total[PK_MIX]);
+    launch_wbuild_lp_packed(dev_jobs, njobs, total[PK_W], prec, host_jobs[0].wshape - NSHAPE, st);
   }
+  if (two_planes(prec))
+    hipLaunchKernelGGL(k_pack_mix<true>, gmix, dim3(512), 0, st, dev_jobs, njobs, total[PK_MIX]);
+  else
+    hipLaunchKernelGGL(k_pack_mix<false>, gmix, dim3(512), 0, st, dev_jobs, njobs, total[PK_MIX]);
   with_shape(host_jobs[0].oshape, [&](auto fm, auto fn) {
-    hipLaunchKernelGGL((k_pack_omega<decltype(fm)::value, decltype(fn)::value>),
-                       dim3(pack_grid(total[PK_OMEGA], 4096)), dim3(WNT), 0, st, dev_jobs, njobs,
-                       total[PK_OMEGA]);
+    constexpr int FM = decltype(fm)::value, FN = decltype(fn)::value;
+    if constexpr (FM * FN != 20 && FM * FN != 10)
+      hipLaunchKernelGGL((k_pack_omega<FM, FN>), dim3(pack_grid(total[PK_OMEGA], 4096)), dim3(WNT),
+                         0, st, dev_jobs, njobs, total[PK_OMEGA]);
   });
   const dim3 goo(pack_grid(total[PK_OO], 8192));
   if (max_no <= 16)

@@ -5,8 +5,8 @@
 //                products hi*hi + hi*lo + lo*hi;
 //   CC3_BF16X6 : 3-piece split x = hi + mid + lo, products hi*hi + hi*mid +
 //                mid*hi + hi*lo + mid*mid + lo*hi.
-// Each W term is accumulated in FP32 over its K range; the two terms of a plane
-// are converted and summed in FP64 and the plane is stored in FP64, so the
+// FP32 and BF16x6 convert every 32-k partial sum and add it in FP64, BF16x3 each term
+// after its whole K range; the planes are stored in FP64, so the
 // permutation sum, the denominator division, the contravariant combination
 // and the Omega accumulation downstream stay FP64.
 //
@@ -22,6 +22,7 @@
 #include "cc3.h"
 #include "cc3_device.hpp"
 #include "cc3_internal.hpp"
+#include "cc3_wplanes.hpp"
 
 namespace cc3 {
 
@@ -37,12 +38,13 @@ __host__ __device__ inline int kpad(int k) { return (k + 31) / 32 * 32; }
 // Operand conversion: FP64 value -> pieces
 // ---------------------------------------------------------------------------
 // Generic re-layout: out[piece][outer][x][kk] (kk < K padded) from an FP64
-// source element (outer, x, k) at src[outer * so + x * sx + k * sk] * sign.
+// source element (outer, x, k) at src[outer * so + x * sx + k * sk] * sign; `slab`: elements
+// of the copy between outer indices.
 // `piece_stride` is the element distance between pieces of the whole array.
 template <int MODE>  // 0: FP32, 2: BF16 2-piece, 3: BF16 3-piece
 __global__ void k_lp_copy(const double* __restrict__ src, int64_t so, int64_t sx, int64_t sk,
-                          double sign, int nouter, int nx, int K, void* __restrict__ dst,
-                          int64_t piece_stride) {
+                          double sign, int nouter, int nx, int K, int64_t slab,
+                          void* __restrict__ dst, int64_t piece_stride) {
   const int Kp = kpad(K);
   const int64_t n = (int64_t)nouter * nx * Kp;
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -51,14 +53,15 @@ __global__ void k_lp_copy(const double* __restrict__ src, int64_t so, int64_t sx
   const int x = (int)((e / Kp) % nx);
   const int64_t o = e / ((int64_t)Kp * nx);
   const double v = (kk < K) ? sign * src[o * so + (int64_t)x * sx + (int64_t)kk * sk] : 0.0;
+  const int64_t at = o * slab + (int64_t)x * Kp + kk;
   if constexpr (MODE == 0) {
-    ((float*)dst)[e] = (float)v;
+    ((float*)dst)[at] = (float)v;
   } else {
     constexpr int P = MODE;
     uint16_t pc[P];
     split_bf16<P>(v, pc);
 #pragma unroll
-    for (int i = 0; i < P; ++i) ((uint16_t*)dst)[i * piece_stride + e] = pc[i];
+    for (int i = 0; i < P; ++i) ((uint16_t*)dst)[i * piece_stride + at] = pc[i];
   }
 }
 
@@ -67,8 +70,9 @@ static int mode_of(int prec) { return prec == CC3_FP32 ? 0 : prec == CC3_BF16X3 
 size_t lp_operand_bytes(int prec, int no, int nv) {
   if (prec == CC3_FP64) return 0;
   const size_t o = no, v = nv, dk = kpad(nv), lk = kpad(no);
-  const size_t elems = o * o * v * dk + o * v * v * lk + o * v * v * dk + o * o * v * lk;
   const size_t esz = prec == CC3_FP32 ? 4 : 2;
+  const size_t gs = lp_slab(nv, nv, (int)esz), ns = lp_slab(nv, no, (int)esz);
+  const size_t elems = o * o * v * dk + o * v * ns + o * v * gs + o * o * v * lk;
   const size_t pieces = prec == CC3_FP32 ? 1 : prec == CC3_BF16X3 ? 2 : 3;
   return elems * esz * pieces + 4 * 256;
 }
@@ -77,24 +81,25 @@ void lp_operand_ptrs(int prec, int no, int nv, void* base, LpOperands& lp) {
   const size_t o = no, v = nv, dk = kpad(nv), lk = kpad(no);
   const size_t esz = prec == CC3_FP32 ? 4 : 2;
   const size_t pieces = prec == CC3_FP32 ? 1 : prec == CC3_BF16X3 ? 2 : 3;
+  const size_t gs = lp_slab(nv, nv, (int)esz), ns = lp_slab(nv, no, (int)esz);
   auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
   char* b = (char*)base;
   lp.t2 = b;
   b += al(o * o * v * dk * esz * pieces);
   lp.t2N = b;
-  b += al(o * v * v * lk * esz * pieces);
+  b += al(o * v * ns * esz * pieces);
   lp.GwT = b;
-  b += al(o * v * v * dk * esz * pieces);
+  b += al(o * v * gs * esz * pieces);
   lp.GoT = b;
   lp.prec = prec;
 }
 
 template <int MODE>
 static void lp_copy(const double* src, int64_t so, int64_t sx, int64_t sk, double sign, int nouter,
-                    int nx, int K, void* dst, int64_t piece_stride, hipStream_t st) {
+                    int nx, int K, int64_t slab, void* dst, int64_t piece_stride, hipStream_t st) {
   const int64_t n = (int64_t)nouter * nx * kpad(K);
   hipLaunchKernelGGL(k_lp_copy<MODE>, dim3(nblk(n, 256)), dim3(256), 0, st, src, so, sx, sk, sign,
-                     nouter, nx, K, dst, piece_stride);
+                     nouter, nx, K, slab, dst, piece_stride);
 }
 
 void launch_lp_convert(const double* t2, const Blocks& b, int no, int nv, const LpOperands& lp,
@@ -103,16 +108,18 @@ void launch_lp_convert(const double* t2, const Blocks& b, int no, int nv, const 
   auto run = [&](auto mode_tag) {
     constexpr int M = decltype(mode_tag)::value;
     constexpr int64_t esz = (M == 0 ? 4 : 2);
+    const int64_t gs = lp_slab(nv, nv, (int)esz), ns = lp_slab(nv, no, (int)esz);
     // t2L[p][q][x][d] = t2[p][q][x][d]
-    lp_copy<M>(t2, v * v, v, 1, 1.0, no * no, nv, nv, lp.t2, o * o * v * dk, st);
+    lp_copy<M>(t2, v * v, v, 1, 1.0, no * no, nv, nv, v * dk, lp.t2, o * o * v * dk, st);
     // t2NL[p][y][x][l] = -t2[p][l][x][y]: for each p, outer = y, x = x, k = l
     for (int p = 0; p < no; ++p)
-      lp_copy<M>(t2 + (int64_t)p * o * v * v, 1, v, v * v, -1.0, nv, nv, no,
-                 (char*)lp.t2N + (size_t)p * v * v * lk * esz, o * v * v * lk, st);
+      lp_copy<M>(t2 + (int64_t)p * o * v * v, 1, v, v * v, -1.0, nv, nv, no, ns,
+                 (char*)lp.t2N + (size_t)p * v * ns * esz, o * v * ns, st);
     // GwTL[r][y][z][d] = Gw[r][y][z][d]: outer = (r, y), x = z, k = d
-    lp_copy<M>(b.Gw, gw_pitch(nv), v, 1, 1.0, no * nv, nv, nv, lp.GwT, o * v * v * dk, st);
+    lp_copy<M>(b.Gw, gw_pitch(nv), v, 1, 1.0, no * nv, nv, nv, gs, lp.GwT, o * v * gs,
+               st);
     // GoTL[q][r][z][l] = Go[q][r][z][l]: outer = (q, r), x = z, k = l
-    lp_copy<M>(b.Go, o * v, o, 1, 1.0, no * no, nv, no, lp.GoT, o * o * v * lk, st);
+    lp_copy<M>(b.Go, o * v, o, 1, 1.0, no * no, nv, no, v * lk, lp.GoT, o * o * v * lk, st);
   };
   const int m = mode_of(lp.prec);
   if (m == 0) run(std::integral_constant<int, 0>());
@@ -123,10 +130,15 @@ void launch_lp_convert(const double* t2, const Blocks& b, int no, int nv, const 
 // ---------------------------------------------------------------------------
 // W build in low precision
 // ---------------------------------------------------------------------------
-// 8 wavefronts as 4 (rows) x 2 (columns), each 32 x 64 outputs (2 x 4 blocks).
-constexpr int LWM = 4, LWN = 2, LFM = 2, LFN = 4;
-constexpr int LNT = 64 * LWM * LWN;
-constexpr int LBM = 16 * LWM * LFM, LBN = 16 * LWN * LFN;  // 128 x 128
+// Tiles of 16 NW x 16 NW outputs on NW wavefronts (4 to 8), each FM x FN blocks of 16 x 16.
+// The edge that pads nv least is taken (lp_tile_waves).
+template <int NW>
+struct LpGeo {
+  static constexpr int WM = NW == 8 ? 4 : NW == 6 ? 3 : NW == 4 ? 2 : NW;
+  static constexpr int WN = NW / WM, FM = NW / WM, FN = NW / WN;
+  static constexpr int NT = 64 * NW, BM = 16 * NW;
+  static_assert(WM * FM == NW && WN * FN == NW, "square tile");
+};
 
 // Engine traits.  FLUSH: each LDS stage (32 k) is accumulated in FP32 from zero
 // and then added into an FP64 accumulator, so the FP32 rounding of the MFMA
@@ -134,21 +146,24 @@ constexpr int LBM = 16 * LWM * LFM, LBN = 16 * LWN * LFN;  // 128 x 128
 // the whole K range.  Used where the split is fine enough for that rounding to
 // dominate the error (FP32 and the 3-piece BF16 split); the 2-piece split is
 // limited by its operands and keeps one FP32 accumulator per term.
-// MINW: waves per SIMD the W kernel is built for (4: two workgroups per CU).
-// NS: LDS stage buffers of the ring (NS - 1 stages of loads in flight).
+// MINW: waves per SIMD the W kernel is built for (4: two workgroups of 8 wavefronts per CU).
+// ns: LDS stage buffers of the ring (ns - 1 stages of loads in flight): two where they let
+// two workgroups share a CU (BF16x6 on 6 wavefronts, nv = 187: 70.4 -> 69.5 ms a call).
 struct EngF32 {
   static constexpr int BK = 32, P = 1, NPROD = 1, ESZ = 4;
   static constexpr bool FLUSH = true;
-  static constexpr int MINW = 4, NS = 2;
+  static constexpr int MINW = 4;
+  static constexpr int ns(int) { return 2; }
 };
 template <int P_>
 struct EngBF16 {
   static constexpr int BK = 32, P = P_, NPROD = (P_ == 2 ? 3 : 6), ESZ = 2;
   static constexpr bool FLUSH = (P_ == 3);
-  static constexpr int MINW = (P_ == 2 ? 4 : 2), NS = (P_ == 2 ? 2 : 3);
+  static constexpr int MINW = (P_ == 2 ? 4 : 2);
+  static constexpr int ns(int nw) { return P_ == 2 || nw <= 6 ? 2 : 3; }
 };
 
-// the piece pairs of the split products
+// the piece pairs of the split products, in the order of their sum
 __device__ inline void prod_pair(int P, int t, int& pa, int& pb) {
   if (P == 2) {
     const int a[3] = {0, 0, 1}, b[3] = {0, 1, 0};
@@ -162,27 +177,28 @@ __device__ inline void prod_pair(int P, int t, int& pa, int& pb) {
 // ---------------------------------------------------------------------------
 // The tile engine.  Operands are row-major (row, k) with k contiguous and
 // zero-padded to a multiple of 32, in P pieces.  A stage holds 32 k of the
-// 128 A rows and 128 B rows of every piece.  It goes from global memory to LDS
+// A rows and B rows of the tile, every piece.  It goes from global memory to LDS
 // directly: a buffer load with the LDS flag writes 16 bytes per lane at
 // consecutive LDS addresses (1 KB per instruction), so the tile needs no
 // staging registers and no LDS stores.  Each LDS row holds the RB bytes of one
 // row and one stage as 16-byte chunks, XOR-swizzled by the row (lp_chunk) so
 // that the 16 rows of one fragment read fall in different banks; the lane that
-// fills LDS slot s loads the global chunk that the swizzle puts there.  Two
-// stage buffers, one barrier per stage: the loads of stage s + 1 are issued
-// before the MFMAs of stage s and waited for after them.
+// fills LDS slot s loads the global chunk that the swizzle puts there.  A ring of NS
+// stage buffers, one barrier per stage: the loads of stage s + NS - 1 are issued
+// before the MFMAs of stage s.
 // ---------------------------------------------------------------------------
-template <class E>
-struct LpTile {
+template <class E, int NW>
+struct LpTile : LpGeo<NW> {
+  typedef LpGeo<NW> G;
   static constexpr int P = E::P, ESZ = E::ESZ;
   static constexpr int RB = E::BK * ESZ;         // bytes of one row in one stage
   static constexpr int CPR = RB / 16;            // 16-byte chunks per row (8 or 4)
-  static constexpr int TILEB = LBM * RB;         // one operand piece of one stage
-  static constexpr int NI = TILEB / (LNT * 16);  // loads per lane per operand piece
+  static constexpr int TILEB = G::BM * RB;       // one operand piece of one stage
+  static constexpr int NI = RB / 64;             // loads per lane per operand piece
   static constexpr int STAGEB = 2 * P * TILEB;
-  static constexpr int NS = E::NS;               // stage buffers
+  static constexpr int NS = E::ns(NW);               // stage buffers
   static constexpr int LPS = 2 * P * NI;         // direct loads per lane per stage
-  static_assert(LBM == LBN && NI * LNT * 16 == TILEB, "tile shape");
+  static_assert(NI * G::NT * 16 == TILEB, "tile shape");
   static_assert(NS >= 2 && (NS - 2) * LPS <= 63, "vmcnt range");
 };
 
@@ -192,7 +208,7 @@ struct LpTile {
 // for 64-byte rows, or no swizzle, gives two-way conflicts.
 template <class E>
 __device__ inline int lp_chunk(int row, int c) {
-  if constexpr (LpTile<E>::CPR == 8) return c ^ ((row >> 1) & 7);
+  if constexpr (E::BK * E::ESZ == 128) return c ^ ((row >> 1) & 7);
   else return c ^ ((row >> 1) & 3);
 }
 
@@ -208,16 +224,16 @@ struct LpSeg {
 };
 
 // The rows this lane loads: for load i of an operand piece, LDS slot
-// s = (8 i + wave) 64 + lane holds row s / CPR and the swizzled chunk of s % CPR.
-template <class E>
+// s = (NW i + wave) 64 + lane holds row s / CPR and the swizzled chunk of s % CPR.
+template <class E, int NW>
 struct LpLanes {
-  int row[LpTile<E>::NI];
-  unsigned cb[LpTile<E>::NI];  // byte offset of the chunk within the row's stage
+  int row[LpTile<E, NW>::NI];
+  unsigned cb[LpTile<E, NW>::NI];  // byte offset of the chunk within the row's stage
   __device__ LpLanes(int wave, int lane) {
-    typedef LpTile<E> L;
+    typedef LpTile<E, NW> L;
 #pragma unroll
     for (int i = 0; i < L::NI; ++i) {
-      const int s = (8 * i + wave) * 64 + lane;
+      const int s = (NW * i + wave) * 64 + lane;
       row[i] = s / L::CPR;
       cb[i] = (unsigned)lp_chunk<E>(row[i], s % L::CPR) * 16u;
     }
@@ -226,19 +242,19 @@ struct LpLanes {
 
 // Issue the direct loads of stage `st` of segment `sg` into the stage buffer
 // `buf`; ar / br: this lane's A and B row indices (already mapped to operand rows)
-template <class E>
+template <class E, int NW>
 __device__ __forceinline__ void lp_load_stage(const LpSeg& sg, int st, char* buf,
                                               const unsigned* cb, const int* ar, const int* br,
                                               int wave) {
-  typedef LpTile<E> L;
+  typedef LpTile<E, NW> L;
   const int64_t ko = (int64_t)st * L::RB;
 #pragma unroll
   for (int pc = 0; pc < L::P; ++pc) {
     const BufRsrc ra = buf_rsrc(sg.a + pc * sg.aps + ko), rb = buf_rsrc(sg.b + pc * sg.bps + ko);
 #pragma unroll
     for (int i = 0; i < L::NI; ++i) {
-      char* la = buf + pc * L::TILEB + (8 * i + wave) * 1024;
-      char* lb = buf + (L::P + pc) * L::TILEB + (8 * i + wave) * 1024;
+      char* la = buf + pc * L::TILEB + (NW * i + wave) * 1024;
+      char* lb = buf + (L::P + pc) * L::TILEB + (NW * i + wave) * 1024;
       __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_ptr_t)la, 16,
                                                (unsigned)ar[i] * sg.ars + cb[i], 0, 0, 0);
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_ptr_t)lb, 16,
@@ -255,9 +271,9 @@ template <int N>
 __device__ __forceinline__ void lp_vmcnt() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
-template <class E>
+template <class E, int NW>
 __device__ __forceinline__ void lp_stage_ready(int later) {
-  typedef LpTile<E> L;
+  typedef LpTile<E, NW> L;
   if constexpr (L::NS >= 3) {
     if (later >= 1) {
       if constexpr (L::NS >= 4) {
@@ -281,10 +297,13 @@ __device__ __forceinline__ void lp_stage_ready(int later) {
 // lane reads chunk 4 h + l/16 (four consecutive k) of its row and supplies its
 // element j to the k-step (h, j) of the 16x16x4 MFMA; A and B use the same k
 // assignment, so the eight k-steps cover the stage's 32 k once each.
-template <class E>
-__device__ __forceinline__ void lp_mfma_stage(const char* buf, f4v (&acc)[LFM][LFN], int lane,
+// SWAP: A and B change places in the order of the piece products.
+template <class E, int NW, bool SWAP = false>
+__device__ __forceinline__ void lp_mfma_stage(const char* buf,
+                                              f4v (&acc)[LpGeo<NW>::FM][LpGeo<NW>::FN], int lane,
                                               int wm, int wn) {
-  typedef LpTile<E> L;
+  typedef LpTile<E, NW> L;
+  constexpr int LFM = L::FM, LFN = L::FN;
   const int g = lane >> 4, r16 = lane & 15;
   // Fragment rows are 16 R + r16, and lp_chunk's XOR depends on bits 1-3 of the row
   // only, that is on r16: the lane's byte offset within a fragment's rows is one value
@@ -327,7 +346,8 @@ __device__ __forceinline__ void lp_mfma_stage(const char* buf, f4v (&acc)[LFM][L
 #pragma unroll
     for (int t = 0; t < E::NPROD; ++t) {
       int pa, pb;
-      prod_pair(L::P, t, pa, pb);
+      if constexpr (SWAP) prod_pair(L::P, t, pb, pa);
+      else prod_pair(L::P, t, pa, pb);
 #pragma unroll
       for (int fm = 0; fm < LFM; ++fm)
 #pragma unroll
@@ -337,17 +357,19 @@ __device__ __forceinline__ void lp_mfma_stage(const char* buf, f4v (&acc)[LFM][L
   }
 }
 
-__device__ __forceinline__ void lp_zero(f4v (&acc)[LFM][LFN]) {
+template <int FM, int FN>
+__device__ __forceinline__ void lp_zero(f4v (&acc)[FM][FN]) {
 #pragma unroll
-  for (int fm = 0; fm < LFM; ++fm)
+  for (int fm = 0; fm < FM; ++fm)
 #pragma unroll
-    for (int fn = 0; fn < LFN; ++fn) acc[fm][fn] = f4v{0.f, 0.f, 0.f, 0.f};
+    for (int fn = 0; fn < FN; ++fn) acc[fm][fn] = f4v{0.f, 0.f, 0.f, 0.f};
 }
-__device__ __forceinline__ void lp_flush(f4v (&acc)[LFM][LFN], d4v (&accd)[LFM][LFN]) {
+template <int FM, int FN>
+__device__ __forceinline__ void lp_flush(f4v (&acc)[FM][FN], d4v (&accd)[FM][FN]) {
 #pragma unroll
-  for (int fm = 0; fm < LFM; ++fm)
+  for (int fm = 0; fm < FM; ++fm)
 #pragma unroll
-    for (int fn = 0; fn < LFN; ++fn) {
+    for (int fn = 0; fn < FN; ++fn) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) accd[fm][fn][r] += (double)acc[fm][fn][r];
       acc[fm][fn] = f4v{0.f, 0.f, 0.f, 0.f};
@@ -357,86 +379,83 @@ __device__ __forceinline__ void lp_flush(f4v (&acc)[LFM][LFN], d4v (&accd)[LFM][
 // ---------------------------------------------------------------------------
 // W build in low precision
 // ---------------------------------------------------------------------------
-// Issue the loads of stage t of the plane (its four K segments in turn) into buf.
-// The segments are passed by value and each call site names one of them, so that they
-// stay in scalar registers.
-template <class E>
-__device__ __forceinline__ void wlp_load(int t, char* buf, const LpSeg s0, const LpSeg s1,
-                                         const LpSeg s2, const LpSeg s3, const unsigned* cb,
-                                         const int* ar, const int* br, int wave) {
-  if (t < s0.nst) { lp_load_stage<E>(s0, t, buf, cb, ar, br, wave); return; }
-  t -= s0.nst;
-  if (t < s1.nst) { lp_load_stage<E>(s1, t, buf, cb, ar, br, wave); return; }
-  t -= s1.nst;
-  if (t < s2.nst) { lp_load_stage<E>(s2, t, buf, cb, ar, br, wave); return; }
-  t -= s2.nst;
-  lp_load_stage<E>(s3, t, buf, cb, ar, br, wave);
-}
-
-// Stages [sb, se) of the plane's nsteps into acc (with FLUSH into accd), the loads
-// running NS - 1 stages ahead in the ring of NS stage buffers.
-template <class E>
-__device__ __forceinline__ void wlp_run(int sb, int se, int nsteps, char* lds, const LpSeg s0,
-                                        const LpSeg s1, const LpSeg s2, const LpSeg s3,
-                                        const unsigned* cb, const int* ar, const int* br,
-                                        int wave, int lane, int wm, int wn,
-                                        f4v (&acc)[LFM][LFN], d4v (&accd)[LFM][LFN]) {
-  typedef LpTile<E> L;
-  for (int s = sb; s < se; ++s) {
-    lp_stage_ready<E>(min(L::NS - 2, nsteps - 1 - s));
-    const int ahead = s + L::NS - 1;
-    if (ahead < nsteps)
-      wlp_load<E>(ahead, lds + (ahead % L::NS) * L::STAGEB, s0, s1, s2, s3, cb, ar, br, wave);
-    lp_mfma_stage<E>(lds + (s % L::NS) * L::STAGEB, acc, lane, wm, wn);
-    if constexpr (E::FLUSH) lp_flush(acc, accd);
-  }
-}
-
-template <class E>
+// One workgroup per (triple, plane, y, tile).  Bound by the MFMAs (BF16x6: 0.76 of 1.34
+// PFLOP/s at nv = 187) and, BF16x3, by the planes that it stores (at nv = 210 8 triples are
+// 1.8 GB, 0.41 of the 1.0 ms).  FP32 and BF16x6 add every stage into FP64, so
+// the order of their segments is free and they build the two planes of the FP64 form; the
+// running FP32 sum of BF16x3 goes over the d sum and then the l sum of a term, which keeps
+// those together and needs the three planes.  (Segments: cc3_wplanes.hpp.)  The pieces of a
+// product are paired in one order per permutation in both (wseg_swap), so the FP32 sums of a
+// stage do not depend on the planes.
+template <class E, int NW>
 __device__ __forceinline__ void wbuild_lp_body(
     const char* __restrict__ t2L, const char* __restrict__ t2NL, const char* __restrict__ GwTL,
     const char* __restrict__ GoTL, const int* __restrict__ tri, double* __restrict__ cubes, int no,
-    int nv, int tiles_m, int tiles_n, int all_terms, int bx, int by, int bz) {
-  typedef LpTile<E> L;
-  constexpr int ESZ = E::ESZ;
+    int nv, int tiles, int all_terms, int bx, int by, int bz) {
+  typedef LpTile<E, NW> L;
+  constexpr int ESZ = E::ESZ, FM = L::FM, FN = L::FN;
+  constexpr bool TWO = E::FLUSH;
   __shared__ __attribute__((aligned(16))) char lds[L::NS * L::STAGEB];
-  const int tpp = tiles_m * tiles_n;
-  const int y = bx / tpp;
-  const int tile = bx % tpp;
-  const int m0 = (tile / tiles_n) * LBM, n0 = (tile % tiles_n) * LBN;
+  const int y = bx / (tiles * tiles);
+  const int tile = bx % (tiles * tiles);
+  const int m0 = (tile / tiles) * L::BM, n0 = (tile % tiles) * L::BM;
   const int plane = by;
   const int z = bz;
   const int i = tri[3 * z], j = tri[3 * z + 1], k = tri[3 * z + 2];
-  int kind = (i == j) ? 1 : (j == k) ? 2 : 0;
-  if (all_terms) kind = 0;
-  if ((kind == 1 && plane == 1) || (kind == 2 && plane == 2)) return;
-  const bool two = (kind == 0) || plane == 0;
-  int p1, q1, r1, p2, q2, r2;
-  if (plane == 0) { p1 = i; q1 = j; r1 = k; p2 = k; q2 = j; r2 = i; }
-  else if (plane == 1) { p1 = j; q1 = i; r1 = k; p2 = k; q2 = i; r2 = j; }
-  else { p1 = i; q1 = k; r1 = j; p2 = j; q2 = k; r2 = i; }
-
+  const int kind = all_terms ? TRI_DISTINCT : tri_kind(i, j, k);
+  if (TWO ? kind != TRI_DISTINCT && plane == 1
+          : (kind == TRI_IJ && plane == 1) || (kind == TRI_JK && plane == 2))
+    return;
+  const bool two = kind == TRI_DISTINCT || plane == 0;  // three planes: both terms
+  const uint64_t segs = TWO ? wplane_segs(plane, kind) : kSegs3[plane];
   const int64_t dk = kpad(nv), lk = kpad(no), v = nv, o = no;
-  // piece strides (bytes) of the four arrays
-  const int64_t ps_t2 = o * o * v * dk * ESZ, ps_t2N = o * v * v * lk * ESZ,
-                ps_Gw = o * v * v * dk * ESZ, ps_Go = o * o * v * lk * ESZ;
-  const unsigned rv = (unsigned)(dk * ESZ), ro = (unsigned)(lk * ESZ);
-  // segments: term 1 vv, term 1 oo, term 2 vv, term 2 oo (rows m for A, n for B)
-  // segments: term 1 vv, term 1 oo, term 2 vv, term 2 oo (rows m for A, n for B)
-  const LpSeg sg0 = {t2L + ((p1 * o + q1) * v) * dk * ESZ, GwTL + ((r1 * v + y) * v) * dk * ESZ,
-                     ps_t2, ps_Gw, rv, rv, (int)(dk / 32)};
-  const LpSeg sg1 = {t2NL + ((p1 * v + y) * v) * lk * ESZ, GoTL + ((q1 * o + r1) * v) * lk * ESZ,
-                     ps_t2N, ps_Go, ro, ro, (int)(lk / 32)};
-  const LpSeg sg2 = {GwTL + ((r2 * v + y) * v) * dk * ESZ, t2L + ((p2 * o + q2) * v) * dk * ESZ,
-                     ps_Gw, ps_t2, rv, rv, (int)(dk / 32)};
-  const LpSeg sg3 = {GoTL + ((q2 * o + r2) * v) * lk * ESZ, t2NL + ((p2 * v + y) * v) * lk * ESZ,
-                     ps_Go, ps_t2N, ro, ro, (int)(lk / 32)};
+  const int64_t gy = lp_slab(nv, nv, ESZ), ty = lp_slab(nv, no, ESZ);
+  const int sv = (int)(dk / 32), so = (int)(lk / 32);  // stages of a d sum and of an l sum
+  int nsteps;
+  if (TWO) nsteps = wplane_dsums(plane, kind) * sv + 3 * so;
+  else nsteps = (two ? 2 : 1) * (sv + so);
+  // the segment being loaded and its next stage
+  LpSeg sg;
+  int seg = 0, st = 0;
+  auto open = [&](int s) {
+    const int code = (int)(segs >> (6 * s)) & 63;
+    const bool lsum = code & 8, col = code & 16, strided = code & 32;
+    int p, q, r;
+    perm_pqr(code & 7, i, j, k, p, q, r);
+    const char *amp, *in;
+    int64_t ap, ip;   // piece strides (bytes)
+    unsigned ar, ir;  // row strides (bytes)
+    if (!lsum) {
+      amp = t2L + (p * o + q) * v * dk * ESZ;
+      ap = o * o * v * dk * ESZ;
+      ar = (unsigned)(dk * ESZ);
+      in = GwTL + (r * v * gy + (strided ? y * dk : y * gy)) * ESZ;
+      ip = o * v * gy * ESZ;
+      ir = (unsigned)((strided ? gy : dk) * ESZ);
+      sg.nst = sv;
+    } else {
+      amp = t2NL + (p * v * ty + (strided ? y * lk : y * ty)) * ESZ;
+      ap = o * v * ty * ESZ;
+      ar = (unsigned)((strided ? ty : lk) * ESZ);
+      in = GoTL + (q * o + r) * v * lk * ESZ;
+      ip = o * o * v * lk * ESZ;
+      ir = (unsigned)(lk * ESZ);
+      sg.nst = so;
+    }
+    sg.a = col ? in : amp;
+    sg.b = col ? amp : in;
+    sg.aps = col ? ip : ap;
+    sg.bps = col ? ap : ip;
+    sg.ars = col ? ir : ar;
+    sg.brs = col ? ar : ir;
+    st = 0;
+  };
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave % LWM, wn = wave / LWM;
-  const LpLanes<E> ln(wave, lane);
+  const int wm = wave % L::WM, wn = wave / L::WM;
+  const LpLanes<E, NW> ln(wave, lane);
   // rows past nv repeat row nv - 1 (their outputs are never stored)
   int ar[L::NI], br[L::NI];
 #pragma unroll
@@ -444,53 +463,97 @@ __device__ __forceinline__ void wbuild_lp_body(
     ar[e] = min(m0 + ln.row[e], nv - 1);
     br[e] = min(n0 + ln.row[e], nv - 1);
   }
-
-  // term 1 (and term 2 when the plane has two), each accumulated in FP32 (with
-  // FLUSH stage by stage into FP64); the plane value is their FP64 sum
-  f4v acc1[LFM][LFN], acc2[LFM][LFN];
-  d4v accd[LFM][LFN];
+  auto load = [&](int t) {  // stage t of the plane, in order
+    lp_load_stage<E, NW>(sg, st, lds + (t % L::NS) * L::STAGEB, ln.cb, ar, br, wave);
+    if (++st == sg.nst && t + 1 < nsteps) open(++seg);
+  };
+  f4v acc1[FM][FN], acc2[FM][FN];
+  d4v accd[FM][FN];
   lp_zero(acc1);
   lp_zero(acc2);
 #pragma unroll
-  for (int fm = 0; fm < LFM; ++fm)
+  for (int fm = 0; fm < FM; ++fm)
 #pragma unroll
-    for (int fn = 0; fn < LFN; ++fn) accd[fm][fn] = d4v{0.0, 0.0, 0.0, 0.0};
-  const int nt1 = sg0.nst + sg1.nst;  // stages of one term
-  const int nsteps = two ? 2 * nt1 : nt1;
+    for (int fn = 0; fn < FN; ++fn) accd[fm][fn] = d4v{0.0, 0.0, 0.0, 0.0};
+  // stages [sb, se) into acc (with FLUSH into accd), the loads NS - 1 stages ahead
+  auto run = [&](auto swap, int sb, int se, f4v (&acc)[FM][FN]) __attribute__((always_inline)) {
+    for (int s = sb; s < se; ++s) {
+      lp_stage_ready<E, NW>(min(L::NS - 2, nsteps - 1 - s));
+      if (s + L::NS - 1 < nsteps) load(s + L::NS - 1);
+      lp_mfma_stage<E, NW, decltype(swap)::value>(lds + (s % L::NS) * L::STAGEB, acc, lane, wm, wn);
+      if constexpr (E::FLUSH) lp_flush(acc, accd);
+    }
+  };
+  open(0);
 #pragma unroll
   for (int t = 0; t < L::NS - 1; ++t)
-    if (t < nsteps) wlp_load<E>(t, lds + t * L::STAGEB, sg0, sg1, sg2, sg3, ln.cb, ar, br, wave);
-  wlp_run<E>(0, nt1, nsteps, lds, sg0, sg1, sg2, sg3, ln.cb, ar, br, wave, lane, wm, wn, acc1, accd);
-  if (two) {
-    f4v (&acc)[LFM][LFN] = E::FLUSH ? acc1 : acc2;
-    wlp_run<E>(nt1, nsteps, nsteps, lds, sg0, sg1, sg2, sg3, ln.cb, ar, br, wave, lane, wm, wn,
-               acc, accd);
+    if (t < nsteps) load(t);
+  if constexpr (!TWO) {  // term 1, then term 2 in an accumulator of its own
+    run(std::false_type(), 0, sv + so, acc1);
+    if (two) run(std::false_type(), sv + so, nsteps, acc2);
+  } else if constexpr (L::P == 1) {
+    run(std::false_type(), 0, nsteps, acc1);
+  } else {
+    const int nd = wplane_dsums(plane, kind);
+    for (int g = 0, s = 0; g < nd + 3; ++g) {
+      const int se = s + (g < nd ? sv : so);
+      if (wseg_swap((int)(segs >> (6 * g)) & 63, kind)) run(std::true_type(), s, se, acc1);
+      else run(std::false_type(), s, se, acc1);
+      s = se;
+    }
   }
 
   // the FP32/BF16 MFMA leaves D[row = 4 (lane/16) + r][col = lane%16] in register r
-  // the padded rows of the triple loop's cubes
   const int64_t rp = cube_pitch(nv);
   double* dst = cubes + ((int64_t)z * 5 + plane) * cube_slot(nv) + (int64_t)y * nv * rp;
 #pragma unroll
-  for (int fm = 0; fm < LFM; ++fm)
+  for (int fm = 0; fm < FM; ++fm)
 #pragma unroll
-    for (int fn = 0; fn < LFN; ++fn)
+    for (int fn = 0; fn < FN; ++fn)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int m = m0 + (wm * LFM + fm) * 16 + 4 * (lane >> 4) + r;
-        const int n = n0 + (wn * LFN + fn) * 16 + (lane & 15);
+        const int m = m0 + (wm * FM + fm) * 16 + 4 * (lane >> 4) + r;
+        const int n = n0 + (wn * FN + fn) * 16 + (lane & 15);
         if (m < nv && n < nv)
           dst[(int64_t)m * rp + n] = accd[fm][fn][r] + ((double)acc1[fm][fn][r] + (double)acc2[fm][fn][r]);
       }
 }
 
-template <class E>
-__global__ __launch_bounds__(LNT, E::MINW) void k_wbuild_lp(
+template <class E, int NW>
+__global__ __launch_bounds__(LpGeo<NW>::NT, E::MINW) void k_wbuild_lp(
     const char* __restrict__ t2L, const char* __restrict__ t2NL, const char* __restrict__ GwTL,
     const char* __restrict__ GoTL, const int* __restrict__ tri, double* __restrict__ cubes, int no,
-    int nv, int tiles_m, int tiles_n, int all_terms) {
-  wbuild_lp_body<E>(t2L, t2NL, GwTL, GoTL, tri, cubes, no, nv, tiles_m, tiles_n, all_terms,
-                    blockIdx.x, blockIdx.y, blockIdx.z);
+    int nv, int tiles, int all_terms) {
+  wbuild_lp_body<E, NW>(t2L, t2NL, GwTL, GoTL, tri, cubes, no, nv, tiles, all_terms, blockIdx.x,
+                        blockIdx.y, blockIdx.z);
+}
+
+// Wavefronts (tile edge 16 NW) that cover an M x N product with the least work: the outputs
+// computed, padding included, with the operand rows loaded per output (1 / edge) on top.
+// MEASURED, whole calls of 9 occupied orbitals at NW = 4 / 5 / 6 / 7 / 8 (the rule's choice
+// is the fastest in each): BF16x6, nv = 112: 13.1 / 16.0 / 16.9 / 12.1 / 12.3 ms, 150: 38.8 /
+// 37.0 / 38.6 / 40.9 / 42.2, 187: 72.6 / 85.0 / 69.5 / 72.7 / 75.3, 240: 177 / 184 / 187 / 198 /
+// 168; BF16x3, 150: 36.1 / 33.7 / 34.5 / 35.8 / 36.1, 180: 62.9 / 64.6 / 59.8 / 61.4 / 63.0,
+// 210: 123 / 120 / 122 / 116 / 116.  Instead, 128 x 128 tiles whose empty blocks are skipped:
+// 73.7 ms for BF16x6 at 187, and the same as 7 wavefronts for BF16x3 at 210.
+int lp_tile_waves(int64_t M, int64_t N) {
+  int best = 8;
+  double cost = 0.0;
+  for (int nw = 8; nw >= 4; --nw) {
+    const double t = 16.0 * nw, c = (double)nblk(M, 16 * nw) * nblk(N, 16 * nw) * t * t * (1.0 + 64.0 / t);
+    if (nw == 8 || c < cost) { best = nw; cost = c; }
+  }
+  return best;
+}
+
+// Calls f with the tile's wavefront count as an integral constant.
+template <class F>
+static void with_waves(int nw, F f) {
+  if (nw == 4) f(std::integral_constant<int, 4>());
+  else if (nw == 5) f(std::integral_constant<int, 5>());
+  else if (nw == 6) f(std::integral_constant<int, 6>());
+  else if (nw == 7) f(std::integral_constant<int, 7>());
+  else f(std::integral_constant<int, 8>());
 }
 
 // ---------------------------------------------------------------------------
@@ -508,15 +571,15 @@ __global__ __launch_bounds__(LNT, E::MINW) void k_wbuild_lp(
 //     nv + q (the Omega1 row) for n >= nv.
 // Each chunk sums in FP32 on the MFMA (with FLUSH, stage by stage into FP64);
 // k_reduce sums the chunks in FP64.  The tile engine is that of k_wbuild_lp.
-template <class E>
-__global__ __launch_bounds__(LNT) void k_omega_lp(const char* __restrict__ YL,
-                                                  const char* __restrict__ GbcL,
-                                                  const char* __restrict__ GcbL,
-                                                  const int* __restrict__ tri,
-                                                  double* __restrict__ Pvv, int no, int nv,
-                                                  int nchunks, int tiles_n) {
-  typedef LpTile<E> L;
-  constexpr int ESZ = E::ESZ;
+template <class E, int NW>
+__global__ __launch_bounds__(LpGeo<NW>::NT) void k_omega_lp(const char* __restrict__ YL,
+                                                            const char* __restrict__ GbcL,
+                                                            const char* __restrict__ GcbL,
+                                                            const int* __restrict__ tri,
+                                                            double* __restrict__ Pvv, int no,
+                                                            int nv, int nchunks, int tiles_n) {
+  typedef LpTile<E, NW> L;
+  constexpr int ESZ = E::ESZ, LFM = L::FM, LFN = L::FN, LBM = L::BM, LBN = L::BM, LWM = L::WM;
   __shared__ __attribute__((aligned(16))) char lds[L::NS * L::STAGEB];
   const int pi = blockIdx.y, z = blockIdx.z;
   const int i = tri[3 * z], j = tri[3 * z + 1], k = tri[3 * z + 2];
@@ -543,7 +606,7 @@ __global__ __launch_bounds__(LNT) void k_omega_lp(const char* __restrict__ YL,
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave % LWM, wn = wave / LWM;
-  const LpLanes<E> ln(wave, lane);
+  const LpLanes<E, NW> ln(wave, lane);
   // rows past nv repeat row nv - 1 (outputs never stored); B rows n >= nv read the
   // Omega1 row nv + q
   int ar[L::NI], br[L::NI];
@@ -563,13 +626,13 @@ __global__ __launch_bounds__(LNT) void k_omega_lp(const char* __restrict__ YL,
   // the loads run NS - 1 stages ahead in the ring of NS stage buffers
 #pragma unroll
   for (int t = 0; t < L::NS - 1; ++t)
-    if (s0 + t < s1) lp_load_stage<E>(sg, s0 + t, lds + t * L::STAGEB, ln.cb, ar, br, wave);
+    if (s0 + t < s1) lp_load_stage<E, NW>(sg, s0 + t, lds + t * L::STAGEB, ln.cb, ar, br, wave);
   for (int s = s0; s < s1; ++s) {
-    lp_stage_ready<E>(min(L::NS - 2, s1 - 1 - s));
+    lp_stage_ready<E, NW>(min(L::NS - 2, s1 - 1 - s));
     const int ahead = s - s0 + L::NS - 1;
     if (s0 + ahead < s1)
-      lp_load_stage<E>(sg, s0 + ahead, lds + (ahead % L::NS) * L::STAGEB, ln.cb, ar, br, wave);
-    lp_mfma_stage<E>(lds + ((s - s0) % L::NS) * L::STAGEB, acc, lane, wm, wn);
+      lp_load_stage<E, NW>(sg, s0 + ahead, lds + (ahead % L::NS) * L::STAGEB, ln.cb, ar, br, wave);
+    lp_mfma_stage<E, NW>(lds + ((s - s0) % L::NS) * L::STAGEB, acc, lane, wm, wn);
     if constexpr (E::FLUSH) lp_flush(acc, accd);
   }
   // the BF16 MFMA leaves D[row = 4 (lane/16) + r][col = lane%16] in register r
@@ -657,63 +720,87 @@ void launch_lp_contract_convert(const Blocks& b, int prec, int no, int nv, void*
 
 void launch_omega_lp(int prec, const void* YL, const void* GbcL, const void* GcbL, const int* tri,
                      int ntri, double* Pvv, int no, int nv, hipStream_t st) {
-  const int tm = (nv + LBM - 1) / LBM, tn = (nv + 1 + LBN - 1) / LBN;
   const int nch = omega_kchunks(nv, ntri, true);
-  const dim3 grid(nch * tm * tn, 6, ntri), block(LNT);
   const char *y = (const char*)YL, *gb = (const char*)GbcL, *gc = (const char*)GcbL;
-  if (prec == CC3_BF16X3)
-    hipLaunchKernelGGL(k_omega_lp<EngBF16<2>>, grid, block, 0, st, y, gb, gc, tri, Pvv, no, nv, nch, tn);
-  else
-    hipLaunchKernelGGL(k_omega_lp<EngBF16<3>>, grid, block, 0, st, y, gb, gc, tri, Pvv, no, nv, nch, tn);
+  with_waves(lp_tile_waves(nv, nv + 1), [&](auto nw) {
+    constexpr int NW = decltype(nw)::value;
+    const int tm = (int)nblk(nv, 16 * NW), tn = (int)nblk(nv + 1, 16 * NW);
+    const dim3 grid(nch * tm * tn, 6, ntri), block(64 * NW);
+    if (prec == CC3_BF16X3)
+      hipLaunchKernelGGL((k_omega_lp<EngBF16<2>, NW>), grid, block, 0, st, y, gb, gc, tri, Pvv, no, nv,
+                         nch, tn);
+    else
+      hipLaunchKernelGGL((k_omega_lp<EngBF16<3>, NW>), grid, block, 0, st, y, gb, gc, tri, Pvv, no, nv,
+                         nch, tn);
+  });
 }
 
-// Packed persistent form of the low-precision W build (serving), as k_pack_wbuild.
-template <class E>
-__global__ __launch_bounds__(LNT) void k_pack_wbuild_lp(const PackJob* __restrict__ jobs,
-                                                        int njobs, unsigned total) {
+// Packed persistent form of the W build (serving), as k_pack_wbuild.
+template <class E, int NW>
+__global__ __launch_bounds__(LpGeo<NW>::NT) void k_pack_wbuild_lp(const PackJob* __restrict__ jobs,
+                                                                  int njobs, unsigned total) {
+  constexpr unsigned planes = E::FLUSH ? 2u : 3u;
   for (unsigned item = blockIdx.x; item < total; item += gridDim.x) {
     int r = 0;
     while (r + 1 < njobs && item >= jobs[r + 1].first[PK_W]) ++r;
     const PackJob& J = jobs[r];
     const unsigned local = item - J.first[PK_W];
-    const int tm = (J.nv + LBM - 1) / LBM, tn = (J.nv + LBN - 1) / LBN;
-    const unsigned gx = (unsigned)J.nv * tm * tn;
-    wbuild_lp_body<E>((const char*)J.lpt2, (const char*)J.lpt2N, (const char*)J.lpGwT,
-                      (const char*)J.lpGoT, J.tri, J.cubes, J.no, J.nv, tm, tn, 0,
-                      (int)(local % gx), (int)((local / gx) % 3), (int)(local / (gx * 3)));
+    const int t = (J.nv + 16 * NW - 1) / (16 * NW);
+    const unsigned gx = (unsigned)J.nv * t * t;
+    wbuild_lp_body<E, NW>((const char*)J.lpt2, (const char*)J.lpt2N, (const char*)J.lpGwT,
+                          (const char*)J.lpGoT, J.tri, J.cubes, J.no, J.nv, t, 0,
+                          (int)(local % gx), (int)((local / gx) % planes),
+                          (int)(local / (gx * planes)));
     __syncthreads();
   }
 }
 
-unsigned wbuild_lp_wgs(int nv, int ntri) {
-  return (unsigned)nv * (unsigned)((nv + LBM - 1) / LBM) * (unsigned)((nv + LBN - 1) / LBN) * 3u *
-         (unsigned)ntri;
+unsigned wbuild_lp_wgs(int prec, int nv, int ntri, int nw) {
+  const unsigned t = nblk(nv, 16 * nw);
+  return (unsigned)nv * t * t * (two_planes(prec) ? 2u : 3u) * (unsigned)ntri;
 }
 
-void launch_wbuild_lp_packed(const PackJob* jobs, int njobs, unsigned total, int prec,
+void launch_wbuild_lp_packed(const PackJob* jobs, int njobs, unsigned total, int prec, int nw,
                              hipStream_t st) {
-  const dim3 grid(total < 2048 ? total : 2048), block(LNT);
-  if (prec == CC3_FP32)
-    hipLaunchKernelGGL(k_pack_wbuild_lp<EngF32>, grid, block, 0, st, jobs, njobs, total);
-  else if (prec == CC3_BF16X3)
-    hipLaunchKernelGGL(k_pack_wbuild_lp<EngBF16<2>>, grid, block, 0, st, jobs, njobs, total);
-  else
-    hipLaunchKernelGGL(k_pack_wbuild_lp<EngBF16<3>>, grid, block, 0, st, jobs, njobs, total);
+  const dim3 grid(total < 2048 ? total : 2048);
+  if (prec == CC3_FP32) {
+    hipLaunchKernelGGL((k_pack_wbuild_lp<EngF32, 8>), grid, dim3(512), 0, st, jobs, njobs, total);
+    return;
+  }
+  with_waves(nw, [&](auto n) {
+    constexpr int NW = decltype(n)::value;
+    if (prec == CC3_BF16X3)
+      hipLaunchKernelGGL((k_pack_wbuild_lp<EngBF16<2>, NW>), grid, dim3(64 * NW), 0, st, jobs, njobs,
+                         total);
+    else
+      hipLaunchKernelGGL((k_pack_wbuild_lp<EngBF16<3>, NW>), grid, dim3(64 * NW), 0, st, jobs, njobs,
+                         total);
+  });
 }
 
 void launch_wbuild_lp(const LpOperands& lp, const int* tri, int ntri, double* cubes, int no, int nv,
                       bool all_terms, hipStream_t st) {
-  const int tm = (nv + LBM - 1) / LBM, tn = (nv + LBN - 1) / LBN;
-  const dim3 grid(nv * tm * tn, 3, ntri), block(LNT);
   const char *a = (const char*)lp.t2, *b = (const char*)lp.t2N, *c = (const char*)lp.GwT,
              *d = (const char*)lp.GoT;
   const int at = all_terms ? 1 : 0;
-  if (lp.prec == CC3_FP32)
-    hipLaunchKernelGGL(k_wbuild_lp<EngF32>, grid, block, 0, st, a, b, c, d, tri, cubes, no, nv, tm, tn, at);
-  else if (lp.prec == CC3_BF16X3)
-    hipLaunchKernelGGL(k_wbuild_lp<EngBF16<2>>, grid, block, 0, st, a, b, c, d, tri, cubes, no, nv, tm, tn, at);
-  else
-    hipLaunchKernelGGL(k_wbuild_lp<EngBF16<3>>, grid, block, 0, st, a, b, c, d, tri, cubes, no, nv, tm, tn, at);
+  const unsigned planes = two_planes(lp.prec) ? 2 : 3;
+  if (lp.prec == CC3_FP32) {
+    const int t = (int)nblk(nv, 128);
+    hipLaunchKernelGGL((k_wbuild_lp<EngF32, 8>), dim3(nv * t * t, planes, ntri), dim3(512), 0, st, a, b,
+                       c, d, tri, cubes, no, nv, t, at);
+    return;
+  }
+  with_waves(lp_tile_waves(nv, nv), [&](auto n) {
+    constexpr int NW = decltype(n)::value;
+    const int t = (int)nblk(nv, 16 * NW);
+    const dim3 grid(nv * t * t, planes, ntri), block(64 * NW);
+    if (lp.prec == CC3_BF16X3)
+      hipLaunchKernelGGL((k_wbuild_lp<EngBF16<2>, NW>), grid, block, 0, st, a, b, c, d, tri, cubes, no,
+                         nv, t, at);
+    else
+      hipLaunchKernelGGL((k_wbuild_lp<EngBF16<3>, NW>), grid, block, 0, st, a, b, c, d, tri, cubes, no,
+                         nv, t, at);
+  });
 }
 
 }  // namespace cc3

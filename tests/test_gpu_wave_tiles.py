@@ -33,6 +33,25 @@ def test_residual_at_tile_edges(no, nv):
     assert rel(o2.cpu().numpy(), r2) < TOL
 
 
+# W (and the contraction) in reduced precision at the edges of its tiles (multiples of 16 from 64 to 128, and the
+# change of FP32 from wave tiles to LDS tiles at 118).  Bars: a partial sum of 32 terms rounded
+# to FP32 is off by at most 32 x 6e-8 of its terms (FP32, BF16x6: 2e-6); the products that the
+# two-piece split leaves out are 2^-16 of a term, and its sums run over K (BF16x3: 1e-4).
+@pytest.mark.parametrize("prec,flags,bar", [
+    (cc3.FP32, 0, 2e-6), (cc3.BF16X6, 0, 2e-6), (cc3.BF16X3, 0, 1e-4),
+    (cc3.BF16X3, cc3.LOWP_CONTRACT, 1e-4)])
+@pytest.mark.parametrize("no,nv", [(2, 15), (3, 63), (3, 65), (2, 81), (3, 97), (2, 112), (3, 113),
+                                   (2, 117), (3, 118), (2, 129)])
+def test_reduced_precision_w_at_tile_edges(no, nv, prec, flags, bar):
+    d = make_inputs(no, nv, 2 * (no + nv), tag=23)
+    ctx = cc3.Context(0)
+    g = {k: torch.from_numpy(d[k]).cuda() for k in ("eps", "L", "t1", "t2")}
+    o1, o2 = ctx.triples_residual(g["eps"], g["L"], g["t1"], g["t2"], prec=prec, flags=flags)
+    r1, r2 = O.triples_residual(d["eps"], d["L"], d["t1"], d["t2"])
+    assert rel(o1.cpu().numpy(), r1) < bar
+    assert rel(o2.cpu().numpy(), r2) < bar
+
+
 @pytest.mark.parametrize("ijk", [(2, 1, 0), (0, 1, 2), (1, 2, 0), (2, 2, 1), (1, 2, 2), (2, 1, 2)])
 def test_t3_block_orderings(ijk):
     """The planes of every kind of ordered triple (the export builds all six terms)."""
