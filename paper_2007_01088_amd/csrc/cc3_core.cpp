@@ -418,8 +418,6 @@ static int triple_loop_body(Runner& rn, Profiler* pf, const Plan& p, const Ws& w
     launch_g_to_f32(w.b.Gcb, (float*)w.GcbX, rows, p.nv, st);
   } else if (lowp_contract) {
     launch_lp_contract_convert(w.b, p.prec, p.no, p.nv, w.GbcX, w.GcbX, st);
-    for (int k = 0; k < 2; ++k)
-      launch_lp_zero_pad(w.cubesX[k], (int64_t)p.batch * 4 * lpP * p.nv, p.nv, st);
   }
   // PLAN_CALLER_STREAM: every batch on the caller's stream, no runner streams or events
   const bool own = (p.flags & PLAN_CALLER_STREAM) != 0;

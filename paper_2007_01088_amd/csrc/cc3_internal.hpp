@@ -76,6 +76,17 @@ __host__ __device__ inline int64_t lp_kb(int x, int y, int nv) {
   return ((int64_t)((x >> 3) * nb + (y >> 3)) * 8 + (x & 7)) * 8 + (y & 7);
 }
 
+// tau~ of one triple in split-BF16 pieces, for the same contraction: two forms in 8 x 8 x 8
+// blocks of 1 KB, [form][piece][X0][X1][X2][x0 % 8][x1 % 8][x2 % 8] with (x0, x1, x2) =
+// (a, b, c) in form 0 and (a, c, b) in form 1, nb = ceil(nv / 8) blocks per index and zeros
+// past nv.  Either form has 8 consecutive values of a contracted index in each 16 bytes for
+// rows x0 with K = (x1, x2) and for rows x1 with K = (x0, x2): the four views of tau~ that
+// the six permutations need.
+__host__ __device__ inline int64_t yl_piece(int nv) {  // bytes of one piece of one form
+  const int64_t nb = (nv + 7) / 8;
+  return nb * nb * nb * 1024;
+}
+
 // The cubes of the triple loop (W planes P0..P2, tau~ and tau~T, [x][y][z] per slot)
 // keep their rows of nv values at a pitch padded to a multiple of 8 doubles, so that the
 // row segments of 8 or 16 values that the W build, the mix and the Omega kernels move
@@ -243,7 +254,6 @@ size_t lp_contract_g_bytes(int prec, int no, int nv);
 size_t lp_contract_cube_bytes(int prec, int nv);
 void launch_lp_contract_convert(const Blocks& b, int prec, int no, int nv, void* GbcL, void* GcbL,
                                 hipStream_t st);
-void launch_lp_zero_pad(void* YL, int64_t rows, int nv, hipStream_t st);
 void launch_omega_lp(int prec, const void* YL, const void* GbcL, const void* GcbL, const int* tri,
                      int ntri, double* Pvv, int no, int nv, hipStream_t st);
 // Ot~2[p][q][a][b] = Ot2[p][q][a][b] + OtT[p][q][b][a]  (contravariant doubles residual)

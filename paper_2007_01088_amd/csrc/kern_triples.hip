@@ -433,9 +433,6 @@ __device__ inline void decode_block_triple(int idx, int& A, int& B, int& C) {
   A = idx; B = b; C = c;
 }
 
-// Threads per mix workgroup (MIXT, 256 or 512): each handles MIXH = 512 / MIXT of
-// the 512 elements of an orientation tile.
-
 // X of a triple whose six terms were all built (kind TRI_DISTINCT)
 template <bool TWO>
 __device__ inline double xval(const double* __restrict__ cz, int64_t nv, int a, int b, int c) {
@@ -447,40 +444,40 @@ __device__ inline double xval(const double* __restrict__ cz, int64_t nv, int a, 
   return x;
 }
 
-// The split-BF16 pieces of x at row `row` and K pair (kx, ky) of view v of triple z in
-// YL[z][4][P][nv][Kr] (rows of pitch Kr = lp_kb_pitch(nv), the pair at lp_kb(kx, ky)).
-__device__ inline void yl_put(uint16_t* YL, int P, int z, int v, int row, int kx, int ky, int nv,
-                              double x) {
-  const int64_t Kr = lp_kb_pitch(nv);
-  uint16_t* base = YL + (((int64_t)z * 4 + v) * P * nv + row) * Kr + lp_kb(kx, ky, nv);
-  const int64_t ps = (int64_t)nv * Kr;
-  if (P == 2) {
-    uint16_t pc[2];
-    split_bf16<2>(x, pc);
-    base[0] = pc[0];
-    base[ps] = pc[1];
-  } else {
-    uint16_t pc[3];
-    split_bf16<3>(x, pc);
-    base[0] = pc[0];
-    base[ps] = pc[1];
-    base[2 * ps] = pc[2];
+// The split-BF16 copies of one orientation tile of tau~ (block A, B, C; values in T): form
+// 0 or 1 of yl_piece, P pieces, each a run of 1 KB, 16 bytes per lane.
+template <int P>
+__device__ __forceinline__ void yl_put(char* Y, int form, const double* T, int A, int B, int C,
+                                       int nv, int lane) {
+  const int x0 = lane >> 3, x1 = lane & 7;
+  const int64_t nb = (nv + 7) / 8;
+  uint32_t w[P][4];
+#pragma unroll
+  for (int h = 0; h < 4; ++h) {
+    uint16_t p0[P], p1[P];
+    split_bf16<P>(form ? T[TP(x0, 2 * h, x1)] : T[TP(x0, x1, 2 * h)], p0);
+    split_bf16<P>(form ? T[TP(x0, 2 * h + 1, x1)] : T[TP(x0, x1, 2 * h + 1)], p1);
+#pragma unroll
+    for (int pc = 0; pc < P; ++pc) w[pc][h] = p0[pc] | (uint32_t)p1[pc] << 16;
   }
+  char* at = Y + form * P * yl_piece(nv) + ((A * nb + (form ? C : B)) * nb + (form ? B : C)) * 1024 +
+             lane * 16;
+#pragma unroll
+  for (int pc = 0; pc < P; ++pc)
+    *(uint4*)(at + pc * yl_piece(nv)) = make_uint4(w[pc][0], w[pc][1], w[pc][2], w[pc][3]);
 }
 
-// Mixed-all copies (nullable): cubesF, FP32 tau~ and tau~T, [triple][2][nv^3];
-// YL, the split-BF16 k-major views of the split-BF16 Omega GEMM (k_omega_lp),
-// [triple][4][piece][a][kk < Kp] with lpP pieces.  TWO: the two planes of the FP64 W
-// build, X = PA[b][a][c] + PB[a][b][c] (PA[a][b][c] for i == j, PA[c][a][b] for j == k in
+// Mixed-all copies: cubesF (nullable), FP32 tau~ and tau~T, [triple][2][nv^3]; LP: YL, the
+// split-BF16 blocks of the split-BF16 Omega GEMM (yl_piece), in lpP pieces.  TWO: the two
+// planes of the W build, X = PA[b][a][c] + PB[a][b][c] (PA[a][b][c] for i == j, PA[c][a][b] for j == k in
 // the place of PB); otherwise the three planes of the BF16x3 build,
 // X = P0[b][a][c] + P1[a][b][c] + P2[c][a][b], where for i == j P1 = P0 and P2 is
 // symmetrised over (a, b), and for j == k P2 = P0 and P1 is symmetrised over (b, c).
-template <int MIXT, bool TWO>
+template <bool TWO, bool LP>
 __device__ __forceinline__ void mix_body(const double* __restrict__ eps,
                                          const int* __restrict__ tri, double* __restrict__ cubes,
-                                         float* __restrict__ cubesF, uint16_t* __restrict__ YL,
-                                         int lpP, int transposed, int no, int nv, int bx, int by) {
-  constexpr int MIXH = 512 / MIXT;
+                                         float* __restrict__ cubesF, char* __restrict__ YL, int lpP,
+                                         int transposed, int no, int nv, int bx, int by) {
   __shared__ double Xs[6 * TSZ];
   const int z = by, ob = bx;
   const int i = tri[3 * z], j = tri[3 * z + 1], k = tri[3 * z + 2];
@@ -522,18 +519,14 @@ __device__ __forceinline__ void mix_body(const double* __restrict__ eps,
     int q0, q1, q2;
     orient(o, q0, q1, q2);
     const int A0 = blk[q0] * MT, B0 = blk[q1] * MT, C0 = blk[q2] * MT;
-#pragma unroll
-    for (int h = 0; h < MIXH; ++h) {
-      const int e = t + MIXT * h;
-      const int u = e >> 6, v = (e >> 3) & 7, w = e & 7;  // pass 0: c fastest
-      const int a = A0 + u, b = B0 + v, c = C0 + w;
-      double x = 0.0;
-      if (a < nv && b < nv && c < nv)
-        x = TWO && kind == TRI_JK
-                ? P0[b * pl + a * rp + c]
-                : P0[b * pl + a * rp + c] + (kind == TRI_IJ ? P0 : P1)[a * pl + b * rp + c];
-      Xs[o * TSZ + TP(u, v, w)] = x;
-    }
+    const int u = t >> 6, v = (t >> 3) & 7, w = t & 7;  // pass 0: c fastest
+    const int a = A0 + u, b = B0 + v, c = C0 + w;
+    double x = 0.0;
+    if (a < nv && b < nv && c < nv)
+      x = TWO && kind == TRI_JK
+              ? P0[b * pl + a * rp + c]
+              : P0[b * pl + a * rp + c] + (kind == TRI_IJ ? P0 : P1)[a * pl + b * rp + c];
+    Xs[o * TSZ + TP(u, v, w)] = x;
   }
   if (!TWO || kind == TRI_JK) {
     __syncthreads();
@@ -543,18 +536,14 @@ __device__ __forceinline__ void mix_body(const double* __restrict__ eps,
       int q0, q1, q2;
       orient(o, q0, q1, q2);
       const int A0 = blk[q0] * MT, B0 = blk[q1] * MT, C0 = blk[q2] * MT;
-#pragma unroll
-      for (int h = 0; h < MIXH; ++h) {
-        const int e = t + MIXT * h;
-        const int u = e >> 6, w = (e >> 3) & 7, v = e & 7;  // pass 1: b fastest
-        const int a = A0 + u, b = B0 + v, c = C0 + w;
-        if (a < nv && b < nv && c < nv) {
-          double x;
-          if (TWO) x = P0[c * pl + a * rp + b];
-          else if (kind == TRI_JK) x = P1[a * pl + c * rp + b] + P0[c * pl + a * rp + b];
-          else x = P2[c * pl + a * rp + b];
-          Xs[o * TSZ + TP(u, v, w)] += x;
-        }
+      const int u = t >> 6, w = (t >> 3) & 7, v = t & 7;  // pass 1: b fastest
+      const int a = A0 + u, b = B0 + v, c = C0 + w;
+      if (a < nv && b < nv && c < nv) {
+        double x;
+        if (TWO) x = P0[c * pl + a * rp + b];
+        else if (kind == TRI_JK) x = P1[a * pl + c * rp + b] + P0[c * pl + a * rp + b];
+        else x = P2[c * pl + a * rp + b];
+        Xs[o * TSZ + TP(u, v, w)] += x;
       }
     }
   }
@@ -566,18 +555,14 @@ __device__ __forceinline__ void mix_body(const double* __restrict__ eps,
       int q0, q1, q2;
       orient(o, q0, q1, q2);
       const int A0 = blk[q0] * MT, B0 = blk[q1] * MT, C0 = blk[q2] * MT;
-#pragma unroll
-      for (int h = 0; h < MIXH; ++h) {
-        const int e = t + MIXT * h;
-        const int v = e >> 6, w = (e >> 3) & 7, u = e & 7;  // pass 2: a fastest
-        const int a = A0 + u, b = B0 + v, c = C0 + w;
-        if (a < nv && b < nv && c < nv) Xs[o * TSZ + TP(u, v, w)] += P2[c * pl + b * rp + a];
-      }
+      const int v = t >> 6, w = (t >> 3) & 7, u = t & 7;  // pass 2: a fastest
+      const int a = A0 + u, b = B0 + v, c = C0 + w;
+      if (a < nv && b < nv && c < nv) Xs[o * TSZ + TP(u, v, w)] += P2[c * pl + b * rp + a];
     }
   }
   __syncthreads();
   // 2. tau~ on the orbit, in registers
-  double tt[6][MIXH];
+  double tt[6];
 #pragma unroll
   for (int o = 0; o < 6; ++o) {
     if (canon[o] != o) continue;
@@ -587,28 +572,24 @@ __device__ __forceinline__ void mix_body(const double* __restrict__ eps,
     const int o_acb = canon[orient_of(q0, q2)], o_cba = canon[orient_of(q2, q1)];
     const int o_bac = canon[orient_of(q1, q0)], o_bca = canon[orient_of(q1, q2)];
     const int o_cab = canon[orient_of(q2, q0)];
-#pragma unroll
-    for (int h = 0; h < MIXH; ++h) {
-      const int e = t + MIXT * h;
-      const int u = e >> 6, v = (e >> 3) & 7, w = e & 7;
-      const int a = A0 + u, b = B0 + v, c = C0 + w;
-      double val = 0.0;
-      if (a < nv && b < nv && c < nv) {
-        // X at permuted virtual labels: (a,c,b), (c,b,a), (b,a,c), (b,c,a), (c,a,b)
-        const double x_abc = Xs[o * TSZ + TP(u, v, w)];
-        const double x_acb = Xs[o_acb * TSZ + TP(u, w, v)];
-        const double x_cba = Xs[o_cba * TSZ + TP(w, v, u)];
-        const double x_bac = Xs[o_bac * TSZ + TP(v, u, w)];
-        const double x_bca = Xs[o_bca * TSZ + TP(v, w, u)];
-        const double x_cab = Xs[o_cab * TSZ + TP(w, u, v)];
-        const double D = eps[no + a] + eps[no + b] + eps[no + c] - eijk;
-        val = -(4.0 * x_abc - 2.0 * x_acb - 2.0 * x_cba - 2.0 * x_bac + x_bca + x_cab) / D;
-      }
-      tt[o][h] = val;
+    const int u = t >> 6, v = (t >> 3) & 7, w = t & 7;
+    const int a = A0 + u, b = B0 + v, c = C0 + w;
+    double val = 0.0;
+    if (a < nv && b < nv && c < nv) {
+      // X at permuted virtual labels: (a,c,b), (c,b,a), (b,a,c), (b,c,a), (c,a,b)
+      const double x_abc = Xs[o * TSZ + TP(u, v, w)];
+      const double x_acb = Xs[o_acb * TSZ + TP(u, w, v)];
+      const double x_cba = Xs[o_cba * TSZ + TP(w, v, u)];
+      const double x_bac = Xs[o_bac * TSZ + TP(v, u, w)];
+      const double x_bca = Xs[o_bca * TSZ + TP(v, w, u)];
+      const double x_cab = Xs[o_cab * TSZ + TP(w, u, v)];
+      const double D = eps[no + a] + eps[no + b] + eps[no + c] - eijk;
+      val = -(4.0 * x_abc - 2.0 * x_acb - 2.0 * x_cba - 2.0 * x_bac + x_bca + x_cab) / D;
     }
+    tt[o] = val;
   }
-  // 3. write tau~[a][b][c], with zeros in the padding columns c >= nv, and its FP32 or
-  //    split-BF16 copies of the same order, straight from the registers
+  // 3. write tau~[a][b][c], with zeros in the padding columns c >= nv, and its FP32
+  //    copy of the same order, straight from the registers
   double* TT = cz + SLOT_TT * cs;
 #pragma unroll
   for (int o = 0; o < 6; ++o) {
@@ -616,35 +597,41 @@ __device__ __forceinline__ void mix_body(const double* __restrict__ eps,
     int q0, q1, q2;
     orient(o, q0, q1, q2);
     const int A0 = blk[q0] * MT, B0 = blk[q1] * MT, C0 = blk[q2] * MT;
-#pragma unroll
-    for (int h = 0; h < MIXH; ++h) {
-      const int e = t + MIXT * h;
-      const int u = e >> 6, v = (e >> 3) & 7, w = e & 7;
-      const int a = A0 + u, b = B0 + v, c = C0 + w;
-      if (a < nv && b < nv) {
-        const double x = tt[o][h];
-        TT[(a * nvl + b) * rp + c] = x;
-        if (cubesF && c < nv) cubesF[(int64_t)z * 2 * nv3 + (a * nvl + b) * nvl + c] = (float)x;
-        if (YL && c < nv) {  // view 0 at [a][(b, c)], view 1 at [b][(a, c)]
-          yl_put(YL, lpP, z, 0, a, b, c, nv, x);
-          yl_put(YL, lpP, z, 1, b, a, c, nv, x);
-        }
-      }
+    const int u = t >> 6, v = (t >> 3) & 7, w = t & 7;
+    const int a = A0 + u, b = B0 + v, c = C0 + w;
+    if (a < nv && b < nv) {
+      const double x = tt[o];
+      TT[(a * nvl + b) * rp + c] = x;
+      if (cubesF && c < nv) cubesF[(int64_t)z * 2 * nv3 + (a * nvl + b) * nvl + c] = (float)x;
     }
   }
   // 4. the copies with a and b, or c and b, exchanged: through LDS, b fastest
-  if (!transposed && !cubesF && !YL) return;
+  if (!LP && !transposed && !cubesF) return;
   __syncthreads();
 #pragma unroll
   for (int o = 0; o < 6; ++o) {
     if (canon[o] != o) continue;
-#pragma unroll
-    for (int h = 0; h < MIXH; ++h) {
-      const int e = t + MIXT * h;
-      Xs[o * TSZ + TP(e >> 6, (e >> 3) & 7, e & 7)] = tt[o][h];
-    }
+    Xs[o * TSZ + TP(t >> 6, (t >> 3) & 7, t & 7)] = tt[o];
   }
   __syncthreads();
+  if constexpr (LP) {  // two wavefronts per orientation, one form each
+    int alive = 0;
+#pragma unroll
+    for (int o = 0; o < 6; ++o) alive |= (canon[o] == o) << o;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    char* Y = YL + (int64_t)z * 2 * lpP * yl_piece(nv);
+    for (int o = wave >> 1; o < 6; o += 4) {
+      if (!(alive >> o & 1)) continue;
+      int q0, q1, q2;
+      orient(o, q0, q1, q2);
+      const int A = q0 == 0 ? blk[0] : q0 == 1 ? blk[1] : blk[2];
+      const int B = q1 == 0 ? blk[0] : q1 == 1 ? blk[1] : blk[2];
+      const int C = q2 == 0 ? blk[0] : q2 == 1 ? blk[1] : blk[2];
+      if (lpP == 2) yl_put<2>(Y, wave & 1, Xs + o * TSZ, A, B, C, nv, t & 63);
+      else yl_put<3>(Y, wave & 1, Xs + o * TSZ, A, B, C, nv, t & 63);
+    }
+  }
+  if (!transposed && !cubesF) return;
   double* TTT = cz + SLOT_TTT * cs;
 #pragma unroll
   for (int o = 0; o < 6; ++o) {
@@ -652,56 +639,37 @@ __device__ __forceinline__ void mix_body(const double* __restrict__ eps,
     int q0, q1, q2;
     orient(o, q0, q1, q2);
     const int A0 = blk[q0] * MT, B0 = blk[q1] * MT, C0 = blk[q2] * MT;
-#pragma unroll
-    for (int h = 0; h < MIXH; ++h) {
-      const int e = t + MIXT * h;
-      const int u = e >> 6, w = (e >> 3) & 7, v = e & 7;
-      const int a = A0 + u, b = B0 + v, c = C0 + w;
-      if (a < nv && b < nv && c < nv) {
-        const double x = Xs[o * TSZ + TP(u, v, w)];
-        if (transposed) TTT[(a * nvl + c) * rp + b] = x;
-        if (cubesF) cubesF[((int64_t)z * 2 + 1) * nv3 + (a * nvl + c) * nvl + b] = (float)x;
-        if (YL) {  // view 2 at [c][(a, b)], view 3 at [a][(c, b)]
-          yl_put(YL, lpP, z, 2, c, a, b, nv, x);
-          yl_put(YL, lpP, z, 3, a, c, b, nv, x);
-        }
-      }
+    const int u = t >> 6, w = (t >> 3) & 7, v = t & 7;
+    const int a = A0 + u, b = B0 + v, c = C0 + w;
+    if (a < nv && b < nv && c < nv) {
+      const double x = Xs[o * TSZ + TP(u, v, w)];
+      if (transposed) TTT[(a * nvl + c) * rp + b] = x;
+      if (cubesF) cubesF[((int64_t)z * 2 + 1) * nv3 + (a * nvl + c) * nvl + b] = (float)x;
     }
   }
 }
 
-template <int MIXT, bool TWO>
-__global__ __launch_bounds__(MIXT) void k_mix(const double* __restrict__ eps,
+template <bool TWO, bool LP>
+__global__ __launch_bounds__(512, LP ? 6 : 8) void k_mix(const double* __restrict__ eps,
                                              const int* __restrict__ tri,
                                              double* __restrict__ cubes, float* __restrict__ cubesF,
-                                             uint16_t* __restrict__ YL, int lpP, int transposed,
-                                             int no, int nv) {
-  mix_body<MIXT, TWO>(eps, tri, cubes, cubesF, YL, lpP, transposed, no, nv, blockIdx.x, blockIdx.y);
+                                             char* __restrict__ YL, int lpP, int transposed, int no,
+                                             int nv) {
+  mix_body<TWO, LP>(eps, tri, cubes, cubesF, YL, lpP, transposed, no, nv, blockIdx.x, blockIdx.y);
 }
 
 void launch_mix(bool two_planes, const double* eps, const int* tri, int ntri, double* cubes,
                 float* cubesF, void* YL, int lpP, bool transposed, int no, int nv, hipStream_t st) {
   const int nb = (nv + MT - 1) / MT;
   const int nbt = nb * (nb + 1) * (nb + 2) / 6;
-  // 512 threads, one element per thread and orientation; the form that also writes
-  // the split-BF16 views of tau~ runs with 256 (two elements each), which measured
-  // faster for it at nv = 250
-  const int tr = transposed ? 1 : 0;
-  if (YL) {
-    if (two_planes)
-      hipLaunchKernelGGL((k_mix<256, true>), dim3(nbt, ntri), dim3(256), 0, st, eps, tri, cubes,
-                         cubesF, (uint16_t*)YL, lpP, tr, no, nv);
-    else
-      hipLaunchKernelGGL((k_mix<256, false>), dim3(nbt, ntri), dim3(256), 0, st, eps, tri, cubes,
-                         cubesF, (uint16_t*)YL, lpP, tr, no, nv);
-  } else {
-    if (two_planes)
-      hipLaunchKernelGGL((k_mix<512, true>), dim3(nbt, ntri), dim3(512), 0, st, eps, tri, cubes,
-                         cubesF, nullptr, 0, tr, no, nv);
-    else
-      hipLaunchKernelGGL((k_mix<512, false>), dim3(nbt, ntri), dim3(512), 0, st, eps, tri, cubes,
-                         cubesF, nullptr, 0, tr, no, nv);
-  }
+  auto run = [&](auto* kernel) {
+    hipLaunchKernelGGL(kernel, dim3(nbt, ntri), dim3(512), 0, st, eps, tri, cubes, cubesF, (char*)YL,
+                       lpP, transposed ? 1 : 0, no, nv);
+  };
+  if (two_planes && YL) run(k_mix<true, true>);
+  else if (two_planes) run(k_mix<true, false>);
+  else if (YL) run(k_mix<false, true>);
+  else run(k_mix<false, false>);
 }
 
 // ---------------------------------------------------------------------------
@@ -1815,7 +1783,7 @@ __global__ __launch_bounds__(512) void k_pack_mix(const PackJob* __restrict__ jo
     const unsigned local = item - J.first[PK_MIX];
     const int nb = (J.nv + MT - 1) / MT;
     const unsigned nbt = (unsigned)(nb * (nb + 1) * (nb + 2) / 6);
-    mix_body<512, TWO>(J.eps, J.tri, J.cubes, nullptr, nullptr, 0, 0, J.no, J.nv, (int)(local % nbt),
+    mix_body<TWO, false>(J.eps, J.tri, J.cubes, nullptr, nullptr, 0, 0, J.no, J.nv, (int)(local % nbt),
                   (int)(local / nbt));
     __syncthreads();
   }

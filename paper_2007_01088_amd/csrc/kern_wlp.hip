@@ -240,25 +240,21 @@ struct LpLanes {
   }
 };
 
-// Issue the direct loads of stage `st` of segment `sg` into the stage buffer
-// `buf`; ar / br: this lane's A and B row indices (already mapped to operand rows)
-template <class E, int NW>
-__device__ __forceinline__ void lp_load_stage(const LpSeg& sg, int st, char* buf,
-                                              const unsigned* cb, const int* ar, const int* br,
-                                              int wave) {
+// Issue the direct loads of one stage into the stage buffer `buf`: a, b, the operands'
+// piece 0 at the stage, aps and bps their piece strides, ao(i), bo(i) this lane's byte offsets
+template <class E, int NW, class A, class B>
+__device__ __forceinline__ void lp_load_stage(const char* a, const char* b, int64_t aps,
+                                              int64_t bps, char* buf, A ao, B bo, int wave) {
   typedef LpTile<E, NW> L;
-  const int64_t ko = (int64_t)st * L::RB;
 #pragma unroll
   for (int pc = 0; pc < L::P; ++pc) {
-    const BufRsrc ra = buf_rsrc(sg.a + pc * sg.aps + ko), rb = buf_rsrc(sg.b + pc * sg.bps + ko);
+    const BufRsrc ra = buf_rsrc(a + pc * aps), rb = buf_rsrc(b + pc * bps);
 #pragma unroll
     for (int i = 0; i < L::NI; ++i) {
       char* la = buf + pc * L::TILEB + (NW * i + wave) * 1024;
       char* lb = buf + (L::P + pc) * L::TILEB + (NW * i + wave) * 1024;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_ptr_t)la, 16,
-                                               (unsigned)ar[i] * sg.ars + cb[i], 0, 0, 0);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_ptr_t)lb, 16,
-                                               (unsigned)br[i] * sg.brs + cb[i], 0, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_ptr_t)la, 16, ao(i), 0, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_ptr_t)lb, 16, bo(i), 0, 0, 0);
     }
   }
 }
@@ -464,7 +460,11 @@ __device__ __forceinline__ void wbuild_lp_body(
     br[e] = min(n0 + ln.row[e], nv - 1);
   }
   auto load = [&](int t) {  // stage t of the plane, in order
-    lp_load_stage<E, NW>(sg, st, lds + (t % L::NS) * L::STAGEB, ln.cb, ar, br, wave);
+    const int64_t ko = (int64_t)st * L::RB;
+    lp_load_stage<E, NW>(
+        sg.a + ko, sg.b + ko, sg.aps, sg.bps, lds + (t % L::NS) * L::STAGEB,
+        [&](int e) { return (unsigned)ar[e] * sg.ars + ln.cb[e]; },
+        [&](int e) { return (unsigned)br[e] * sg.brs + ln.cb[e]; }, wave);
     if (++st == sg.nst && t + 1 < nsteps) open(++seg);
   };
   f4v acc1[FM][FN], acc2[FM][FN];
@@ -561,14 +561,15 @@ static void with_waves(int nw, F f) {
 // ---------------------------------------------------------------------------
 // The long-K GEMM of k_omega per (triple, permutation, 128 x 128 tile, K chunk):
 //   Pvv[z][pi][chunk][a][n] = sum_{kk in chunk} Y_v(pi)[a][kk] G[r][n'][kk],
-// with every operand row k-contiguous, K = (x, y) in the blocked order lp_kb (8 x 8
-// blocks of 64 contiguous values, Kp = lp_kb_len(nv), zero where x or y >= nv):
-//   YL[z][v][piece][a][kk]: the four k-major views of tau~ that the six
-//     permutations need, kk = lp_kb(x, y), written by k_mix:
-//     v = 0: tau~[a][x][y] (pi 0);  1: tau~[x][a][y] (pi 1, 4);
-//     v = 2: tau~[x][y][a] (pi 2, 5);  3: tau~[a][y][x] (pi 3);
+// with K = (x, y) in 8 x 8 blocks (lp_kb), so that a stage is half a block: four x, eight
+// consecutive y each.  The six permutations need four views of tau~: rows a with
+// K = (b, c) (pi 0), b with (a, c) (1, 4), c with (a, b) (2, 5) and a with (c, b) (3); the two
+// forms of YL (yl_piece) hold all four, the rows being their first or second index.  B:
 //   GL[piece][r][n'][kk]: Gbc (or Gcb for pi 2, 4) rows, n' = n for n < nv and
 //     nv + q (the Omega1 row) for n >= nv.
+// Against one k-major copy per view, written value by value: the mix of 8 triples of nv = 210
+// 1.21 -> 0.84 ms (40 B per element at 3.5 TB/s), this kernel 0.85 -> 0.78 (its MFMAs at 0.72
+// PFLOP/s: one barrier per stage and the loads behind it, not the 32 KB that a stage moves).
 // Each chunk sums in FP32 on the MFMA (with FLUSH, stage by stage into FP64);
 // k_reduce sums the chunks in FP64.  The tile engine is that of k_wbuild_lp.
 template <class E, int NW>
@@ -588,19 +589,17 @@ __global__ __launch_bounds__(LpGeo<NW>::NT) void k_omega_lp(const char* __restri
   perm_pqr(pi, i, j, k, p, q, r);
   const int ch = blockIdx.x % nchunks, tile = blockIdx.x / nchunks;
   const int m0 = (tile / tiles_n) * LBM, n0 = (tile % tiles_n) * LBN;
-  const int64_t Kp = lp_kb_len(nv);  // the blocked K of the views and of GL
-  const int S = (int)(Kp / E::BK);
-  const int64_t Kr = lp_kb_pitch(nv);  // their row pitch
+  const int S = (int)(lp_kb_len(nv) / E::BK);
   const int s0 = (int)((int64_t)ch * S / nchunks), s1 = (int)((int64_t)(ch + 1) * S / nchunks);
   if (s0 >= s1) return;
-  const int view = pi == 0 ? 0 : pi == 3 ? 3 : (pi == 1 || pi == 4) ? 1 : 2;
+  const int form = pi == 2 || pi == 3 || pi == 5;
+  const bool second = pi != 0 && pi != 3;  // rows: the form's second index
   const bool cb = (pi == 2 || pi == 4);
-  const int64_t rs = Kr * ESZ;                                   // row stride, bytes
-  const int64_t y_ps = (int64_t)nv * rs;                         // piece stride of a view
-  const int64_t g_ps = (int64_t)no * (nv + no) * rs;             // piece stride of GL
-  const LpSeg sg = {YL + ((int64_t)z * 4 + view) * E::P * y_ps,
-                    (cb ? GcbL : GbcL) + (int64_t)r * (nv + no) * rs, y_ps, g_ps,
-                    (unsigned)rs, (unsigned)rs, S};
+  const unsigned nb = (unsigned)(nv + 7) / 8;
+  const unsigned rs = (unsigned)(lp_kb_pitch(nv) * ESZ);         // row stride of GL, bytes
+  const int64_t y_ps = yl_piece(nv), g_ps = (int64_t)no * (nv + no) * rs;  // piece strides
+  const char* ga = YL + ((int64_t)z * 2 + form) * E::P * y_ps;
+  const char* gb = (cb ? GcbL : GbcL) + (int64_t)r * (nv + no) * rs;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -609,12 +608,13 @@ __global__ __launch_bounds__(LpGeo<NW>::NT) void k_omega_lp(const char* __restri
   const LpLanes<E, NW> ln(wave, lane);
   // rows past nv repeat row nv - 1 (outputs never stored); B rows n >= nv read the
   // Omega1 row nv + q
-  int ar[L::NI], br[L::NI];
+  unsigned ao[L::NI], bo[L::NI];
 #pragma unroll
   for (int e = 0; e < L::NI; ++e) {
-    ar[e] = min(m0 + ln.row[e], nv - 1);
-    const int n = n0 + ln.row[e];
-    br[e] = n < nv ? n : nv + q;
+    const unsigned m = (unsigned)min(m0 + ln.row[e], nv - 1), n = (unsigned)(n0 + ln.row[e]);
+    ao[e] = second ? (m >> 3) * nb * 1024 + (m & 7) * 16 + ln.cb[e] * 8
+                   : (m >> 3) * nb * nb * 1024 + (m & 7) * 128 + ln.cb[e];
+    bo[e] = (n < (unsigned)nv ? n : (unsigned)(nv + q)) * rs + ln.cb[e];
   }
   f4v acc[LFM][LFN];
   d4v accd[LFM][LFN];  // FLUSH: each stage's FP32 sum added in FP64
@@ -624,14 +624,21 @@ __global__ __launch_bounds__(LpGeo<NW>::NT) void k_omega_lp(const char* __restri
 #pragma unroll
     for (int fn = 0; fn < LFN; ++fn) accd[fm][fn] = d4v{0.0, 0.0, 0.0, 0.0};
   // the loads run NS - 1 stages ahead in the ring of NS stage buffers
+  auto load = [&](int t) {
+    const unsigned blk = (unsigned)(s0 + t) >> 1, half = (unsigned)(s0 + t) & 1;  // of K
+    const int64_t ko = second ? ((int64_t)(blk / nb) * nb * nb + blk % nb) * 1024 + half * 512
+                              : (int64_t)blk * 1024 + half * 64;
+    lp_load_stage<E, NW>(
+        ga + ko, gb + (int64_t)(s0 + t) * L::RB, y_ps, g_ps, lds + (t % L::NS) * L::STAGEB,
+        [&](int e) { return ao[e]; }, [&](int e) { return bo[e]; }, wave);
+  };
 #pragma unroll
   for (int t = 0; t < L::NS - 1; ++t)
-    if (s0 + t < s1) lp_load_stage<E, NW>(sg, s0 + t, lds + t * L::STAGEB, ln.cb, ar, br, wave);
+    if (s0 + t < s1) load(t);
   for (int s = s0; s < s1; ++s) {
     lp_stage_ready<E, NW>(min(L::NS - 2, s1 - 1 - s));
     const int ahead = s - s0 + L::NS - 1;
-    if (s0 + ahead < s1)
-      lp_load_stage<E, NW>(sg, s0 + ahead, lds + (ahead % L::NS) * L::STAGEB, ln.cb, ar, br, wave);
+    if (s0 + ahead < s1) load(ahead);
     lp_mfma_stage<E, NW>(lds + ((s - s0) % L::NS) * L::STAGEB, acc, lane, wm, wn);
     if constexpr (E::FLUSH) lp_flush(acc, accd);
   }
@@ -650,33 +657,13 @@ __global__ __launch_bounds__(LpGeo<NW>::NT) void k_omega_lp(const char* __restri
       }
 }
 
-// Zero n 16-bit values (the YL views, whose blocked K positions with an index past nv
-// k_mix never writes), 8 per thread and pass.
-__global__ void k_zero_pad(uint16_t* __restrict__ p, int64_t n) {
-  const int64_t n8 = n / 8;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n8;
-       e += (int64_t)gridDim.x * blockDim.x)
-    ((uint4*)p)[e] = make_uint4(0u, 0u, 0u, 0u);
-  for (int64_t e = n8 * 8 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n;
-       e += (int64_t)gridDim.x * blockDim.x)
-    p[e] = 0;
-}
-
-void launch_lp_zero_pad(void* YL, int64_t rows, int nv, hipStream_t st) {
-  if (nv % 8 == 0 || rows == 0) return;  // no position of the blocked K lies past nv
-  const int64_t n = rows * lp_kb_pitch(nv);
-  unsigned g = nblk(n / 8 + 1, 256);
-  if (g > 65536) g = 65536;
-  hipLaunchKernelGGL(k_zero_pad, dim3(g), dim3(256), 0, st, (uint16_t*)YL, n);
-}
-
 size_t lp_contract_g_bytes(int prec, int no, int nv) {
   const int P = prec == CC3_BF16X3 ? 2 : 3;
   return (size_t)P * no * (nv + no) * (size_t)lp_kb_pitch(nv) * 2;  // one of Gbc, Gcb
 }
 size_t lp_contract_cube_bytes(int prec, int nv) {
   const int P = prec == CC3_BF16X3 ? 2 : 3;
-  return (size_t)4 * P * nv * (size_t)lp_kb_pitch(nv) * 2;  // per triple
+  return (size_t)2 * P * (size_t)yl_piece(nv);  // per triple
 }
 
 // Split-BF16 pieces of the rows of Gbc or Gcb with K = (x, y) (padded rows in the source)
