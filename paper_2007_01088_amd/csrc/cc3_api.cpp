@@ -382,9 +382,7 @@ static int subset_from_blocks(cc3_ctx* c, const Plan& p, const Ws& w, HostArgs& 
                               int ntriples, HostArgs::Out& O1, HostArgs::Out& O2, hipStream_t st) {
   const int no = p.no, nv = p.nv;
   int rc;
-  launch_fill(w.Ot1, (int64_t)no * nv, 0.0, st);
-  launch_fill(w.Ot2, (int64_t)no * no * nv * nv, 0.0, st);
-  launch_fill(w.OtT, (int64_t)no * no * nv * nv, 0.0, st);
+  launch_loop_begin(nullptr, 1, w.Ot1, ot_count(p, w), t2, w.t2N, no, nv, st);
   if (ntriples > 0) {
     HIPCHK(hipMemcpyAsync(w.tri, triples, sizeof(int) * 3 * (size_t)ntriples,
                           hipMemcpyHostToDevice, st));
@@ -455,7 +453,7 @@ static int t3_from_blocks(const Plan& p, const Ws& w, HostArgs& hs, const double
   int rc;
   const int h[3] = {i, j, k};
   HIPCHK(hipMemcpyAsync(w.tri, h, sizeof h, hipMemcpyHostToDevice, st));
-  launch_t2N(t2, w.t2N, no, nv, st);
+  launch_loop_begin(nullptr, 1, nullptr, 0, t2, w.t2N, no, nv, st);
   if (p.prec == CC3_FP64) {
     launch_wbuild(t2, w.t2N, w.b, w.tri, 1, w.cubes[0], no, nv, true, st);
   } else {

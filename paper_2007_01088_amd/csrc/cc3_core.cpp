@@ -336,7 +336,7 @@ static void batch_range(int n, int nbatch, int g, int* t0, int* nb) {
   *nb = q + (g < r ? 1 : 0);
 }
 
-// Host copy of the device triple table (launch_triple_table): the restricted loop
+// Host copy of the device triple table (launch_loop_begin): the restricted loop
 // in lexicographic order, dealt round-robin over nbatch batches.
 static void host_triples(int no, int nbatch, std::vector<int>& t) {
   std::vector<int> lex;
@@ -361,8 +361,7 @@ int prepare_cholesky(Profiler* pf, const Plan& p, const Ws& w, const double* L, 
                      hipStream_t st) {
   {
     Timer tm(pf, st, FAM_T1, 0.0, 0.0);
-    launch_t1_transform(L, t1, w.cs, p.no, p.nv, p.nchol, st);
-    launch_fock(t1, w.cs, w.b.F, p.no, p.nv, p.nchol, st);
+    launch_t1_fock(L, t1, w.cs, w.b.F, p.no, p.nv, p.nchol, st);
   }
   {
     const double v = p.nv, o = p.no, J = p.nchol;
@@ -408,7 +407,6 @@ static int triple_loop_body(Runner& rn, Profiler* pf, const Plan& p, const Ws& w
                             const double* eps, const double* t2, const int* tri, const int* ht,
                             int n, hipStream_t st) {
   std::vector<int> kinds;
-  launch_t2N(t2, w.t2N, p.no, p.nv, st);
   if (p.prec != CC3_FP64) launch_lp_convert(t2, w.b, p.no, p.nv, w.lp, st);
   const bool lowp_contract = w.GbcX != nullptr;
   const int lpP = !lowp_contract || p.prec == CC3_FP32 ? 0 : p.prec == CC3_BF16X3 ? 2 : 3;
@@ -419,8 +417,10 @@ static int triple_loop_body(Runner& rn, Profiler* pf, const Plan& p, const Ws& w
   } else if (lowp_contract) {
     launch_lp_contract_convert(w.b, p.prec, p.no, p.nv, w.GbcX, w.GcbX, st);
   }
-  // PLAN_CALLER_STREAM: every batch on the caller's stream, no runner streams or events
-  const bool own = (p.flags & PLAN_CALLER_STREAM) != 0;
+  const int ngroups = (n + p.batch - 1) / p.batch;
+  // PLAN_CALLER_STREAM, or a single batch: on the caller's stream, without runner streams or
+  // the events that join them
+  const bool own = (p.flags & PLAN_CALLER_STREAM) != 0 || ngroups <= 1;
   if (!own) {
     HIPCHK(hipEventRecord(rn.ev_fork, st));
     for (int k = 0; k < NSTREAM; ++k) HIPCHK(hipStreamWaitEvent(rn.s[k], rn.ev_fork, 0));
@@ -432,7 +432,6 @@ static int triple_loop_body(Runner& rn, Profiler* pf, const Plan& p, const Ws& w
   static const int env_serial = env_int("CC3_SERIAL", 0);
   const int nstream =
       (own || env_serial || (p.flags & CC3_ONE_STREAM) || p.nv > 192) ? 1 : NSTREAM;
-  const int ngroups = (n + p.batch - 1) / p.batch;
   for (int nbatch = 0; nbatch < ngroups; ++nbatch) {
     int t0, nb;
     batch_range(n, ngroups, nbatch, &t0, &nb);
@@ -493,10 +492,7 @@ int residual_from_blocks(Runner& rn, Profiler* pf, const Plan& p, const Ws& w, c
                          const double* t2, double* omega1, double* omega2, bool accumulate,
                          hipStream_t st, const double* omega2_in) {
   const int no = p.no, nv = p.nv;
-  launch_fill(w.Ot1, (int64_t)no * nv, 0.0, st);
-  launch_fill(w.Ot2, (int64_t)no * no * nv * nv, 0.0, st);
-  launch_fill(w.OtT, (int64_t)no * no * nv * nv, 0.0, st);
-  launch_triple_table(w.tri, no, nbatches(p), st);
+  launch_loop_begin(w.tri, nbatches(p), w.Ot1, ot_count(p, w), t2, w.t2N, no, nv, st);
   std::vector<int> ht;
   host_triples(no, nbatches(p), ht);
   int rc = triple_loop(rn, pf, p, w, eps, t2, w.tri, ht.data(), p.ntri, st);
@@ -528,11 +524,7 @@ int packed_residuals(const std::vector<PackMember>& ms, int prec, PackJob* dev_j
     const int no = p.no, nv = p.nv;
     int rc;
     if (m.rebuild && (rc = prepare_cholesky(nullptr, p, m.w, m.L, m.t1, st))) return rc;
-    launch_fill(m.w.Ot1, (int64_t)no * nv, 0.0, st);
-    launch_fill(m.w.Ot2, (int64_t)no * no * nv * nv, 0.0, st);
-    launch_fill(m.w.OtT, (int64_t)no * no * nv * nv, 0.0, st);
-    launch_triple_table(m.w.tri, no, nbatches(p), st);
-    launch_t2N(m.t2, m.w.t2N, no, nv, st);
+    launch_loop_begin(m.w.tri, nbatches(p), m.w.Ot1, ot_count(p, m.w), m.t2, m.w.t2N, no, nv, st);
     if (prec != CC3_FP64) launch_lp_convert(m.t2, m.w.b, no, nv, m.w.lp, st);
     nsteps = std::max(nsteps, nbatches(p));
   }
@@ -608,23 +600,25 @@ static int jacobian_prep_body(Runner& rn, Profiler* pf, const Plan& p, const Ws&
     launch_fill(zv, (int64_t)nv * nv * nv * no, 0.0, st);
     launch_fill(zo, (int64_t)nv * no * no * no, 0.0, st);
   }
-  launch_triple_table(w.tri, no, nbatches(p), st);
+  launch_loop_begin(w.tri, nbatches(p), nullptr, 0, t2, w.t2N, no, nv, st);
   std::vector<int> ht, kinds;
   host_triples(no, nbatches(p), ht);
-  launch_t2N(t2, w.t2N, no, nv, st);
   if (p.prec != CC3_FP64) launch_lp_convert(t2, w.b, no, nv, w.lp, st);
-  HIPCHK(hipEventRecord(rn.ev_fork, st));
-  for (int k = 0; k < NSTREAM; ++k) HIPCHK(hipStreamWaitEvent(rn.s[k], rn.ev_fork, 0));
+  const int n = p.ntri;
+  const int ngroups = nbatches(p);
+  const bool own = ngroups <= 1;  // as in the residual loop
+  if (!own) {
+    HIPCHK(hipEventRecord(rn.ev_fork, st));
+    for (int k = 0; k < NSTREAM; ++k) HIPCHK(hipStreamWaitEvent(rn.s[k], rn.ev_fork, 0));
+  }
   static const int env_serial = env_int("CC3_SERIAL", 0);
   // one stream from nv = 192 on, as in the residual loop
   const int nstream = (env_serial || (p.flags & CC3_ONE_STREAM) || p.nv > 192) ? 1 : NSTREAM;
-  const int n = p.ntri;
-  const int ngroups = nbatches(p);
   for (int nbatch = 0; nbatch < ngroups; ++nbatch) {
     int t0, nb;
     batch_range(n, ngroups, nbatch, &t0, &nb);
     const int k = nbatch % nstream;
-    hipStream_t sk = rn.s[k];
+    hipStream_t sk = own ? st : rn.s[k];
     kinds.resize(nb);
     for (int t = 0; t < nb; ++t)
       kinds[t] = kind_of(ht[3 * (t0 + t)], ht[3 * (t0 + t) + 1], ht[3 * (t0 + t) + 2]);
@@ -656,11 +650,13 @@ static int jacobian_prep_body(Runner& rn, Profiler* pf, const Plan& p, const Ws&
       Timer tm(pf, sk, FAM_ZPREP, zprep_flops(no, nv, kinds.data(), nb) * ((double)nv / (nv + no)), 0.0);
       launch_zv(w.cubes[k], w.b, tb, nb, zv, no, nv, sk);
     }
-    HIPCHK(hipEventRecord(rn.ev_red[k], sk));
+    if (!own) HIPCHK(hipEventRecord(rn.ev_red[k], sk));
   }
-  for (int k = 0; k < NSTREAM; ++k) {
-    HIPCHK(hipEventRecord(rn.ev_done[k], rn.s[k]));
-    HIPCHK(hipStreamWaitEvent(st, rn.ev_done[k], 0));
+  if (!own) {
+    for (int k = 0; k < NSTREAM; ++k) {
+      HIPCHK(hipEventRecord(rn.ev_done[k], rn.s[k]));
+      HIPCHK(hipStreamWaitEvent(st, rn.ev_done[k], 0));
+    }
   }
   HIPCHK(hipGetLastError());
   return CC3_OK;

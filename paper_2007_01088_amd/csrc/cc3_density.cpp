@@ -203,15 +203,14 @@ extern "C" int cc3_transition_density(cc3_ctx* c, int no, int nv, int nchol, con
   HIPCHK(hipStreamSynchronize(st));  // the host table may go out of scope
   {
     Timer tm(pf, st, FAM_T1, 0.0, 0.0);
-    launch_t1_transform(L, t1, cs, no, nv, nchol, st);
-    launch_fock(t1, cs, F, no, nv, nchol, st);
+    launch_t1_fock(L, t1, cs, F, no, nv, nchol, st);
   }
   {
     const double fl = 2.0 * J * (2.0 * v * v * v * o + o * o * v * v + 2.0 * o * o * o * v);
     Timer tm(pf, st, FAM_BUILD, fl, 0.0);
     launch_build_density_blocks(cs, Gw, Go, Jo, Go3, Gl, gtmp, no, nv, nchol, st);
   }
-  launch_t2N(t2, t2N, no, nv, st);
+  launch_loop_begin(nullptr, 1, nullptr, 0, t2, t2N, no, nv, st);
   launch_d3_l2(l2, l2M, E, no, nv, st);
   launch_fill(Y, (int64_t)o * o * o * v, 0.0, st);
   if (!acc) {

@@ -103,6 +103,11 @@ Ws carve(const Plan& p, void* ws, const Blocks* external_blocks);
 size_t block_bytes(int no, int nv);
 Blocks carve_blocks(int no, int nv, void* base);
 
+// Doubles from Ot1 to the end of OtT: the three accumulators follow each other (carve)
+inline int64_t ot_count(const Plan& p, const Ws& w) {
+  return (w.OtT - w.Ot1) + (int64_t)p.no * p.no * p.nv * p.nv;
+}
+
 // ---- launch sequences ---------------------------------------------------------
 int prepare_cholesky(Profiler* pf, const Plan& p, const Ws& w, const double* L, const double* t1,
                      hipStream_t st);

@@ -189,10 +189,8 @@ void launch_wbuild_lp(const LpOperands& lp, const int* tri, int ntri, double* cu
 // ---- launchers (all enqueue on `st`) ----
 void launch_fill(double* p, int64_t n, double v, hipStream_t st);
 void launch_add(double* y, const double* x, int64_t n, hipStream_t st);  // y += x
-void launch_t1_transform(const double* L, const double* t1, const CholeskyScratch& cs, int no,
-                         int nv, int nJ, hipStream_t st);
-void launch_fock(const double* t1, const CholeskyScratch& cs, double* F, int no, int nv, int nJ,
-                 hipStream_t st);
+void launch_t1_fock(const double* L, const double* t1, const CholeskyScratch& cs, double* F, int no,
+                    int nv, int nJ, hipStream_t st);
 void launch_build_blocks(const CholeskyScratch& cs, const Blocks& b, int no, int nv, int nJ,
                          hipStream_t st);
 // The paper-order blocks into the internal layouts, in three parts: the
@@ -205,8 +203,9 @@ void launch_relayout_vv(const double* g_vvvo_y, const double* g_vvov_y, int y0, 
                         const Blocks& b, int no, int nv, hipStream_t st);
 void launch_gcb(const Blocks& b, int no, int nv, hipStream_t st);
 // The full triple table, the restricted loop dealt round-robin over nbatch batches.
-void launch_triple_table(int* tri, int no, int nbatch, hipStream_t st);
-void launch_t2N(const double* t2, double* t2N, int no, int nv, hipStream_t st);
+// The triple table in nbatch batches (unless tri is null), n zeros at Z and t2N
+void launch_loop_begin(int* tri, int nbatch, double* Z, int64_t n, const double* t2, double* t2N,
+                       int no, int nv, hipStream_t st);
 // t2N[p][y][x][l] = -t2[p][l][x][y], each (p, y) slab at the pitch t2n_pitch
 void launch_wbuild(const double* t2, const double* t2N, const Blocks& b, const int* tri, int ntri,
                    double* cubes, int no, int nv, bool all_terms, hipStream_t st);

@@ -3,6 +3,8 @@
 // integral-block build (FP64 MFMA GEMMs over the Cholesky index, writing the
 // internal layouts the triple loop streams), the re-layout of caller-given
 // blocks, the triple table, and the covariant back-transformation after it.
+#include <algorithm>
+
 #include "cc3_device.hpp"
 #include "cc3_internal.hpp"
 
@@ -41,27 +43,26 @@ void launch_add(double* y, const double* x, int64_t n, hipStream_t st) {
 //   Lt_bd = L_bd - sum_l t1[l][b] L_ld        Lt_lj = L_lj + sum_d L_ld t1[j][d]
 //   Lt_ck = L_ck + sum_d L_cd t1[k][d] - sum_l t1[l][c] Lt_lk      Lt_kc = L_kc
 // ---------------------------------------------------------------------------
-__global__ void k_t1_vv(const double* __restrict__ L, const double* __restrict__ t1,
-                        double* __restrict__ Lvv, int no, int nv) {
-  const int J = blockIdx.y;
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// First launch, one grid row per J: blocks of the vv part, blocks of the oo part (with the
+// copy of the ov block), and one for the sums of the Fock block,
+//   s_J = sum_ld t1[l][d] L_ld,  M_J[k][l] = sum_d L_kd t1[l][d].
+__device__ __forceinline__ void t1_vv(const double* __restrict__ LJ, const double* __restrict__ t1,
+                                      double* __restrict__ Lvv, int J, int bx, int no, int nv) {
+  const int64_t idx = (int64_t)bx * blockDim.x + threadIdx.x;
   if (idx >= (int64_t)nv * nv) return;
   const int b = (int)(idx / nv), d = (int)(idx % nv);
   const int nmo = no + nv;
-  const double* LJ = L + (int64_t)J * nmo * nmo;
   double v = LJ[(int64_t)(no + b) * nmo + no + d];
   for (int l = 0; l < no; ++l) v -= t1[(int64_t)l * nv + b] * LJ[(int64_t)l * nmo + no + d];
-  const int64_t base = (int64_t)J * nv * nv;
-  Lvv[base + (int64_t)b * nv + d] = v;
+  Lvv[(int64_t)J * nv * nv + idx] = v;
 }
 
-__global__ void k_t1_oo(const double* __restrict__ L, const double* __restrict__ t1,
-                        double* __restrict__ Loo, double* __restrict__ LooT,
-                        double* __restrict__ Lov, int no, int nv) {
-  const int J = blockIdx.y;
+__device__ __forceinline__ void t1_oo(const double* __restrict__ LJ, const double* __restrict__ t1,
+                                      double* __restrict__ Loo, double* __restrict__ LooT,
+                                      double* __restrict__ Lov, int J, int bx, int nblocks, int no,
+                                      int nv) {
   const int nmo = no + nv;
-  const double* LJ = L + (int64_t)J * nmo * nmo;
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+  const int idx = bx * blockDim.x + threadIdx.x;
   if (idx < no * no) {
     const int l = idx / no, j = idx % no;
     double v = LJ[(int64_t)l * nmo + j];
@@ -70,88 +71,20 @@ __global__ void k_t1_oo(const double* __restrict__ L, const double* __restrict__
     LooT[(int64_t)J * no * no + (int64_t)j * no + l] = v;
   }
   // untransformed ov block, Lov[J][k][c] = L_{k, no+c}
-  for (int e = idx; e < no * nv; e += gridDim.x * blockDim.x) {
+  for (int e = idx; e < no * nv; e += nblocks * blockDim.x) {
     const int k = e / nv, c = e % nv;
     Lov[(int64_t)J * no * nv + e] = LJ[(int64_t)k * nmo + no + c];
   }
 }
 
-// LvoT[J][k][c] for 16 consecutive c of one J.  The rows L_{no+c, no+d} and t1
-// pass through LDS in chunks of 64 d, so every global read is a row segment;
-// each sum keeps the order of the formula above (d ascending, then l).
-__global__ __launch_bounds__(256) void k_t1_vo(const double* __restrict__ L,
-                                               const double* __restrict__ t1,
-                                               const double* __restrict__ Loo,
-                                               double* __restrict__ LvoT, int no, int nv) {
-  constexpr int RC = 16, DC = 64, PER = (RC * 64 + 255) / 256;  // no <= 63
-  __shared__ double Ls[RC][DC + 1];
-  __shared__ double Ts[64][DC + 1];
-  const int J = blockIdx.y, c0 = blockIdx.x * RC, tid = threadIdx.x;
+__device__ __forceinline__ void fock_sm(const double* __restrict__ LJ,
+                                        const double* __restrict__ t1, double* __restrict__ s,
+                                        double* __restrict__ M, int J, int no, int nv) {
   const int nmo = no + nv;
-  const double* LJ = L + (int64_t)J * nmo * nmo;
-  double acc[PER];
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int e = tid + 256 * i, ci = e % RC, k = e / RC, c = c0 + ci;
-    acc[i] = (k < no && c < nv) ? LJ[(int64_t)(no + c) * nmo + k] : 0.0;
-  }
-  for (int d0 = 0; d0 < nv; d0 += DC) {
-    const int dn = min(DC, nv - d0);
-    for (int e = tid; e < RC * DC; e += 256) {
-      const int ci = e / DC, dd = e % DC, c = c0 + ci;
-      Ls[ci][dd] = (c < nv && dd < dn) ? LJ[(int64_t)(no + c) * nmo + no + d0 + dd] : 0.0;
-    }
-    for (int e = tid; e < no * DC; e += 256) {
-      const int k = e / DC, dd = e % DC;
-      Ts[k][dd] = dd < dn ? t1[(int64_t)k * nv + d0 + dd] : 0.0;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int e = tid + 256 * i, ci = e % RC, k = e / RC;
-      if (k < no) {
-        double v = acc[i];
-        for (int dd = 0; dd < dn; ++dd) v += Ls[ci][dd] * Ts[k][dd];
-        acc[i] = v;
-      }
-    }
-    __syncthreads();
-  }
-  const double* LooJ = Loo + (int64_t)J * no * no;
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int e = tid + 256 * i, ci = e % RC, k = e / RC, c = c0 + ci;
-    if (k >= no || c >= nv) continue;
-    double v = acc[i];
-    for (int l = 0; l < no; ++l) v -= t1[(int64_t)l * nv + c] * LooJ[(int64_t)l * no + k];
-    LvoT[(int64_t)J * no * nv + (int64_t)k * nv + c] = v;
-  }
-}
-
-void launch_t1_transform(const double* L, const double* t1, const CholeskyScratch& cs, int no,
-                         int nv, int nJ, hipStream_t st) {
-  hipLaunchKernelGGL(k_t1_vv, dim3(nblk((int64_t)nv * nv, 256), nJ), dim3(256), 0, st, L, t1,
-                     cs.Lvv, no, nv);
-  int m = no * no > no * nv ? no * no : no * nv;
-  hipLaunchKernelGGL(k_t1_oo, dim3(nblk(m, 256), nJ), dim3(256), 0, st, L, t1, cs.Loo, cs.LooT,
-                     cs.Lov, no, nv);
-  hipLaunchKernelGGL(k_t1_vo, dim3(nblk(nv, 16), nJ), dim3(256), 0, st, L, t1, cs.Loo, cs.LvoT,
-                     no, nv);
-}
-
-// ---------------------------------------------------------------------------
-// Fock ov block of the T1-transformed Hamiltonian (canonical reference):
-//   F_kc = sum_ld t1[l][d] (2 g_kcld - g_kdlc),  g_kcld = sum_J L_kc L_ld
-//        = sum_J [ 2 s_J L_kc - sum_l M_J[k][l] L_lc ],
-//   s_J = sum_ld t1[l][d] L_ld,  M_J[k][l] = sum_d L_kd t1[l][d].
-// ---------------------------------------------------------------------------
-__global__ void k_fock_sm(const double* __restrict__ t1, const double* __restrict__ Lov,
-                          double* __restrict__ s, double* __restrict__ M, int no, int nv) {
-  const int J = blockIdx.x;
-  const double* LJ = Lov + (int64_t)J * no * nv;
   __shared__ double red[256];
   double acc = 0.0;
-  for (int e = threadIdx.x; e < no * nv; e += blockDim.x) acc += t1[e] * LJ[e];
+  for (int e = threadIdx.x; e < no * nv; e += blockDim.x)
+    acc += t1[e] * LJ[(int64_t)(e / nv) * nmo + no + e % nv];
   red[threadIdx.x] = acc;
   __syncthreads();
   for (int w = blockDim.x / 2; w > 0; w >>= 1) {
@@ -162,21 +95,71 @@ __global__ void k_fock_sm(const double* __restrict__ t1, const double* __restric
   for (int e = threadIdx.x; e < no * no; e += blockDim.x) {
     const int k = e / no, l = e % no;
     double v = 0.0;
-    for (int d = 0; d < nv; ++d) v += LJ[(int64_t)k * nv + d] * t1[(int64_t)l * nv + d];
+    for (int d = 0; d < nv; ++d) v += LJ[(int64_t)k * nmo + no + d] * t1[(int64_t)l * nv + d];
     M[(int64_t)J * no * no + e] = v;
   }
 }
 
+__global__ __launch_bounds__(256) void k_t1_first(const double* __restrict__ L,
+                                                  const double* __restrict__ t1,
+                                                  CholeskyScratch cs, int nvv, int noo, int no,
+                                                  int nv) {
+  const int J = blockIdx.y, bx = blockIdx.x;
+  const double* LJ = L + (int64_t)J * (no + nv) * (no + nv);
+  if (bx < nvv) t1_vv(LJ, t1, cs.Lvv, J, bx, no, nv);
+  else if (bx < nvv + noo) t1_oo(LJ, t1, cs.Loo, cs.LooT, cs.Lov, J, bx - nvv, noo, no, nv);
+  else fock_sm(LJ, t1, cs.s, cs.M, J, no, nv);
+}
+
+// LvoT[J][k][c] for 16 consecutive c of one J.  The rows L_{no+c, no+d} and t1
+// pass through LDS in chunks of 64 d, so every global read is a row segment;
+// each sum keeps the order of the formula above (d ascending, then l).
+constexpr int VO_RC = 16, VO_DC = 64;
+__device__ __forceinline__ void t1_vo(const double* __restrict__ L, const double* __restrict__ t1,
+                                      const double* __restrict__ Loo, double* __restrict__ LvoT,
+                                      double (&Ls)[VO_RC][VO_DC + 1], double (&Ts)[64][VO_DC + 1],
+                                      int J, int bx, int no, int nv) {
+  constexpr int RC = VO_RC, DC = VO_DC;
+  const int c0 = bx * RC, tid = threadIdx.x;
+  const int nmo = no + nv;
+  const double* LJ = L + (int64_t)J * nmo * nmo;
+  const int ci = tid % RC, k = tid / RC, c = c0 + ci;  // no <= 63: one sum per thread
+  double v = (k < no && c < nv) ? LJ[(int64_t)(no + c) * nmo + k] : 0.0;
+  for (int d0 = 0; d0 < nv; d0 += DC) {
+    const int dn = min(DC, nv - d0);
+    for (int e = tid; e < RC * DC; e += 1024) {
+      const int r = e / DC, dd = e % DC;
+      Ls[r][dd] = (c0 + r < nv && dd < dn) ? LJ[(int64_t)(no + c0 + r) * nmo + no + d0 + dd] : 0.0;
+    }
+    for (int e = tid; e < no * DC; e += 1024) {
+      const int r = e / DC, dd = e % DC;
+      Ts[r][dd] = dd < dn ? t1[(int64_t)r * nv + d0 + dd] : 0.0;
+    }
+    __syncthreads();
+    if (k < no)
+      for (int dd = 0; dd < dn; ++dd) v += Ls[ci][dd] * Ts[k][dd];
+    __syncthreads();
+  }
+  const double* LooJ = Loo + (int64_t)J * no * no;
+  if (k >= no || c >= nv) return;
+  for (int l = 0; l < no; ++l) v -= t1[(int64_t)l * nv + c] * LooJ[(int64_t)l * no + k];
+  LvoT[(int64_t)J * no * nv + (int64_t)k * nv + c] = v;
+}
+
+// ---------------------------------------------------------------------------
+// Fock ov block of the T1-transformed Hamiltonian (canonical reference):
+//   F_kc = sum_ld t1[l][d] (2 g_kcld - g_kdlc),  g_kcld = sum_J L_kc L_ld
+//        = sum_J [ 2 s_J L_kc - sum_l M_J[k][l] L_lc ],
+//   s_J = sum_ld t1[l][d] L_ld,  M_J[k][l] = sum_d L_kd t1[l][d].
+// ---------------------------------------------------------------------------
 // F[k][c] for 64 consecutive c of one k; sixteen slices of the Cholesky index
 // summed through LDS in a fixed order.
-__global__ __launch_bounds__(1024) void k_fock(const double* __restrict__ Lov,
-                                               const double* __restrict__ s,
-                                               const double* __restrict__ M, double* __restrict__ F,
-                                               int no, int nv, int nJ) {
+__device__ __forceinline__ void fock(const double* __restrict__ Lov, const double* __restrict__ s,
+                                     const double* __restrict__ M, double* __restrict__ F,
+                                     double* __restrict__ red, int k, int by, int no, int nv,
+                                     int nJ) {
   constexpr int NS = 16;
-  __shared__ double red[64 * NS];
-  const int k = blockIdx.x;
-  const int c = blockIdx.y * 64 + (threadIdx.x & 63);
+  const int c = by * 64 + (threadIdx.x & 63);
   const int js = threadIdx.x >> 6;
   double v = 0.0;
   if (c < nv) {
@@ -197,11 +180,30 @@ __global__ __launch_bounds__(1024) void k_fock(const double* __restrict__ Lov,
   if (js == 0 && c < nv) F[(int64_t)k * nv + c] = red[threadIdx.x];
 }
 
-void launch_fock(const double* t1, const CholeskyScratch& cs, double* F, int no, int nv, int nJ,
-                 hipStream_t st) {
-  hipLaunchKernelGGL(k_fock_sm, dim3(nJ), dim3(256), 0, st, t1, cs.Lov, cs.s, cs.M, no, nv);
-  hipLaunchKernelGGL(k_fock, dim3(no, nblk(nv, 64)), dim3(1024), 0, st, cs.Lov, cs.s, cs.M, F, no,
-                     nv, nJ);
+// Second launch: the Fock blocks first (they sum over J), then LvoT.  Two launches instead of
+// five, since each is a few microseconds of latency at 4/20 (MEASURED, with the one-launch
+// start of the triple loop and a single batch on the caller's stream: 166 -> 99 us a call).
+__global__ __launch_bounds__(1024) void k_t1_second(const double* __restrict__ L,
+                                                    const double* __restrict__ t1,
+                                                    CholeskyScratch cs, double* __restrict__ F,
+                                                    int no, int nv, int nJ) {
+  __shared__ double Ls[VO_RC][VO_DC + 1];
+  __shared__ double Ts[64][VO_DC + 1];
+  const int nf = no * ((nv + 63) / 64), nc = (nv + VO_RC - 1) / VO_RC;
+  const int bx = blockIdx.x;
+  if (bx < nf) fock(cs.Lov, cs.s, cs.M, F, &Ls[0][0], bx % no, bx / no, no, nv, nJ);
+  else t1_vo(L, t1, cs.Loo, cs.LvoT, Ls, Ts, (bx - nf) / nc, (bx - nf) % nc, no, nv);
+}
+static_assert(VO_RC * (VO_DC + 1) >= 64 * 16, "the Fock sums use Ls");
+
+void launch_t1_fock(const double* L, const double* t1, const CholeskyScratch& cs, double* F, int no,
+                    int nv, int nJ, hipStream_t st) {
+  const int nvv = (int)nblk((int64_t)nv * nv, 256);
+  const int noo = (int)nblk(no * std::max(no, nv), 256);
+  hipLaunchKernelGGL(k_t1_first, dim3(nvv + noo + 1, nJ), dim3(256), 0, st, L, t1, cs, nvv, noo, no,
+                     nv);
+  hipLaunchKernelGGL(k_t1_second, dim3(no * nblk(nv, 64) + nblk(nv, VO_RC) * nJ), dim3(1024), 0, st,
+                     L, t1, cs, F, no, nv, nJ);
 }
 
 // ---------------------------------------------------------------------------
@@ -558,9 +560,7 @@ void launch_relayout_vv(const double* g_vvvo_y, const double* g_vvov_y, int y0, 
 // a batch spread evenly over the first occupied index, which the
 // output-stationary kernels are parallel over.
 // ---------------------------------------------------------------------------
-__global__ void k_triples(int* __restrict__ tri, int no, int nbatch) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= no * no * no) return;
+__device__ __forceinline__ void triple_entry(int* __restrict__ tri, int e, int no, int nbatch) {
   const int i = e / (no * no), j = (e / no) % no, k = e % no;
   if (!(i >= j && j >= k) || (i == j && j == k)) return;
   const int n = no * (no + 1) * (no + 2) / 6 - no;
@@ -572,9 +572,28 @@ __global__ void k_triples(int* __restrict__ tri, int no, int nbatch) {
   tri[3 * pos + 2] = k;
 }
 
-void launch_triple_table(int* tri, int no, int nbatch, hipStream_t st) {
-  hipLaunchKernelGGL(k_triples, dim3(nblk((int64_t)no * no * no, 256)), dim3(256), 0, st, tri, no,
-                     nbatch < 1 ? 1 : nbatch);
+// What a triple loop starts from, in one launch: the triple table (tri, unless null), zeros
+// (n of them at Z) and t2N[p][y][x][l] = -t2[p][l][x][y], the slab (p, y) at t2n_pitch.
+__global__ void k_loop_begin(int* __restrict__ tri, int nbatch, double* __restrict__ Z, int64_t n,
+                             const double* __restrict__ t2, double* __restrict__ t2N, int no,
+                             int nv) {
+  const int64_t nvl = nv, n2 = (int64_t)no * no * nvl * nvl, stride = (int64_t)gridDim.x * blockDim.x;
+  const int64_t e0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (tri && e0 < no * no * no) triple_entry(tri, (int)e0, no, nbatch);
+  for (int64_t e = e0; e < n2; e += stride) {
+    const int l = (int)(e % no), x = (int)((e / no) % nvl), y = (int)((e / (no * nvl)) % nvl);
+    const int p = (int)(e / (no * nvl * nvl));
+    t2N[((int64_t)p * nvl + y) * t2n_pitch(no, nv) + (int64_t)x * no + l] =
+        -t2[(((int64_t)p * no + l) * nvl + x) * nvl + y];
+  }
+  for (int64_t e = e0; e < n; e += stride) Z[e] = 0.0;
+}
+
+void launch_loop_begin(int* tri, int nbatch, double* Z, int64_t n, const double* t2, double* t2N,
+                       int no, int nv, hipStream_t st) {
+  const int64_t m = std::max((int64_t)no * no * nv * nv, (int64_t)no * no * no);
+  hipLaunchKernelGGL(k_loop_begin, dim3(nblk(m, 256)), dim3(256), 0, st, tri, nbatch < 1 ? 1 : nbatch,
+                     Z, n, t2, t2N, no, nv);
 }
 
 void launch_set_triples(int* tri_dev, const int* host_tri, int n, hipStream_t st) {

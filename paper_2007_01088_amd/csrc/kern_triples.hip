@@ -381,20 +381,6 @@ void launch_wbuild_f32(const LpOperands& lp, const int* tri, int ntri, double* c
 }
 
 // t2N[p][y][x][l] = -t2[p][l][x][y]
-__global__ void k_t2N(const double* __restrict__ t2, double* __restrict__ t2N, int no, int nv) {
-  const int64_t nvl = nv, n = (int64_t)no * no * nvl * nvl;
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= n) return;
-  const int l = (int)(e % no), x = (int)((e / no) % nvl), y = (int)((e / (no * nvl)) % nvl);
-  const int p = (int)(e / (no * nvl * nvl));
-  t2N[((int64_t)p * nvl + y) * t2n_pitch(no, nv) + (int64_t)x * no + l] = -t2[(((int64_t)p * no + l) * nvl + x) * nvl + y];
-}
-
-void launch_t2N(const double* t2, double* t2N, int no, int nv, hipStream_t st) {
-  const int64_t n = (int64_t)no * no * nv * nv;
-  hipLaunchKernelGGL(k_t2N, dim3(nblk(n, 256)), dim3(256), 0, st, t2, t2N, no, nv);
-}
-
 // ---------------------------------------------------------------------------
 // Mix: X, tau, tau~ on the S3 orbit of an 8x8x8 block triple (A <= B <= C).
 // ---------------------------------------------------------------------------
@@ -1243,6 +1229,9 @@ __device__ inline void u_view(int pi, int nv, int rp, int& slot, int& sbb, int& 
 // in the MFMA layout directly (16 consecutive a per row of c); views with c
 // contiguous are loaded along c (4 rows of 16 consecutive c per instruction) and
 // transposed through a wavefront-private LDS tile.
+// WS > 1: the workgroup has 4 WS wavefronts; 1, 2 or 4 of them lie side by side over a and
+// the others take shares of the (pair, step) loop, added in share order: a small launch
+// is one chain of loads per wavefront (at 4/20 28 -> 14 us, at 6/45 40 -> 28 us).
 // the view of U_pi as (column m, fixed index b, contracted c) in TT[x][y][z]
 __device__ inline void oo_view(int pi, int nv, int rp, int& sbb, int& sm, int& sk) {
   const int pl = nv * rp;
@@ -1255,7 +1244,17 @@ __device__ inline void oo_view(int pi, int nv, int rp, int& sbb, int& sm, int& s
     default: sbb = pl; sm = 1; sk = rp; break;  // TT[b][c][a]
   }
 }
-template <int FNO>
+// SEQ: the packed form, where a wavefront takes the shares in turn: the sums of the call alone.
+// wavefronts side by side over a in the form with shares, and its shares (1: the other form).
+// Shares where fewer than 640 workgroups run (no <= 16, so that 16 wavefronts have the
+// registers).  MEASURED, calls with / without: 4/20 (80) 84 / 99 us, 5/30 (150) 130 / 156,
+// 6/45 (276) 461 / 506, 8/64 (512) 1593 / 1633, 12/60 (720) 3.82 / 3.79 ms, 3/140 (1260)
+// 1.459 / 1.436.
+__host__ __device__ inline int oo_waves_a(int nv) { return nv <= 16 ? 1 : nv <= 32 ? 2 : 4; }
+__host__ __device__ inline int oo_shares(int no, int nv) {
+  return no <= 16 && ((nv + 1) / 2) * ((nv + 63) / 64) * no * 2 < 640 ? 16 / oo_waves_a(nv) : 1;
+}
+template <int FNO, int WS, bool SEQ>
 __device__ __forceinline__ void omega_oo_body(const double* __restrict__ cubes,
                                               const double* __restrict__ Hs,
                                               const int* __restrict__ tri, int ntri,
@@ -1263,15 +1262,21 @@ __device__ __forceinline__ void omega_oo_body(const double* __restrict__ cubes,
                                               double* __restrict__ OtT, int no, int nv,
                                               int tiles_a, int bx, int by, int form) {
   constexpr int NB = 2;
+  // per wavefront: 16 rows a x 16 c (+1 pad) of each b; with WS its share's sums
+  constexpr int LT = WS > 1 && NB * FNO * 256 > NB * 16 * 17 ? NB * FNO * 256 : NB * 16 * 17;
+  __shared__ double lts[4 * WS][LT];
   __shared__ int lz[PLIST_MAX], lqr[PLIST_MAX], cz[LIST_SCRATCH];
   double* __restrict__ Out = form ? Ot2 : OtT;
-  __shared__ double lt[4][NB][16][17];  // per wavefront: 16 rows a x 16 c (+1 pad)
   const int p = by;
   const int bp = bx / tiles_a;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int a0 = (bx % tiles_a) * 64 + 16 * wave;
+  const int wa = WS > 1 ? oo_waves_a(nv) : 4;  // wavefronts over a
+  const int share = wave / wa;
+  const int shares = WS > 1 ? 4 * WS / wa : SEQ ? oo_shares(no, nv) : 1;
+  const int a0 = (bx % tiles_a) * 16 * wa + 16 * (wave % wa);
+  double (*lt)[16][17] = (double (*)[16][17])lts[wave];
   const int n = list_pairs(tri, ntri, p, -1, form ? 0x18u : 0x27u, no, lz, lqr, cz);
-  if (n == 0 || a0 >= nv) return;  // no workgroup barrier follows
+  if (n == 0 || (WS == 1 && a0 >= nv)) return;  // no workgroup barrier follows
   const int m = lane & 15, kq = lane >> 4;
   int bb[NB];
 #pragma unroll
@@ -1285,7 +1290,6 @@ __device__ __forceinline__ void omega_oo_body(const double* __restrict__ cubes,
   // flattened (pair, 16-c step) loop with the next step's loads issued before
   // the current step's MFMAs
   const int cs = (nv + 15) / 16;
-  const int nit = n * cs;
   // Elements with c past nv load a valid element (c clamped) and are zeroed when they
   // are used (cm: bit i or tt set for c < nv), so that the next step's loads stay in
   // flight over the current step's MFMAs.
@@ -1336,12 +1340,12 @@ __device__ __forceinline__ void omega_oo_body(const double* __restrict__ cubes,
 #pragma unroll
       for (int j = 0; j < NB; ++j)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) lt[wave][j][4 * i + kq][m] = cm ? uu[j][i] : 0.0;
+        for (int i = 0; i < 4; ++i) lt[j][4 * i + kq][m] = cm ? uu[j][i] : 0.0;
       __builtin_amdgcn_wave_barrier();
 #pragma unroll
       for (int j = 0; j < NB; ++j)
 #pragma unroll
-        for (int tt = 0; tt < 4; ++tt) x[j][tt] = lt[wave][j][m][4 * kq + tt];
+        for (int tt = 0; tt < 4; ++tt) x[j][tt] = lt[j][m][4 * kq + tt];
       __builtin_amdgcn_wave_barrier();
     } else {
 #pragma unroll
@@ -1357,14 +1361,56 @@ __device__ __forceinline__ void omega_oo_body(const double* __restrict__ cubes,
         for (int f = 0; f < FNO; ++f)
           acc[j][f] = __builtin_amdgcn_mfma_f64_16x16x4f64(hh[f][tt], x[j][tt], acc[j][f], 0, 0, 0);
   };
-  load(0, u[0], h[0], cc1[0], cm1[0]);
-  for (int it = 0; it < nit; it += 2) {
-    if (it + 1 < nit) load(it + 1, u[1], h[1], cc1[1], cm1[1]);
-    mma(u[0], h[0], cc1[0], cm1[0]);
-    if (it + 1 < nit) {
-      if (it + 2 < nit) load(it + 2, u[0], h[0], cc1[0], cm1[0]);
-      mma(u[1], h[1], cc1[1], cm1[1]);
+  auto run = [&](int sh) __attribute__((always_inline)) {  // one share of the loop into acc
+    const int it0 = n * cs * sh / shares, nit = n * cs * (sh + 1) / shares;
+    if (it0 < nit) load(it0, u[0], h[0], cc1[0], cm1[0]);
+    for (int it = it0; it < nit; it += 2) {
+      if (it + 1 < nit) load(it + 1, u[1], h[1], cc1[1], cm1[1]);
+      mma(u[0], h[0], cc1[0], cm1[0]);
+      if (it + 1 < nit) {
+        if (it + 2 < nit) load(it + 2, u[0], h[0], cc1[0], cm1[0]);
+        mma(u[1], h[1], cc1[1], cm1[1]);
+      }
     }
+  };
+  if constexpr (!SEQ) {
+    if (a0 < nv) run(WS > 1 ? share : 0);
+  } else {
+    d4v tot[NB][FNO];
+    for (int sh = 0; sh < shares; ++sh) {
+      run(sh);
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int f = 0; f < FNO; ++f) {
+          tot[j][f] = sh == 0 ? acc[j][f] : tot[j][f] + acc[j][f];
+          acc[j][f] = d4v{0.0, 0.0, 0.0, 0.0};
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int f = 0; f < FNO; ++f) acc[j][f] = tot[j][f];
+  }
+  if constexpr (WS > 1) {
+    if (share > 0) {
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int f = 0; f < FNO; ++f)
+#pragma unroll
+          for (int rr = 0; rr < 4; ++rr) lts[wave][((j * FNO + f) * 4 + rr) * 64 + lane] = acc[j][f][rr];
+    }
+    __syncthreads();
+    if (share > 0) return;
+    for (int h = 1; h < shares; ++h)
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int f = 0; f < FNO; ++f)
+#pragma unroll
+          for (int rr = 0; rr < 4; ++rr)
+            acc[j][f][rr] += lts[wave + h * wa][((j * FNO + f) * 4 + rr) * 64 + lane];
   }
   const int ac = a0 + m;
 #pragma unroll
@@ -1381,14 +1427,14 @@ __device__ __forceinline__ void omega_oo_body(const double* __restrict__ cubes,
   }
 }
 
-template <int FNO>
-__global__ __launch_bounds__(256) void k_omega_oo(const double* __restrict__ cubes,
-                                                  const double* __restrict__ Hs,
-                                                  const int* __restrict__ tri, int ntri,
-                                                  double* __restrict__ Ot2,
-                                                  double* __restrict__ OtT, int no, int nv,
-                                                  int tiles_a) {
-  omega_oo_body<FNO>(cubes, Hs, tri, ntri, Ot2, OtT, no, nv, tiles_a, blockIdx.x, blockIdx.y,
+template <int FNO, int WS>
+__global__ __launch_bounds__(256 * WS) void k_omega_oo(const double* __restrict__ cubes,
+                                                       const double* __restrict__ Hs,
+                                                       const int* __restrict__ tri, int ntri,
+                                                       double* __restrict__ Ot2,
+                                                       double* __restrict__ OtT, int no, int nv,
+                                                       int tiles_a) {
+  omega_oo_body<FNO, WS, false>(cubes, Hs, tri, ntri, Ot2, OtT, no, nv, tiles_a, blockIdx.x, blockIdx.y,
                      blockIdx.z);
 }
 
@@ -1723,19 +1769,16 @@ void launch_g_to_f32(const double* src, float* dst, int64_t rows, int nv, hipStr
 void launch_omega_oo(const double* cubes, const Blocks& b, const int* tri, int ntri, double* Ot2,
                      double* OtT, int no, int nv, hipStream_t st) {
   const int ta = (nv + 63) / 64;
-  const dim3 grid(((nv + 1) / 2) * ta, no, 2), block(256);
-  if (no <= 16)
-    hipLaunchKernelGGL(k_omega_oo<1>, grid, block, 0, st, cubes, b.Hs, tri, ntri, Ot2, OtT, no, nv,
+  const dim3 grid(((nv + 1) / 2) * ta, no, 2);
+  auto run = [&](auto* kernel, unsigned threads) {
+    hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, st, cubes, b.Hs, tri, ntri, Ot2, OtT, no, nv,
                        ta);
-  else if (no <= 32)
-    hipLaunchKernelGGL(k_omega_oo<2>, grid, block, 0, st, cubes, b.Hs, tri, ntri, Ot2, OtT, no, nv,
-                       ta);
-  else if (no <= 48)
-    hipLaunchKernelGGL(k_omega_oo<3>, grid, block, 0, st, cubes, b.Hs, tri, ntri, Ot2, OtT, no, nv,
-                       ta);
-  else
-    hipLaunchKernelGGL(k_omega_oo<4>, grid, block, 0, st, cubes, b.Hs, tri, ntri, Ot2, OtT, no, nv,
-                       ta);
+  };
+  if (oo_shares(no, nv) > 1) run(k_omega_oo<1, 4>, 1024);
+  else if (no <= 16) run(k_omega_oo<1, 1>, 256);
+  else if (no <= 32) run(k_omega_oo<2, 1>, 256);
+  else if (no <= 48) run(k_omega_oo<3, 1>, 256);
+  else run(k_omega_oo<4, 1>, 256);
 }
 
 void launch_reduce(const int* tri, int ntri, const double* Pvv, double* Ot1, double* Ot2, int no,
@@ -1810,7 +1853,7 @@ __global__ __launch_bounds__(256) void k_pack_omega_oo(const PackJob* __restrict
     const unsigned local = item - J.first[PK_OO];
     const int ta = (J.nv + 63) / 64;
     const unsigned gx = (unsigned)((J.nv + 1) / 2) * ta;
-    omega_oo_body<FNO>(J.cubes, J.Hs, J.tri, J.ntri, J.Ot2, J.OtT, J.no, J.nv, ta,
+    omega_oo_body<FNO, 1, true>(J.cubes, J.Hs, J.tri, J.ntri, J.Ot2, J.OtT, J.no, J.nv, ta,
                        (int)(local % gx), (int)((local / gx) % J.no), (int)(local / (gx * J.no)));
     __syncthreads();
   }
