@@ -53,6 +53,9 @@ __device__ inline BufRsrc buf_rsrc_n(const E* base, int64_t n) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<E*>(base), 0,
                                            bytes > 0x7fffffff ? 0x7fffffff : (int)bytes, 0x00020000);
 }
+__device__ inline double buf_load_f64_at(BufRsrc r, unsigned voff, unsigned soff) {
+  return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (int)voff, (int)soff, 0));
+}
 template <class V>
 __device__ inline V buf_load_16(BufRsrc r, unsigned voff, unsigned soff) {
   return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, 0));

@@ -1195,7 +1195,8 @@ __device__ inline int list_pairs(const int* __restrict__ tri, int ntri, int p, i
 #define LIST_SCRATCH 16
 
 // The view of U_pi[a, b, c] at fixed b as a strided (a, c) matrix: base + b * sbb, (sm, sk)
-// (the Jacobian preparation, which keeps tau~T too), in the cubes [x][y][z] with the row pitch rp (x stride nv rp, y stride rp).
+// (k_zv, for which the mix writes tau~T too), in the cubes [x][y][z] with the row pitch rp (x
+// stride nv rp, y stride rp).
 __device__ inline void u_view(int pi, int nv, int rp, int& slot, int& sbb, int& sm, int& sk) {
   const int pl = nv * rp;
   switch (pi) {
@@ -1520,106 +1521,251 @@ static dim3 reduce_grid(int no, int nv) {
 //   Zo[a][q][p][l] += sum_{bc} U[a,b,c] g_{lbrc}     (g_{lbrc} = Jo[l][r][b][c])
 // ---------------------------------------------------------------------------
 
-// Zv, output-stationary: one workgroup per (p, b, 128 x 128 tile of (a, d)) sums the
-// batch's (triple, permutation) pairs with that p, in batch order, over c, and
-// subtracts the result from Zv (read-modify-write; the batches run in order).
-typedef TileCfg<4, 2, 2, 4, 16> ZvCfg;
-
-__global__ __launch_bounds__(ZvCfg::NT) void k_zv(const double* __restrict__ cubes,
-                                                  const double* __restrict__ Jo,
-                                                  const int* __restrict__ tri, int ntri,
-                                                  double* __restrict__ Zv, int no, int nv,
-                                                  int tiles_m, int tiles_n) {
-  typedef ZvCfg T;
-  __shared__ double lds[T::LDS_DOUBLES];
+// Zv, output-stationary on wave tiles: one wavefront per (p, b, FM x FN blocks of (a, d))
+// sums the batch's (triple, permutation) pairs with that p, in batch order, over c and
+// subtracts the sum from Zv (read-modify-write; the batches run in order).  Units of 8 c, two
+// in flight, no LDS; lane (r16, kq) holds c = 2 kq + h of row r16 of each block, loaded 8 bytes
+// at a time from the views of U, which have c or a contiguous (one form for both: a loop for
+// each kind doubled the registers), and 16 bytes from the rows of Jo.  Past c = nv the U
+// operand is zero (an offset outside the resource); the unpadded rows of Jo go on in the next.
+// Bound by the FP64 MFMAs.  Against 128 x 128 tiles through LDS with a barrier per 16 c, at
+// 12/120: 2.42 -> 1.91 ms per batch of 32 triples (beside the other stream's kernels; 1.1 ms of
+// MFMA), the call 43.5 -> 40.8 ms; with k_zo, 20/64 60.7 -> 21.5 ms.
+template <int FM, int FN>
+__global__ __launch_bounds__(WNT, shape_waves(FM, FN)) void k_zv(
+    const double* __restrict__ cubes, const double* __restrict__ Jo, const int* __restrict__ tri,
+    int ntri, double* __restrict__ Zv, int no, int nv, int tiles_m, int tiles_n) {
   __shared__ int lz[PLIST_MAX], lqr[PLIST_MAX], cz[LIST_SCRATCH];
-  const int p = blockIdx.y;
-  const int tpp = tiles_m * tiles_n;
-  const int b = blockIdx.x / tpp, tile = blockIdx.x % tpp;
-  const int m0 = (tile / tiles_n) * T::BM, n0 = (tile % tiles_n) * T::BN;
-  const int n = list_pairs(tri, ntri, p, -1, 0x3fu, no, lz, lqr, cz);
-  if (n == 0) return;
-  const int64_t nvl = nv, nv2 = nvl * nvl;
-  const int cs = (nv + T::BK - 1) / T::BK;
-  auto ops = [&](int s, Opnd& A, Opnd& B, int& k0) {
-    const int t = s / cs;
-    k0 = (s % cs) * T::BK;
-    const int zp = lz[t], z = zp / 6, pi = zp % 6;
-    int slot, sbb, sm, sk;
-    u_view(pi, nv, cube_pitch(nv), slot, sbb, sm, sk);
-    A = make_opnd(cubes + ((int64_t)z * NSLOT + slot) * cube_slot(nv) + (int64_t)b * sbb, sm, sk,
-                  nv, nv, sm == 1);
-    B = make_opnd(Jo + (int64_t)lqr[t] * nv2, nv, 1, nv, nv, false);  // rows d, k = c
+  // the wave tiles of one p: column tiles fastest, then row tiles, then b
+  const int per = nv * tiles_m * tiles_n, wgs = (per + 3) / 4;
+  const unsigned wg = xcd_item(blockIdx.x, gridDim.x, (unsigned)(tiles_m * tiles_n));
+  const int p = (int)(wg / (unsigned)wgs);
+  const int n = __builtin_amdgcn_readfirstlane(list_pairs(tri, ntri, p, -1, 0x3fu, no, lz, lqr, cz));
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int item = (int)(wg % (unsigned)wgs) * 4 + wave;
+  if (n == 0 || item >= per) return;  // no barrier follows
+  const int n0 = item % tiles_n * (FN * 16), m0 = item / tiles_n % tiles_m * (FM * 16);
+  const int b = item / (tiles_n * tiles_m);
+  const int lane = threadIdx.x & 63, r16 = lane & 15, kq = lane >> 4;
+  const int rp = cube_pitch(nv), ux = rp / 8;
+  const int64_t css = cube_slot(nv), nv2 = (int64_t)nv * nv, nj = (int64_t)no * no * nv2;
+  // the pair being loaded: its operands at the next unit, elements left in their arrays
+  const double *pa, *pb;
+  int64_t na, nb;
+  int sm, sk, t = 0, uu = 0;
+  auto open = [&](int at) {
+    const int zp = __builtin_amdgcn_readfirstlane(lz[at]);
+    const int qr = __builtin_amdgcn_readfirstlane(lqr[at]);
+    int slot, sbb;
+    u_view(zp % 6, nv, rp, slot, sbb, sm, sk);
+    const int64_t off = (int64_t)b * sbb + (int64_t)m0 * sm;
+    pa = cubes + ((int64_t)(zp / 6) * NSLOT + slot) * css + off;
+    na = css - off;
+    const int64_t jo = qr * nv2 + (int64_t)n0 * nv;
+    pb = Jo + jo;
+    nb = nj - jo;
+    uu = 0;
   };
-  d4v acc[T::FM][T::FN];
-  zero_acc<T>(acc);
-  k_loop<T>(n * cs, m0, n0, ops, acc, lds);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave % T::WM, wn = wave / T::WM;
+  const unsigned vb = (unsigned)(r16 * nv + 2 * kq) * 8u, bs = (unsigned)nv * 128u;
+  auto fetch = [&](double (&a)[FM][2], double (&bb)[FN][2]) __attribute__((always_inline)) {
+    const BufRsrc ra = buf_rsrc_n(pa, na), rb = buf_rsrc_n(pb, nb);
 #pragma unroll
-  for (int fm = 0; fm < T::FM; ++fm)
+    for (int h = 0; h < 2; ++h) {
+      const int c = 2 * kq + h;
+      const unsigned va = uu * 8 + c < nv ? (unsigned)(c * sk + r16 * sm) * 8u : 0x80000000u;
 #pragma unroll
-    for (int fn = 0; fn < T::FN; ++fn)
+      for (int f = 0; f < FM; ++f) a[f][h] = buf_load_f64_at(ra, va, (unsigned)(f * sm) * 128u);
+    }
 #pragma unroll
-      for (int rr = 0; rr < 4; ++rr) {
-        const int a = m0 + acc_row<T>(wm, fm, lane, rr);
-        const int d = n0 + acc_col<T>(wn, fn, lane);
-        if (a < nv && d < nv) Zv[(((int64_t)a * nv + b) * no + p) * nv + d] -= acc[fm][fn][rr];
+    for (int f = 0; f < FN; ++f) {
+      const d2v v = buf_load_2f64(rb, vb, (unsigned)f * bs);
+      bb[f][0] = v[0];
+      bb[f][1] = v[1];
+    }
+    pa += 8 * sk;
+    na = na > 8 * sk ? na - 8 * sk : 0;
+    pb += 8;
+    nb = nb > 8 ? nb - 8 : 0;
+    if (++uu == ux) open(t = min(t + 1, n - 1));  // past the last pair: loads that nothing uses
+  };
+  d4v acc[FM][FN];
+#pragma unroll
+  for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+    for (int fn = 0; fn < FN; ++fn) acc[fm][fn] = d4v{0.0, 0.0, 0.0, 0.0};
+  double a[2][FM][2], bb[2][FN][2];
+  open(0);
+  fetch(a[0], bb[0]);
+  fetch(a[1], bb[1]);
+  const int nu = n * ux;
+  for (int u = 0; u < nu; u += 2) {
+#pragma unroll
+    for (int d = 0; d < 2; ++d) {
+      if (u + d < nu) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+            for (int fn = 0; fn < FN; ++fn)
+              acc[fm][fn] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[d][fm][h], bb[d][fn][h],
+                                                                 acc[fm][fn], 0, 0, 0);
+      }
+      fetch(a[d], bb[d]);
+    }
+  }
+#pragma unroll
+  for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+    for (int fn = 0; fn < FN; ++fn)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int a = m0 + frag_row<true, FM>(fm, kq, r), d = n0 + fn * 16 + r16;
+        if (a < nv && d < nv) Zv[(((int64_t)a * nv + b) * no + p) * nv + d] -= acc[fm][fn][r];
       }
 }
 
-// Zo partials: per (triple, permutation, 128-row tile of a, 16-column tile of l, b chunk)
-//   Pzo[z][pi][chunk][a][l] = sum_{b in chunk} sum_c U[a,b,c] Jo[l][r][b][c]   (l < no)
-// The l extent is no (12 at the benchmark size), so the tile is 128 x 16: eight
-// wavefronts of 16 x 16, and the stage is mostly the streamed U rows.
-typedef TileCfg<8, 1, 1, 1, 16> ZoCfg;
-
-__global__ __launch_bounds__(ZoCfg::NT) void k_zo(const double* __restrict__ cubes,
-                                                  const double* __restrict__ Jo,
-                                                  const int* __restrict__ tri,
-                                                  double* __restrict__ Pzo, int no, int nv,
-                                                  int nbchunks) {
-  typedef ZoCfg T;
-  __shared__ double lds[T::LDS_DOUBLES];
-  const int pi = blockIdx.y, z = blockIdx.z;
-  const int i = tri[3 * z], j = tri[3 * z + 1], k = tri[3 * z + 2];
-  if (!perm_active(tri_kind(i, j, k), pi)) return;
-  int p, q, r;
-  perm_pqr(pi, i, j, k, p, q, r);
-  const int tm = (nv + T::BM - 1) / T::BM;
-  const int bc = blockIdx.x % nbchunks;
-  const int m0 = ((blockIdx.x / nbchunks) % tm) * T::BM;
-  const int n0 = (blockIdx.x / nbchunks / tm) * T::BN;
-  const int bb0 = (int)((int64_t)bc * nv / nbchunks);
-  const int bb1 = (int)((int64_t)(bc + 1) * nv / nbchunks);
-  if (bb0 >= bb1) return;
-  const int64_t nvl = nv, nv2 = nvl * nvl;
-  int slot, sbb, sm, sk;
-  u_view(pi, nv, cube_pitch(nv), slot, sbb, sm, sk);
-  const double* ub = cubes + ((int64_t)z * NSLOT + slot) * cube_slot(nv);
-  const int cs = (nv + T::BK - 1) / T::BK;
-  auto ops = [&](int s, Opnd& A, Opnd& B, int& k0) {
-    const int b = bb0 + s / cs;
-    k0 = (s % cs) * T::BK;
-    A = make_opnd(ub + (int64_t)b * sbb, sm, sk, nv, nv, sm == 1);
-    B = make_opnd(Jo + (int64_t)r * nv2 + (int64_t)b * nv, (int64_t)no * nv2, 1, no, nv, false);
-  };
-  d4v acc[T::FM][T::FN];
-  zero_acc<T>(acc);
-  k_loop<T>((bb1 - bb0) * cs, m0, n0, ops, acc, lds);
-  double* out = Pzo + (((int64_t)z * 6 + pi) * nbchunks + bc) * nvl * no;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave % T::WM, wn = wave / T::WM;
+// Zo partials on wave tiles: per (triple, permutation, chunk of K)
+//   Pzo[z][pi][chunk][a][l] = sum_{(x, y) in chunk} T[a,x,y] J_l[x][y]   (l < no)
+// As in k_omega, two permutations share each view T of tau~ (rows a over its first, second or
+// third index): (0, 3), (1, 4), (5, 2), the first with (b, c) = (x, y) and J_l = Jo[l][r], the
+// second with (c, b) = (x, y) and J_l = Jo[r][l] (g_{lbrc} = g_{rclb}).  One wavefront per
+// (triple, view, FM blocks of a, chunk) and both permutations, FN blocks of l each; units of 8
+// y, two in flight, no LDS.  Past y = nv the U operand is zero (the padding of its rows, or an
+// offset outside the resource) and the J operand repeats y = nv - 1.
+// Bound by the cubes that it streams (1.3 GB a batch at 12/120).  Against 128 x 16 tiles
+// through LDS, one permutation each and the transposed cube for two of them: 1.03 -> 0.72 ms a
+// batch (beside the other stream's kernels), the call 40.8 -> 39.4 ms.
+template <bool ROWS, int FM, int FN>
+__device__ __forceinline__ void zo_tile(const double* ta, int64_t na, int sm, int sx, int sk,
+                                        const double* const (&jb)[2][FN], int u0, int u1, int ux,
+                                        int nv, d4v (&acc)[2][FM][FN]) {
+  const int lane = threadIdx.x & 63, r16 = lane & 15, kq = lane >> 4;
+  int x = u0 / ux, yu = u0 - x * ux;
+  auto fetch = [&](double (&a)[FM][2], double (&b)[2][FN][2]) __attribute__((always_inline)) {
+    const int64_t off = (int64_t)x * sx + (int64_t)yu * 8 * sk;
+    const BufRsrc ra = buf_rsrc_n(ta + off, na > off ? na - off : 0);
+    const int y = yu * 8 + 2 * kq;
+    if constexpr (ROWS) {
+      const unsigned va = (unsigned)(r16 * sm + 2 * kq) * 8u;
 #pragma unroll
-  for (int fm = 0; fm < T::FM; ++fm)
-#pragma unroll
-    for (int fn = 0; fn < T::FN; ++fn)
-#pragma unroll
-      for (int rr = 0; rr < 4; ++rr) {
-        const int a = m0 + acc_row<T>(wm, fm, lane, rr);
-        const int l = n0 + acc_col<T>(wn, fn, lane);
-        if (a < nv && l < no) out[(int64_t)a * no + l] = acc[fm][fn][rr];
+      for (int f = 0; f < FM; ++f) {
+        const d2v v = buf_load_2f64(ra, va, (unsigned)(f * sm) * 128u);
+        a[f][0] = v[0];
+        a[f][1] = v[1];
       }
+    } else {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const unsigned va = y + h < nv ? (unsigned)((2 * kq + h) * sk + 2 * r16) * 8u : 0x80000000u;
+#pragma unroll
+        for (int f = 0; f < FM; f += 2) {
+          const d2v v = buf_load_2f64(ra, va, (unsigned)f * 128u);
+          a[f][h] = v[0];
+          a[f + 1][h] = v[1];
+        }
+      }
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int64_t jo = (int64_t)x * nv + min(y + h, nv - 1);
+#pragma unroll
+      for (int e = 0; e < 2; ++e)
+#pragma unroll
+        for (int f = 0; f < FN; ++f) b[e][f][h] = jb[e][f][jo];
+    }
+    if (++yu == ux) {
+      yu = 0;
+      x = min(x + 1, nv - 1);  // past the last unit: loads that nothing uses
+    }
+  };
+  double a[2][FM][2], b[2][2][FN][2];
+  fetch(a[0], b[0]);
+  fetch(a[1], b[1]);
+  for (int u = u0; u < u1; u += 2) {
+#pragma unroll
+    for (int d = 0; d < 2; ++d) {
+      if (u + d < u1) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int e = 0; e < 2; ++e)
+#pragma unroll
+            for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+              for (int f = 0; f < FN; ++f)
+                acc[e][fm][f] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[d][fm][h], b[d][e][f][h],
+                                                                     acc[e][fm][f], 0, 0, 0);
+      }
+      fetch(a[d], b[d]);
+    }
+  }
+}
+
+template <int FM, int FN>
+__global__ __launch_bounds__(WNT) void k_zo(const double* __restrict__ cubes,
+                                            const double* __restrict__ Jo,
+                                            const int* __restrict__ tri, int ntri,
+                                            double* __restrict__ Pzo, int no, int nv, int nchunks,
+                                            int tiles_m) {
+  static_assert(FM % 2 == 0, "pairs of row blocks");
+  unsigned item = xcd_item(blockIdx.x, gridDim.x, 1) * 4 +
+                  __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int m0 = (int)(item % (unsigned)tiles_m) * (FM * 16);
+  item /= (unsigned)tiles_m;
+  const int ch = (int)(item % (unsigned)nchunks);
+  item /= (unsigned)nchunks;
+  const int op = (int)(item % 3u), z = (int)(item / 3u);
+  if (z >= ntri) return;
+  const int i = tri[3 * z], j = tri[3 * z + 1], k = tri[3 * z + 2];
+  const int kind = tri_kind(i, j, k);
+  const int pis[2] = {op == 0 ? 0 : op == 1 ? 1 : 5, op == 0 ? 3 : op == 1 ? 4 : 2};
+  const bool on[2] = {perm_active(kind, pis[0]), perm_active(kind, pis[1])};
+  if (!on[0] && !on[1]) return;
+  const int rp = cube_pitch(nv), ux = rp / 8, units = nv * ux;
+  const int u0 = (int)((int64_t)ch * units / nchunks), u1 = (int)((int64_t)(ch + 1) * units / nchunks);
+  const int lane = threadIdx.x & 63, r16 = lane & 15, kq = lane >> 4;
+  const int64_t nvl = nv, nv2 = nvl * nvl, css = cube_slot(nv);
+  const int pl = nv * rp;
+  const double* jb[2][FN];
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    int p, q, r;
+    perm_pqr(pis[e], i, j, k, p, q, r);
+#pragma unroll
+    for (int f = 0; f < FN; ++f) {
+      const int64_t l = min(f * 16 + r16, no - 1);
+      jb[e][f] = Jo + (e ? r * (int64_t)no + l : l * no + r) * nv2;
+    }
+  }
+  d4v acc[2][FM][FN];
+#pragma unroll
+  for (int e = 0; e < 2; ++e)
+#pragma unroll
+    for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+      for (int f = 0; f < FN; ++f) acc[e][fm][f] = d4v{0.0, 0.0, 0.0, 0.0};
+  const double* TT = cubes + ((int64_t)z * NSLOT + SLOT_TT) * css;
+  const int sm = op == 0 ? pl : op == 1 ? rp : 1;
+  const double* ta = TT + (int64_t)m0 * sm;
+  const int64_t na = css - (int64_t)m0 * sm;
+  if (op == 2) zo_tile<false, FM, FN>(ta, na, 1, pl, rp, jb, u0, u1, ux, nv, acc);
+  else zo_tile<true, FM, FN>(ta, na, sm, op == 0 ? rp : pl, 1, jb, u0, u1, ux, nv, acc);
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    if (!on[e]) continue;
+    double* out = Pzo + (((int64_t)z * 6 + pis[e]) * nchunks + ch) * nvl * no;
+#pragma unroll
+    for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+      for (int f = 0; f < FN; ++f)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int a = m0 + (op == 2 ? frag_row<false, FM>(fm, kq, r) : frag_row<true, FM>(fm, kq, r));
+          const int l = f * 16 + r16;
+          if (a < nv && l < no) out[(int64_t)a * no + l] = acc[e][fm][f][r];
+        }
+  }
 }
 
 // Zo[a][q][p][l] += the chunk sums of the batch's pairs with that (p, q), in batch order.
@@ -1644,24 +1790,34 @@ __global__ __launch_bounds__(256) void k_zo_reduce(const int* __restrict__ tri, 
 
 void launch_zv(const double* cubes, const Blocks& b, const int* tri, int ntri, double* Zv, int no,
                int nv, hipStream_t st) {
-  typedef ZvCfg T;
-  const int tm = (nv + T::BM - 1) / T::BM, tn = (nv + T::BN - 1) / T::BN;
-  hipLaunchKernelGGL(k_zv, dim3(nv * tm * tn, no), dim3(T::NT), 0, st, cubes, b.Jo, tri, ntri, Zv,
-                     no, nv, tm, tn);
+  const int shape = pick_shape(nv, nv);
+  int tm, tn;
+  shape_tiles(shape, nv, nv, &tm, &tn);
+  const unsigned wgs = nblk((int64_t)nv * tm * tn, 4) * (unsigned)no;
+  with_shape(shape, [&](auto fm, auto fn) {
+    constexpr int FM = decltype(fm)::value, FN = decltype(fn)::value;
+    hipLaunchKernelGGL((k_zv<FM, FN>), dim3(wgs), dim3(WNT), 0, st, cubes, b.Jo, tri, ntri, Zv, no, nv,
+                       tm, tn);
+  });
 }
 
 void launch_zo(const double* cubes, const Blocks& b, const int* tri, int ntri, double* Pzo,
                double* Zo, int no, int nv, hipStream_t st, bool reduce) {
-  typedef ZoCfg T;
   const int nbc = zo_nbchunks(nv, ntri);
-  if (!reduce) {
-    const int tm = (nv + T::BM - 1) / T::BM, tn = (no + T::BN - 1) / T::BN;
-    hipLaunchKernelGGL(k_zo, dim3(nbc * tm * tn, 6, ntri), dim3(T::NT), 0, st, cubes, b.Jo, tri,
-                       Pzo, no, nv, nbc);
-  } else {
+  if (reduce) {
     hipLaunchKernelGGL(k_zo_reduce, dim3(nblk((int64_t)nv * no, 256), no, no), dim3(256), 0, st,
                        tri, ntri, Pzo, Zo, no, nv, nbc);
+    return;
   }
+  auto run = [&](auto* kernel, int fm) {
+    const int tm = (int)nblk(nv, 16 * fm);
+    hipLaunchKernelGGL(kernel, dim3(nblk((int64_t)tm * nbc * 3 * ntri, 4)), dim3(WNT), 0, st, cubes,
+                       b.Jo, tri, ntri, Pzo, no, nv, nbc, tm);
+  };
+  if (no <= 16) run(k_zo<4, 1>, 4);
+  else if (no <= 32) run(k_zo<4, 2>, 4);
+  else if (no <= 48) run(k_zo<2, 3>, 2);
+  else run(k_zo<2, 4>, 2);
 }
 
 double zprep_flops(int no, int nv, const int* kinds, int n) {

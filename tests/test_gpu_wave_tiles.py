@@ -62,3 +62,16 @@ def test_t3_block_orderings(ijk):
     tau = ctx.t3_block(g["eps"], g["L"], g["t1"], g["t2"], *ijk).cpu().numpy()
     blk = O.IntegralBlocks(O.t1_transform(d["L"], d["t1"]), no)
     assert rel(tau, O.t3_amplitudes(*ijk, d["eps"], d["t2"], blk)) < TOL
+
+
+@pytest.mark.parametrize("no,nv", [(2, 1), (3, 15), (2, 17), (3, 33), (2, 49), (17, 10), (2, 65),
+                                   (33, 5), (2, 97), (49, 2), (2, 129)])
+def test_jacobian_at_tile_edges(no, nv):
+    """Zv (tiles of (a, d)) and Zo (tiles of a, 16 l per block and up to four blocks)."""
+    d = make_inputs(no, nv, 2 * (no + nv), tag=24)
+    ctx = cc3.Context(0)
+    g = {k: torch.from_numpy(d[k]).cuda() for k in ("eps", "L", "t1", "t2")}
+    zv, zo = ctx.jacobian_prep(g["eps"], g["L"], g["t1"], g["t2"])
+    rv, ro = O.jacobian_prep(d["eps"], d["L"], d["t1"], d["t2"])
+    assert rel(zv.cpu().numpy(), rv) < TOL
+    assert rel(zo.cpu().numpy(), ro) < TOL
