@@ -202,19 +202,21 @@ int make_plan_ex(int no, int nv, int nchol, int prec, unsigned flags, bool with_
   memset(p, 0, sizeof *p);
   p->no = no; p->nv = nv; p->nchol = nchol; p->prec = prec; p->flags = flags;
   const size_t o = no, v = nv, J = nchol;
+  // cube buffer sets: one per stream of the triple loop
+  const size_t sets = (flags & PLAN_CALLER_STREAM) ? 1 : 2;
   p->ntri = (int)((size_t)no * (no + 1) * (no + 2) / 6 - no);
   p->cube = (size_t)cube_slot(nv);  // one padded cube slot
   // triples per batch: enough W-build workgroups per launch to fill 256 CUs
   // many times over, and at least min(no, 16) triples, so that the kernels that
   // are parallel over the first occupied index p (the oo contraction, the
   // reductions) find pairs for many p in every batch; bounded by a cube-memory
-  // budget per buffer set (32 GiB by default: 12 triples at nv = 400)
+  // budget per buffer set (32 GiB by default: 22 triples at nv = 400)
   const size_t wg_per_triple = 3 * v * ((v + 127) / 128) * ((v + 127) / 128);
   int batch = (int)std::max<size_t>(1, (size_t)(12288 + wg_per_triple - 1) / wg_per_triple);
   batch = std::max(batch, std::min(no, 8));
   const size_t budget =
       cube_budget ? cube_budget : ((size_t)env_int("CC3_CUBE_BUDGET_MB", 32768) << 20);
-  const size_t per_triple = 5 * p->cube * sizeof(double);
+  const size_t per_triple = NSLOT * p->cube * sizeof(double);
   batch = (int)std::min<size_t>((size_t)batch, std::max<size_t>(1, budget / per_triple));
   batch = env_int("CC3_BATCH", batch);
   batch = std::min(batch, MAX_BATCH);  // bounds the kernels' per-p pair lists
@@ -252,7 +254,7 @@ int make_plan_ex(int no, int nv, int nchol, int prec, unsigned flags, bool with_
       p->cubef_bytes = align256((size_t)batch * lp_contract_cube_bytes(prec, nv));
     }
     p->off_gf = take(2 * p->gf_bytes);
-    p->off_cubef = take(2 * p->cubef_bytes);
+    p->off_cubef = take(sets * p->cubef_bytes);
   }
   p->off_tri = take((size_t)std::max(1, p->ntri) * 3 * sizeof(int) + 64);
   p->off_flag = take(64);
@@ -260,8 +262,8 @@ int make_plan_ex(int no, int nv, int nchol, int prec, unsigned flags, bool with_
   p->chol_bytes = J ? align256(J * v * v * 8) + align256(J * o * o * 8) * 2 +
                           align256(J * o * v * 8) * 2 + align256(J * 8) + align256(J * o * o * 8)
                     : 0;
-  p->cube_bytes = align256((size_t)batch * 5 * p->cube * 8);
-  size_t region = std::max(p->chol_bytes, 2 * p->cube_bytes);
+  p->cube_bytes = align256((size_t)batch * NSLOT * p->cube * 8);
+  size_t region = std::max(p->chol_bytes, sets * p->cube_bytes);
   if (with_blocks) {
     const size_t nmo = o + v;
     p->off_stage = take(align256(nmo * 8) + 2 * align256(o * v * 8) + align256(o * o * v * v * 8));

@@ -115,6 +115,12 @@ __host__ __device__ inline int64_t g_pitch(int nv) {
   return odd_line_pitch((int64_t)nv * cube_pitch(nv));
 }
 
+// Cube slots of one triple's workspace: the W planes (PA and PB; P0, P1, P2 of the BF16x3
+// build), tau~ and, for the Jacobian preparation, tau~T.  The mix reads the planes of an orbit
+// of 8^3 blocks, which nothing else reads, before it writes those blocks, so tau~ shares a slot
+// with P2 and tau~T one with P0.  (tau~ in the place of PA, which leaves two slots, measured
+// 2% slower for a call of 12/120.)
+enum { SLOT_P0 = 0, SLOT_P1 = 1, SLOT_P2 = 2, SLOT_TT = SLOT_P2, SLOT_TTT = SLOT_P0, NSLOT = 3 };
 // Whether the W build of a precision writes two planes per triple (all but CC3_BF16X3).
 inline bool two_planes(int prec) { return prec != 2; }
 

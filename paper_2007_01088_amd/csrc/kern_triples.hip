@@ -33,9 +33,6 @@ namespace cc3 {
 
 static inline unsigned nblk(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 
-// cube slots of one triple's workspace: the W planes (PA and PB; P0, P1, P2 of the BF16x3
-// build), tau~ and tau~T
-enum { SLOT_P0 = 0, SLOT_P1 = 1, SLOT_P2 = 2, SLOT_TT = 3, SLOT_TTT = 4, NSLOT = 5 };
 enum { SLOT_PA = SLOT_P0, SLOT_PB = SLOT_P1 };
 
 // ---------------------------------------------------------------------------

@@ -505,7 +505,7 @@ __device__ __forceinline__ void wbuild_lp_body(
 
   // the FP32/BF16 MFMA leaves D[row = 4 (lane/16) + r][col = lane%16] in register r
   const int64_t rp = cube_pitch(nv);
-  double* dst = cubes + ((int64_t)z * 5 + plane) * cube_slot(nv) + (int64_t)y * nv * rp;
+  double* dst = cubes + ((int64_t)z * NSLOT + plane) * cube_slot(nv) + (int64_t)y * nv * rp;
 #pragma unroll
   for (int fm = 0; fm < FM; ++fm)
 #pragma unroll
