@@ -438,12 +438,14 @@ __device__ __forceinline__ void wbuild_lp_body(
       ir = (unsigned)(lk * ESZ);
       sg.nst = so;
     }
-    sg.a = col ? in : amp;
-    sg.b = col ? amp : in;
     sg.aps = col ? ip : ap;
     sg.bps = col ? ap : ip;
     sg.ars = col ? ir : ar;
     sg.brs = col ? ar : ir;
+    // the tile's first rows: the lanes' offsets from them stay below 2 GiB at every nv (a row
+    // stride of one slab is 4 nv^2 bytes)
+    sg.a = (col ? in : amp) + (int64_t)m0 * sg.ars;
+    sg.b = (col ? amp : in) + (int64_t)n0 * sg.brs;
     st = 0;
   };
 
@@ -456,8 +458,8 @@ __device__ __forceinline__ void wbuild_lp_body(
   int ar[L::NI], br[L::NI];
 #pragma unroll
   for (int e = 0; e < L::NI; ++e) {
-    ar[e] = min(m0 + ln.row[e], nv - 1);
-    br[e] = min(n0 + ln.row[e], nv - 1);
+    ar[e] = min(ln.row[e], nv - 1 - m0);
+    br[e] = min(ln.row[e], nv - 1 - n0);
   }
   auto load = [&](int t) {  // stage t of the plane, in order
     const int64_t ko = (int64_t)st * L::RB;
@@ -598,8 +600,10 @@ __global__ __launch_bounds__(LpGeo<NW>::NT) void k_omega_lp(const char* __restri
   const unsigned nb = (unsigned)(nv + 7) / 8;
   const unsigned rs = (unsigned)(lp_kb_pitch(nv) * ESZ);         // row stride of GL, bytes
   const int64_t y_ps = yl_piece(nv), g_ps = (int64_t)no * (nv + no) * rs;  // piece strides
-  const char* ga = YL + ((int64_t)z * 2 + form) * E::P * y_ps;
-  const char* gb = (cb ? GcbL : GbcL) + (int64_t)r * (nv + no) * rs;
+  // from the tile's first rows, as in the W build (m0 is a multiple of 8)
+  const int64_t m8 = (int64_t)(m0 >> 3) * nb * 1024;
+  const char* ga = YL + ((int64_t)z * 2 + form) * E::P * y_ps + (second ? m8 : m8 * nb);
+  const char* gb = (cb ? GcbL : GbcL) + ((int64_t)r * (nv + no) + n0) * rs;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -611,10 +615,10 @@ __global__ __launch_bounds__(LpGeo<NW>::NT) void k_omega_lp(const char* __restri
   unsigned ao[L::NI], bo[L::NI];
 #pragma unroll
   for (int e = 0; e < L::NI; ++e) {
-    const unsigned m = (unsigned)min(m0 + ln.row[e], nv - 1), n = (unsigned)(n0 + ln.row[e]);
+    const unsigned m = (unsigned)min(ln.row[e], nv - 1 - m0);
     ao[e] = second ? (m >> 3) * nb * 1024 + (m & 7) * 16 + ln.cb[e] * 8
                    : (m >> 3) * nb * nb * 1024 + (m & 7) * 128 + ln.cb[e];
-    bo[e] = (n < (unsigned)nv ? n : (unsigned)(nv + q)) * rs + ln.cb[e];
+    bo[e] = (unsigned)(n0 + ln.row[e] < nv ? ln.row[e] : nv + q - n0) * rs + ln.cb[e];
   }
   f4v acc[LFM][LFN];
   d4v accd[LFM][LFN];  // FLUSH: each stage's FP32 sum added in FP64

@@ -52,6 +52,20 @@ def test_reduced_precision_w_at_tile_edges(no, nv, prec, flags, bar):
     assert rel(o2.cpu().numpy(), r2) < bar
 
 
+@pytest.mark.parametrize("prec,flags,bar", [
+    (cc3.FP32, 0, 2e-6), (cc3.BF16X3, cc3.LOWP_CONTRACT, 1e-4)])
+def test_reduced_precision_beyond_2_gib_of_rows(prec, flags, bar):
+    """nv = 896: the rows of Gw that are one slab apart span 2.9 GB in FP32, more than a
+    buffer load's offset reaches.  The FP64 form (bars as above) is the reference."""
+    d = make_inputs(2, 896, 24, tag=25)
+    ctx = cc3.Context(0)
+    g = {k: torch.from_numpy(d[k]).cuda() for k in ("eps", "L", "t1", "t2")}
+    r1, r2 = (x.cpu().numpy() for x in ctx.triples_residual(g["eps"], g["L"], g["t1"], g["t2"]))
+    o1, o2 = ctx.triples_residual(g["eps"], g["L"], g["t1"], g["t2"], prec=prec, flags=flags)
+    assert rel(o1.cpu().numpy(), r1) < bar
+    assert rel(o2.cpu().numpy(), r2) < bar
+
+
 @pytest.mark.parametrize("ijk", [(2, 1, 0), (0, 1, 2), (1, 2, 0), (2, 2, 1), (1, 2, 2), (2, 1, 2)])
 def test_t3_block_orderings(ijk):
     """The planes of every kind of ordered triple (the export builds all six terms)."""
