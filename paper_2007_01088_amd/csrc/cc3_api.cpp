@@ -585,9 +585,17 @@ extern "C" int cc3_triples_residual_noalloc(cc3_ctx* c, int no, int nv, int ncho
   // 6/45 in one batch instead of three: 453 -> 327 us)
   flags |= PLAN_CALLER_STREAM;
   make_plan_ex(no, nv, nchol, prec, flags, true, 0, &p);
-  const size_t per_triple = NSLOT * p.cube * sizeof(double);
-  for (int b = p.batch - 1; p.total > SCRATCH_BYTES && b >= 1; --b)
-    make_plan_ex(no, nv, nchol, prec, flags, true, (size_t)b * per_triple, &p);
+  if (p.total > SCRATCH_BYTES) {
+    // the workspace grows with the batch: bisect for the largest that fits
+    const size_t per_triple = NSLOT * p.cube * sizeof(double);
+    int fits = 0, over = p.batch;
+    while (over - fits > 1) {
+      const int b = (fits + over) / 2;
+      make_plan_ex(no, nv, nchol, prec, flags, true, (size_t)b * per_triple, &p);
+      (p.total > SCRATCH_BYTES ? over : fits) = b;
+    }
+    make_plan_ex(no, nv, nchol, prec, flags, true, (size_t)std::max(fits, 1) * per_triple, &p);
+  }
   if (p.total > SCRATCH_BYTES)
     return fail(CC3_E_NOMEM, "no=%d nv=%d nchol=%d needs %zu bytes of workspace at one triple per "
                 "batch; the allocation-free call has %zu", no, nv, nchol, p.total, SCRATCH_BYTES);

@@ -229,11 +229,8 @@ int make_plan_ex(int no, int nv, int nchol, int prec, unsigned flags, bool with_
   }
   p->batch = batch;
   // largest (triples x chunks) product over the batch sizes the loop can see
-  size_t tc = 1;
-  for (int nb = 1; nb <= batch; ++nb)
-    tc = std::max(tc, (size_t)nb * std::max(omega_kchunks(nv, nb, (flags & CC3_LOWP_CONTRACT) != 0),
-                                            zo_nbchunks(nv, nb)));
-  p->pvv_entries = tc;
+  const size_t tc = std::max(omega_slabs(nv, batch, (flags & CC3_LOWP_CONTRACT) != 0),
+                             zo_slabs(nv, batch));
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t at = off; off = align256(off + bytes); return at; };
   p->off_blocks = with_blocks ? take(block_bytes(no, nv)) : 0;

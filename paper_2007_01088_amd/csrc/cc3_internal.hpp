@@ -159,7 +159,6 @@ struct Plan {
   unsigned flags;
   int ntri;     // unordered triples i >= j >= k, not all equal
   int batch;    // triples per batch of the triple loop
-  size_t pvv_entries;  // max (triples x chunks) of one Omega or Zo launch
   size_t cube;  // doubles per cube slot (cube_slot: nv x nv rows at the padded pitch)
   // byte offsets into the workspace
   size_t off_blocks;  // integral blocks (when the workspace holds them)
@@ -268,6 +267,9 @@ void launch_combine(const double* Ot1, const double* Ot2, const double* OtT, dou
 // forms), at most 4096 k each
 int omega_kchunks(int nv, int ntri, bool fp32acc = false);
 int zo_nbchunks(int nv, int ntri);    // b chunks of one Zo product
+// The largest triples x chunks of a launch of either over the batches of 1 to `batch` triples
+size_t omega_slabs(int nv, int batch, bool fp32acc);
+size_t zo_slabs(int nv, int batch);
 void launch_back_transform(const double* Ot1, const double* Ot2, const double* OtT, double* O1,
                            double* O2, int no, int nv, bool accumulate, hipStream_t st);
 void launch_set_triples(int* tri_dev, const int* host_tri, int n, hipStream_t st);

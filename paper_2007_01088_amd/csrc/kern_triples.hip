@@ -1846,33 +1846,57 @@ int zo_nbchunks(int nv, int ntri) {
 // dispatched to the same XCD; at least 16 stages of 16 k per chunk and at most 4096 k,
 // which the MFMA sums in FP32, so that their rounding does not grow with the batch (the
 // split-BF16 form's K is the blocked lp_kb_len(nv) >= nv^2).
-int omega_kchunks(int nv, int ntri, bool fp32acc) {
-  static const int target = [] {
+struct OmegaSplit {
+  int64_t per, units;  // tiles of one triple (wave tiles, or LDS tiles), units (stages) of K
+  int target, need;    // tiles of a launch; chunks that hold fp32acc's K to 4096
+};
+static OmegaSplit omega_split(int nv, bool fp32acc) {
+  static const int env = [] {
     const char* e = getenv("CC3_OMEGA_WG");
-    const int v = e ? atoi(e) : 0;
-    return v > 0 ? v : 0;
+    return e ? atoi(e) : 0;
   }();
-  const int nt = ntri > 0 ? ntri : 1;
-  int nch;
+  OmegaSplit s;
+  int tm, tn;
   if (!fp32acc) {
-    int tm, tn;
     shape_tiles(pick_shape(nv, nv + 1), nv, nv + 1, &tm, &tn);
-    const int64_t per = 6ll * tm * tn * nt, units = (int64_t)nv * (cube_pitch(nv) / 8);
-    const int64_t big = ((target ? target : 12288) + per - 1) / per, small = (3072 + per - 1) / per;
-    nch = (int)std::max(std::min(big, units / 64), std::min(small, units / 8));
-    return nch < 1 ? 1 : nch;
+    s.units = (int64_t)nv * (cube_pitch(nv) / 8);
+  } else {
+    tm = (nv + OCfg::BM - 1) / OCfg::BM;
+    tn = (nv + 1 + OCfg::BN - 1) / OCfg::BN;
+    s.units = ((int64_t)nv * nv + OCfg::BK - 1) / OCfg::BK;
   }
-  typedef OCfg T;
-  const int tm = (nv + T::BM - 1) / T::BM, tn = (nv + 1 + T::BN - 1) / T::BN;
-  const int per = 6 * tm * tn * nt;
-  nch = ((target ? target : 2048) + per - 1) / per;
-  if (nch > 8) nch = (nch + 7) / 8 * 8;
-  const int S = (nv * nv + T::BK - 1) / T::BK;
-  const int cap = S / 16 > 1 ? S / 16 : 1;
-  if (nch > cap) nch = cap;
-  const int need = (int)((lp_kb_len(nv) + 4095) / 4096);
-  if (nch < need) nch = need > 8 ? (need + 7) / 8 * 8 : need;
-  return nch < 1 ? 1 : nch;
+  s.per = 6ll * tm * tn;
+  s.target = env > 0 ? env : fp32acc ? 2048 : 12288;
+  s.need = fp32acc ? (int)((lp_kb_len(nv) + 4095) / 4096) : 1;
+  return s;
+}
+static int omega_chunks(const OmegaSplit& s, int ntri, bool fp32acc) {
+  const int64_t per = s.per * (ntri > 0 ? ntri : 1), big = (s.target + per - 1) / per;
+  if (!fp32acc) {
+    const int64_t small = (3072 + per - 1) / per;
+    return (int)std::max<int64_t>(1, std::max(std::min(big, s.units / 64), std::min(small, s.units / 8)));
+  }
+  auto eights = [](int64_t n) { return n > 8 ? (n + 7) / 8 * 8 : n; };
+  const int64_t nch = std::min(eights(big), std::max<int64_t>(1, s.units / 16));
+  return (int)(nch < s.need ? eights(s.need) : nch);
+}
+
+int omega_kchunks(int nv, int ntri, bool fp32acc) {
+  return omega_chunks(omega_split(nv, fp32acc), ntri, fp32acc);
+}
+
+size_t omega_slabs(int nv, int batch, bool fp32acc) {
+  const OmegaSplit s = omega_split(nv, fp32acc);
+  size_t most = 1;
+  for (int nb = 1; nb <= batch; ++nb)
+    most = std::max(most, (size_t)nb * omega_chunks(s, nb, fp32acc));
+  return most;
+}
+
+size_t zo_slabs(int nv, int batch) {
+  size_t most = 1;
+  for (int nb = 1; nb <= batch; ++nb) most = std::max(most, (size_t)nb * zo_nbchunks(nv, nb));
+  return most;
 }
 
 static unsigned omega_wgs(int nv, int ntri, int nch, int shape) {
