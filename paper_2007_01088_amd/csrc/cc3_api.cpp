@@ -587,7 +587,7 @@ extern "C" int cc3_triples_residual_noalloc(cc3_ctx* c, int no, int nv, int ncho
   make_plan_ex(no, nv, nchol, prec, flags, true, 0, &p);
   if (p.total > SCRATCH_BYTES) {
     // the workspace grows with the batch: bisect for the largest that fits
-    const size_t per_triple = NSLOT * p.cube * sizeof(double);
+    const size_t per_triple = BUDGET_CUBES * p.cube * sizeof(double);
     int fits = 0, over = p.batch;
     while (over - fits > 1) {
       const int b = (fits + over) / 2;

@@ -207,16 +207,16 @@ int make_plan_ex(int no, int nv, int nchol, int prec, unsigned flags, bool with_
   p->ntri = (int)((size_t)no * (no + 1) * (no + 2) / 6 - no);
   p->cube = (size_t)cube_slot(nv);  // one padded cube slot
   // triples per batch: enough W-build workgroups per launch to fill 256 CUs
-  // many times over, and at least min(no, 16) triples, so that the kernels that
+  // many times over, and at least min(no, 8) triples, so that the kernels that
   // are parallel over the first occupied index p (the oo contraction, the
   // reductions) find pairs for many p in every batch; bounded by a cube-memory
-  // budget per buffer set (32 GiB by default: 22 triples at nv = 400)
+  // budget per buffer set (32 GiB by default: 13 triples at nv = 400)
   const size_t wg_per_triple = 3 * v * ((v + 127) / 128) * ((v + 127) / 128);
   int batch = (int)std::max<size_t>(1, (size_t)(12288 + wg_per_triple - 1) / wg_per_triple);
   batch = std::max(batch, std::min(no, 8));
   const size_t budget =
       cube_budget ? cube_budget : ((size_t)env_int("CC3_CUBE_BUDGET_MB", 32768) << 20);
-  const size_t per_triple = NSLOT * p->cube * sizeof(double);
+  const size_t per_triple = BUDGET_CUBES * p->cube * sizeof(double);
   batch = (int)std::min<size_t>((size_t)batch, std::max<size_t>(1, budget / per_triple));
   batch = env_int("CC3_BATCH", batch);
   batch = std::min(batch, MAX_BATCH);  // bounds the kernels' per-p pair lists
@@ -228,9 +228,6 @@ int make_plan_ex(int no, int nv, int nchol, int prec, unsigned flags, bool with_
     batch = (p->ntri + nb - 1) / nb;
   }
   p->batch = batch;
-  // largest (triples x chunks) product over the batch sizes the loop can see
-  const size_t tc = std::max(omega_slabs(nv, batch, (flags & CC3_LOWP_CONTRACT) != 0),
-                             zo_slabs(nv, batch));
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t at = off; off = align256(off + bytes); return at; };
   p->off_blocks = with_blocks ? take(block_bytes(no, nv)) : 0;
@@ -239,8 +236,11 @@ int make_plan_ex(int no, int nv, int nchol, int prec, unsigned flags, bool with_
   p->off_OtT = take(o * o * v * v * 8);
   p->off_t2N = take(o * v * t2n_pitch(no, nv) * 8);
   p->off_lp = take(lp_operand_bytes(prec, no, nv));
-  // partial slabs: Omega chunks of nv x (nv + 1), or Jacobian-preparation chunks of nv x no
-  p->pvv_bytes = align256(tc * 6 * v * std::max(v + 1, o) * 8);
+  // partial slabs of the batch size that needs most of them: Omega chunks of nv x (nv + 1) or,
+  // in the one-shot plans, which may serve the Jacobian preparation, its chunks of nv x no
+  size_t pvv = omega_slabs(nv, p->ntri ? batch : 0, (flags & CC3_LOWP_CONTRACT) != 0) * (v + 1);
+  if (with_blocks) pvv = std::max(pvv, zo_slabs(nv, batch) * o);
+  p->pvv_bytes = align256(pvv * 6 * v * 8);
   p->off_Pvv = take(2 * p->pvv_bytes);
   if (flags & CC3_LOWP_CONTRACT) {
     if (prec == CC3_FP32) {

@@ -121,6 +121,10 @@ __host__ __device__ inline int64_t g_pitch(int nv) {
 // with P2 and tau~T one with P0.  (tau~ in the place of PA, which leaves two slots, measured
 // 2% slower for a call of 12/120.)
 enum { SLOT_P0 = 0, SLOT_P1 = 1, SLOT_P2 = 2, SLOT_TT = SLOT_P2, SLOT_TTT = SLOT_P0, NSLOT = 3 };
+// Cubes that a plan's cube budget counts per triple: its slots, and two for its partial slabs.
+// (Counting the slots alone, a server's request of 3/190 at a budget of 512 MiB takes three
+// triples per batch and 1.6 GiB of its arena; so counted, one and 0.56 GiB.)
+constexpr int BUDGET_CUBES = NSLOT + 2;
 // Whether the W build of a precision writes two planes per triple (all but CC3_BF16X3).
 inline bool two_planes(int prec) { return prec != 2; }
 

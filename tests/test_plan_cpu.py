@@ -34,3 +34,16 @@ def test_planning_time_does_not_follow_the_batch(size):
             t.append(time.perf_counter() - t0)
         return min(t) / 200
     assert best(31, 16) - best(1, 16) < 5e-6
+
+
+# (no, nv, cube budget in MiB): bytes of the plan at nchol = 3 (no + nv) in FP64 with five cube
+# slots per triple; a server's requests, whose budget is a share of its arena, fit where they did
+SMALL_BUDGET = {
+    (3, 119, 128): 427615488, (4, 95, 128): 547965696, (8, 43, 128): 312605184,
+    (10, 53, 128): 455077888, (3, 190, 512): 1373221120, (6, 302, 4096): 11227156992}
+
+
+@pytest.mark.parametrize("no,nv,mb", sorted(SMALL_BUDGET))
+def test_small_cube_budget_bounds_the_plan(size, monkeypatch, no, nv, mb):
+    monkeypatch.setenv("CC3_CUBE_BUDGET_MB", str(mb))
+    assert size(no, nv) <= SMALL_BUDGET[no, nv, mb]
