@@ -206,8 +206,8 @@ int cc3_triples_residual_subset_blocks(cc3_ctx* ctx, int no, int nv, const doubl
  * stream are safe.  The array keeps the last call's contents; the call clears what
  * must start at zero itself.
  * Errors: CC3_E_INVAL (sizes, flags, host pointers), CC3_E_NOMEM (the workspace at
- * one triple per batch exceeds 256 MiB: roughly nv above 70 at no = 10),
- * CC3_E_DEVICE. */
+ * one triple per batch exceeds 256 MiB: with about 3 (no + nv) Cholesky vectors in FP64,
+ * nv above 112 at no = 4, 87 at no = 10, 72 at no = 16), CC3_E_DEVICE. */
 int cc3_triples_residual_noalloc(cc3_ctx* ctx, int no, int nv, int nchol, const double* eps,
                                  const double* L, const double* t1, const double* t2,
                                  double* omega1, double* omega2, int prec, unsigned flags,

@@ -572,18 +572,10 @@ extern "C" int cc3_triples_residual_noalloc(cc3_ctx* c, int no, int nv, int ncho
     if ((rc = check_dev_ptr(ptrs[i], names[i]))) return rc;
   void* ws = scratch_ptr(c->device);
   if (!ws) return fail(CC3_E_DEVICE, "the scratch array of device %d was not set up", c->device);
-  // The sizes it serves: those whose one-shot plan, at one triple per batch, fits the array
-  // with two sets of five cubes.
-  Plan p;
-  make_plan_ex(no, nv, nchol, prec, flags, true, 1, &p);
-  const size_t need =
-      p.off_cubes + std::max({p.chol_bytes, p.stage_region, (size_t)10 * p.cube * sizeof(double)});
-  if (need > SCRATCH_BYTES)
-    return fail(CC3_E_NOMEM, "no=%d nv=%d nchol=%d needs %zu bytes of workspace at one triple per "
-                "batch; the allocation-free call has %zu", no, nv, nchol, need, SCRATCH_BYTES);
-  // every batch on the caller's stream, from one set of cubes (as many triples per batch as fit:
-  // 6/45 in one batch instead of three: 453 -> 327 us)
+  // every batch on the caller's stream, from one set of buffers and without host staging, as
+  // many triples per batch as fit (6/45 in one batch instead of three: 453 -> 327 us)
   flags |= PLAN_CALLER_STREAM;
+  Plan p;
   make_plan_ex(no, nv, nchol, prec, flags, true, 0, &p);
   if (p.total > SCRATCH_BYTES) {
     // the workspace grows with the batch: bisect for the largest that fits

@@ -202,8 +202,10 @@ int make_plan_ex(int no, int nv, int nchol, int prec, unsigned flags, bool with_
   memset(p, 0, sizeof *p);
   p->no = no; p->nv = nv; p->nchol = nchol; p->prec = prec; p->flags = flags;
   const size_t o = no, v = nv, J = nchol;
-  // cube buffer sets: one per stream of the triple loop
-  const size_t sets = (flags & PLAN_CALLER_STREAM) ? 1 : 2;
+  // the one-shot calls with a workspace: neither serving nor the allocation-free call
+  const bool one_shot = with_blocks && !(flags & PLAN_CALLER_STREAM);
+  // buffer sets of cubes and partial slabs: one per stream of the triple loop
+  p->sets = (flags & PLAN_CALLER_STREAM) ? 1 : 2;
   p->ntri = (int)((size_t)no * (no + 1) * (no + 2) / 6 - no);
   p->cube = (size_t)cube_slot(nv);  // one padded cube slot
   // triples per batch: enough W-build workgroups per launch to fill 256 CUs
@@ -239,9 +241,9 @@ int make_plan_ex(int no, int nv, int nchol, int prec, unsigned flags, bool with_
   // partial slabs of the batch size that needs most of them: Omega chunks of nv x (nv + 1) or,
   // in the one-shot plans, which may serve the Jacobian preparation, its chunks of nv x no
   size_t pvv = omega_slabs(nv, p->ntri ? batch : 0, (flags & CC3_LOWP_CONTRACT) != 0) * (v + 1);
-  if (with_blocks) pvv = std::max(pvv, zo_slabs(nv, batch) * o);
+  if (one_shot) pvv = std::max(pvv, zo_slabs(nv, batch) * o);
   p->pvv_bytes = align256(pvv * 6 * v * 8);
-  p->off_Pvv = take(2 * p->pvv_bytes);
+  p->off_Pvv = take(p->sets * p->pvv_bytes);
   if (flags & CC3_LOWP_CONTRACT) {
     if (prec == CC3_FP32) {
       p->gf_bytes = align256(o * (v + o) * v * v * 4);
@@ -251,7 +253,7 @@ int make_plan_ex(int no, int nv, int nchol, int prec, unsigned flags, bool with_
       p->cubef_bytes = align256((size_t)batch * lp_contract_cube_bytes(prec, nv));
     }
     p->off_gf = take(2 * p->gf_bytes);
-    p->off_cubef = take(sets * p->cubef_bytes);
+    p->off_cubef = take(p->sets * p->cubef_bytes);
   }
   p->off_tri = take((size_t)std::max(1, p->ntri) * 3 * sizeof(int) + 64);
   p->off_flag = take(64);
@@ -260,8 +262,8 @@ int make_plan_ex(int no, int nv, int nchol, int prec, unsigned flags, bool with_
                           align256(J * o * v * 8) * 2 + align256(J * 8) + align256(J * o * o * 8)
                     : 0;
   p->cube_bytes = align256((size_t)batch * NSLOT * p->cube * 8);
-  size_t region = std::max(p->chol_bytes, sets * p->cube_bytes);
-  if (with_blocks) {
+  size_t region = std::max(p->chol_bytes, p->sets * p->cube_bytes);
+  if (one_shot) {
     const size_t nmo = o + v;
     p->off_stage = take(align256(nmo * 8) + 2 * align256(o * v * 8) + align256(o * o * v * v * 8));
     // setup-time staging in the cube region: a host L after the Cholesky scratch,
@@ -287,15 +289,15 @@ Ws carve(const Plan& p, void* ws, const Blocks* external_blocks) {
   w.OtT = (double*)(base + p.off_OtT);
   w.t2N = (double*)(base + p.off_t2N);
   lp_operand_ptrs(p.prec, p.no, p.nv, base + p.off_lp, w.lp);
-  for (int k = 0; k < 2; ++k) {
-    w.Pvv[k] = (double*)(base + p.off_Pvv + k * p.pvv_bytes);
-    w.cubes[k] = (double*)(base + p.off_cubes + k * p.cube_bytes);
+  for (int k = 0; k < 2; ++k) {  // a plan with one set has no second
+    w.Pvv[k] = k < p.sets ? (double*)(base + p.off_Pvv + k * p.pvv_bytes) : nullptr;
+    w.cubes[k] = k < p.sets ? (double*)(base + p.off_cubes + k * p.cube_bytes) : nullptr;
   }
   w.GbcX = w.GcbX = w.cubesX[0] = w.cubesX[1] = nullptr;
   if (p.gf_bytes) {
     w.GbcX = base + p.off_gf;
     w.GcbX = base + p.off_gf + p.gf_bytes;
-    for (int k = 0; k < 2; ++k) w.cubesX[k] = base + p.off_cubef + k * p.cubef_bytes;
+    for (int k = 0; k < p.sets; ++k) w.cubesX[k] = base + p.off_cubef + k * p.cubef_bytes;
   }
   w.tri = (int*)(base + p.off_tri);
   w.flag = (int*)(base + p.off_flag);

@@ -163,6 +163,7 @@ struct Plan {
   unsigned flags;
   int ntri;     // unordered triples i >= j >= k, not all equal
   int batch;    // triples per batch of the triple loop
+  int sets;     // buffer sets of cubes and partial slabs
   size_t cube;  // doubles per cube slot (cube_slot: nv x nv rows at the padded pitch)
   // byte offsets into the workspace
   size_t off_blocks;  // integral blocks (when the workspace holds them)
@@ -174,7 +175,7 @@ struct Plan {
   // and omega1 at off_stage; a host L, or the host integral blocks, pass through
   // the cube region during setup (stage_region bytes from off_cubes)
   size_t off_stage, stage_region;
-  size_t chol_bytes, cube_bytes, pvv_bytes;  // per buffer set (two sets)
+  size_t chol_bytes, cube_bytes, pvv_bytes;  // cube_bytes and pvv_bytes: per buffer set
   size_t total;
 };
 

@@ -6,6 +6,8 @@ import time
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SCRATCH = 256 << 20      # the allocation-free call's array
+CALLER_STREAM = 1 << 30  # the plan of that call (PLAN_CALLER_STREAM)
 
 
 @pytest.fixture(scope="module")
@@ -47,3 +49,24 @@ SMALL_BUDGET = {
 def test_small_cube_budget_bounds_the_plan(size, monkeypatch, no, nv, mb):
     monkeypatch.setenv("CC3_CUBE_BUDGET_MB", str(mb))
     assert size(no, nv) <= SMALL_BUDGET[no, nv, mb]
+
+
+NO = (2, 3, 4, 6, 8, 10, 12, 16, 18, 24, 31, 40, 63)
+# Largest nv per no, at nchol = 3 (no + nv), of a loop on two streams with five cubes per
+# triple and integral blocks without padding; every smaller nv fitted too.
+TAKEN = {
+    (0, 0): (104, 101, 97, 91, 86, 81, 77, 69, 66, 56, 46, 36, 19),
+    (1, 0): (103, 98, 95, 88, 82, 77, 73, 65, 62, 53, 43, 33, 17),
+    (1, 8): (98, 95, 90, 83, 78, 72, 68, 61, 58, 49, 41, 32, 17),
+    (2, 0): (103, 98, 95, 88, 82, 77, 73, 65, 62, 53, 43, 33, 17),
+    (2, 8): (96, 92, 88, 81, 76, 72, 67, 61, 57, 48, 40, 32, 16),
+    (3, 0): (102, 97, 94, 87, 81, 75, 71, 64, 61, 51, 42, 32, 16),
+    (3, 8): (94, 88, 85, 79, 72, 68, 64, 57, 55, 46, 38, 29, 16)}
+
+
+@pytest.mark.parametrize("prec,flags", sorted(TAKEN))
+def test_allocation_free_call_takes_these_sizes(size, monkeypatch, prec, flags):
+    monkeypatch.setenv("CC3_BATCH", "1")  # one triple per batch: the least it can do with
+    for no, top in zip(NO, TAKEN[prec, flags]):
+        for nv in range(1, top + 1):
+            assert size(no, nv, prec, flags | CALLER_STREAM) <= SCRATCH, (no, nv)
