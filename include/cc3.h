@@ -259,15 +259,19 @@ int cc3_jacobian_prep(cc3_ctx* ctx, int no, int nv, int nchol, const double* eps
 int cc3_batch_plan(int no, int nv, int nchol, int prec, unsigned flags, int* triples_per_batch,
                    int* nbatches);
 
-/* Bytes of device workspace for cc3_transition_density at these sizes (host-only).
- * Where the two cubes of every unordered triple fit 64 GiB (twice the per-set cube budget,
- * CC3_CUBE_BUDGET_MB in the environment) the size includes them, and each triple is built
- * once; otherwise, and for a call that is given less, down to about 4 no + 2 cubes of
- * nv^3 doubles, the loop rebuilds triples per occupied pair (the same densities to
- * rounding, two to three times the time).
+/* Bytes of device workspace with which cc3_transition_density is fastest at these sizes
+ * (host-only).  Where the two cubes of every unordered triple fit 64 GiB (twice the per-set
+ * cube budget, CC3_CUBE_BUDGET_MB in the environment) they are included and each triple is
+ * built once; otherwise this is the least size.
  * Supported sizes: 1 <= no <= 63, 1 <= nv <= 400, nchol >= 1.
  * Errors: CC3_E_INVAL. */
 int cc3_transition_density_workspace_size(int no, int nv, int nchol, size_t* bytes);
+
+/* The least bytes of workspace that cc3_transition_density accepts at these sizes (host-only).
+ * With less than cc3_transition_density_workspace_size the loop rebuilds triples per occupied
+ * pair: the same densities to rounding in more time (12/120/400: 1.1 GB and 152 ms instead of
+ * 11.0 GB and 69 ms).  Errors as above. */
+int cc3_transition_density_workspace_min(int no, int nv, int nchol, size_t* bytes);
 
 /* The triples contributions to the transition density D^{m,0} of one left state
  * (Sec. "Implementation", Algorithm 3).  With tau the ground-state t3 of
@@ -284,7 +288,7 @@ int cc3_transition_density_workspace_size(int no, int nv, int nchol, size_t* byt
  * The integrals and F_kc are the T1-transformed ones of cc3_triples_residual.
  * The occupied-occupied block, which the paper evaluates in a loop over virtual
  * triples, is evaluated here as the Gram matrices <L~_{ijk}, tau_{ijl}> of the
- * cubes of each occupied pair (i, j); the loop runs over those pairs.
+ * cubes of each occupied pair (i, j).
  * Inputs (device memory only): eps[no+nv], L[nchol][nmo][nmo], t1[no][nv],
  * t2[no][no][nv][nv] as for cc3_triples_residual; l1[no][nv] = L^a_i and
  * l2[no][no][nv][nv] = L^{ab}_{ij} (l2[i][j][a][b] == l2[j][i][b][a]) of the left
@@ -292,7 +296,8 @@ int cc3_transition_density_workspace_size(int no, int nv, int nchol, size_t* byt
  * Outputs (device memory, row-major, overwritten or added with CC3_ACCUMULATE):
  * D_cd[nv][nv], D_kc[no][nv], D_ld[no][nv], D_lk[no][no]; Yo[nv][no][no][no] = Y^o
  * (may be NULL).  FP64 throughout.  flags: CC3_ACCUMULATE, CC3_DETERMINISTIC.
- * workspace: at least cc3_transition_density_workspace_size bytes, 256-byte aligned.
+ * workspace: at least cc3_transition_density_workspace_min bytes, better
+ * cc3_transition_density_workspace_size, 256-byte aligned.
  * Errors: CC3_E_INVAL (sizes, flags, host pointers), CC3_E_NOMEM, CC3_E_DEVICE. */
 int cc3_transition_density(cc3_ctx* ctx, int no, int nv, int nchol, const double* eps,
                            const double* L, const double* t1, const double* t2, const double* l1,

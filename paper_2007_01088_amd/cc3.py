@@ -69,6 +69,8 @@ _residual_noalloc = _sig("cc3_triples_residual_noalloc",
                           ctypes.c_uint, _vp])
 _td_ws = _sig("cc3_transition_density_workspace_size",
                [_c_int, _c_int, _c_int, ctypes.POINTER(_c_size)])
+_td_ws_min = _sig("cc3_transition_density_workspace_min",
+                  [_c_int, _c_int, _c_int, ctypes.POINTER(_c_size)])
 _td = _sig("cc3_transition_density",
            [_vp, _c_int, _c_int, _c_int, _dp, _dp, _dp, _dp, _dp, _dp, ctypes.c_double, _dp, _dp,
             _dp, _dp, _dp, ctypes.c_uint, _vp, _c_size, _vp])
@@ -123,7 +125,8 @@ EXPORTED = ["cc3_create", "cc3_destroy", "cc3_last_error", "cc3_workspace_size",
             "cc3_triples_residual", "cc3_triples_residual_blocks", "cc3_triples_residual_subset",
             "cc3_t3_block", "cc3_triples_residual_subset_blocks", "cc3_t3_block_blocks",
             "cc3_flops", "cc3_batch_plan", "cc3_triples_residual_noalloc",
-            "cc3_transition_density_workspace_size", "cc3_transition_density", "cc3_cvs_triples", "cc3_profile_enable", "cc3_profile_get",
+            "cc3_transition_density_workspace_size", "cc3_transition_density_workspace_min",
+            "cc3_transition_density", "cc3_cvs_triples", "cc3_profile_enable", "cc3_profile_get",
             "cc3_jacobian_prep", "cc3_server_create", "cc3_server_destroy", "cc3_server_footprint",
             "cc3_molecule_register", "cc3_molecule_release", "cc3_submit", "cc3_poll",
             "cc3_wait", "cc3_cancel", "cc3_server_get_stats", "cc3_server_set_packing"]
@@ -202,6 +205,10 @@ def flops(no: int, nv: int) -> tuple[float, float]:
     return a.value, b.value
 
 
+# Bytes of workspace that a transition-density call may leave cached in its Context.
+KEEP_WORKSPACE = 16 << 30
+
+
 class Context:
     """A libcc3 context on one device, with a cached workspace tensor."""
 
@@ -229,6 +236,27 @@ class Context:
             self._ws = torch.empty(max(nbytes, 256), dtype=torch.uint8,
                                    device=f"cuda:{self.device}")
         return self._ws
+
+    def _density_workspace(self, no: int, nv: int, nchol: int) -> torch.Tensor:
+        """The cached workspace, grown to the fastest loop's where the device has that much
+        free, else to the least."""
+        n = _c_size(0)
+        _check(_td_ws(no, nv, nchol, ctypes.byref(n)), "cc3_transition_density_workspace_size")
+        best, have = n.value, 0 if self._ws is None else self._ws.numel()
+        if have < best:
+            _check(_td_ws_min(no, nv, nchol, ctypes.byref(n)),
+                   "cc3_transition_density_workspace_min")
+            if n.value < best:
+                dev = self.device
+                free = (torch.cuda.mem_get_info(dev)[0] + torch.cuda.memory_reserved(dev)
+                        - torch.cuda.memory_allocated(dev) + have)
+                if best <= free:
+                    try:
+                        return self.workspace(best)
+                    except torch.OutOfMemoryError:  # not in one piece
+                        pass
+                return self.workspace(n.value)
+        return self.workspace(best)
 
     # ---- residual calls ------------------------------------------------
     def triples_residual(self, eps, L, t1, t2, omega1=None, omega2=None, prec=FP64, flags=0,
@@ -366,15 +394,22 @@ class Context:
                    torch.empty((no, no), dtype=torch.float64, device=dev),
                    torch.empty((nv, no, no, no), dtype=torch.float64, device=dev)
                    if want_yo else None)
-        n = _c_size(0)
-        _check(_td_ws(no, nv, nchol, ctypes.byref(n)), "cc3_transition_density_workspace_size")
-        ws = self.workspace(n.value)
+        cached = self._ws
+        ws = self._density_workspace(no, nv, nchol)
         dcd, dkc, dld, dlk, yo = out
-        _check(_td(self._h, no, nv, nchol, _ptr(eps, "eps"), _ptr(L, "L"), _ptr(t1, "t1"),
-                   _ptr(t2, "t2"), _ptr(l1, "l1"), _ptr(l2, "l2"), float(omega),
-                   _ptr(dcd, "D_cd"), _ptr(dkc, "D_kc"), _ptr(dld, "D_ld"), _ptr(dlk, "D_lk"),
-                   _ptr(yo, "Yo"), flags, ws.data_ptr(), ws.numel(), _stream(stream)),
-               "cc3_transition_density")
+        try:
+            _check(_td(self._h, no, nv, nchol, _ptr(eps, "eps"), _ptr(L, "L"), _ptr(t1, "t1"),
+                       _ptr(t2, "t2"), _ptr(l1, "l1"), _ptr(l2, "l2"), float(omega),
+                       _ptr(dcd, "D_cd"), _ptr(dkc, "D_kc"), _ptr(dld, "D_ld"),
+                       _ptr(dlk, "D_lk"), _ptr(yo, "Yo"), flags, ws.data_ptr(), ws.numel(),
+                       _stream(stream)), "cc3_transition_density")
+        finally:
+            # a buffer of tens of GB goes back to torch, which may hand it out again only
+            # after the work on `stream`
+            if ws is not cached and ws.numel() > KEEP_WORKSPACE:
+                if stream is not None:
+                    ws.record_stream(torch.cuda.ExternalStream(_stream(stream), ws.device))
+                self._ws = None
         return out if want_yo else out[:4]
 
     # ---- kernel timing ---------------------------------------------------

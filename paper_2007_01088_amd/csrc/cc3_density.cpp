@@ -135,6 +135,20 @@ extern "C" int cc3_transition_density_workspace_size(int no, int nv, int nchol, 
   return CC3_OK;
 }
 
+extern "C" int cc3_transition_density_workspace_min(int no, int nv, int nchol, size_t* bytes) {
+  if (!bytes) return fail(CC3_E_INVAL, "cc3_transition_density_workspace_min: bytes is NULL");
+  int rc = check_density_sizes(no, nv, nchol);
+  if (rc) return rc;
+  DPlan p;
+  make_dplan(no, nv, nchol, false, &p);
+  *bytes = p.total;
+  if (resident_fits(no, nv)) {
+    make_dplan(no, nv, nchol, true, &p);
+    *bytes = std::min(*bytes, p.total);
+  }
+  return CC3_OK;
+}
+
 extern "C" int cc3_transition_density(cc3_ctx* c, int no, int nv, int nchol, const double* eps,
                                       const double* L, const double* t1, const double* t2,
                                       const double* l1, const double* l2, double omega,

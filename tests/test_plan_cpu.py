@@ -70,3 +70,23 @@ def test_allocation_free_call_takes_these_sizes(size, monkeypatch, prec, flags):
     for no, top in zip(NO, TAKEN[prec, flags]):
         for nv in range(1, top + 1):
             assert size(no, nv, prec, flags | CALLER_STREAM) <= SCRATCH, (no, nv)
+
+
+def test_transition_density_sizes():
+    lib = ctypes.CDLL(os.path.join(ROOT, "paper_2007_01088_amd", "libcc3.so"))
+    best, least = ctypes.c_size_t(0), ctypes.c_size_t(0)
+    fb, fl = lib.cc3_transition_density_workspace_size, lib.cc3_transition_density_workspace_min
+    for f in (fb, fl):
+        f.argtypes = [ctypes.c_int] * 3 + [ctypes.POINTER(ctypes.c_size_t)]
+    for no, nv in ((2, 9), (12, 120), (16, 150), (40, 60), (63, 400)):
+        assert fb(no, nv, 3 * (no + nv), ctypes.byref(best)) == 0
+        assert fl(no, nv, 3 * (no + nv), ctypes.byref(least)) == 0
+        if no == 63:  # cubes beyond 64 GiB
+            assert least.value == best.value
+        else:
+            assert least.value < best.value
+    # the loop by pairs at 12/120: 1.1 GB
+    assert fl(12, 120, 400, ctypes.byref(least)) == 0 and least.value < 1.2e9
+    for bad in ((0, 9, 9), (4, 401, 9), (4, 9, 0)):
+        assert fl(*bad, ctypes.byref(least)) == -1
+    assert fl(4, 9, 9, None) == -1
