@@ -104,8 +104,10 @@ void make_dplan(int no, int nv, int nchol, bool resident, DPlan* p) {
   p->total = off;
 }
 
-// Whether the resident loop's cubes fit the budget.
+// Whether the resident loop's cubes fit the budget.  (no = 1 has no triple to share between
+// pairs, and the loop by pairs skips the contractions of its one, all-equal triple.)
 bool resident_fits(int no, int nv) {
+  if (no == 1) return false;
   const size_t n = (size_t)no * (no + 1) * (no + 2) / 6;
   return 2 * n * (size_t)cube_slot(nv) * 8 <= cube_budget();
 }

@@ -78,10 +78,10 @@ def test_transition_density_sizes():
     fb, fl = lib.cc3_transition_density_workspace_size, lib.cc3_transition_density_workspace_min
     for f in (fb, fl):
         f.argtypes = [ctypes.c_int] * 3 + [ctypes.POINTER(ctypes.c_size_t)]
-    for no, nv in ((2, 9), (12, 120), (16, 150), (40, 60), (63, 400)):
+    for no, nv in ((1, 64), (2, 9), (12, 120), (16, 150), (40, 60), (63, 400)):
         assert fb(no, nv, 3 * (no + nv), ctypes.byref(best)) == 0
         assert fl(no, nv, 3 * (no + nv), ctypes.byref(least)) == 0
-        if no == 63:  # cubes beyond 64 GiB
+        if no in (1, 63):  # nothing to keep between pairs; cubes beyond 64 GiB
             assert least.value == best.value
         else:
             assert least.value < best.value
