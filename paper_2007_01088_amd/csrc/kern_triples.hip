@@ -1227,9 +1227,8 @@ __device__ inline void u_view(int pi, int nv, int rp, int& slot, int& sbb, int& 
 // in the MFMA layout directly (16 consecutive a per row of c); views with c
 // contiguous are loaded along c (4 rows of 16 consecutive c per instruction) and
 // transposed through a wavefront-private LDS tile.
-// WS > 1: the workgroup has 4 WS wavefronts; 1, 2 or 4 of them lie side by side over a and
-// the others take shares of the (pair, step) loop, added in share order: a small launch
-// is one chain of loads per wavefront (at 4/20 28 -> 14 us, at 6/45 40 -> 28 us).
+// SHARES: of the workgroup's 4 WS wavefronts 1, 2 or 4 (oo_waves_a) lie side by side over a
+// and the others take shares of the (pair, step) loop, added in share order.
 // the view of U_pi as (column m, fixed index b, contracted c) in TT[x][y][z]
 __device__ inline void oo_view(int pi, int nv, int rp, int& sbb, int& sm, int& sk) {
   const int pl = nv * rp;
@@ -1242,17 +1241,21 @@ __device__ inline void oo_view(int pi, int nv, int rp, int& sbb, int& sm, int& s
     default: sbb = pl; sm = 1; sk = rp; break;  // TT[b][c][a]
   }
 }
-// SEQ: the packed form, where a wavefront takes the shares in turn: the sums of the call alone.
 // wavefronts side by side over a in the form with shares, and its shares (1: the other form).
-// Shares where fewer than 640 workgroups run (no <= 16, so that 16 wavefronts have the
-// registers).  MEASURED, calls with / without: 4/20 (80) 84 / 99 us, 5/30 (150) 130 / 156,
-// 6/45 (276) 461 / 506, 8/64 (512) 1593 / 1633, 12/60 (720) 3.82 / 3.79 ms, 3/140 (1260)
-// 1.459 / 1.436.
+// no <= 16, where 16 wavefronts have the registers: shares where fewer than 640 workgroups
+// run, since a small launch is one chain of loads per wavefront.  MEASURED, calls with /
+// without: 4/20 (80) 84 / 99 us, 5/30 (150) 130 / 156, 6/45 (276) 461 / 506, 8/64 (512) 1593 /
+// 1633, 12/60 (720) 3.82 / 3.79 ms, 3/140 (1260) 1.459 / 1.436.
+// Above, 4 wavefronts: shares up to nv = 32, where 2 or 3 of them would have no columns.
+// MEASURED, BF16x3 mixed-all calls with / without: 63/8 27.1 / 32.6 ms, 63/16 47.2 / 57.5,
+// 40/12 6.6 / 7.9, 48/24 27.5 / 31.7, 30/20 4.7 / 5.7, 20/32 2.65 / 2.87.
 __host__ __device__ inline int oo_waves_a(int nv) { return nv <= 16 ? 1 : nv <= 32 ? 2 : 4; }
 __host__ __device__ inline int oo_shares(int no, int nv) {
-  return no <= 16 && ((nv + 1) / 2) * ((nv + 63) / 64) * no * 2 < 640 ? 16 / oo_waves_a(nv) : 1;
+  if (no > 16) return 4 / oo_waves_a(nv);
+  return ((nv + 1) / 2) * ((nv + 63) / 64) * no * 2 < 640 ? 16 / oo_waves_a(nv) : 1;
 }
-template <int FNO, int WS, bool SEQ>
+// SEQ: the packed form, where a wavefront takes the shares in turn: the sums of the call alone.
+template <int FNO, int WS, bool SHARES, bool SEQ>
 __device__ __forceinline__ void omega_oo_body(const double* __restrict__ cubes,
                                               const double* __restrict__ Hs,
                                               const int* __restrict__ tri, int ntri,
@@ -1260,21 +1263,21 @@ __device__ __forceinline__ void omega_oo_body(const double* __restrict__ cubes,
                                               double* __restrict__ OtT, int no, int nv,
                                               int tiles_a, int bx, int by, int form) {
   constexpr int NB = 2;
-  // per wavefront: 16 rows a x 16 c (+1 pad) of each b; with WS its share's sums
-  constexpr int LT = WS > 1 && NB * FNO * 256 > NB * 16 * 17 ? NB * FNO * 256 : NB * 16 * 17;
+  // per wavefront: 16 rows a x 16 c (+1 pad) of each b; with SHARES its share's sums
+  constexpr int LT = SHARES && NB * FNO * 256 > NB * 16 * 17 ? NB * FNO * 256 : NB * 16 * 17;
   __shared__ double lts[4 * WS][LT];
   __shared__ int lz[PLIST_MAX], lqr[PLIST_MAX], cz[LIST_SCRATCH];
   double* __restrict__ Out = form ? Ot2 : OtT;
   const int p = by;
   const int bp = bx / tiles_a;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wa = WS > 1 ? oo_waves_a(nv) : 4;  // wavefronts over a
+  const int wa = SHARES ? oo_waves_a(nv) : 4;  // wavefronts over a
   const int share = wave / wa;
-  const int shares = WS > 1 ? 4 * WS / wa : SEQ ? oo_shares(no, nv) : 1;
+  const int shares = SHARES ? 4 * WS / wa : SEQ ? oo_shares(no, nv) : 1;
   const int a0 = (bx % tiles_a) * 16 * wa + 16 * (wave % wa);
   double (*lt)[16][17] = (double (*)[16][17])lts[wave];
   const int n = list_pairs(tri, ntri, p, -1, form ? 0x18u : 0x27u, no, lz, lqr, cz);
-  if (n == 0 || (WS == 1 && a0 >= nv)) return;  // no workgroup barrier follows
+  if (n == 0 || (!SHARES && a0 >= nv)) return;  // no workgroup barrier follows
   const int m = lane & 15, kq = lane >> 4;
   int bb[NB];
 #pragma unroll
@@ -1372,7 +1375,7 @@ __device__ __forceinline__ void omega_oo_body(const double* __restrict__ cubes,
     }
   };
   if constexpr (!SEQ) {
-    if (a0 < nv) run(WS > 1 ? share : 0);
+    if (a0 < nv) run(SHARES ? share : 0);
   } else {
     d4v tot[NB][FNO];
     for (int sh = 0; sh < shares; ++sh) {
@@ -1390,7 +1393,7 @@ __device__ __forceinline__ void omega_oo_body(const double* __restrict__ cubes,
 #pragma unroll
       for (int f = 0; f < FNO; ++f) acc[j][f] = tot[j][f];
   }
-  if constexpr (WS > 1) {
+  if constexpr (SHARES) {
     if (share > 0) {
 #pragma unroll
       for (int j = 0; j < NB; ++j)
@@ -1425,15 +1428,15 @@ __device__ __forceinline__ void omega_oo_body(const double* __restrict__ cubes,
   }
 }
 
-template <int FNO, int WS>
+template <int FNO, int WS, bool SHARES>
 __global__ __launch_bounds__(256 * WS) void k_omega_oo(const double* __restrict__ cubes,
                                                        const double* __restrict__ Hs,
                                                        const int* __restrict__ tri, int ntri,
                                                        double* __restrict__ Ot2,
                                                        double* __restrict__ OtT, int no, int nv,
                                                        int tiles_a) {
-  omega_oo_body<FNO, WS, false>(cubes, Hs, tri, ntri, Ot2, OtT, no, nv, tiles_a, blockIdx.x, blockIdx.y,
-                     blockIdx.z);
+  omega_oo_body<FNO, WS, SHARES, false>(cubes, Hs, tri, ntri, Ot2, OtT, no, nv, tiles_a, blockIdx.x,
+                                        blockIdx.y, blockIdx.z);
 }
 
 // For output block (p, x):
@@ -1951,11 +1954,11 @@ void launch_omega_oo(const double* cubes, const Blocks& b, const int* tri, int n
     hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, st, cubes, b.Hs, tri, ntri, Ot2, OtT, no, nv,
                        ta);
   };
-  if (oo_shares(no, nv) > 1) run(k_omega_oo<1, 4>, 1024);
-  else if (no <= 16) run(k_omega_oo<1, 1>, 256);
-  else if (no <= 32) run(k_omega_oo<2, 1>, 256);
-  else if (no <= 48) run(k_omega_oo<3, 1>, 256);
-  else run(k_omega_oo<4, 1>, 256);
+  const bool sh = oo_shares(no, nv) > 1;
+  if (no <= 16) sh ? run(k_omega_oo<1, 4, true>, 1024) : run(k_omega_oo<1, 1, false>, 256);
+  else if (no <= 32) run(sh ? k_omega_oo<2, 1, true> : k_omega_oo<2, 1, false>, 256);
+  else if (no <= 48) run(sh ? k_omega_oo<3, 1, true> : k_omega_oo<3, 1, false>, 256);
+  else run(sh ? k_omega_oo<4, 1, true> : k_omega_oo<4, 1, false>, 256);
 }
 
 void launch_reduce(const int* tri, int ntri, const double* Pvv, double* Ot1, double* Ot2, int no,
@@ -2030,7 +2033,7 @@ __global__ __launch_bounds__(256) void k_pack_omega_oo(const PackJob* __restrict
     const unsigned local = item - J.first[PK_OO];
     const int ta = (J.nv + 63) / 64;
     const unsigned gx = (unsigned)((J.nv + 1) / 2) * ta;
-    omega_oo_body<FNO, 1, true>(J.cubes, J.Hs, J.tri, J.ntri, J.Ot2, J.OtT, J.no, J.nv, ta,
+    omega_oo_body<FNO, 1, false, true>(J.cubes, J.Hs, J.tri, J.ntri, J.Ot2, J.OtT, J.no, J.nv, ta,
                        (int)(local % gx), (int)((local / gx) % J.no), (int)(local / (gx * J.no)));
     __syncthreads();
   }

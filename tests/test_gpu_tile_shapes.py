@@ -14,7 +14,7 @@ import torch
 
 from oracle import cc3_oracle as O
 from paper_2007_01088_amd import cc3
-from paper_2007_01088_amd.synth import make_inputs, make_left_inputs
+from paper_2007_01088_amd.synth import make_inputs, make_left_inputs, sample_triples
 
 pytestmark = pytest.mark.gpu
 TOL = 1e-11
@@ -100,7 +100,8 @@ def test_mixed_all_at_tile_edges(no, nv, prec, bar):
 GROUPS = [(cc3.FP32, [(6, 150), (5, 120), (4, 93), (3, 118), (3, 117)]),
           (cc3.FP32, [(9, 120), (4, 145), (5, 64), (3, 128)]),
           (cc3.BF16X6, [(7, 113), (5, 63), (4, 81), (3, 97), (2, 130)]),
-          (cc3.BF16X3, [(7, 81), (5, 64), (4, 113), (3, 97), (2, 33)])]
+          (cc3.BF16X3, [(7, 81), (5, 64), (4, 113), (3, 97), (2, 33)]),
+          (cc3.FP64, [(17, 30), (20, 12), (9, 40), (33, 16), (18, 33)])]
 
 
 @pytest.mark.parametrize("prec,members", GROUPS)
@@ -120,3 +121,19 @@ def test_packed_group_of_mixed_tiles_equals_alone(prec, members):
         a1, a2, _ = srv.wait(srv.submit(m, g[3], prec=prec), mol=m)
         assert torch.equal(a1, p1) and torch.equal(a2, p2)
     srv.close()
+
+
+@pytest.mark.parametrize("no,nv", [(17, 1), (17, 16), (20, 5), (18, 17), (21, 32), (18, 33), (33, 7),
+                                   (34, 17), (49, 3), (63, 16)])
+def test_oo_terms_in_shares_above_16_occupied(no, nv):
+    """Wavefronts without columns of their own (nv <= 32) take shares of the oo terms: each
+    count of row blocks, one and two wavefronts side by side, and the next size up."""
+    d = make_inputs(no, nv, 20, tag=66)
+    tri = np.unique(np.concatenate([sample_triples(no, 150, seed=no),
+                                    [[no - 1, no - 1, 0], [no - 1, 0, 0]]]), axis=0).astype(np.int32)
+    ctx = cc3.Context(0)
+    g = cuda(d["eps"], d["L"], d["t1"], d["t2"])
+    o1, o2 = ctx.triples_residual_subset(*g, tri)
+    r1, r2 = O.omega_tilde_subset(d["eps"], d["L"], d["t1"], d["t2"], tri)
+    assert rel(o1.cpu().numpy(), r1) < TOL
+    assert rel(o2.cpu().numpy(), r2) < TOL
