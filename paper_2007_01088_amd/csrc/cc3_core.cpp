@@ -218,17 +218,25 @@ int make_plan_ex(int no, int nv, int nchol, int prec, unsigned flags, bool with_
   batch = std::max(batch, std::min(no, 8));
   const size_t budget =
       cube_budget ? cube_budget : ((size_t)env_int("CC3_CUBE_BUDGET_MB", 32768) << 20);
-  const size_t per_triple = BUDGET_CUBES * p->cube * sizeof(double);
-  batch = (int)std::min<size_t>((size_t)batch, std::max<size_t>(1, budget / per_triple));
-  batch = env_int("CC3_BATCH", batch);
-  batch = std::min(batch, MAX_BATCH);  // bounds the kernels' per-p pair lists
-  batch = std::max(1, std::min(batch, std::max(1, p->ntri)));
-  // balanced: the loop is split into ceil(ntri / batch) batches whose sizes differ by at
-  // most one, and `batch` becomes the largest of them
-  if (p->ntri > 0) {
-    const int nb = (p->ntri + batch - 1) / batch;
-    batch = (p->ntri + nb - 1) / nb;
+  // balanced: the loop is split into ceil(ntri / n) batches whose sizes differ by at most
+  // one; the largest of them
+  auto balanced = [&](int n) {
+    n = std::max(1, std::min(n, std::max(1, p->ntri)));
+    const int nb = std::max(1, (p->ntri + n - 1) / n);
+    return std::max(1, (p->ntri + nb - 1) / nb);
+  };
+  const size_t held =
+      std::max<size_t>(1, budget / (BUDGET_CUBES * p->cube * sizeof(double)));
+  if (held < (size_t)batch) {
+    // batches of `held` triples with five cubes each, and slabs of one Omega-sized chunk per Zo
+    // chunk: within that much memory (1% less, for the padding of the operands), as many triples
+    // of three slots and their own slabs as it holds
+    const size_t b = balanced((int)std::min<size_t>(held, MAX_BATCH));
+    const size_t doubles = b * BUDGET_CUBES * p->cube + zo_slabs(nv, (int)b) * 6 * v * (v + 1);
+    batch = flags & CC3_LOWP_CONTRACT ? (int)b : batch_within(nv, (int)b, batch, doubles / 100 * 99);
   }
+  batch = env_int("CC3_BATCH", batch);
+  batch = balanced(std::min(batch, MAX_BATCH));  // bounds the kernels' per-p pair lists
   p->batch = batch;
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t at = off; off = align256(off + bytes); return at; };

@@ -121,9 +121,11 @@ __host__ __device__ inline int64_t g_pitch(int nv) {
 // with P2 and tau~T one with P0.  (tau~ in the place of PA, which leaves two slots, measured
 // 2% slower for a call of 12/120.)
 enum { SLOT_P0 = 0, SLOT_P1 = 1, SLOT_P2 = 2, SLOT_TT = SLOT_P2, SLOT_TTT = SLOT_P0, NSLOT = 3 };
-// Cubes that a plan's cube budget counts per triple: its slots, and two for its partial slabs.
-// (Counting the slots alone, a server's request of 3/190 at a budget of 512 MiB takes three
-// triples per batch and 1.6 GiB of its arena; so counted, one and 0.56 GiB.)
+// Cubes per triple that a plan's cube budget is divided by; the batch is then as large as the
+// memory of so many triples holds (make_plan_ex).  A request of a server, whose budget is a
+// share of its arena, takes no more of it than with five slots per triple.  (Dividing by the
+// slots alone: 3/190 at a budget of 512 MiB three triples per batch and 1.6 GiB, against one
+// and 0.56.)
 constexpr int BUDGET_CUBES = NSLOT + 2;
 // Whether the W build of a precision writes two planes per triple (all but CC3_BF16X3).
 inline bool two_planes(int prec) { return prec != 2; }
@@ -275,6 +277,8 @@ int zo_nbchunks(int nv, int ntri);    // b chunks of one Zo product
 // The largest triples x chunks of a launch of either over the batches of 1 to `batch` triples
 size_t omega_slabs(int nv, int batch, bool fp32acc);
 size_t zo_slabs(int nv, int batch);
+// The most triples, from `least` to `most`, whose slots and Omega slabs take at most `doubles`
+int batch_within(int nv, int least, int most, size_t doubles);
 void launch_back_transform(const double* Ot1, const double* Ot2, const double* OtT, double* O1,
                            double* O2, int no, int nv, bool accumulate, hipStream_t st);
 void launch_set_triples(int* tri_dev, const int* host_tri, int n, hipStream_t st);

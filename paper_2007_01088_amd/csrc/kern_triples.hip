@@ -1902,6 +1902,18 @@ size_t zo_slabs(int nv, int batch) {
   return most;
 }
 
+int batch_within(int nv, int least, int most, size_t doubles) {
+  const OmegaSplit s = omega_split(nv, false);
+  const size_t cube = (size_t)cube_slot(nv), slab = 6 * (size_t)nv * (nv + 1);
+  size_t slabs = 1;
+  int best = least;
+  for (int nb = 1; nb <= most; ++nb) {
+    slabs = std::max(slabs, (size_t)nb * omega_chunks(s, nb, false));
+    if (nb > best && NSLOT * nb * cube + slabs * slab <= doubles) best = nb;
+  }
+  return best;
+}
+
 static unsigned omega_wgs(int nv, int ntri, int nch, int shape) {
   int tm, tn;
   shape_tiles(shape, nv, nv + 1, &tm, &tn);
