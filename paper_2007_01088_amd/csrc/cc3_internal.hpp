@@ -273,6 +273,7 @@ void launch_combine(const double* Ot1, const double* Ot2, const double* OtT, dou
 // K chunks of one Omega GEMM; fp32acc: its chunks are summed in FP32 (the mixed-all
 // forms), at most 4096 k each
 int omega_kchunks(int nv, int ntri, bool fp32acc = false);
+bool omega_lds(int nv);  // the FP64 Omega GEMM runs on LDS tiles
 int zo_nbchunks(int nv, int ntri);    // b chunks of one Zo product
 // The largest triples x chunks of a launch of either over the batches of 1 to `batch` triples
 size_t omega_slabs(int nv, int batch, bool fp32acc);

@@ -237,9 +237,10 @@ int cc3_server::ensure_slot(Slot& s) {
 }
 
 // A request may join a packed group: a W-only precision, and small enough that
-// its own launches would leave the device partly idle.
+// its own launches would leave the device partly idle; the packed Omega GEMM has the wave-tile
+// form only, whose sums run in another order than those of the LDS form.
 bool cc3_server::packable(const Request& r) const {
-  if (max_pack < 2) return false;
+  if (max_pack < 2 || omega_lds(r.plan.nv)) return false;
   const double v = r.plan.nv, o = r.plan.no;
   return 4.0 * v * v * v * v * o * o * o <= pack_flops;
 }

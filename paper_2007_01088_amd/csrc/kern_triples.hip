@@ -273,15 +273,19 @@ __device__ __forceinline__ void wbuild_body(const E* __restrict__ t2, const E* _
 // relative time per block measured at nv = 150 to 400 about 1 + 0.7 (1/FM + 1/FN - 1/2)
 // (3 x 3 1.04 to 1.2, 5 x 2 1.16 to 1.26, 4 x 3 1.0 to 1.09, 5 x 4 0.98 to 1.05 of 4 x 4).
 // The item loop of the packed kernels takes registers that 5 x 4 and 5 x 2 do not leave.
+static double shape_cost(int s, int64_t M, int64_t N) {
+  const double fm = kShapes[s].fm, fn = kShapes[s].fn;
+  int tm, tn;
+  shape_tiles(s, M, N, &tm, &tn);
+  return tm * fm * tn * fn * (0.65 + 0.7 * (1.0 / fm + 1.0 / fn));
+}
 int pick_shape(int64_t M, int64_t N, bool packed, int most) {
   int best = 0;
   double cost = 0.0;
   for (int s = 0; s < NSHAPE; ++s) {
-    const double fm = kShapes[s].fm, fn = kShapes[s].fn;
-    if (fm * fn > most || (packed && (fm * fn == 20 || fm * fn == 10))) continue;
-    int tm, tn;
-    shape_tiles(s, M, N, &tm, &tn);
-    const double c = tm * fm * tn * fn * (0.65 + 0.7 * (1.0 / fm + 1.0 / fn));
+    const int blocks = kShapes[s].fm * kShapes[s].fn;
+    if (blocks > most || (packed && (blocks == 20 || blocks == 10))) continue;
+    const double c = shape_cost(s, M, N);
     if (cost == 0.0 || c < cost) { best = s; cost = c; }
   }
   return best;
@@ -993,6 +997,143 @@ __global__ __launch_bounds__(WNT, shape_waves(FM, FN)) void k_omega(
 // 128 x 128 tiles on 8 wavefronts of 32 x 64 through LDS, 16 k per stage.
 typedef TileCfg<4, 2, 2, 4, 16> OCfg;
 typedef float f4v_ __attribute__((ext_vector_type(4)));
+
+// The FP64 form for large nv (omega_lds): the products of k_omega, with its views, K and
+// slabs, on 128 x 128 tiles of 8 wavefronts through LDS, 16 k (two units of 8) per stage.
+// From nv = 448 on the rows of both operands are 1.6 MB and more apart. A wave tile touches
+// 64 bytes of each of 128 rows per unit, and what its neighbours share has left the caches by
+// then; the LDS tile touches 128 bytes of each of 256 rows for four times the outputs.
+// U: tau~ at the tile's first row; AMAJ: a contiguous (rs = 1), else y.  xs, ys, rs: doubles
+// between x, y and rows.  Elements outside K or past y = nv load a valid element, and their
+// zero is applied at the LDS store, so that the loads stay in flight over the current stage's
+// MFMAs.  Rows past nv repeat row nv - 1 (their outputs are never stored).
+template <bool AMAJ>
+__device__ __forceinline__ void omega_lds_tile(const double* __restrict__ U,
+                                               const double* __restrict__ G, int64_t xs, int ys,
+                                               int64_t rs, int64_t gp, int rows, int brow, int nv,
+                                               int s0, int s1, double* lds,
+                                               d4v (&acc)[OCfg::FM][OCfg::FN]) {
+  typedef OCfg T;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave % T::WM, wn = wave / T::WM;
+  const int ux = cube_pitch(nv) / 8, units = nv * ux;
+  // element e: rows xt + 32 e at k = kt; with AMAJ, A's row am at k = ak + 4 e.  Offsets stay
+  // below 191 rows of 8 nv (nv + 7) bytes, below 2^31.
+  const int kt = tid % T::BK, xt = tid / T::BK, am = tid % T::BM, ak = tid / T::BM;
+  static_assert(T::NT / T::BK == 32 && T::NT / T::BM == 4 && T::EA == 4 && T::EB == 4, "mapping");
+  unsigned aoff[AMAJ ? 1 : 4], boff[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    if (!AMAJ) aoff[e] = (unsigned)(min(xt + 32 * e, rows - 1) * rs + (kt & 7)) * 8u;
+    // rows n >= nv of B (only in the last column tile) read the Omega1 row
+    const int n = xt + 32 * e;
+    boff[e] = ((unsigned)(n < brow >> 6 ? n : (brow >> 6) + (brow & 63)) * (unsigned)gp + (unsigned)kt) * 8u;
+  }
+  if (AMAJ) aoff[0] = (unsigned)(min(am, rows - 1) + ak * ys) * 8u;
+  double ra[4], rb[4];
+  unsigned amask = 0u;  // bit e (AMAJ), or bit 0: element inside K
+  bool inb = true;
+  int x0 = 2 * s0 / ux, y0 = 2 * s0 % ux;  // the stage's first unit: x, and y / 8
+  auto fetch = [&](int s) __attribute__((always_inline)) {
+    const bool two = 2 * s + 1 < units;  // the last stage may hold one unit
+    const bool wrap = y0 + 1 == ux;
+    const int64_t at = x0 * xs + (int64_t)y0 * 8 * ys;
+    const int64_t step = wrap ? xs - (int64_t)y0 * 8 * ys : 8 * (int64_t)ys;  // to the second
+    const BufRsrc sa = buf_rsrc(U + at), sb = buf_rsrc(G + (int64_t)s * T::BK);
+    if constexpr (AMAJ) {
+      // rows y >= nv hold the next x, or end the array
+      const int left0 = nv - y0 * 8, left1 = !two ? 0 : wrap ? nv : left0 - 8;
+      amask = 0u;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const bool in = ak + 4 * (e & 1) < (e < 2 ? left0 : left1);
+        ra[e] = buf_load_f64(sa, in ? aoff[0] + (unsigned)((e < 2 ? 0 : step) + (e & 1) * 4 * ys) * 8u
+                                    : 0u);
+        amask |= in ? 1u << e : 0u;
+      }
+    } else {
+      const unsigned h = kt < 8 ? 0u : two ? (unsigned)step * 8u : 0u;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) ra[e] = buf_load_f64(sa, aoff[e] + h);
+    }
+    inb = kt < 8 || two;
+    const unsigned kb = inb ? 0u : 64u;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) rb[e] = buf_load_f64(sb, boff[e] - kb);
+    y0 += 2;
+    while (y0 >= ux) { y0 -= ux; ++x0; }
+  };
+  // lds_idx: row k at k LDA, the column XOR-ed by k
+  double* wa = lds + (AMAJ ? ak * T::LDA : kt * T::LDA + (xt ^ kt));
+  double* wb = lds + T::BK * T::LDA + kt * T::LDB + (xt ^ kt);
+  auto store = [&](int o) __attribute__((always_inline)) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if constexpr (AMAJ)
+        wa[o + 4 * e * T::LDA + (am ^ (ak + 4 * e))] = ((amask >> e) & 1u) ? ra[e] : 0.0;
+      else
+        wa[o + 32 * e] = inb ? ra[e] : 0.0;
+      wb[o + 32 * e] = inb ? rb[e] : 0.0;
+    }
+  };
+  fetch(s0);
+  store(0);
+  __syncthreads();
+  for (int s = s0; s < s1; ++s) {
+    const int cur = ((s - s0) & 1) * T::STAGE;
+    const bool more = s + 1 < s1;
+    if (more) fetch(s + 1);
+    mfma_stage<T>(lds + cur, lds + cur + T::BK * T::LDA, acc, lane, wm, wn);
+    if (more) store(T::STAGE - cur);
+    __syncthreads();
+  }
+}
+
+__global__ __launch_bounds__(OCfg::NT, 4) void k_omega_lds(const double* __restrict__ cubes,
+                                                           const double* __restrict__ Gbc,
+                                                           const double* __restrict__ Gcb,
+                                                           const int* __restrict__ tri,
+                                                           double* __restrict__ Pvv, int no, int nv,
+                                                           int nchunks, int tiles_n) {
+  typedef OCfg T;
+  __shared__ double lds[T::LDS_DOUBLES];
+  const int pi = blockIdx.y, z = blockIdx.z;
+  const int i = tri[3 * z], j = tri[3 * z + 1], k = tri[3 * z + 2];
+  if (!perm_active(tri_kind(i, j, k), pi)) return;
+  int p, q, r;
+  perm_pqr(pi, i, j, k, p, q, r);
+  const int ch = blockIdx.x % nchunks, tile = blockIdx.x / nchunks;
+  const int m0 = (tile / tiles_n) * T::BM, n0 = (tile % tiles_n) * T::BN;
+  const int rp = cube_pitch(nv), S = (nv * (rp / 8) + 1) / 2;
+  const int s0 = (int)((int64_t)ch * S / nchunks), s1 = (int)((int64_t)(ch + 1) * S / nchunks);
+  if (s0 >= s1) return;  // nchunks <= S, so never taken
+  const int64_t pl = (int64_t)nv * rp, gp = g_pitch(nv);
+  const double* U = cubes + ((int64_t)z * NSLOT + SLOT_TT) * cube_slot(nv);
+  const double* G = (pi >= 2 && pi <= 4 ? Gcb : Gbc) + ((int64_t)r * (nv + no) + n0) * gp;
+  const int brow = (nv - n0) << 6 | q;  // rows of B in the tile, and from there to the Omega1 row
+  d4v acc[T::FM][T::FN];
+  zero_acc<T>(acc);
+  if (pi == 2 || pi == 5) {  // rows TT[x][y][a]
+    omega_lds_tile<true>(U + m0, G, pl, rp, 1, gp, nv - m0, brow, nv, s0, s1, lds, acc);
+  } else {  // TT[x][a][y], or TT[a][x][y]
+    const bool mid = pi == 1 || pi == 4;
+    const int64_t rs = mid ? rp : pl;
+    omega_lds_tile<false>(U + m0 * rs, G, mid ? pl : rp, 1, rs, gp, nv - m0, brow, nv, s0, s1, lds, acc);
+  }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int wm = wave % T::WM, wn = wave / T::WM;
+  const int NV1 = nv + 1;
+  double* pvv = Pvv + (((int64_t)z * 6 + pi) * nchunks + ch) * nv * (int64_t)NV1;
+#pragma unroll
+  for (int fm = 0; fm < T::FM; ++fm)
+#pragma unroll
+    for (int fn = 0; fn < T::FN; ++fn)
+#pragma unroll
+      for (int rr = 0; rr < 4; ++rr) {
+        const int a = m0 + acc_row<T>(wm, fm, lane, rr), n = n0 + acc_col<T>(wn, fn, lane);
+        if (a < nv && n <= nv) pvv[(int64_t)a * NV1 + n] = acc[fm][fn][rr];
+      }
+}
 
 // cubes: TT and TTT of each triple
 __global__ __launch_bounds__(OCfg::NT) void k_omega_f32(const float* __restrict__ cubes,
@@ -1843,20 +1984,35 @@ int zo_nbchunks(int nv, int ntri) {
   return nbc < 1 ? 1 : nbc;
 }
 
+// The LDS form of the FP64 Omega GEMM: from nv = 448 on, unless its 128 x 128 tiles are so
+// much emptier than the wave tiles that a 1.19 times higher rate per block does not make up for
+// it.  MEASURED, LDS / wave tiles, ms per launch of 8 triples: 416 46.4 / 40.7, 448 54.4 / 52.6,
+// 464 58.6 / 58.7, 480 62.9 / 60.6, 500 70.3 / 73.7, 512 97 / 122; of 3: 448 20.2 / 22.4, 530 41.0 /
+// 34.0, 576 48.8 / 45.0, 644 84.0 / 80.4, 700 98.4 / 91.1, 768 121 / 148; of one: 576 14.1 / 15.1,
+// 600 15.3 / 17.4, 772 58.7 / 47.3, 832 68.8 / 69.7, 900 92 / 95, 960 107 / 118, 1000 118 / 139, 1024
+// 152 / 168.  (Rows a power of two of lines apart, as at 512, 768 and 1024, cost the wave tiles
+// most.)
+bool omega_lds(int nv) {
+  const int t = OCfg::BM;
+  return nv >= 448 && (double)nblk(nv, t) * nblk(nv + 1, t) * (t / 16) * (t / 16) <
+                          1.19 * shape_cost(pick_shape(nv, nv + 1), nv, nv + 1);
+}
+
 // K chunks of the Omega GEMM of one (triple, permutation, tile).
 // FP64: enough wave tiles for six rounds of the 2048 that are resident at two per SIMD
 // (4096, 8192, 12288, 24576 tiles: 23/250 CVS list 585, 562, 548, 552 ms per call, 12/120
 // 40.5, 39.6, 39.5, 40.6), as long as a chunk keeps 64 units of 8 k; small products are split further, down to 8 units
 // per chunk, while there are fewer than 3072 wave tiles (CC3_OMEGA_WG in the environment
 // sets the larger target instead).
-// fp32acc (the mixed-all forms, 128 x 128 LDS tiles): about 2048 workgroups, as a
+// 128 x 128 LDS tiles (omega_lds, and fp32acc, the mixed-all forms): about 2048 workgroups, as a
 // multiple of 8 beyond 8 so that the tiles of one (triple, permutation, chunk) are
-// dispatched to the same XCD; at least 16 stages of 16 k per chunk and at most 4096 k,
-// which the MFMA sums in FP32, so that their rounding does not grow with the batch (the
+// dispatched to the same XCD; at least 16 stages of 16 k per chunk and, with fp32acc, at most
+// 4096 k, which the MFMA sums in FP32, so that their rounding does not grow with the batch (the
 // split-BF16 form's K is the blocked lp_kb_len(nv) >= nv^2).
 struct OmegaSplit {
   int64_t per, units;  // tiles of one triple (wave tiles, or LDS tiles), units (stages) of K
   int target, need;    // tiles of a launch; chunks that hold fp32acc's K to 4096
+  bool lds;
 };
 static OmegaSplit omega_split(int nv, bool fp32acc) {
   static const int env = [] {
@@ -1865,22 +2021,23 @@ static OmegaSplit omega_split(int nv, bool fp32acc) {
   }();
   OmegaSplit s;
   int tm, tn;
-  if (!fp32acc) {
+  s.lds = fp32acc || omega_lds(nv);
+  if (!s.lds) {
     shape_tiles(pick_shape(nv, nv + 1), nv, nv + 1, &tm, &tn);
     s.units = (int64_t)nv * (cube_pitch(nv) / 8);
   } else {
     tm = (nv + OCfg::BM - 1) / OCfg::BM;
     tn = (nv + 1 + OCfg::BN - 1) / OCfg::BN;
-    s.units = ((int64_t)nv * nv + OCfg::BK - 1) / OCfg::BK;
+    s.units = ((int64_t)nv * (fp32acc ? nv : cube_pitch(nv)) + OCfg::BK - 1) / OCfg::BK;
   }
   s.per = 6ll * tm * tn;
-  s.target = env > 0 ? env : fp32acc ? 2048 : 12288;
+  s.target = env > 0 ? env : s.lds ? 2048 : 12288;
   s.need = fp32acc ? (int)((lp_kb_len(nv) + 4095) / 4096) : 1;
   return s;
 }
-static int omega_chunks(const OmegaSplit& s, int ntri, bool fp32acc) {
+static int omega_chunks(const OmegaSplit& s, int ntri) {
   const int64_t per = s.per * (ntri > 0 ? ntri : 1), big = (s.target + per - 1) / per;
-  if (!fp32acc) {
+  if (!s.lds) {
     const int64_t small = (3072 + per - 1) / per;
     return (int)std::max<int64_t>(1, std::max(std::min(big, s.units / 64), std::min(small, s.units / 8)));
   }
@@ -1890,14 +2047,14 @@ static int omega_chunks(const OmegaSplit& s, int ntri, bool fp32acc) {
 }
 
 int omega_kchunks(int nv, int ntri, bool fp32acc) {
-  return omega_chunks(omega_split(nv, fp32acc), ntri, fp32acc);
+  return omega_chunks(omega_split(nv, fp32acc), ntri);
 }
 
 size_t omega_slabs(int nv, int batch, bool fp32acc) {
   const OmegaSplit s = omega_split(nv, fp32acc);
   size_t most = 1;
   for (int nb = 1; nb <= batch; ++nb)
-    most = std::max(most, (size_t)nb * omega_chunks(s, nb, fp32acc));
+    most = std::max(most, (size_t)nb * omega_chunks(s, nb));
   return most;
 }
 
@@ -1913,7 +2070,7 @@ int batch_within(int nv, int least, int most, size_t doubles) {
   size_t slabs = 1;
   int best = least;
   for (int nb = 1; nb <= most; ++nb) {
-    slabs = std::max(slabs, (size_t)nb * omega_chunks(s, nb, false));
+    slabs = std::max(slabs, (size_t)nb * omega_chunks(s, nb));
     if (nb > best && NSLOT * nb * cube + slabs * slab <= doubles) best = nb;
   }
   return best;
@@ -1927,8 +2084,16 @@ static unsigned omega_wgs(int nv, int ntri, int nch, int shape) {
 
 void launch_omega(const double* cubes, const Blocks& b, const int* tri, int ntri, double* Pvv,
                   int no, int nv, hipStream_t st) {
-  const int shape = pick_shape(nv, nv + 1), nch = omega_kchunks(nv, ntri);
+  const int nch = omega_kchunks(nv, ntri);
   int tm, tn;
+  if (omega_lds(nv)) {
+    typedef OCfg T;
+    tm = (nv + T::BM - 1) / T::BM, tn = (nv + 1 + T::BN - 1) / T::BN;
+    hipLaunchKernelGGL(k_omega_lds, dim3(nch * tm * tn, 6, ntri), dim3(T::NT), 0, st, cubes, b.Gbc,
+                       b.Gcb, tri, Pvv, no, nv, nch, tn);
+    return;
+  }
+  const int shape = pick_shape(nv, nv + 1);
   shape_tiles(shape, nv, nv + 1, &tm, &tn);
   with_shape(shape, [&](auto fm, auto fn) {
     hipLaunchKernelGGL((k_omega<decltype(fm)::value, decltype(fn)::value>),

@@ -137,3 +137,63 @@ def test_oo_terms_in_shares_above_16_occupied(no, nv):
     r1, r2 = O.omega_tilde_subset(d["eps"], d["L"], d["t1"], d["t2"], tri)
     assert rel(o1.cpu().numpy(), r1) < TOL
     assert rel(o2.cpu().numpy(), r2) < TOL
+
+
+@pytest.mark.parametrize("nv", [448, 451, 465, 500, 512, 513, 576, 601, 641])
+def test_omega_on_lds_tiles_at_large_nv(nv):
+    """The LDS form of the Omega GEMM (448 and more virtuals; 513 stays on wave tiles): 24
+    virtuals spread over nv against the oracle, zeros elsewhere.  Odd and even counts of units
+    of 8 k, rows with and without padding, the column of Omega1 in a tile of its own."""
+    no, nv0 = 3, 24
+    print(f"omega on LDS tiles nv={nv}", flush=True)
+    d = make_inputs(no, nv0, 12, tag=67)
+    at = np.sort(np.random.default_rng(nv).choice(nv, nv0, replace=False))
+    mo = np.concatenate([np.arange(no), no + at])
+    eps = np.full(no + nv, 10.0)
+    eps[mo] = d["eps"]
+    L, t1, t2 = np.zeros((12, no + nv, no + nv)), np.zeros((no, nv)), np.zeros((no, no, nv, nv))
+    L[np.ix_(range(12), mo, mo)] = d["L"]
+    t1[:, at] = d["t1"]
+    t2[np.ix_(range(no), range(no), at, at)] = d["t2"]
+    ctx = cc3.Context(0)
+    o1, o2 = (x.cpu().numpy() for x in ctx.triples_residual(*cuda(eps, L, t1, t2)))
+    r1, r2 = O.triples_residual(d["eps"], d["L"], d["t1"], d["t2"])
+    ix = np.ix_(range(no), range(no), at, at)
+    assert rel(o1[:, at], r1) < TOL and rel(o2[ix], r2) < TOL
+    o1[:, at] = 0.0
+    o2[ix] = 0.0
+    assert not o1.any() and not o2.any()
+    ctx.close()
+
+
+@pytest.mark.parametrize("no,nv", [(2, 451), (3, 500)])
+def test_omega_on_lds_tiles_dense(no, nv):
+    """Every value in use: against the split-BF16 W build and contraction, which is another
+    kernel on other operands (BF16x6: 2e-6)."""
+    print(f"omega on LDS tiles, dense no={no} nv={nv}", flush=True)
+    d = make_inputs(no, nv, 24, tag=68)
+    ctx = cc3.Context(0)
+    g = cuda(d["eps"], d["L"], d["t1"], d["t2"])
+    o1, o2 = ctx.triples_residual(*g)
+    r1, r2 = ctx.triples_residual(*g, prec=cc3.BF16X6, flags=cc3.LOWP_CONTRACT)
+    assert float((o1 - r1).norm()) < 2e-6 * float(r1.norm())
+    assert float((o2 - r2).norm()) < 2e-6 * float(r2.norm())
+    ctx.close()
+
+
+def test_lds_tile_requests_are_not_packed():
+    """Requests whose Omega GEMM runs on LDS tiles stay out of packed groups, whose form is
+    another, and give the bits of the same request alone."""
+    arena = torch.empty(40 << 30, dtype=torch.uint8, device="cuda")
+    srv = cc3.Server(arena, max_inflight=1)
+    srv.set_packing(8, 1e13)
+    ds = [make_inputs(2, 448, 24, tag=69 + t) for t in range(3)]
+    gs = [cuda(d["eps"], d["L"], d["t1"], d["t2"]) for d in ds]
+    ms = [srv.register(2, 448, *g[:3]) for g in gs]
+    tks = [srv.submit(m, g[3]) for m, g in zip(ms, gs)]
+    got = [srv.wait(t, mol=m) for t, m in zip(tks, ms)]
+    assert srv.stats()["packed"] == 0
+    for m, g, (p1, p2, _) in zip(ms, gs, got):
+        a1, a2, _ = srv.wait(srv.submit(m, g[3]), mol=m)
+        assert torch.equal(a1, p1) and torch.equal(a2, p2)
+    srv.close()
