@@ -228,12 +228,14 @@ int make_plan_ex(int no, int nv, int nchol, int prec, unsigned flags, bool with_
   const size_t held =
       std::max<size_t>(1, budget / (BUDGET_CUBES * p->cube * sizeof(double)));
   if (held < (size_t)batch) {
-    // batches of `held` triples with five cubes each, and slabs of one Omega-sized chunk per Zo
-    // chunk: within that much memory (1% less, for the padding of the operands), as many triples
-    // of three slots and their own slabs as it holds
-    const size_t b = balanced((int)std::min<size_t>(held, MAX_BATCH));
-    const size_t doubles = b * BUDGET_CUBES * p->cube + zo_slabs(nv, (int)b) * 6 * v * (v + 1);
-    batch = flags & CC3_LOWP_CONTRACT ? (int)b : batch_within(nv, (int)b, batch, doubles / 100 * 99);
+    // batches of `held` triples with five cubes each, and slabs of chunks_2048: within that much
+    // memory (1% less, for the padding of the operands), as many triples of three slots and
+    // their own slabs as it holds
+    const int b = balanced((int)std::min<size_t>(held, MAX_BATCH));
+    size_t slabs = 1;
+    for (int nb = 1; nb <= b; ++nb) slabs = std::max(slabs, (size_t)nb * chunks_2048(nv, nb));
+    const size_t doubles = b * BUDGET_CUBES * p->cube + slabs * 6 * v * (v + 1);
+    batch = flags & CC3_LOWP_CONTRACT ? b : batch_within(nv, b, batch, doubles / 100 * 99);
   }
   batch = env_int("CC3_BATCH", batch);
   batch = balanced(std::min(batch, MAX_BATCH));  // bounds the kernels' per-p pair lists

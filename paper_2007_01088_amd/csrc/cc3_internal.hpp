@@ -274,7 +274,8 @@ void launch_combine(const double* Ot1, const double* Ot2, const double* OtT, dou
 // forms), at most 4096 k each
 int omega_kchunks(int nv, int ntri, bool fp32acc = false);
 bool omega_lds(int nv);  // the FP64 Omega GEMM runs on LDS tiles
-int zo_nbchunks(int nv, int ntri);    // b chunks of one Zo product
+int zo_nbchunks(int nv, int ntri);    // K chunks of one Zo product
+int chunks_2048(int nv, int ntri);
 // The largest triples x chunks of a launch of either over the batches of 1 to `batch` triples
 size_t omega_slabs(int nv, int batch, bool fp32acc);
 size_t zo_slabs(int nv, int batch);

@@ -1973,15 +1973,26 @@ double zprep_flops(int no, int nv, const int* kinds, int n) {
   return perms * (2.0 * v * v * v * v + 2.0 * v * v * v * o);
 }
 
-// Split-K chunks of the b index of the Zo partials per (triple, permutation, a
-// tile): about 2048 workgroups per launch, as a multiple of 8 beyond 8.
-int zo_nbchunks(int nv, int ntri) {
+// K chunks that make about 2048 workgroups of 128 x 128 tiles per launch, six products per
+// triple; a multiple of 8 beyond 8.
+int chunks_2048(int nv, int ntri) {
   const int t = (nv + 127) / 128;
   const int per = 6 * t * t * (ntri > 0 ? ntri : 1);
   int nbc = (2048 + per - 1) / per;
   if (nbc > 8) nbc = (nbc + 7) / 8 * 8;
   if (nbc > nv) nbc = nv;
   return nbc < 1 ? 1 : nbc;
+}
+
+// K chunks of the Zo partials per (triple, permutation pair, rows of a): chunks_2048, or where
+// that leaves fewer than 2048 wavefronts of 64 rows (two per SIMD), as many as make 4096, of at
+// least 64 units of 8 k.  MEASURED, k_zv and k_zo of a call with chunks_2048 alone / so raised:
+// 8/187 34.3 / 32.8 ms, 4/250 11.9 / 11.4, 2/512 20.5 / 18.9, 2/896 186 / 160, 2/1024 359 / 305
+// (from 288 wavefronts); 4096 at 12/120, which has 3072: 19.9 / 20.5.
+int zo_nbchunks(int nv, int ntri) {
+  const int n = chunks_2048(nv, ntri), per = 3 * (int)nblk(nv, 64) * (ntri > 0 ? ntri : 1);
+  if (n * per >= 2048) return n;
+  return std::max(n, std::min((4096 + per - 1) / per, nv * (cube_pitch(nv) / 8) / 64));
 }
 
 // The LDS form of the FP64 Omega GEMM: from nv = 448 on, unless its 128 x 128 tiles are so
