@@ -131,7 +131,7 @@ void launch_lp_convert(const double* t2, const Blocks& b, int no, int nv, const 
 // W build in low precision
 // ---------------------------------------------------------------------------
 // Tiles of 16 NW x 16 NW outputs on NW wavefronts (4 to 8), each FM x FN blocks of 16 x 16.
-// The edge that pads nv least is taken (lp_tile_waves).
+// The edge that costs least with its padding is taken (lp_tile_waves).
 template <int NW>
 struct LpGeo {
   static constexpr int WM = NW == 8 ? 4 : NW == 6 ? 3 : NW == 4 ? 2 : NW;
@@ -531,18 +531,24 @@ __global__ __launch_bounds__(LpGeo<NW>::NT, E::MINW) void k_wbuild_lp(
 }
 
 // Wavefronts (tile edge 16 NW) that cover an M x N product with the least work: the outputs
-// computed, padding included, with the operand rows loaded per output (1 / edge) on top.
+// computed, padding included, weighted by the time per output of the W build's launches relative
+// to NW = 8 (nv = 150 to 900: 4 1.4 to 2.3, 5 1.4 to 1.7, 6 1.4 to 1.7, 7 1.1 to 1.3).
 // MEASURED, whole calls of 9 occupied orbitals at NW = 4 / 5 / 6 / 7 / 8 (the rule's choice
 // is the fastest in each): BF16x6, nv = 112: 13.1 / 16.0 / 16.9 / 12.1 / 12.3 ms, 150: 38.8 /
 // 37.0 / 38.6 / 40.9 / 42.2, 187: 72.6 / 85.0 / 69.5 / 72.7 / 75.3, 240: 177 / 184 / 187 / 198 /
 // 168; BF16x3, 150: 36.1 / 33.7 / 34.5 / 35.8 / 36.1, 180: 62.9 / 64.6 / 59.8 / 61.4 / 63.0,
-// 210: 123 / 120 / 122 / 116 / 116.  Instead, 128 x 128 tiles whose empty blocks are skipped:
-// 73.7 ms for BF16x6 at 187, and the same as 7 wavefronts for BF16x3 at 210.
+// 210: 123 / 120 / 122 / 116 / 116.  The W build of 8 triples in BF16x3 and x6: 400 12.3 / 10.0 /
+// 10.6 / 9.2 / 10.3 and 24.0 / 19.1 / 19.5 / 15.8 / 17.4, 450 14.9 / 13.2 / 12.7 / 13.4 / 10.4 and
+// 22.9 / 26.6 / 22.0 / 23.8 / 18.3; of one, 900: 35.6 / 22.5 / 21.6 / 22.8 / 17.3 and 65.2 / 44.7 /
+// 37.5 / 36.1 / 32.6.  Instead, 128 x 128 tiles whose empty blocks are skipped: 73.7 ms for
+// BF16x6 at 187, and the same as 7 wavefronts for BF16x3 at 210.
 int lp_tile_waves(int64_t M, int64_t N) {
+  constexpr double weight[] = {1.5, 1.6, 1.42, 1.2, 1.0};  // NW = 4 to 8
   int best = 8;
   double cost = 0.0;
   for (int nw = 8; nw >= 4; --nw) {
-    const double t = 16.0 * nw, c = (double)nblk(M, 16 * nw) * nblk(N, 16 * nw) * t * t * (1.0 + 64.0 / t);
+    const double t = 16.0 * nw;
+    const double c = (double)nblk(M, 16 * nw) * nblk(N, 16 * nw) * t * t * weight[nw - 4];
     if (nw == 8 || c < cost) { best = nw; cost = c; }
   }
   return best;
