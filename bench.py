@@ -9,7 +9,7 @@ measured time per call.  Prints one JSON line.
     python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload mixed]
 
 The default workload is no=23 nv=250 nchol=800, the largest size whose timed
-calls fit a run of a few minutes (one FP64 call takes about 5 s); the extra
+calls fit a run of a few minutes (one FP64 call takes about 4 s); the extra
 measurements after the timed region (standalone kernel durations, the mixed
 precisions, the Jacobian preparation, the CVS worklist, host buffers) take
 --extra-steps calls each.

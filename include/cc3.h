@@ -457,7 +457,8 @@ int cc3_cancel(cc3_server* srv, uint64_t ticket);
  * in the same launches (one persistent kernel per step of the triple loop, whose
  * workgroups loop over the union of the requests' work items), and completes
  * together.  Each request keeps its own plan, batches and reduction order, so its
- * result is bit for bit the result it has alone.  Defaults: max_pack 8,
+ * result is bit for bit the result it has alone.  A request whose FP64 Omega
+ * contraction runs on LDS tiles (most nv from 448 on) runs alone.  Defaults: max_pack 8,
  * max_request_flops 2e12; max_pack 1 turns packing off.
  * Errors: CC3_E_INVAL (max_pack outside [1, 64], max_request_flops < 0). */
 int cc3_server_set_packing(cc3_server* srv, int max_pack, double max_request_flops);

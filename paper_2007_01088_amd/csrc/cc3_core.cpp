@@ -208,9 +208,10 @@ int make_plan_ex(int no, int nv, int nchol, int prec, unsigned flags, bool with_
   p->sets = (flags & PLAN_CALLER_STREAM) ? 1 : 2;
   p->ntri = (int)((size_t)no * (no + 1) * (no + 2) / 6 - no);
   p->cube = (size_t)cube_slot(nv);  // one padded cube slot
-  // triples per batch: enough W-build workgroups per launch to fill 256 CUs
-  // many times over, and at least min(no, 8) triples, so that the kernels that
-  // are parallel over the first occupied index p (the oo contraction, the
+  // triples per batch: as many as would give 12288 workgroups of 128 x 128 tiles of three
+  // planes, whatever tiles and planes the precision builds (a size for the launches, of which
+  // every form then has thousands of wavefronts), and at least min(no, 8) triples, so that
+  // the kernels that are parallel over the first occupied index p (the oo contraction, the
   // reductions) find pairs for many p in every batch; bounded by a cube-memory
   // budget per buffer set (32 GiB by default: 13 triples at nv = 400)
   const size_t wg_per_triple = 3 * v * ((v + 127) / 128) * ((v + 127) / 128);

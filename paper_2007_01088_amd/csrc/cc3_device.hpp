@@ -1,6 +1,7 @@
-// Device-side building blocks shared by the gfx950 kernels of libcc3: the
-// FP64 MFMA tile engine (v_mfma_f64_16x16x4f64, 64-wide wavefronts, LDS-staged
-// operands with register prefetch and double-buffered LDS).
+// Device-side building blocks shared by the gfx950 kernels of libcc3: tile shapes, buffer
+// loads and wavefront helpers, and an FP64 MFMA tile engine through LDS (register prefetch,
+// double-buffered LDS), which k_d3_ld runs on.  (The other FP64 GEMMs have loops of their own:
+// wave tiles without LDS, k_omega_lds through it.)
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>

@@ -71,6 +71,7 @@ __host__ __device__ inline int64_t lp_kb_len(int nv) {
 // Row pitch of those operands: Kb plus 32 values, so that rows do not fall a power of
 // two apart (Kb is one whenever nv / 8 is) and share memory channels.
 __host__ __device__ inline int64_t lp_kb_pitch(int nv) { return lp_kb_len(nv) + 32; }
+// Position of (x, y) in it (the converter and the mix write whole blocks in this order).
 __host__ __device__ inline int64_t lp_kb(int x, int y, int nv) {
   const int nb = (nv + 7) / 8;
   return ((int64_t)((x >> 3) * nb + (y >> 3)) * 8 + (x & 7)) * 8 + (y & 7);
@@ -214,11 +215,12 @@ void launch_relayout_small(const double* g_oovo, const double* g_ovov, const dou
 void launch_relayout_vv(const double* g_vvvo_y, const double* g_vvov_y, int y0, int ny,
                         const Blocks& b, int no, int nv, hipStream_t st);
 void launch_gcb(const Blocks& b, int no, int nv, hipStream_t st);
-// The full triple table, the restricted loop dealt round-robin over nbatch batches.
-// The triple table in nbatch batches (unless tri is null), n zeros at Z and t2N
+// One launch: the full triple table, the restricted loop dealt round-robin over nbatch batches
+// (unless tri is null), n zeros at Z, and t2N[p][y][x][l] = -t2[p][l][x][y], each (p, y) slab at
+// the pitch t2n_pitch
 void launch_loop_begin(int* tri, int nbatch, double* Z, int64_t n, const double* t2, double* t2N,
                        int no, int nv, hipStream_t st);
-// t2N[p][y][x][l] = -t2[p][l][x][y], each (p, y) slab at the pitch t2n_pitch
+// The FP64 W build of a batch into its planes
 void launch_wbuild(const double* t2, const double* t2N, const Blocks& b, const int* tri, int ntri,
                    double* cubes, int no, int nv, bool all_terms, hipStream_t st);
 // The FP64 W build's engine with explicit operands and output strides (doubles between
@@ -229,8 +231,9 @@ void launch_wbuild(const double* t2, const double* t2N, const Blocks& b, const i
 void launch_wbuild_ex(int mode, const double* X, const double* XN, const double* G, const double* H,
                       const int* tri, int ntri, double* cubes, int64_t zs, int64_t ss, int pitch,
                       int no, int nv, bool all_terms, hipStream_t st);
-// two_planes: the planes are PA and PB, else the three of the BF16x3 W build.  transposed: write tau~T too.  Mixed-all copies (nullable): cubesF, FP32 tau~ and tau~T,
-// [triple][2][nv^3]; YL, the split-BF16 k-major views of k_omega_lp with lpP pieces
+// two_planes: the planes are PA and PB, else the three of the BF16x3 W build.  transposed: write
+// tau~T too.  Mixed-all copies (nullable): cubesF, FP32 tau~ and tau~T, [triple][2][nv^3]; YL,
+// the split-BF16 blocks of k_omega_lp (yl_piece) with lpP pieces
 void launch_mix(bool two_planes, const double* eps, const int* tri, int ntri, double* cubes,
                 float* cubesF, void* YL, int lpP, bool transposed, int no, int nv, hipStream_t st);
 void launch_tau_export(bool two_planes, const double* eps, const int* tri, const double* cubes,
@@ -275,7 +278,7 @@ void launch_combine(const double* Ot1, const double* Ot2, const double* OtT, dou
 int omega_kchunks(int nv, int ntri, bool fp32acc = false);
 bool omega_lds(int nv);  // the FP64 Omega GEMM runs on LDS tiles
 int zo_nbchunks(int nv, int ntri);    // K chunks of one Zo product
-int chunks_2048(int nv, int ntri);
+int chunks_2048(int nv, int ntri);    // K chunks that make about 2048 LDS tiles of a launch
 // The largest triples x chunks of a launch of either over the batches of 1 to `batch` triples
 size_t omega_slabs(int nv, int batch, bool fp32acc);
 size_t zo_slabs(int nv, int batch);

@@ -381,7 +381,6 @@ void launch_wbuild_f32(const LpOperands& lp, const int* tri, int ntri, double* c
   });
 }
 
-// t2N[p][y][x][l] = -t2[p][l][x][y]
 // ---------------------------------------------------------------------------
 // Mix: X, tau, tau~ on the S3 orbit of an 8x8x8 block triple (A <= B <= C).
 // ---------------------------------------------------------------------------
@@ -456,8 +455,8 @@ __device__ __forceinline__ void yl_put(char* Y, int form, const double* T, int A
 
 // Mixed-all copies: cubesF (nullable), FP32 tau~ and tau~T, [triple][2][nv^3]; LP: YL, the
 // split-BF16 blocks of the split-BF16 Omega GEMM (yl_piece), in lpP pieces.  TWO: the two
-// planes of the W build, X = PA[b][a][c] + PB[a][b][c] (PA[a][b][c] for i == j, PA[c][a][b] for j == k in
-// the place of PB); otherwise the three planes of the BF16x3 build,
+// planes of the W build, X = PA[b][a][c] + PB[a][b][c] (for i == j PA[a][b][c], for j == k
+// PA[c][a][b] in the place of PB); otherwise the three planes of the BF16x3 build,
 // X = P0[b][a][c] + P1[a][b][c] + P2[c][a][b], where for i == j P1 = P0 and P2 is
 // symmetrised over (a, b), and for j == k P2 = P0 and P1 is symmetrised over (b, c).
 template <bool TWO, bool LP>
@@ -841,12 +840,12 @@ void launch_tau_export(bool two_planes, const double* eps, const int* tri, const
 // slab Pvv[z][pi][chunk][a][n] (n <= nv) that k_reduce sums in a fixed order.
 //
 // Wave tiles as in the W build: no LDS, two units of 8 k in flight.  The waves of one
-// (triple, operand, chunk) are neighbours on one XCD and share the rows of tau~ (both
-// permutations) and of G in its L2.  Bound by MFMA and by the loads' way through L1 and L2
-// (16 B per cycle and CU at 4 x 4 blocks).  Per launch, before (128 x 128 LDS tiles) and
-// now: 23/250, 8 triples 6.14 -> 5.81 ms; 8/400, 8 triples 49.0 -> 36.2; 7/93 1.91 -> 1.07;
-// 6/45 0.137 -> 0.032 ms.
-
+// (triple, operand, chunk, permutation) are neighbours on one XCD and share the rows of tau~ and
+// of G in its L2; the operand's second permutation follows and finds part of tau~ there.  Bound
+// by MFMA and by the loads' way through L1 and L2 (16 B per cycle and CU at 4 x 4 blocks).  Per
+// launch, 128 x 128 LDS tiles -> this, before the order of items at omega_body: 23/250, 8 triples
+// 6.14 -> 5.81 ms; 8/400, 8 triples 49.0 -> 36.2; 7/93 1.91 -> 1.07; 6/45 0.137 -> 0.032 ms.
+// From nv = 448 on: omega_lds.
 template <bool ROWS, int FM, int FN>
 __device__ __forceinline__ void omega_tile(const double* __restrict__ U, int64_t un, unsigned va0,
                                            unsigned bs, unsigned us, int64_t xs, BufRsrc rb,
@@ -1974,7 +1973,7 @@ double zprep_flops(int no, int nv, const int* kinds, int n) {
 }
 
 // K chunks that make about 2048 workgroups of 128 x 128 tiles per launch, six products per
-// triple; a multiple of 8 beyond 8.
+// triple; a multiple of 8 beyond 8.  (The Zo partials below, and the limit of the cube budget.)
 int chunks_2048(int nv, int ntri) {
   const int t = (nv + 127) / 128;
   const int per = 6 * t * t * (ntri > 0 ? ntri : 1);
@@ -2012,9 +2011,9 @@ bool omega_lds(int nv) {
 // K chunks of the Omega GEMM of one (triple, permutation, tile).
 // FP64: enough wave tiles for six rounds of the 2048 that are resident at two per SIMD
 // (4096, 8192, 12288, 24576 tiles: 23/250 CVS list 585, 562, 548, 552 ms per call, 12/120
-// 40.5, 39.6, 39.5, 40.6), as long as a chunk keeps 64 units of 8 k; small products are split further, down to 8 units
-// per chunk, while there are fewer than 3072 wave tiles (CC3_OMEGA_WG in the environment
-// sets the larger target instead).
+// 40.5, 39.6, 39.5, 40.6), as long as a chunk keeps 64 units of 8 k; small products are split
+// further, down to 8 units per chunk, while there are fewer than 3072 wave tiles (CC3_OMEGA_WG in
+// the environment sets the larger target instead).
 // 128 x 128 LDS tiles (omega_lds, and fp32acc, the mixed-all forms): about 2048 workgroups, as a
 // multiple of 8 beyond 8 so that the tiles of one (triple, permutation, chunk) are
 // dispatched to the same XCD; at least 16 stages of 16 k per chunk and, with fp32acc, at most
