@@ -394,7 +394,8 @@ class Context:
                    torch.empty((no, no), dtype=torch.float64, device=dev),
                    torch.empty((nv, no, no, no), dtype=torch.float64, device=dev)
                    if want_yo else None)
-        cached = self._ws
+        # (the size, not the tensor: a buffer that is outgrown is freed before the next is made)
+        have = 0 if self._ws is None else self._ws.numel()
         ws = self._density_workspace(no, nv, nchol)
         dcd, dkc, dld, dlk, yo = out
         try:
@@ -406,7 +407,7 @@ class Context:
         finally:
             # a buffer of tens of GB goes back to torch, which may hand it out again only
             # after the work on `stream`
-            if ws is not cached and ws.numel() > KEEP_WORKSPACE:
+            if ws.numel() > max(have, KEEP_WORKSPACE):
                 if stream is not None:
                     ws.record_stream(torch.cuda.ExternalStream(_stream(stream), ws.device))
                 self._ws = None

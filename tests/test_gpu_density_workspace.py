@@ -2,6 +2,8 @@
 that the library reports is enough, the binding takes it where the device has no more, and a
 large buffer does not stay with the Context.  Both loops sum the same FP64 terms in other orders:
 the parity bar, 1e-11."""
+import weakref
+
 import numpy as np
 import pytest
 import torch
@@ -98,3 +100,20 @@ def test_large_buffer_is_given_back(monkeypatch):
     keep = ctx._ws
     ctx.transition_density(*g, omega)
     assert ctx._ws is keep
+
+
+def test_outgrown_buffer_is_freed_first(monkeypatch):
+    no, nv, nJ = 5, 21, 30
+    g, omega = inputs(no, nv, nJ)
+    ctx = cc3.Context(0)
+    old = weakref.ref(ctx.workspace(4096))
+    alive = []
+    empty = torch.empty
+
+    def spy(*a, **k):
+        if k.get("dtype") is torch.uint8:
+            alive.append(old() is not None)
+        return empty(*a, **k)
+    monkeypatch.setattr(torch, "empty", spy)
+    ctx.transition_density(*g, omega)
+    assert alive == [False]
